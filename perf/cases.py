@@ -1,0 +1,334 @@
+"""The calls whose speed is measured: what a trainer or a recovery has the library do, over its range of sizes.
+
+A case names an operation and a shard layout.  Operations, each through the public entry points:
+
+  encode       reft_parity_encode: parity of the k shards of a node, read in place from their tensors
+  decode       reft_reconstruct_spans: the lost shard, straight into its tensors
+  pack_encode  reft_parity_encode_pack: the parity and the packed stream of the own shard in one call
+  pack_unpack  reft_pack_device, then reft_unpack_device into fresh tensors
+  rotated      reft_parity_encode_rotated for one member, then reft_reconstruct_rotated of a lost one
+  save_load    reft_snapshot_pack to pinned host memory, then reft_restore into fresh tensors (staged)
+
+A shard holds, per weight tensor, a bf16 parameter and fp32 master, first and second moment (14 bytes
+per parameter), kind after kind.  Layouts:
+
+  drawn   `tensors` one-dimensional tensors of log-uniform sizes, odd element counts among them, so
+          that most spans start at stream offsets that are not multiples of 16
+  llama   the tensor-parallel share (one eighth) of a Llama-shaped decoder stage
+
+Every result is bytes: equal bit for bit or wrong.
+"""
+from __future__ import annotations
+
+import ctypes
+import math
+
+import numpy as np
+import torch
+
+import paper_2310_12670_amd as reft
+
+TP = 8                       # tensor-parallel width of the llama layouts
+ALIGN = 512                  # a tensor's place: PyTorch's allocator hands out multiples of 512 bytes
+MiB = 1 << 20
+# (bytes per element, standard deviation, absolute value): parameter, master, first, second moment
+KINDS = ((2, 0.02, False), (4, 0.02, False), (4, 1e-3, False), (4, 1e-6, True))
+# the stages that the repository's configurations 1 to 4 are shares of: (d, ffn, kv width)
+STAGES = ((4096, 11008, 4096), (5120, 13824, 5120), (8192, 22016, 1024), (8192, 28672, 1024))
+
+
+def listed():
+    return [
+        # A small adapter or a test model checkpointed every step: the call's latency counts.
+        dict(name="encode_shrunk", op="encode", k=4, layout="drawn", params=65536, tensors=64,
+             lo=64, hi=65536, layout_seed=1),
+        # The tiny configuration: 64 tensors of all sizes, 14 MB per shard, four shards, odd offsets.
+        dict(name="encode_tiny", op="encode", k=4, layout="drawn", params=1048576, tensors=64,
+             lo=64, hi=65536, layout_seed=2),
+        # Its recovery: the lost shard decoded into its tensors.
+        dict(name="decode_tiny", op="decode", k=4, layout="drawn", params=1048576, tensors=64,
+             lo=64, hi=65536, layout_seed=3),
+        # Its snapshot to host memory and the load of that snapshot: bound by the host link.
+        dict(name="save_load_tiny", op="save_load", k=1, layout="drawn", params=1048576, tensors=64,
+             lo=64, hi=65536, layout_seed=4),
+        # The save of a 7B-shaped stage on an eight-GPU node: the node's parity.
+        dict(name="encode_7b", op="encode", k=8, layout="llama", d=4096, ffn=11008, kv=4096,
+             layers=8, shuffle=False, layout_seed=5),
+        # The recovery of a 13B-shaped stage whose tensor list is in no particular order.
+        dict(name="decode_13b", op="decode", k=8, layout="llama", d=5120, ffn=13824, kv=5120,
+             layers=4, shuffle=True, layout_seed=6),
+        # A scheduler that gathers and encodes in a pipeline bubble, 34B-shaped.
+        dict(name="pack_encode_34b", op="pack_encode", k=8, layout="llama", d=8192, ffn=22016,
+             kv=1024, layers=1, shuffle=False, layout_seed=7),
+        # Packing a shard into one buffer and back, 70B-shaped.
+        dict(name="pack_unpack_70b", op="pack_unpack", k=1, layout="llama", d=8192, ffn=28672,
+             kv=1024, layers=4, shuffle=False, layout_seed=8),
+        # Models of very many small tensors (norms, biases, adapters, experts): the parity.
+        dict(name="encode_ragged", op="encode", k=8, layout="drawn", params=9437185, tensors=3072,
+             lo=50, hi=32768, layout_seed=9),
+        # The same kind of state packed and unpacked.
+        dict(name="pack_unpack_ragged", op="pack_unpack", k=1, layout="drawn", params=37748737,
+             tensors=12288, lo=50, hi=32768, layout_seed=10),
+        # Snapshot and load of a 34B-shaped shard over the host link.
+        dict(name="save_load_34b", op="save_load", k=1, layout="llama", d=8192, ffn=22016, kv=1024,
+             layers=1, shuffle=False, layout_seed=11),
+        # The rotated placement in a group of sixteen: one member's unit, and a lost member's shard.
+        dict(name="rotated_13b", op="rotated", k=16, layout="llama", d=5120, ffn=13824, kv=5120,
+             layers=1, shuffle=False, layout_seed=12),
+    ]
+
+
+def draw(rng):
+    """One more case of the same ranges; never above encode_7b's traffic."""
+    op = rng.choice(("encode", "encode", "decode", "decode", "pack_encode", "pack_unpack", "rotated",
+                     "save_load"))
+    k = 1 if op in ("pack_unpack", "save_load") else rng.choice((2, 3, 4, 5, 8, 8, 12, 16))
+    case = dict(op=op, k=k, layout_seed=rng.randrange(1 << 20))
+    if rng.random() < 0.3:
+        d, ffn, kv = rng.choice(STAGES)
+        case.update(layout="llama", d=d, ffn=ffn, kv=kv, layers=rng.randint(1, 4),
+                    shuffle=rng.random() < 0.5)
+        # at most the listed cases' traffic, and their bytes over the host link
+        most = 6.6e9 if op == "save_load" else 27.5e9
+        while case["layers"] > 1 and work(case)["bytes"] > most:
+            case["layers"] -= 1
+        if work(case)["bytes"] > most:
+            case.update(d=4096, ffn=11008, kv=4096)
+    else:
+        tensors = int(round(2 ** rng.uniform(4, 12)))
+        mean = 2 ** rng.uniform(10, 16)
+        params = min(max(65536, int(tensors * mean)), 40_000_000) | 1
+        case.update(layout="drawn", params=params, tensors=tensors, lo=50, hi=65536)
+    return case
+
+
+# ---------------------------------------------------------------------------------------------
+# layouts
+# ---------------------------------------------------------------------------------------------
+def tensor_sizes(case):
+    """Elements of every weight tensor, in canonical order."""
+    if case["layout"] == "drawn":
+        rng = np.random.default_rng(case["layout_seed"])
+        n = case["tensors"]
+        raw = np.exp(rng.uniform(math.log(case["lo"]), math.log(case["hi"]), n))
+        sizes = np.maximum(1, (raw * (case["params"] / raw.sum())).astype(np.int64))
+        odd = rng.choice(n, size=max(1, n // 8), replace=False)
+        sizes[odd] |= 1
+        sizes[n - 1] = max(1, sizes[n - 1] + case["params"] - int(sizes.sum()))
+        return sizes
+    d, ffn, kv = case["d"], case["ffn"] // TP, case["kv"] // TP
+    layer = [d // TP * d, kv * d, kv * d, d * d // TP, ffn * d, ffn * d, ffn * d, d, d]
+    return np.array([32000 // TP * d] + layer * case["layers"], dtype=np.int64)
+
+
+class Layout:
+    """Where the spans lie: in a shard's memory (kind after kind, each span at a multiple of ALIGN)
+    and in the stream (the same order, or shuffled)."""
+
+    def __init__(self, case):
+        sizes = tensor_sizes(case)
+        nbytes = np.concatenate([sizes * esz for esz, _, _ in KINDS])
+        padded = (nbytes + ALIGN - 1) // ALIGN * ALIGN
+        place = np.concatenate([[0], np.cumsum(padded)])
+        self.slab_bytes = int(place[-1])
+        n = len(sizes)
+        self.kind_range = [(int(place[i * n]), int(place[(i + 1) * n])) for i in range(len(KINDS))]
+        order = np.arange(len(nbytes))
+        if case.get("shuffle"):
+            order = np.random.default_rng(case["layout_seed"]).permutation(len(nbytes))
+        self.nbytes = nbytes[order]
+        self.place = place[:-1][order]
+        self.L = int(nbytes.sum())
+
+    def fill(self, seed):
+        """One shard's memory: normal values of the kinds' scales."""
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        slab = torch.empty(self.slab_bytes, dtype=torch.uint8, device="cuda")
+        for (a, b), (esz, std, absolute) in zip(self.kind_range, KINDS):
+            part = slab[a:b].view(torch.bfloat16 if esz == 2 else torch.float32)
+            part.normal_(0.0, std, generator=gen)
+            if absolute:
+                part.abs_()
+        return slab
+
+    def empty(self):
+        return torch.zeros(self.slab_bytes, dtype=torch.uint8, device="cuda")
+
+    def pointers(self, *slabs):
+        """The spans' addresses in each of the slabs, as the library takes them (made once)."""
+        addresses = np.concatenate([slab.data_ptr() + self.place for slab in slabs]).astype(np.uint64)
+        return (ctypes.c_void_p * len(addresses)).from_buffer(addresses)
+
+    def stream(self, slab):
+        """The shard's stream as plain torch builds it."""
+        return torch.cat([slab[p:p + n] for p, n in zip(self.place.tolist(), self.nbytes.tolist())])
+
+    def unstream(self, stream):
+        """The memory of a shard that holds this stream, zero between the tensors."""
+        slab = self.empty()
+        at = 0
+        for p, n in zip(self.place.tolist(), self.nbytes.tolist()):
+            slab[p:p + n] = stream[at:at + n]
+            at += n
+        return slab
+
+
+class Plan:
+    """A plan that is destroyed with the state that holds it."""
+
+    def __init__(self, nbytes, bucket):
+        self.handle = reft.reft_plan_create([int(n) for n in nbytes], None, bucket)
+
+    def __del__(self):
+        reft.reft_plan_destroy(self.handle)
+
+
+def shard_seed(seed, s):
+    return (seed * 64 + s) & (2 ** 62 - 1)
+
+
+def random_bytes(n, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen)
+
+
+def random_units(case, lay, seed):
+    return [random_bytes(segment(case, lay), shard_seed(seed, case["k"] + i)) for i in range(case["k"])]
+
+
+def lost_shard(case):
+    return case["layout_seed"] % case["k"]
+
+
+def segment(case, lay):
+    return -(-lay.L // (case["k"] - 1))
+
+
+# ---------------------------------------------------------------------------------------------
+# the measured calls
+# ---------------------------------------------------------------------------------------------
+def prepare(case, seed):
+    lay = Layout(case)
+    op, k = case["op"], case["k"]
+    shards = [lay.fill(shard_seed(seed, s)) for s in range(k)]
+    # save_load: 64 MiB buckets, as a trainer would cut the stream
+    st = dict(op=op, k=k, shards=shards, spans=lay.pointers(*shards),
+              plan=Plan(lay.nbytes, 64 * MiB if op == "save_load" else 0))
+
+    def buffer(n):
+        return torch.zeros(n, dtype=torch.uint8, device="cuda")
+
+    def fresh():
+        st["fresh"] = lay.empty()
+        st["fresh_spans"] = lay.pointers(st["fresh"])
+
+    if op in ("encode", "pack_encode"):
+        st["parity"] = buffer(lay.L)
+    if op in ("pack_encode", "pack_unpack"):
+        st["packed"] = buffer(lay.L)
+    if op == "pack_encode":
+        st["own"] = lost_shard(case)
+    if op in ("decode", "rotated"):
+        st["lost"] = lost_shard(case)
+    if op == "decode":
+        # the node's parity (any bytes do: the result is their XOR with the survivors)
+        st["parity"] = random_bytes(lay.L, shard_seed(seed, k))
+    if op == "rotated":
+        st["member"] = (st["lost"] + 1) % k
+        st["units"] = random_units(case, lay, seed)          # the other members' (any bytes do)
+        st["unit_ptrs"] = reft.ptr_array(st["units"])
+    if op in ("decode", "rotated", "pack_unpack", "save_load"):
+        fresh()
+    if op == "save_load":
+        st["host"] = torch.zeros(lay.L, dtype=torch.uint8, pin_memory=True)
+        slot = reft.reft_plan_staging_slot_bytes(st["plan"].handle)
+        st["save_ring"] = torch.empty(4 * slot, dtype=torch.uint8, device="cuda")
+        st["load_ring"] = torch.empty(4 * slot, dtype=torch.uint8, device="cuda")
+    return st
+
+
+def run(st):
+    plan, spans, k = st["plan"].handle, st["spans"], st["k"]
+    if st["op"] == "encode":
+        reft.reft_parity_encode(plan, spans, k, st["parity"])
+        return st["parity"]
+    if st["op"] == "decode":
+        reft.reft_reconstruct_spans(plan, spans, k, st["lost"], st["parity"], st["fresh_spans"])
+        return st["fresh"]
+    if st["op"] == "pack_encode":
+        reft.reft_parity_encode_pack(plan, spans, k, st["own"], st["parity"], st["packed"])
+        return [st["parity"], st["packed"]]
+    if st["op"] == "pack_unpack":
+        reft.reft_pack_device(plan, spans, st["packed"])
+        reft.reft_unpack_device(plan, st["packed"], st["fresh_spans"])
+        return [st["packed"], st["fresh"]]
+    if st["op"] == "rotated":
+        reft.reft_parity_encode_rotated(plan, spans, k, st["member"], st["units"][st["member"]])
+        reft.reft_reconstruct_rotated(plan, spans, st["unit_ptrs"], k, st["lost"], st["fresh_spans"])
+        return [st["units"][st["member"]], st["fresh"]]
+    reft.reft_snapshot_pack(plan, spans, st["save_ring"], st["host"])
+    reft.reft_restore(plan, st["host"], st["load_ring"], st["fresh_spans"])
+    return [st["host"], st["fresh"]]
+
+
+def work(case):
+    """Every operand byte read once and every result byte written once.  No arithmetic but XOR."""
+    L = int(sum(int(tensor_sizes(case).sum()) * esz for esz, _, _ in KINDS))
+    k, op = case["k"], case["op"]
+    if op in ("encode", "decode"):
+        n = (k + 1) * L
+    elif op == "pack_encode":
+        n = (k + 2) * L
+    elif op == "rotated":
+        n = k * -(-L // (k - 1)) + k * L
+    else:                                    # there and back: read and written twice
+        n = 4 * L
+    return {"bytes": n, "flops": 0}
+
+
+def tolerance(case):
+    return "exact"
+
+
+def exact(case, seed):
+    """The same outputs by plain torch: concatenation, slices and bitwise XOR."""
+    lay = Layout(case)
+    op, k = case["op"], case["k"]
+
+    def stream(s):
+        return lay.stream(lay.fill(shard_seed(seed, s)))
+
+    def xor(streams):
+        total = torch.zeros(lay.L, dtype=torch.uint8, device="cuda")
+        for x in streams:
+            total ^= x
+        return total
+
+    if op == "encode":
+        return xor(stream(s) for s in range(k))
+    if op == "decode":
+        total = random_bytes(lay.L, shard_seed(seed, k))
+        total ^= xor(stream(s) for s in range(k) if s != lost_shard(case))
+        return lay.unstream(total)
+    if op == "pack_encode":
+        return [xor(stream(s) for s in range(k)), stream(lost_shard(case))]
+    if op == "rotated":
+        # member i keeps the XOR, over the others j, of segment i (i < j) or i - 1 of shard j
+        seg, lost = segment(case, lay), lost_shard(case)
+        member = (lost + 1) % k
+        streams = [torch.nn.functional.pad(stream(s), (0, seg * (k - 1) - lay.L)) for s in range(k)]
+
+        def fold(unit, i, without):
+            for j in range(k):
+                if j not in without:
+                    r = i if i < j else i - 1
+                    unit ^= streams[j][r * seg:(r + 1) * seg]
+            return unit
+
+        units = random_units(case, lay, seed)
+        units[member] = fold(torch.zeros_like(units[member]), member, (member,))
+        out = torch.cat([fold(units[i].clone(), i, (i, lost)) for i in range(k) if i != lost])
+        return [units[member], lay.unstream(out[:lay.L])]
+    return [stream(0), lay.unstream(stream(0))]
