@@ -22,6 +22,7 @@ from __future__ import annotations
 
 import ctypes
 import math
+import weakref
 
 import numpy as np
 import torch
@@ -179,9 +180,7 @@ class Plan:
 
     def __init__(self, nbytes, bucket):
         self.handle = reft.reft_plan_create([int(n) for n in nbytes], None, bucket)
-
-    def __del__(self):
-        reft.reft_plan_destroy(self.handle)
+        weakref.finalize(self, reft.reft_plan_destroy, self.handle)
 
 
 def shard_seed(seed, s):
