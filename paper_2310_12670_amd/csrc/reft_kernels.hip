@@ -28,7 +28,15 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // only becomes a valid address once a stream offset is added).  They are turned into pointers in
 // the global address space here, so that the accesses compile to global_load / global_store.
 #define REFT_GLOBAL __attribute__((address_space(1)))
-typedef const REFT_GLOBAL u32x4 *gcptr16;
+//
+// Loads of 16 bytes take any byte address: global memory is in unaligned access mode, one
+// global_load_dwordx4 serves a lane whatever its address.  Measured as a copy whose source is 0, 4,
+// 2 or 1 bytes off a 16-byte boundary: 2 GiB at 4.94, 4.91, 5.48, 5.49 TB/s, 14 MiB in 4.3, 4.3,
+// 5.2, 5.2 us.  (Two aligned loads per 16 bytes and a funnel shift in registers, with one chunk in
+// flight per source, was up to 2.7 times slower: the decode of one of 4 x 14.7 MB at odd offsets took
+// 150 us, with these loads 56 us; the parity of 8 x 132 MB of small odd tensors 417 and 313 us.)
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef const REFT_GLOBAL u32x4_any *gcptr16;
 typedef REFT_GLOBAL u32x4 *gptr16;
 
 __device__ __forceinline__ gcptr16 as_gc16(uint64_t a) { return (gcptr16)a; }
@@ -48,41 +56,6 @@ __device__ __forceinline__ void st16(gptr16 p, u32x4 v)
 {
     if constexpr (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
-}
-
-// The 16 bytes that start r bytes (0 < r < 16) into the 32 bytes lo || hi (little endian).
-__device__ __forceinline__ u32x4 shift_bytes(u32x4 lo, u32x4 hi, uint32_t r)
-{
-    const uint32_t q = r >> 2, b = (r & 3u) * 8u;
-    uint32_t x0, x1, x2, x3, x4;
-    switch (q) {
-    case 0:  x0 = lo.x; x1 = lo.y; x2 = lo.z; x3 = lo.w; x4 = hi.x; break;
-    case 1:  x0 = lo.y; x1 = lo.z; x2 = lo.w; x3 = hi.x; x4 = hi.y; break;
-    case 2:  x0 = lo.z; x1 = lo.w; x2 = hi.x; x3 = hi.y; x4 = hi.z; break;
-    default: x0 = lo.w; x1 = hi.x; x2 = hi.y; x3 = hi.z; x4 = hi.w; break;
-    }
-    if (b) {
-        x0 = (x0 >> b) | (x1 << (32u - b));
-        x1 = (x1 >> b) | (x2 << (32u - b));
-        x2 = (x2 >> b) | (x3 << (32u - b));
-        x3 = (x3 >> b) | (x4 << (32u - b));
-    }
-    u32x4 v = {x0, x1, x2, x3};
-    return v;
-}
-
-// 16 source bytes at byte address addr + 16*c for any alignment of addr, using only aligned
-// 16-byte loads.  Both aligned blocks that are read contain at least one of the wanted bytes, so
-// no load reaches outside the 16-byte-aligned hull of the source range.
-template <bool NT>
-__device__ __forceinline__ u32x4 load_any(uint64_t addr, uint32_t c)
-{
-    const uint32_t r = (uint32_t)addr & 15u;
-    gcptr16 a = as_gc16(addr - r) + c;
-    const u32x4 lo = ld16<NT>(a);
-    if (r == 0) return lo;
-    const u32x4 hi = ld16<NT>(a + 1);
-    return shift_bytes(lo, hi, r);
 }
 
 // Where the bytes of a piece go: to their global address, or into an LDS image of a destination
@@ -115,10 +88,8 @@ struct NoSink {
 
 // One piece: n bytes at destination address d = XOR of the n bytes at each source address s[j].
 // The whole workgroup cooperates.  Destination stores are 16-byte aligned: up to 15 head bytes
-// and 15 tail bytes are moved bytewise, the body as 16-byte chunks.  If every source is
-// co-aligned with the destination (the case for tensors whose sizes and addresses are multiples
-// of 16) the body is plain vector loads, U chunks in flight per thread and source; otherwise each
-// misaligned source is read as two aligned chunks and byte-shifted in registers.
+// and 15 tail bytes are moved bytewise, the body as 16-byte chunks, U in flight per thread and
+// source, whatever the sources' alignment.
 // With a second sink, the bytes of the first source alone also go to address d2 (+ the same
 // offsets) of that sink: the packed copy of one shard beside the parity of all.  d2 must be
 // congruent to d modulo 16.
@@ -150,47 +121,33 @@ __device__ __forceinline__ void xor_piece(uint64_t d, const uint64_t (&s)[K], ui
 
     const uint64_t da = d + head;
     const uint64_t da2 = d2 + head;
-    uint32_t mis = 0;
+    gcptr16 sp[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) mis |= (uint32_t)(s[j] + head) & 15u;
-
-    if (mis == 0) {
-        gcptr16 sp[K];
+    for (int j = 0; j < K; ++j) sp[j] = as_gc16(s[j] + head);
+    constexpr uint32_t step = kThreads * U;
+    const uint32_t full = nb / step * step;
+    for (uint32_t c = tid; c < full; c += step) {
+        u32x4 v[U];
 #pragma unroll
-        for (int j = 0; j < K; ++j) sp[j] = as_gc16(s[j] + head);
-        constexpr uint32_t step = kThreads * U;
-        const uint32_t full = nb / step * step;
-        for (uint32_t c = tid; c < full; c += step) {
-            u32x4 v[U];
+        for (int u = 0; u < U; ++u) v[u] = ld16<NT>(sp[0] + c + u * kThreads);
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = ld16<NT>(sp[0] + c + u * kThreads);
+        for (int u = 0; u < U; ++u)
+            sink2.template put16<NT>(da2 + ((uint64_t)(c + u * kThreads) << 4), v[u]);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                sink2.template put16<NT>(da2 + ((uint64_t)(c + u * kThreads) << 4), v[u]);
+        for (int j = 1; j < K; ++j) {
 #pragma unroll
-            for (int j = 1; j < K; ++j) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) v[u] ^= ld16<NT>(sp[j] + c + u * kThreads);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                sink.template put16<NT>(da + ((uint64_t)(c + u * kThreads) << 4), v[u]);
+            for (int u = 0; u < U; ++u) v[u] ^= ld16<NT>(sp[j] + c + u * kThreads);
         }
-        for (uint32_t c = full + tid; c < nb; c += kThreads) {
-            u32x4 v = ld16<NT>(sp[0] + c);
-            sink2.template put16<NT>(da2 + ((uint64_t)c << 4), v);
 #pragma unroll
-            for (int j = 1; j < K; ++j) v ^= ld16<NT>(sp[j] + c);
-            sink.template put16<NT>(da + ((uint64_t)c << 4), v);
-        }
-    } else {
-        for (uint32_t c = tid; c < nb; c += kThreads) {
-            u32x4 v = load_any<NT>(s[0] + head, c);
-            sink2.template put16<NT>(da2 + ((uint64_t)c << 4), v);
+        for (int u = 0; u < U; ++u)
+            sink.template put16<NT>(da + ((uint64_t)(c + u * kThreads) << 4), v[u]);
+    }
+    for (uint32_t c = full + tid; c < nb; c += kThreads) {
+        u32x4 v = ld16<NT>(sp[0] + c);
+        sink2.template put16<NT>(da2 + ((uint64_t)c << 4), v);
 #pragma unroll
-            for (int j = 1; j < K; ++j) v ^= load_any<NT>(s[j] + head, c);
-            sink.template put16<NT>(da + ((uint64_t)c << 4), v);
-        }
+        for (int j = 1; j < K; ++j) v ^= ld16<NT>(sp[j] + c);
+        sink.template put16<NT>(da + ((uint64_t)c << 4), v);
     }
 }
 
@@ -202,7 +159,7 @@ __device__ __forceinline__ void xor_piece(uint64_t d, const uint64_t (&s)[K], ui
 // the span pointers of every source - is staged in LDS once, and the tile is cut into 16-byte
 // destination chunks that are dealt to the threads: each thread finds the span that owns its
 // chunk by binary search in the LDS copy of the offsets.  A chunk inside one span is moved as a
-// vector (realigned in registers if the source is not co-aligned); a chunk that straddles a span
+// vector, whatever the source's alignment; a chunk that straddles a span
 // boundary is assembled byte by byte.  At most kLdsSpans spans are staged per pass; a tile with
 // more is handled in several passes.
 // ------------------------------------------------------------------------------------------------
@@ -284,9 +241,9 @@ __device__ __forceinline__ void gather_small(const PlanTables &pt, const uint64_
                 u32x4 v;
                 if (x + 16 <= s_off[q + 1]) {              // the chunk lies inside one span
                     const uint64_t r = x - s_off[q];
-                    v = load_any<NT>(s_ptr[0][q] + r, 0);
+                    v = ld16<NT>(as_gc16(s_ptr[0][q] + r));
 #pragma unroll
-                    for (int j = 1; j < K; ++j) v ^= load_any<NT>(s_ptr[j][q] + r, 0);
+                    for (int j = 1; j < K; ++j) v ^= ld16<NT>(as_gc16(s_ptr[j][q] + r));
                 } else {                                   // it straddles a span boundary
                     uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -318,7 +275,7 @@ __device__ __forceinline__ void scatter_small(const PlanTables &pt, const uint64
         const uint64_t sub_e = s_off[n] < e ? s_off[n] : e;
         // Are all destinations of this pass co-aligned with the source stream?  (True for tensors
         // whose sizes and addresses are multiples of 16.)  If not, 16-byte source chunks would
-        // have to be stored in narrow pieces; the piece routine, which realigns on the load side,
+        // have to be stored in narrow pieces; the piece routine, which aligns on the store side,
         // is the better tool then, fed from the LDS copy of the tables.
         int mis = 0;
         for (uint32_t q = tid; q < n; q += kThreads)
