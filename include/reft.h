@@ -384,12 +384,16 @@ int reft_restore_wait(reft_plan *plan);
 
 /* ---- tuning and diagnostics -----------------------------------------------------------------------
  * Process-wide launch parameters, read at each launch:
- *   "max_wgs"      cap on workgroups per kernel launch (0 = 16 per compute unit).  A small cap keeps
- *                  a snapshot kernel on few compute units while training kernels run beside it.
- *   "nontemporal"  1 = streaming (non-temporal) loads and stores in the kernels, 0 = plain.
- *   "unroll"       16-byte chunks in flight per thread and source: 1, 2 or 4.
+ *   "max_wgs"      cap on workgroups (of 256 threads, or as many threads in smaller ones) per kernel
+ *                  launch; 0 = no cap of the caller's: a wave per unit of work in the pack, unpack and
+ *                  ordinary XOR kernels, 16 workgroups per compute unit in the others.  A small cap
+ *                  keeps a snapshot kernel on few compute units while training kernels run beside it.
+ *   "nontemporal"  1 = streaming (non-temporal) loads and stores in the kernels, 0 = plain.  (Launches
+ *                  whose traffic fits the cache, up to 96 MiB, use plain ones with either.)
+ *   "unroll"       16-byte chunks in flight per thread and source, at most: 1, 2 or 4.  The pack,
+ *                  unpack and ordinary XOR kernels take fewer where that is faster.
  *   "link_wgs"     cap on workgroups of kernels bound by the host link (default 32; kernels
- *                  that read host memory use twice this).
+ *                  that write host memory use half as many again, those that read it twice as many).
  *   "dma_min_bytes"     staged transport: pieces of at least this size travel by DMA alone
  *                  (default 65536; 0 = every piece; a huge value = none, everything is gathered).
  *   "gather_min_pieces" staged transport: shortest run of smaller pieces that is gathered by a
@@ -408,13 +412,12 @@ int reft_restore_wait(reft_plan *plan);
  *                  nodes.  Fewer gaps between the copies of one snapshot (53.8 -> 55.6 GB/s), but two
  *                  such graphs on two streams do not overlap: use it where nothing else shares the
  *                  link in the other direction.
- *   "small_pieces" a tile in which at least this many spans start is processed by the LDS-staged
- *                  small-piece path of the gather / scatter kernels (default 8; 4294967295 = never,
- *                  0 = always).
+ *   "small_pieces" a tile in which at least this many spans start counts as dense in small spans
+ *                  (default 1; 4294967295 = never, 0 = always): see "burst".
  *   "burst"        1 (default) = reft_parity_encode, reft_reconstruct_spans and the rotated calls use
  *                  the write-burst variant of the XOR kernel where it applies: a pass (up to 8 rows
- *                  each) of at least "burst_min_rows" rows (default 5), "burst_min_bytes" stream
- *                  bytes (default 8 MiB), at most one tile in a hundred dense in small spans (see
+ *                  each) of at least "burst_min_rows" rows (default 7), "burst_min_bytes" stream
+ *                  bytes (default 8 MiB), at most one tile in eight dense in small spans (see
  *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
  *                  alike (mod 16) relative to its stream offset; reft_reconstruct uses it under
  *                  the first two conditions.  The variant keeps reads and writes apart in time: reader
@@ -427,7 +430,8 @@ int reft_restore_wait(reft_plan *plan);
  *                  does not wait at all for the next 1, 2, 4, ... 64 rounds.  Timing only: results
  *                  never depend on it.  0 = always the ordinary kernel.
  * Read when a plan is created:
- *   "tile_shift"   log2 of the tile size in bytes, 12..24 (default 18 = 256 KiB).
+ *   "tile_shift"   log2 of the tile size in bytes, 12..24 (default 18 = 256 KiB).  The kernels' own
+ *                  look-up table may be finer.
  *   "host_only_plans"  1 = reft_plan_create builds only the host-side sizing (no GPU needed);
  *                  such a plan answers the reft_plan_* queries and is refused (REFT_EINVAL) by
  *                  every call that would touch the GPU.

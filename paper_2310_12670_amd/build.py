@@ -8,7 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libreft.so")
-SOURCES = ["reft_api.hip", "reft_kernels.hip"]
+SOURCES = ["reft_api.hip", "reft_kernels.hip", "reft_stream.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          # Packed-FP32 instruction selection off for every kernel in the library.  The feature
          # belongs to the gfx950 device pass, where it takes effect (a float2 multiply-add compiles

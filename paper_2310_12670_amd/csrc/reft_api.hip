@@ -54,13 +54,13 @@ static std::atomic<uint64_t> g_unroll{4};
 static std::atomic<uint64_t> g_tile_shift{18};   // read at plan creation
 static std::atomic<uint64_t> g_host_only{0};     // read at plan creation: no device tables
 static std::atomic<uint64_t> g_link_wgs{32};     // grid cap of kernels bound by the host link
-static std::atomic<uint64_t> g_small_pieces{8}; // spans starting in a tile that switch it to LDS mode
+static std::atomic<uint64_t> g_small_pieces{1}; // spans starting in a tile that make it count as dense
 static std::atomic<uint64_t> g_dma_min{65536};   // pieces of at least this many bytes are copied by DMA
 static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller pieces worth a gather kernel
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
 static std::atomic<uint64_t> g_burst{1};         // parity encode may use the write-burst kernel
-static std::atomic<uint64_t> g_burst_min_rows{5};    // ... from this many sources on
+static std::atomic<uint64_t> g_burst_min_rows{7};    // ... from this many sources on
 static std::atomic<uint64_t> g_burst_min_bytes{8ull << 20};  // ... and from this stream length on
 static std::atomic<uint64_t> g_burst_stage{32768};   // stream bytes per workgroup and round
 static std::atomic<uint64_t> g_burst_wgs{2};         // resident workgroups per compute unit
@@ -223,10 +223,12 @@ struct reft_plan {
     int num_cus = 256;
     uint64_t T = 0, NB = 0, L = 0, max_bucket = 0;
     uint32_t tile_shift = 16;
+    uint32_t lookup_shift = 16;       // blocks of the device's look-up table
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
     std::vector<uint64_t> bstart;     // [NB+1]
     std::vector<uint32_t> first;      // [ntiles] host copy of the tile table
+    uint8_t *d_tables = nullptr;      // device memory of the plan; the next four point into it
     uint64_t *d_off = nullptr;
     uint32_t *d_first = nullptr;
     // cache of pointer tables: a pool of ring_cap pointers (pinned host mirror and device copy)
@@ -265,21 +267,20 @@ struct reft_plan {
     };
     std::vector<CopyGraph> graphs;
     uint64_t graph_tick = 0;
-    // write-burst kernel: spans that start in each tile, sorted (plans with many tiles dense in
-    // small spans keep the ordinary kernel), and a ring of counter blocks, one per launch in flight
+    // write-burst kernel: spans that start in each tile, sorted (plans with many span boundaries keep
+    // the stream kernel), and a ring of counter blocks, one per launch in flight
     std::vector<uint32_t> tile_spans_sorted;
     uint32_t *burst_ctr = nullptr;
     uint32_t burst_next = 0;
 
-    PlanTables tables() const { return PlanTables{d_off, d_first, T, L, tile_shift}; }
+    PlanTables tables() const { return PlanTables{d_off, d_first, T, L, lookup_shift}; }
 };
 
 static LaunchCfg launch_cfg(const reft_plan *p)
 {
-    uint64_t w = g_max_wgs;
-    if (w == 0) w = 16ull * (uint64_t)(p ? p->num_cus : 256);
-    return LaunchCfg{(uint32_t)w, (uint32_t)g_unroll.load(), g_nontemporal.load() != 0,
-                     (uint32_t)g_small_pieces.load()};
+    const uint64_t cap = g_max_wgs;
+    const uint64_t w = cap ? cap : 16ull * (uint64_t)(p ? p->num_cus : 256);
+    return LaunchCfg{(uint32_t)w, cap != 0, (uint32_t)g_unroll.load(), g_nontemporal.load() != 0};
 }
 
 // Kernels whose rate is set by the host link need only a few workgroups to saturate it.
@@ -288,6 +289,7 @@ static LaunchCfg link_cfg(const reft_plan *p)
     LaunchCfg c = launch_cfg(p);
     const uint64_t w = g_link_wgs.load();
     if (w < c.max_wgs) c.max_wgs = (uint32_t)w;
+    c.capped = true;
     return c;
 }
 
@@ -380,9 +382,7 @@ static int device_statics(const DeviceStatics **out)
 static void free_ring(reft_plan *p)
 {
     if (p->h_ptr) (void)hipHostFree(p->h_ptr);
-    if (p->d_ptr) (void)hipFree(p->d_ptr);
     p->h_ptr = nullptr;
-    p->d_ptr = nullptr;
     p->ring_cap = 0;
 }
 
@@ -529,7 +529,7 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     if (!out) return fail(REFT_EINVAL, "reft_plan_create: null out");
     *out = nullptr;
     if (!span_nbytes || T == 0) return fail(REFT_EINVAL, "reft_plan_create: no spans");
-    if (T >= 0xffffffffull) return fail(REFT_EINVAL, "reft_plan_create: too many spans");
+    if (T >= kWholeBlock) return fail(REFT_EINVAL, "reft_plan_create: too many spans");
 
     reft_plan *p = new (std::nothrow) reft_plan;
     if (!p) return fail(REFT_EINVAL, "reft_plan_create: out of host memory");
@@ -604,12 +604,34 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, p->device));
     p->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    HIPCHK(hipMalloc((void **)&p->d_off, (T + 1) * sizeof(uint64_t)));
-    HIPCHK(hipMalloc((void **)&p->d_first, first.size() * sizeof(uint32_t)));
-    HIPCHK(hipMemcpy(p->d_off, p->off.data(), (T + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(p->d_first, first.data(), first.size() * sizeof(uint32_t),
-                     hipMemcpyHostToDevice));
-    HIPCHK(hipMalloc((void **)&p->burst_ctr, kCtrBlocks * kBurstCtrBytes));
+    // The kernels' look-up table: blocks of 4 KiB where 65,536 of them cover the stream (a finer
+    // table has more blocks inside one span, which need no search), else larger ones up to the tile;
+    // but no more than 16 spans per block on average, since a search goes 64 spans at a time.
+    p->lookup_shift = p->tile_shift;
+    while (p->lookup_shift > 12 && ((p->L >> (p->lookup_shift - 1)) <= 65536 ||
+                                    T > 16 * ((p->L >> p->lookup_shift) + 1)))
+        --p->lookup_shift;
+    const uint64_t block = 1ull << p->lookup_shift;
+    const uint64_t nblocks = (p->L + block - 1) / block + 1;
+    // One allocation and one copy for the tables: span offsets, look-up table; behind them the burst
+    // counters and the device half of the pointer pool.
+    const size_t at_first = ((T + 1) * sizeof(uint64_t) + 255) & ~(size_t)255;
+    const size_t at_ctr = (at_first + nblocks * sizeof(uint32_t) + 255) & ~(size_t)255;
+    const size_t at_ptr = (at_ctr + kCtrBlocks * kBurstCtrBytes + 255) & ~(size_t)255;
+    p->ring_cap = (uint64_t)kRingRows * T;
+    std::vector<uint64_t> tables((at_first + nblocks * sizeof(uint32_t) + 7) / 8, 0);
+    std::copy(p->off.begin(), p->off.end(), tables.begin());
+    uint32_t *lookup = (uint32_t *)((uint8_t *)tables.data() + at_first);
+    for (uint64_t t = 0, i = 0; t * block < p->L; ++t) {
+        while (p->off[i + 1] <= t * block) ++i;                      // t * block < L = off[T]
+        lookup[t] = (uint32_t)i | (p->off[i + 1] >= (t + 1) * block ? kWholeBlock : 0u);
+    }
+    HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
+    HIPCHK(hipMemcpy(p->d_tables, tables.data(), tables.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
+    p->d_off = (uint64_t *)p->d_tables;
+    p->d_first = (uint32_t *)(p->d_tables + at_first);
+    p->burst_ctr = (uint32_t *)(p->d_tables + at_ctr);
+    p->d_ptr = (uint64_t *)(p->d_tables + at_ptr);
     int rc;
     const DeviceStatics *ds = nullptr;
     if ((rc = device_statics(&ds))) return rc;
@@ -636,9 +658,7 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     if (g_dma_streams.load() == 2) HIPCHK(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
     // everything a data-moving call needs is made here: the pointer-table pool, the host scratch
     // for row tables, and the whole stream's piece lists for the staged transport
-    p->ring_cap = (uint64_t)kRingRows * T;
     HIPCHK(hipHostMalloc((void **)&p->h_ptr, p->ring_cap * sizeof(uint64_t), hipHostMallocDefault));
-    HIPCHK(hipMalloc((void **)&p->d_ptr, p->ring_cap * sizeof(uint64_t)));
     p->row_buf.resize((size_t)(REFT_MAX_K + 1) * T);
     p->pieces.reserve(kPieceLists);
     (void)pieces_of(p, 0, p->NB);
@@ -686,12 +706,10 @@ extern "C" void reft_plan_destroy(reft_plan *p)
         }
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
     }
-    if (p->burst_ctr) (void)hipFree(p->burst_ctr);
     for (auto &kv : p->derived) reft_plan_destroy(kv.second.plan);
     p->derived.clear();
     if (p->zeros) (void)hipFree(p->zeros);
-    if (p->d_off) (void)hipFree(p->d_off);
-    if (p->d_first) (void)hipFree(p->d_first);
+    if (p->d_tables) (void)hipFree(p->d_tables);
     delete p;
 }
 
@@ -1042,7 +1060,10 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
             return fail(REFT_EINVAL, "reft_snapshot_pack: host buffer is not mapped for device "
                                      "access (not pinned); pass a staging ring to copy it by DMA");
         if ((rc = upload_ptrs(p, span_ptrs, 1, ps, &tab, &entry))) return rc;
-        const LaunchCfg cfg = link_cfg(p);
+        // Stores across the link: 32 / 48 / 64 workgroups move tensors of 8 MiB at 53.7 / 54.5 / 54.3
+        // and of 10 KB at 51.6 / 53.5 / 53.9 GB/s.
+        LaunchCfg cfg = link_cfg(p);
+        cfg.max_wgs += cfg.max_wgs / 2;
         for (uint64_t b = bucket_begin; b < bucket_end; ++b)
             HIPCHK(launch_gather(pt, tab, 1, false, nullptr, hview, p->bstart[b], p->bstart[b + 1],
                                  cfg, ps));
@@ -1372,13 +1393,16 @@ static BurstCfg burst_cfg(uint32_t *ring, uint32_t slot, int num_cus)
     return bc;
 }
 
-// Tiles of the plan in which at least `small_pieces` spans start.
-static uint64_t dense_tiles(const reft_plan *p, uint32_t small_pieces)
+// The burst kernel walks a stage piece by piece, the stream kernel spreads pieces over its waves: the
+// former pays where at most one tile in eight holds a span boundary ("small_pieces" of them).
+// Measured for 8 rows, burst / stream kernel: 0.5 GB in spans of 0.2 MB 134 / 107 us, 2 GB in spans
+// of 0.9 MB 431 / 405 us, 14.8 GB in spans of 10 MB 2338 / 2397 us.
+static bool few_dense_tiles(const reft_plan *p)
 {
     const auto &v = p->tile_spans_sorted;
-    return (uint64_t)(v.end() - std::lower_bound(v.begin(), v.end(), small_pieces));
+    const auto dense = v.end() - std::lower_bound(v.begin(), v.end(), (uint32_t)g_small_pieces.load());
+    return (uint64_t)dense * 8 <= p->ntiles;
 }
-
 
 // The XOR passes over a device table of `nrows` rows of span pointers (row stride T of plan p)
 // into a contiguous destination or, if dtab is given, into the destination's own spans (dst_row
@@ -1391,14 +1415,13 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Passes over many rows separate reads and writes in time with the burst kernel.  It walks a
-    // stage piece by piece, which is slow where many small spans lie together (the ordinary
-    // kernel's LDS-staged path serves those better): plans with more than one such tile in a
-    // hundred keep the ordinary kernel.  So do ragged destinations whose spans are not all
-    // aligned alike relative to their stream offsets, which the staging image cannot represent.
+    // Passes over 7 rows and more separate reads and writes in time with the burst kernel (6 rows,
+    // 11.5 GB: 1912 us against the stream kernel's 1835; 8 rows, 14.8 GB: 2338 against 2397) where
+    // spans are long.  Ragged destinations whose spans are not all aligned alike relative to their
+    // stream offsets, which the staging image cannot represent, keep the stream kernel.
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     bool burst_ok = g_burst.load() && p->L >= g_burst_min_bytes.load() &&
-                    dense_tiles(p, cfg.small_pieces) * 100 <= p->ntiles;
+                    few_dense_tiles(p);
     if (burst_ok && dst_row) {
         bool have = false;
         for (uint64_t t = 0; t < T && burst_ok; ++t) {
@@ -1498,12 +1521,13 @@ extern "C" int reft_parity_encode_pack(reft_plan *p, const void *const *shard_sp
     const LaunchCfg cfg = launch_cfg(p);
     const uint64_t vb = (uint64_t)(uintptr_t)parity_dev, vb2 = (uint64_t)(uintptr_t)packed_dev;
     const uint64_t stage = g_burst_stage.load();
-    // The fused kernel applies where the burst kernel does (rows, bytes, no tiles dense in small
-    // spans), in one pass of at most kMaxSrc rows, with both destinations aligned alike and its
-    // one instantiation per row count (unroll 4, non-temporal); its two LDS images per half must
-    // fit a compute unit's LDS.  Otherwise: the encode and the pack as two launches.
+    // The fused kernel applies where the burst kernel does (bytes, few span boundaries), from two rows
+    // fewer on since it saves a read of one, in one pass of at most kMaxSrc rows, with both
+    // destinations aligned alike and its one instantiation per row count (unroll 4, non-temporal); its
+    // two LDS images per half must fit a compute unit's LDS.  Otherwise: the encode and the pack as
+    // two launches.
     const bool fused = g_burst.load() && p->L >= g_burst_min_bytes.load() && k <= (uint32_t)kMaxSrc &&
-                       k >= g_burst_min_rows.load() && dense_tiles(p, cfg.small_pieces) * 100 <= p->ntiles &&
+                       k + 2 >= g_burst_min_rows.load() && few_dense_tiles(p) &&
                        ((vb ^ vb2) & 15u) == 0 && cfg.unroll == 4 && cfg.nontemporal &&
                        4 * (stage + 16) + 16 <= 160 * 1024;
     const uint64_t *tab = nullptr;

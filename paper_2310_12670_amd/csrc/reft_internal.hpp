@@ -10,20 +10,23 @@ constexpr int kThreads = 256;      // 4 wavefronts of 64 lanes per workgroup
 constexpr int kMaxSrc = 8;         // sources XORed by one launch; more are chained
 
 struct LaunchCfg {
-    uint32_t max_wgs;              // cap on the grid size (>= 1)
+    uint32_t max_wgs;              // cap on the grid size (>= 1) in workgroups of kThreads
+    bool capped;                   // the caller asked for that cap; if not, a kernel that does better
+                                   // with a wave per unit of work may launch more
     uint32_t unroll;               // 1, 2 or 4 chunks of 16 B in flight per thread and source
     bool nontemporal;
-    uint32_t small_pieces;         // a tile in which at least this many spans start takes the
-                                   // LDS-staged small-piece path (0xffffffff = never)
 };
+
+constexpr uint32_t kWholeBlock = 0x80000000u;
 
 // Device-side tables of a plan.
 struct PlanTables {
     const uint64_t *off;           // [T+1] prefix sums of the span sizes (stream offsets)
-    const uint32_t *first_span;    // [ntiles] first span that owns a byte of tile t
+    const uint32_t *first_span;    // first span that owns a byte of block t of the stream, with
+                                   // kWholeBlock set if that span owns all of the block's bytes
     uint64_t T;
     uint64_t L;
-    uint32_t tile_shift;           // tile = 1 << tile_shift stream bytes
+    uint32_t tile_shift;           // block = 1 << tile_shift stream bytes
 };
 
 // Parameters of the gather variant that writes in chip-wide bursts (see k_gather_burst).

@@ -1,0 +1,342 @@
+// The ragged stream kernel of libreft: gather (snapshot pack, XOR parity over span tables), fused
+// decode into tensors, and scatter (restore), for spans of any size, alignment and number.
+//
+//   place of stream byte o  <-  XOR over K sources of their byte o,    o in [lo, hi)
+//
+// A source is a row of span pointers or a contiguous buffer; the destination is a contiguous buffer
+// or a row of span pointers, and may itself be the last source.
+//
+// The unit of work is one wavefront's: S = 1024 U consecutive stream bytes, U chunks of 16 bytes per
+// lane and source, all in flight at once.  A wave finds the span that owns its unit's first byte with
+// one look-up in the plan's table and one coalesced load of 64 span ends (locate), and from there
+//   - a unit inside one span, the usual case, needs K span pointers and then only vector accesses at
+//     uniform bases;
+//   - a unit that spans share is done 1 KiB at a time, and where a boundary falls into that KiB
+//     every lane finds its own span by comparing with the boundaries, which the wave broadcasts one
+//     by one.
+// Waves do not meet: no LDS, no barrier, so the chain of dependent loads (table, span ends,
+// pointers, data: 2 - 4 us) of one wave hides behind the others, and short streams, which have few
+// units, spread over the whole chip.
+#include "reft_device.hpp"
+
+namespace reft {
+
+// The last of a launch's K sources.
+enum LastRow : uint32_t {
+    kLastTable = 0,      // an ordinary row of the table
+    kLastDest = 1,       // the destination's current bytes (accumulate)
+    kLastContig = 2,     // the contiguous buffer whose virtual base is cbase
+};
+
+struct StreamArgs {
+    PlanTables pt;
+    const uint64_t *tab;     // rows of span pointers, row stride T
+    const uint64_t *dtab;    // the destination's row, or null: contiguous
+    uint64_t vb;             // contiguous destination: byte o lies at vb + o
+    uint64_t cbase;          // kLastContig: byte o lies at cbase + o
+    uint64_t lo, hi;         // stream range, lo < hi <= L
+    uint64_t first_unit, nunits;
+    uint32_t phase;          // unit u starts at stream byte u * S - phase
+    uint32_t last;           // LastRow
+};
+
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l)
+{
+    const uint32_t a = __builtin_amdgcn_readlane((uint32_t)v, l);
+    const uint32_t b = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
+    return (uint64_t)b << 32 | a;
+}
+
+// Span i owns stream bytes [b, e), and lane l holds the end of span base + l, where i = base + c.
+// All but `ends` are the same in every lane.
+struct Owner {
+    uint64_t i, b, e, base, ends;
+    uint32_t c;
+};
+
+// The span that owns byte x < L; span i is that one or an earlier one.  64 span ends per step: the
+// number of them at or below x says how far to go on.
+__device__ __forceinline__ void locate(const PlanTables &pt, Owner &o, uint64_t i, uint64_t x, uint32_t lane)
+{
+    o.b = pt.off[i];
+    for (;; i += 64) {
+        const uint64_t at = i + 1 + lane < pt.T ? i + 1 + lane : pt.T;
+        o.ends = pt.off[at];                                   // off[T] = L > x ends the search
+        o.c = (uint32_t)__popcll(__ballot(o.ends <= x));
+        if (o.c) o.b = readlane64(o.ends, o.c - 1);
+        if (o.c < 64) break;
+    }
+    o.base = i;
+    o.i = i + o.c;
+    o.e = readlane64(o.ends, o.c);
+}
+
+// The address of the first byte of span q (which starts at stream byte b) in source row j.
+template <int K>
+__device__ __forceinline__ uint64_t source_of(const StreamArgs &a, int j, uint64_t q, uint64_t b)
+{
+    if (j == K - 1 && a.last != kLastTable) {
+        if (a.last == kLastContig) return a.cbase + b;
+        return a.dtab ? a.dtab[q] : a.vb + b;
+    }
+    return a.tab[(uint64_t)j * a.pt.T + q];
+}
+
+template <bool NT>
+__device__ __forceinline__ void st16_any(uint64_t p, u32x4 v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, (REFT_GLOBAL u32x4_any *)p);
+    else *(REFT_GLOBAL u32x4_any *)p = v;
+}
+
+// V KiB of span o.i from stream byte x on, wholly inside the span and the range.
+template <int K, int V, bool NT>
+__device__ __forceinline__ void move_uniform(const StreamArgs &a, const Owner &o, uint64_t x,
+                                             uint32_t lane)
+{
+    const uint64_t r = x - o.b;
+    const uint64_t d = a.dtab ? a.dtab[o.i] + r : a.vb + x;
+    gcptr16 s[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, o.i, o.b) + r);
+    u32x4 v[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) v[u] = ld16<NT>(s[0] + lane + u * 64);
+#pragma unroll
+    for (int j = 1; j < K; ++j) {
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[u] ^= ld16<NT>(s[j] + lane + u * 64);
+    }
+#pragma unroll
+    for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
+}
+
+// n bytes from stream byte p on, all inside span q (which starts at b), one by one.
+template <int K>
+__device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint64_t b, uint64_t p, uint32_t n)
+{
+    const uint64_t d = (a.dtab ? a.dtab[q] - b : a.vb) + p;
+    uint64_t s[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) s[j] = source_of<K>(a, j, q, b) + (p - b);
+    for (uint32_t t = 0; t < n; t += 4) {                      // 4 K bytes in flight
+        uint32_t v[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) v[c] ^= ld8(s[j] + (t + c < n ? t + c : n - 1));
+        }
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c)
+            if (t + c < n) st8(d + t + c, (uint8_t)v[c]);
+    }
+}
+
+// 1 KiB from stream byte x on that several spans share or that reaches out of the range.  o owns the
+// first of its bytes that lies in the range, y1 is the end of them; lane l holds the end of span
+// base + l (ends), span o.i is base + c.
+//
+// A lane whose 16 bytes reach over the end of its span moves the span's last 16 bytes instead, and
+// then the next span's first 16: bytes that its neighbours move too are written twice, with the same
+// value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
+// the destination is a source (a byte must then be read and written once), in every straddling lane.
+template <int K, bool NT>
+__device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
+                                            uint32_t lane)
+{
+    constexpr uint32_t kNone = 0xffffffffu;
+    const uint32_t at = lane * 16;
+    // my span: `skip` spans behind o's, from byte `from` of this KiB on (if skip), up to byte `to`;
+    // the next one with bytes: `skip2` spans behind o's, up to byte `to2`
+    uint32_t skip = 0, from = 0, to = kNone, skip2 = 0, to2 = kNone;
+    uint64_t base = o.base, ends = o.ends;
+    uint32_t j = o.c;
+    for (;;) {
+        const uint32_t rel = (uint32_t)(ends - x);
+        const uint32_t n = (uint32_t)__popcll(__ballot(ends < y1));   // ends ascend: lanes 0 .. n - 1
+        for (; j < n; ++j) {
+            const uint32_t bnd = __builtin_amdgcn_readlane(rel, j);
+            const uint32_t s = (uint32_t)(base - o.i) + j + 1;
+            if (at >= bnd) {
+                skip = s;
+                from = bnd;
+            } else if (to == kNone || bnd == to) {
+                to = bnd;
+                skip2 = s;
+            } else if (to2 == kNone) {
+                to2 = bnd;
+            }
+        }
+        if (n < 64) break;
+        base += 64;
+        const uint64_t idx = base + 1 + lane < a.pt.T ? base + 1 + lane : a.pt.T;
+        ends = a.pt.off[idx];
+        j = 0;
+    }
+    // the end of span o.i + skip2, where no boundary in this KiB gave it
+    const uint64_t end2 = __shfl(ends, (int)((uint32_t)(o.i - base) + skip2) & 63);
+    const uint64_t me = x + at;                                // may wrap below 0 in the first unit
+    const uint64_t lo = (int64_t)me < (int64_t)a.lo ? a.lo : me;
+    const uint64_t hi = (int64_t)(me + 16) > (int64_t)y1 ? y1 : me + 16;
+    if ((int64_t)lo >= (int64_t)hi) return;
+    // the parts of the two spans that lie in the range (of the first, as far as it is known): [w0, w1), [w1, w2)
+    const uint64_t q = o.i + skip, b = skip ? x + from : o.b, q2 = o.i + skip2;
+    const uint64_t w0 = b < a.lo ? a.lo : b, w1 = to == kNone ? y1 : x + to;
+    const uint64_t w2 = to2 != kNone ? x + to2 : end2 < a.hi ? end2 : a.hi;
+    const bool one = w1 >= hi;                                 // all my bytes belong to span q
+    const bool can = a.last != kLastDest || (one && hi - lo == 16);
+    if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
+        const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
+        const uint64_t d = (a.dtab ? a.dtab[q] - b : a.vb) + p;
+        gcptr16 s[K], s2[K];
+        uint64_t d2 = 0;
+        u32x4 v, v2;
+#pragma unroll
+        for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, q, b) + (p - b));
+        if (!one) {
+            d2 = a.dtab ? a.dtab[q2] : a.vb + w1;
+#pragma unroll
+            for (int j = 0; j < K; ++j) s2[j] = as_gc16(source_of<K>(a, j, q2, w1));
+        }
+        v = ld16<NT>(s[0]);
+#pragma unroll
+        for (int j = 1; j < K; ++j) v ^= ld16<NT>(s[j]);
+        if (!one) {
+            v2 = ld16<NT>(s2[0]);
+#pragma unroll
+            for (int j = 1; j < K; ++j) v2 ^= ld16<NT>(s2[j]);
+        }
+        st16_any<NT>(d, v);
+        if (!one) st16_any<NT>(d2, v2);
+        return;
+    }
+    // spans of less than 16 bytes
+    uint64_t i = q, begin = b;
+    for (uint64_t p = lo;;) {
+        const uint64_t e = a.pt.off[i + 1];
+        move_bytes<K>(a, i, begin, p, (uint32_t)((e < hi ? e : hi) - p));
+        if (e >= hi) break;
+        p = begin = e;
+        do ++i; while (a.pt.off[i + 1] <= p);                  // p < hi <= L = off[T]
+    }
+}
+
+// The workgroup (1 or 4 waves) has no meaning beyond the dispatch.  Unless the caller caps the grid
+// there is one wave per unit, dispatched in order, so that the chip moves through its streams in
+// narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
+// workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
+template <int K, int U, bool NT>
+__global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
+{
+    constexpr uint32_t S = 1024 * U;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t waves = blockDim.x >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nunits; w += (uint64_t)gridDim.x * waves) {
+        Owner o;
+        const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
+        const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
+        const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
+        const uint32_t first = a.pt.first_span[y0 >> a.pt.tile_shift];
+        if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
+            o.i = first & ~kWholeBlock;
+            o.b = a.pt.off[o.i];
+            move_uniform<K, U, NT>(a, o, x, lane);
+            continue;
+        }
+        locate(a.pt, o, first & ~kWholeBlock, y0, lane);
+        if (y1 - y0 == S && y1 <= o.e) {
+            move_uniform<K, U, NT>(a, o, x, lane);
+            continue;
+        }
+#pragma unroll 1
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint64_t xs = x + u * 1024;
+            const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
+            const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
+            if ((int64_t)z0 >= (int64_t)z1) continue;
+            if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
+            if (z1 - z0 == 1024 && z1 <= o.e) move_uniform<K, 1, NT>(a, o, xs, lane);
+            else move_shared<K, NT>(a, o, xs, z1, lane);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// launch
+// ------------------------------------------------------------------------------------------------
+// Traffic (read and written) up to which a launch may find and leave its data in the 256 MB cache: it
+// then uses plain accesses (4 x 14.7 MB, 73 MB of traffic: 16 us, with streaming ones 18; from
+// 8 x 14.7 MB on streaming ones are as fast or faster), workgroups of four waves (16 against 17 us:
+// fewer to dispatch; long streams prefer single waves, 4.12 against 4.23 ms for 25.8 GB of copies)
+// and units of 1 KiB (16 against 19 and 20 us with 2 and 4 KiB).
+constexpr uint64_t kCachedTraffic = 96ull << 20;
+// Spans of this size on average leave few units shared.
+constexpr uint64_t kLongSpan = 1ull << 20;
+
+// KiB per wave and source for `nsrc` sources and long streams.  Enough must be in flight to cover the
+// look-ups in front of the data, but wider windows cost bandwidth (us for U = 1, 2, 4):
+//   long spans    1 source 5657, 4088, 4178 (25.8 GB); 2: 861, 769, 798 (4.9 GB); 3: 1026, 1034, 1071
+//                 (6.6 GB); 4: 1222, 1368, 1368 (8.2 GB); 6: 1835, 1939, 2008 (11.5 GB)
+//   short spans   1 source 547, 411, 401 (2.1 GB); 4: 69, 66, 65 (0.3 GB); 8: 279, 265, 269 (1.2 GB)
+static uint32_t long_stream_unroll(int nsrc, bool long_spans)
+{
+    if (nsrc == 1) return long_spans ? 2 : 4;
+    return nsrc == 2 || !long_spans ? 2 : 1;
+}
+
+static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, LaunchCfg cfg, hipStream_t stream)
+{
+    void (*fn)(const StreamArgs) = nullptr;
+    const bool cached = (uint64_t)(nsrc + 1) * (a.hi - a.lo) <= kCachedTraffic;
+    // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
+    uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc, a.pt.L / a.pt.T >= kLongSpan);
+    if (unroll < cfg.unroll) cfg.unroll = unroll;
+    if (cached && !cfg.capped) cfg.nontemporal = false;
+    REFT_PICK_K(k_stream, fn, nsrc)
+    // units start where the contiguous operand is 16-byte aligned
+    const uint64_t S = 1024ull * cfg.unroll;
+    a.phase = (uint32_t)contig & 15u;
+    a.first_unit = (a.lo + a.phase) / S;
+    a.nunits = (a.hi - 1 + a.phase) / S - a.first_unit + 1;
+    const uint32_t waves = cached || cfg.capped ? 4 : 1;
+    uint64_t g = (a.nunits + waves - 1) / waves;
+    if (cfg.capped && g > cfg.max_wgs) g = cfg.max_wgs;
+    if (g > (1u << 30) / waves) g = (1u << 30) / waves;      // a wave takes more than one unit then
+    hipLaunchKernelGGL(fn, dim3((uint32_t)g), dim3(64 * waves), 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc,
+                         const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
+                         const LaunchCfg &cfg, hipStream_t stream)
+{
+    if (lo >= hi) return hipSuccess;
+    if (hi > pt.L) return hipErrorInvalidValue;
+    StreamArgs a{};
+    a.pt = pt;
+    a.tab = tab;
+    a.dtab = dtab;
+    a.vb = dst_vbase;
+    a.lo = lo;
+    a.hi = hi;
+    a.last = acc ? kLastDest : kLastTable;
+    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, cfg, stream);
+}
+
+hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,
+                          uint64_t lo, uint64_t hi, const LaunchCfg &cfg, hipStream_t stream)
+{
+    if (lo >= hi) return hipSuccess;
+    if (hi > pt.L) return hipErrorInvalidValue;
+    StreamArgs a{};
+    a.pt = pt;
+    a.dtab = tab;
+    a.cbase = src_vbase;
+    a.lo = lo;
+    a.hi = hi;
+    a.last = kLastContig;
+    return launch_stream(a, 1, src_vbase, cfg, stream);
+}
+
+}  // namespace reft

@@ -1,0 +1,168 @@
+"""GPU parity of the ragged stream kernel at the places where it can go wrong: span boundaries near
+the ends of its 16-byte chunks, its KiB steps and its units, spans shorter than a chunk, empty ones,
+ranges that start and end anywhere, and streams on both sides of the size at which it changes from
+cached to streaming accesses, from four waves per workgroup to one, and from 1 KiB per step to more.
+Bytes: equal to the oracle or wrong."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2310_12670_amd as reft
+
+pytestmark = pytest.mark.gpu
+CANARY = 0x96
+GUARD = 512
+NAMES = ("unroll", "nontemporal", "max_wgs", "burst", "dma_min_bytes", "gather_min_pieces")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    d = torch.device("cuda:0")
+    torch.cuda.set_device(d)
+    return d
+
+
+@pytest.fixture(autouse=True)
+def stream_kernel_only():
+    saved = {n: reft.reft_get_tunable(n) for n in NAMES}
+    reft.reft_set_tunable("burst", 0)
+    yield
+    for n, v in saved.items():
+        reft.reft_set_tunable(n, v)
+
+
+def arena(sizes, phases, dev, gen):
+    starts, pos = [], GUARD
+    for n, ph in zip(sizes, phases):
+        starts.append(pos + int(ph))
+        pos += (n + int(ph) + 31) // 16 * 16
+    raw = torch.randint(0, 256, (pos + GUARD,), dtype=torch.uint8, device=dev, generator=gen)
+    return raw, [raw[a:a + n] for a, n in zip(starts, sizes)]
+
+
+def check_all(dev, sizes, k, buckets, seed, align):
+    """Encode, decode, pack, unpack and a staged snapshot and restore that gather every byte."""
+    rng = np.random.default_rng(seed)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+    T, L = len(sizes), sum(sizes)
+
+    def phases():
+        return rng.integers(0, 16, T) // align * align
+
+    held = [arena(sizes, phases(), dev, gen) for _ in range(k)]
+    shards = [h[1] for h in held]
+    streams = [oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in shards]
+    parity = oracle.encode(streams)
+    plan = reft.reft_plan_create(sizes, buckets)
+    try:
+        def guarded(phase):
+            raw = torch.full((L + 2 * GUARD + phase,), CANARY, dtype=torch.uint8, device=dev)
+            return raw, raw[GUARD + phase:GUARD + phase + L]
+
+        def check(raw, view, want, what):
+            r = raw.cpu().numpy()
+            at = view.storage_offset()
+            assert np.array_equal(r[at:at + L], want), what
+            assert np.all(r[:at] == CANARY) and np.all(r[at + L:] == CANARY), what + ": wrote outside"
+
+        def check_spans(raw, spans, want, what):
+            r = raw.cpu().numpy()
+            mask = np.ones(r.shape, bool)
+            for t in spans:
+                mask[t.storage_offset():t.storage_offset() + t.numel()] = False
+            got = np.concatenate([r[t.storage_offset():t.storage_offset() + t.numel()] for t in spans])
+            assert np.array_equal(got, want), what
+            assert np.all(r[mask] == CANARY), what + ": wrote outside"
+
+        def fresh():
+            raw, spans = arena(sizes, phases(), dev, gen)
+            raw.fill_(CANARY)
+            return raw, spans
+
+        phase = int(rng.integers(0, 16)) // align * align
+        raw, par = guarded(phase)
+        reft.reft_parity_encode(plan, [t for sh in shards for t in sh], k, par)
+        check(raw, par, parity, "encode")
+        lost = int(rng.integers(k))
+        raw2, outs = fresh()
+        rows = [None if s == lost else t for s, sh in enumerate(shards) for t in sh]
+        reft.reft_reconstruct_spans(plan, rows, k, lost, par, outs)
+        check_spans(raw2, outs, streams[lost], "decode")
+        raw, packed = guarded(phase)
+        reft.reft_pack_device(plan, shards[0], packed)
+        check(raw, packed, streams[0], "pack")
+        raw2, outs = fresh()
+        reft.reft_unpack_device(plan, packed, outs)
+        check_spans(raw2, outs, streams[0], "unpack")
+        reft.reft_set_tunable("dma_min_bytes", 1 << 62)
+        reft.reft_set_tunable("gather_min_pieces", 1)
+        ring = torch.empty(2 * reft.reft_plan_staging_slot_bytes(plan), dtype=torch.uint8, device=dev)
+        host = torch.empty(L, dtype=torch.uint8, pin_memory=True)
+        reft.reft_snapshot_pack(plan, shards[0], ring, host)
+        reft.reft_snapshot_wait(plan)
+        assert np.array_equal(host.numpy(), streams[0]), "staged snapshot"
+        raw2, outs = fresh()
+        reft.reft_restore(plan, host, ring, outs)
+        reft.reft_restore_wait(plan)
+        check_spans(raw2, outs, streams[0], "staged restore")
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)
+
+
+def boundary_sizes(rng):
+    """Spans whose boundaries fall 1 .. 17 bytes around multiples of 1 KiB, with runs of spans of 0 to
+    17 bytes between them."""
+    cuts = set()
+    for m in range(1, 48):
+        for _ in range(int(rng.integers(0, 4))):
+            cuts.add(1024 * m + int(rng.integers(-17, 18)))
+    at = sorted(cuts)
+    sizes = list(np.diff([0] + at + [1024 * 49 + int(rng.integers(0, 1024))]))
+    for _ in range(6):
+        i = int(rng.integers(0, len(sizes) + 1))
+        sizes[i:i] = [int(x) for x in rng.integers(0, 18, int(rng.integers(1, 90)))]
+    return [int(x) for x in sizes]
+
+
+@pytest.mark.parametrize("unroll,max_wgs,nt", [(1, 0, 1), (1, 2, 0), (2, 3, 1), (4, 1, 1), (4, 64, 0)])
+@pytest.mark.parametrize("k", [1, 2, 5, 8, 9, 17])
+def test_boundaries(dev, k, unroll, max_wgs, nt):
+    reft.reft_set_tunable("unroll", unroll)
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    reft.reft_set_tunable("nontemporal", nt)
+    rng = np.random.default_rng(1000 * k + 10 * unroll + max_wgs)
+    for align in (1, 4, 16):
+        sizes = boundary_sizes(rng)
+        if align > 1:
+            sizes = [(n + align - 1) // align * align for n in sizes]
+        L, buckets = sum(sizes), []
+        while L:
+            buckets.append(min(L, int(rng.integers(1, 9000))))
+            L -= buckets[-1]
+        check_all(dev, sizes, k, buckets, seed=k * 64 + unroll * 8 + align, align=align)
+
+
+# one launch below and one above the traffic at which the launch changes, for every number of
+# sources whose rule differs, with short and with long spans
+@pytest.mark.parametrize("k", [1, 2, 3, 6, 8])
+@pytest.mark.parametrize("mean", [40_000, 3_000_000])
+@pytest.mark.parametrize("traffic", [80 << 20, 130 << 20])
+def test_sizes_around_the_launch_rule(dev, k, mean, traffic):
+    rng = np.random.default_rng(k + mean + traffic)
+    L = traffic // (k + 1)
+    sizes = []
+    while sum(sizes) < L:
+        sizes.append(int(rng.integers(mean // 2, mean * 3 // 2)) | 1)
+    check_all(dev, sizes, k, None, seed=k, align=1)
+
+
+def test_more_spans_than_one_search_step(dev):
+    """Blocks of the look-up table that own several hundred spans, and wide gaps of empty ones."""
+    rng = np.random.default_rng(5)
+    sizes = [int(x) for x in rng.integers(0, 3, 20000)] + [100_000] + [0] * 500 + [int(x) for x in rng.integers(0, 40, 9000)]
+    check_all(dev, sizes, 3, None, seed=11, align=1)
