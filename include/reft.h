@@ -115,11 +115,11 @@ int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *
 /* ---- S1 + S2 + S3: bucketed snapshot of one shard into pinned host memory -----------------------
  * Bucket by bucket, in order, the shard's stream is moved from the ragged span tensors to
  * host_dst + B_b.  Two transports, chosen per call by the staging argument:
- *   staged (staging != NULL)  the transport for snapshots taken beside training.  Every piece
- *       (bucket x span) of at least "dma_min_bytes" is copied by hipMemcpyAsync on copy_stream
- *       straight from its tensor to host_dst: no kernel runs, so kernels of the training step
- *       are not disturbed.  Smaller pieces are copied the same way when few lie together; a run
- *       of at least "gather_min_pieces" consecutive small pieces within a bucket is gathered by
+ *   staged (staging != NULL)  the transport for snapshots taken beside training.  Every span
+ *       of at least "dma_min_bytes" (in the call's bucket range) is copied by hipMemcpyAsync on
+ *       copy_stream straight from its tensor to host_dst: no kernel runs, so kernels of the training
+ *       step are not disturbed.  Smaller spans are copied the same way when few lie together; a run
+ *       of at least "gather_min_pieces" consecutive pieces of them within a bucket is gathered by
  *       one kernel launch on pack_stream into a slot of the staging ring and leaves as one copy
  *       (many small tensors would otherwise mean thousands of tiny transfers).  The ring's slots
  *       form two groups used alternately; the two streams synchronise through events once per
@@ -394,10 +394,10 @@ int reft_restore_wait(reft_plan *plan);
  *                  unpack and ordinary XOR kernels take fewer where that is faster.
  *   "link_wgs"     cap on workgroups of kernels bound by the host link (default 32; kernels
  *                  that write host memory use half as many again, those that read it twice as many).
- *   "dma_min_bytes"     staged transport: pieces of at least this size travel by DMA alone
- *                  (default 65536; 0 = every piece; a huge value = none, everything is gathered).
- *   "gather_min_pieces" staged transport: shortest run of smaller pieces that is gathered by a
- *                  kernel instead of being copied piece by piece (default 8, at least 1).
+ *   "dma_min_bytes"     staged transport: spans of at least this size travel by DMA alone
+ *                  (default 1 MiB; 0 = every span; a huge value = none, everything is gathered).
+ *   "gather_min_pieces" staged transport: shortest run of pieces of smaller spans that is gathered
+ *                  by a kernel instead of being copied piece by piece (default 8, at least 1).
  *   "dma_streams"  staged transport: 1 (default) = all piece copies on copy_stream; 2 = they
  *                  alternate between copy_stream and a helper stream owned by the plan (forked from
  *                  and joined to copy_stream, default priority), which hides the set-up gap between

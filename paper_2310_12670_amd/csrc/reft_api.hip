@@ -55,7 +55,7 @@ static std::atomic<uint64_t> g_tile_shift{18};   // read at plan creation
 static std::atomic<uint64_t> g_host_only{0};     // read at plan creation: no device tables
 static std::atomic<uint64_t> g_link_wgs{32};     // grid cap of kernels bound by the host link
 static std::atomic<uint64_t> g_small_pieces{1}; // spans starting in a tile that make it count as dense
-static std::atomic<uint64_t> g_dma_min{65536};   // pieces of at least this many bytes are copied by DMA
+static std::atomic<uint64_t> g_dma_min{1 << 20}; // spans of at least this many bytes are copied by DMA
 static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller pieces worth a gather kernel
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
@@ -179,7 +179,7 @@ struct Event {
 struct Run {            // stream range [a, b) of consecutive small pieces: gather kernel + one copy
     uint64_t a, b;
 };
-struct Dma {            // one piece (bucket x span) copied by the DMA path straight from its tensor
+struct Dma {            // a span, or a bucket's piece of one, copied by the DMA path straight from its tensor
     uint64_t o, n, span;
 };
 // How the bytes of a bucket range travel in the staged transport (see classify_pieces); depends
@@ -807,17 +807,22 @@ extern "C" int reft_plan_burst_stats(reft_plan *p, uint64_t stats[4])
 // ------------------------------------------------------------------------------------------------
 // how the bytes of a bucket range travel between the tensors and the host (staged transport)
 // ------------------------------------------------------------------------------------------------
-// A piece of at least dma_min bytes needs no kernel: the runtime's copy engines move it between
-// the tensor and the host buffer, which costs kernels running beside it next to nothing.  Smaller
-// pieces are worth a copy of their own only when few of them lie together; a run of at least
-// gather_min consecutive small pieces inside one bucket is gathered into a staging slot by one
-// kernel launch and leaves as one copy (many small tensors would otherwise mean thousands of tiny
-// transfers).
+// A span of at least dma_min bytes (in the range) needs no kernel: the runtime's copy engines move it
+// between the tensor and the host buffer in one copy, wherever bucket boundaries fall, which costs
+// kernels running beside it next to nothing.  Smaller spans are worth copies of their own only when
+// few of them lie together; a run of at least gather_min consecutive pieces of them inside one
+// bucket is gathered into a staging slot by one kernel launch and leaves as one copy.
+//
+// Where the line lies: a copy costs 9.3 us on the link beside its bytes, as much as 530 KB (spans of
+// 64 KiB, 256 KiB, 1 MiB, 4 MiB one by one: 6.3, 18.6, 37.5, 50.1 GB/s; gathered: 54.8 at all sizes);
+// gathering a span of 1 MiB costs the device 0.4 us, which kernels beside it lose.
 static void classify_pieces(const reft_plan *p, uint64_t bucket_begin, uint64_t bucket_end,
                             uint64_t dma_min, uint64_t gather_min, std::vector<Run> &runs,
                             std::vector<Dma> &dmas)
 {
-    std::vector<Dma> pending;
+    if (bucket_begin >= bucket_end) return;
+    const uint64_t lo = p->bstart[bucket_begin], hi = p->bstart[bucket_end];
+    std::vector<Dma> pending;                            // pieces of small spans, all in bucket b
     auto flush = [&]() {
         if (pending.empty()) return;
         if (pending.size() >= gather_min)
@@ -826,53 +831,27 @@ static void classify_pieces(const reft_plan *p, uint64_t bucket_begin, uint64_t 
             dmas.insert(dmas.end(), pending.begin(), pending.end());
         pending.clear();
     };
-    uint64_t i = 0;
-    for (uint64_t b = bucket_begin; b < bucket_end; ++b) {
-        const uint64_t lo = p->bstart[b], hi = p->bstart[b + 1];
-        if (b == bucket_begin) {
-            // the span that owns byte lo: last one with off <= lo that is not empty
-            uint64_t l = 0, h = p->T;
-            while (h - l > 1) {
-                const uint64_t m = (l + h) / 2;
-                if (p->off[m] <= lo) l = m;
-                else h = m;
-            }
-            i = l;
+    uint64_t b = bucket_begin;
+    // the span that owns byte lo: the last one that starts at or before it
+    uint64_t i = (uint64_t)(std::upper_bound(p->off.begin(), p->off.end() - 1, lo) - p->off.begin()) - 1;
+    for (; i < p->T && p->off[i] < hi; ++i) {
+        uint64_t o = p->off[i] < lo ? lo : p->off[i];
+        const uint64_t e = p->off[i + 1] < hi ? p->off[i + 1] : hi;
+        if (o >= e) continue;                            // no bytes
+        if (e - o >= dma_min) {
+            flush();
+            dmas.push_back(Dma{o, e - o, i});
+            continue;
         }
-        for (uint64_t o = lo; o < hi;) {
-            while (p->off[i + 1] <= o) ++i;              // o < hi <= L = off[T]
-            const uint64_t pe = p->off[i + 1] < hi ? p->off[i + 1] : hi;
-            // (a piece carried over from the previous bucket, see below, leaves now unless the
-            // bucket's first piece is the large rest of its span: a run never crosses a bucket)
-            if (o == lo && !pending.empty() &&
-                !(pe - o >= dma_min && pending.back().span == i &&
-                  pending.back().o + pending.back().n == o))
+        while (o < e) {
+            if (o >= p->bstart[b + 1]) {                 // a run never crosses a bucket
                 flush();
-            // A bucket boundary is no reason to split a copy that needs no staging: a piece that
-            // continues the previous copy's span is added to that copy, and a small first piece of
-            // a span is carried into the large one that follows it.
-            if (pending.empty() && !dmas.empty() && dmas.back().span == i &&
-                dmas.back().o + dmas.back().n == o && dmas.back().n >= dma_min) {
-                dmas.back().n += pe - o;
-            } else if (pe - o >= dma_min) {
-                uint64_t start = o;
-                if (!pending.empty() && pending.back().span == i &&
-                    pending.back().o + pending.back().n == o) {
-                    start = pending.back().o;
-                    pending.pop_back();
-                }
-                flush();
-                dmas.push_back(Dma{start, pe - start, i});
-            } else {
-                pending.push_back(Dma{o, pe - o, i});
+                while (o >= p->bstart[b + 1]) ++b;       // o < hi = bstart[bucket_end]
             }
+            const uint64_t pe = p->bstart[b + 1] < e ? p->bstart[b + 1] : e;
+            pending.push_back(Dma{o, pe - o, i});
             o = pe;
         }
-        // a run never crosses a bucket; a single small piece at the bucket's end may still be
-        // the head of a span that continues in the next bucket
-        if (pending.size() == 1 && b + 1 < bucket_end && p->off[pending.back().span + 1] > hi)
-            continue;
-        flush();
     }
     flush();
 }
