@@ -4,12 +4,13 @@ from __future__ import annotations
 import os
 import re
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libreft.so")
 SOURCES = ["reft_api.hip", "reft_kernels.hip", "reft_stream.hip"]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          # Packed-FP32 instruction selection off for every kernel in the library.  The feature
          # belongs to the gfx950 device pass, where it takes effect (a float2 multiply-add compiles
          # to v_pk_fma_f32 without it and to two v_fma_f32 with it).  hipcc hands the same -Xclang
@@ -53,16 +54,28 @@ def check_burst_registers(compiler_output: str) -> dict:
 
 
 def build(verbose: bool = False) -> str:
-    cmd = ["hipcc", *FLAGS, "-o", LIB, *[os.path.join(CSRC, s) for s in SOURCES]]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
-    counts = check_burst_registers(res.stdout)
+    """Compile the sources side by side, then link."""
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        cmds = [["hipcc", *FLAGS, "-c", "-o", o, os.path.join(CSRC, s)] for s, o in zip(SOURCES, objs)]
+        if verbose:
+            for cmd in cmds:
+                print(" ".join(cmd), flush=True)
+        procs = [subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+                 for cmd in cmds]
+        outs = [p.communicate()[0] for p in procs]
+        for p, text in zip(procs, outs):
+            if p.returncode != 0:
+                raise RuntimeError("hipcc failed:\n" + text)
+        link = subprocess.run(["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB, *objs],
+                              stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if link.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + link.stdout)
+    output = "\n".join(outs)
+    counts = check_burst_registers(output)
     if verbose:
         # the resource remarks and the source lines they quote are not worth showing
-        print("\n".join(l for l in res.stdout.splitlines()
+        print("\n".join(l for l in output.splitlines()
                         if "remark:" not in l and not re.match(r"\s*\d*\s*\|", l)
                         and HOST_PASS_NOTE not in l))
         print("burst kernels: %d instantiations, at most %d VGPRs" % (len(counts), max(counts.values())))

@@ -7,7 +7,8 @@
 namespace reft {
 
 constexpr int kThreads = 256;      // 4 wavefronts of 64 lanes per workgroup
-constexpr int kMaxSrc = 8;         // sources XORed by one launch; more are chained
+constexpr int kMaxSrc = 8;         // sources XORed by one launch of the burst and contiguous kernels
+constexpr int kMaxStreamSrc = 16;  // ... and of the stream kernel
 
 struct LaunchCfg {
     uint32_t max_wgs;              // cap on the grid size (>= 1) in workgroups of kThreads
@@ -27,6 +28,7 @@ struct PlanTables {
     uint64_t T;
     uint64_t L;
     uint32_t tile_shift;           // block = 1 << tile_shift stream bytes
+    bool even;                     // every span starts at a multiple of 16 stream bytes
 };
 
 // Parameters of the gather variant that writes in chip-wide bursts (see k_gather_burst).
@@ -51,16 +53,16 @@ struct SrcBases {
 // The destination address of stream byte o, for o in [lo, hi), is dst_vbase + o, or, when dtab
 // (one row of T span pointers) is not null, the byte's place in the destination's own span.
 // tab holds nrows rows of T span pointers (row stride T); the kernel XORs the rows' streams and,
-// if acc, the destination's current contents.  nrows + acc <= kMaxSrc.
+// if acc, the destination's current contents.  nrows + acc <= kMaxStreamSrc.
 hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc,
                          const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
                          const LaunchCfg &cfg, hipStream_t stream);
 
-// The same result as launch_gather, by the burst kernel.  With dtab == null the destination is
+// The same result as launch_gather for up to kMaxSrc rows, by the burst kernel.  With dtab == null the destination is
 // contiguous and vb its virtual base.  With dtab, every span with bytes must
 // satisfy (dtab[i] - off[i]) mod 16 == vb mod 16 (the caller checks; otherwise use launch_gather).
 // stage_bytes: a multiple of 4096, at most 65536.
-hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc,
+hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows,
                                const uint64_t *dtab, uint64_t vb, uint64_t lo, uint64_t hi,
                                const LaunchCfg &cfg, const BurstCfg &bc, hipStream_t stream);
 

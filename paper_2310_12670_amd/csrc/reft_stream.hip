@@ -271,29 +271,47 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 // fewer to dispatch; long streams prefer single waves, 4.12 against 4.23 ms for 25.8 GB of copies)
 // and units of 1 KiB (16 against 19 and 20 us with 2 and 4 KiB).
 constexpr uint64_t kCachedTraffic = 96ull << 20;
-// Spans of this size on average leave few units shared.
+// Spans of this size on average leave few units shared; if they also start at multiples of 16 the
+// sources' cache lines are not split between units.
 constexpr uint64_t kLongSpan = 1ull << 20;
 
 // KiB per wave and source for `nsrc` sources and long streams.  Enough must be in flight to cover the
 // look-ups in front of the data, but wider windows cost bandwidth (us for U = 1, 2, 4):
-//   long spans    1 source 5657, 4088, 4178 (25.8 GB); 2: 861, 769, 798 (4.9 GB); 3: 1026, 1034, 1071
-//                 (6.6 GB); 4: 1222, 1368, 1368 (8.2 GB); 6: 1835, 1939, 2008 (11.5 GB)
-//   short spans   1 source 547, 411, 401 (2.1 GB); 4: 69, 66, 65 (0.3 GB); 8: 279, 265, 269 (1.2 GB)
-static uint32_t long_stream_unroll(int nsrc, bool long_spans)
+//   long, even    1 source 5657, 4088, 4178 (25.8 GB); 2: 861, 769, 798 (4.9 GB); 3: 1026, 1034, 1071
+//                 (6.6 GB); 4: 1222, 1368, 1368 (8.2 GB); 6: 1835, 1939, 2008 (11.5 GB); 16: 2298, 2445
+//                 (14.3 GB)
+//   others        1 source 547, 411, 401 (2.1 GB); 4: 69, 66, 65 (0.3 GB); 8: 279, 265, 269 (1.2 GB);
+//                 15, at odd offsets: 2736, 2640 (14.4 GB)
+static uint32_t long_stream_unroll(int nsrc, bool long_even_spans)
 {
-    if (nsrc == 1) return long_spans ? 2 : 4;
-    return nsrc == 2 || !long_spans ? 2 : 1;
+    if (nsrc == 1) return long_even_spans ? 2 : 4;
+    return nsrc == 2 || !long_even_spans ? 2 : 1;
 }
+
+#define REFT_PICK_MANY(K)                                                                         \
+    (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
+                     : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
 
 static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, LaunchCfg cfg, hipStream_t stream)
 {
     void (*fn)(const StreamArgs) = nullptr;
     const bool cached = (uint64_t)(nsrc + 1) * (a.hi - a.lo) <= kCachedTraffic;
     // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
-    uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc, a.pt.L / a.pt.T >= kLongSpan);
+    uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc, a.pt.even && a.pt.L / a.pt.T >= kLongSpan);
     if (unroll < cfg.unroll) cfg.unroll = unroll;
     if (cached && !cfg.capped) cfg.nontemporal = false;
-    REFT_PICK_K(k_stream, fn, nsrc)
+    if (nsrc > kMaxSrc && cfg.unroll > 2) cfg.unroll = 2;    // 2 KiB of 9 sources and more: 18 loads a lane
+    switch (nsrc) {
+    case 9: fn = REFT_PICK_MANY(9); break;
+    case 10: fn = REFT_PICK_MANY(10); break;
+    case 11: fn = REFT_PICK_MANY(11); break;
+    case 12: fn = REFT_PICK_MANY(12); break;
+    case 13: fn = REFT_PICK_MANY(13); break;
+    case 14: fn = REFT_PICK_MANY(14); break;
+    case 15: fn = REFT_PICK_MANY(15); break;
+    case 16: fn = REFT_PICK_MANY(16); break;
+    default: REFT_PICK_K(k_stream, fn, nsrc)
+    }
     // units start where the contiguous operand is 16-byte aligned
     const uint64_t S = 1024ull * cfg.unroll;
     a.phase = (uint32_t)contig & 15u;
