@@ -308,9 +308,9 @@ static uint64_t device_view_of_host(const void *host)
     return (uint64_t)(uintptr_t)d;
 }
 
-static int make_event(Event &e)
+static int make_event(Event &e, unsigned flags = hipEventDisableTiming)
 {
-    HIPCHK(hipEventCreateWithFlags(&e.ev, hipEventDisableTiming));
+    HIPCHK(hipEventCreateWithFlags(&e.ev, flags));
     e.recorded = false;
     return REFT_OK;
 }
@@ -642,8 +642,13 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->scratch = ds->scratch;
     for (int i = 0; i < kRing; ++i) {
         if ((rc = make_event(p->ring[i].uploaded))) return rc;
+        // A use of a table is only ever waited for (by the host, so that the table may be overwritten);
+        // nothing is read that the kernels in front of the event wrote.  So the event needs no
+        // system fence, which would write the caches back behind every call: 4 x 14.7 MB encoded
+        // call after call 16.2 us with it, 14.2 without.
         for (int u = 0; u < kUsers; ++u)
-            if ((rc = make_event(p->ring[i].used[u]))) return rc;
+            if ((rc = make_event(p->ring[i].used[u], hipEventDisableTiming | hipEventDisableSystemFence)))
+                return rc;
     }
     for (int i = 0; i < kGroups; ++i) {
         if ((rc = make_event(p->pack_filled[i])) || (rc = make_event(p->pack_free[i])) ||
