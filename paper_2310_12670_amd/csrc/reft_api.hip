@@ -226,7 +226,6 @@ struct reft_plan {
     uint64_t T = 0, NB = 0, L = 0, max_bucket = 0;
     uint32_t tile_shift = 16;
     uint32_t lookup_shift = 16;       // blocks of the device's look-up table
-    bool even = true;                 // every span starts at a multiple of 16 stream bytes
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
     std::vector<uint64_t> bstart;     // [NB+1]
@@ -276,7 +275,7 @@ struct reft_plan {
     uint32_t *burst_ctr = nullptr;
     uint32_t burst_next = 0;
 
-    PlanTables tables() const { return PlanTables{d_off, d_first, T, L, lookup_shift, even}; }
+    PlanTables tables() const { return PlanTables{d_off, d_first, T, L, lookup_shift}; }
 };
 
 static LaunchCfg launch_cfg(const reft_plan *p)
@@ -548,7 +547,6 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
         if (__builtin_add_overflow(p->off[t], span_nbytes[t], &p->off[t + 1]))
             return fail(REFT_ESIZE, "reft_plan_create: stream length overflows 64 bits");
     p->L = p->off[T];
-    for (uint64_t t = 0; t < T; ++t) p->even = p->even && p->off[t] % 16 == 0;
 
     // buckets
     p->bstart.push_back(0);

@@ -28,7 +28,6 @@ struct PlanTables {
     uint64_t T;
     uint64_t L;
     uint32_t tile_shift;           // block = 1 << tile_shift stream bytes
-    bool even;                     // every span starts at a multiple of 16 stream bytes
 };
 
 // Parameters of the gather variant that writes in chip-wide bursts (see k_gather_burst).

@@ -40,6 +40,19 @@ struct StreamArgs {
     uint32_t last;           // LastRow
 };
 
+// The tables do not change while the kernel runs; read through the constant address space, entries at
+// a uniform index are scalar loads (through ordinary pointers the compiler takes vector loads, since
+// the kernel's stores might alias, and then waits for them one by one).
+#define REFT_CONST __attribute__((address_space(4)))
+__device__ __forceinline__ uint64_t entry(const uint64_t *tab, uint64_t i)
+{
+    return ((const REFT_CONST uint64_t *)(uint64_t)tab)[i];
+}
+__device__ __forceinline__ uint32_t entry(const uint32_t *tab, uint64_t i)
+{
+    return ((const REFT_CONST uint32_t *)(uint64_t)tab)[i];
+}
+
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l)
 {
     const uint32_t a = __builtin_amdgcn_readlane((uint32_t)v, l);
@@ -58,10 +71,10 @@ struct Owner {
 // number of them at or below x says how far to go on.
 __device__ __forceinline__ void locate(const PlanTables &pt, Owner &o, uint64_t i, uint64_t x, uint32_t lane)
 {
-    o.b = pt.off[i];
+    o.b = entry(pt.off, i);
     for (;; i += 64) {
         const uint64_t at = i + 1 + lane < pt.T ? i + 1 + lane : pt.T;
-        o.ends = pt.off[at];                                   // off[T] = L > x ends the search
+        o.ends = entry(pt.off, at);                                   // off[T] = L > x ends the search
         o.c = (uint32_t)__popcll(__ballot(o.ends <= x));
         if (o.c) o.b = readlane64(o.ends, o.c - 1);
         if (o.c < 64) break;
@@ -77,9 +90,9 @@ __device__ __forceinline__ uint64_t source_of(const StreamArgs &a, int j, uint64
 {
     if (j == K - 1 && a.last != kLastTable) {
         if (a.last == kLastContig) return a.cbase + b;
-        return a.dtab ? a.dtab[q] : a.vb + b;
+        return a.dtab ? entry(a.dtab, q) : a.vb + b;
     }
-    return a.tab[(uint64_t)j * a.pt.T + q];
+    return entry(a.tab, (uint64_t)j * a.pt.T + q);
 }
 
 template <bool NT>
@@ -89,23 +102,92 @@ __device__ __forceinline__ void st16_any(uint64_t p, u32x4 v)
     else *(REFT_GLOBAL u32x4_any *)p = v;
 }
 
-// V KiB of span o.i from stream byte x on, wholly inside the span and the range.
-template <int K, int V, bool NT>
-__device__ __forceinline__ void move_uniform(const StreamArgs &a, const Owner &o, uint64_t x,
-                                             uint32_t lane)
+// The XOR of the 16 bytes at address(j), j < K; all loads before the first use.
+template <int K, bool NT, class Address>
+__device__ __forceinline__ u32x4 xor_16(Address address)
 {
-    const uint64_t r = x - o.b;
-    const uint64_t d = a.dtab ? a.dtab[o.i] + r : a.vb + x;
     gcptr16 s[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, o.i, o.b) + r);
-    u32x4 v[V];
+    for (int j = 0; j < K; ++j) s[j] = as_gc16(address(j));
+    u32x4 t[K];
 #pragma unroll
-    for (int u = 0; u < V; ++u) v[u] = ld16<NT>(s[0] + lane + u * 64);
+    for (int j = 0; j < K; ++j) t[j] = ld16<NT>(s[j]);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 v = t[0];
 #pragma unroll
-    for (int j = 1; j < K; ++j) {
+    for (int j = 1; j < K; ++j) v ^= t[j];
+    return v;
+}
+
+// 1 KiB of span o.i from stream byte x on, wholly inside the span and the range.
+template <int K, bool NT>
+__device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, uint64_t x, uint32_t lane)
+{
+    const uint64_t r = x - o.b + lane * 16;
+    const u32x4 v = xor_16<K, NT>([&](int j) { return source_of<K>(a, j, o.i, o.b) + r; });
+    st16_any<NT>(a.dtab ? entry(a.dtab, o.i) + r : a.vb + x + lane * 16, v);
+}
+
+// The unit of V KiB at stream byte x, wholly inside span i and the range.  Inside a span the units
+// move together by up to 127 bytes so that the first source, and with it those that are aligned like
+// it, is read in whole cache lines, or, where it stands (nearly) alone, the destination is written in
+// such: a unit then starts where the one before it in the span ends, the span's first such unit moves
+// the bytes in front of it as well, and the last one, behind which there is no room, stays where it
+// is; the few bytes that come twice get the same value.  Where the destination is a source nothing may
+// come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
+// 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
+template <int K, int V, bool NT>
+__device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane)
+{
+    constexpr uint32_t S = 1024 * V;
+    // everything that is known of span i in one go, without branches between the loads (where there
+    // is no such table, an entry of another one is loaded and not used)
+    const uint64_t b = entry(a.pt.off, i), e = entry(a.pt.off, i + 1);
+    const uint64_t dt = entry(a.dtab ? a.dtab : a.pt.off, i);
+    uint64_t p[K];
 #pragma unroll
-        for (int u = 0; u < V; ++u) v[u] ^= ld16<NT>(s[j] + lane + u * 64);
+    for (int j = 0; j < K - 1; ++j) p[j] = entry(a.tab, (uint64_t)j * a.pt.T + i);
+    p[K - 1] = entry(a.last == kLastTable ? a.tab + (uint64_t)(K - 1) * a.pt.T : a.pt.off, i);
+    const uint64_t r = x - b;
+    uint64_t d = (a.dtab ? dt : a.vb + b) + r;
+    if (a.last == kLastContig) p[K - 1] = a.cbase + b;
+    if (a.last == kLastDest) p[K - 1] = d - r;
+    gcptr16 s[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) s[j] = as_gc16(p[j] + r);
+    uint32_t alike = 0;
+#pragma unroll
+    for (int j = 1; j < K; ++j) alike += (((uint32_t)(uint64_t)s[j] ^ (uint32_t)(uint64_t)s[0]) & 15u) == 0;
+    uint32_t lead = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
+    if (lead) {
+        if (a.last == kLastDest || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
+    }
+    if (lead) {
+        const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
+        if ((int64_t)x - (int64_t)S < first && lane * 16 < lead) {
+            st16_any<NT>(d + lane * 16, xor_16<K, NT>([&](int j) { return (uint64_t)s[j] + lane * 16; }));
+        }
+        d += lead;
+#pragma unroll
+        for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + lead);
+    }
+    // all loads of up to 16 chunks before the first use (left alone, the compiler alternates them)
+    constexpr int R = K * V <= 16 ? K : 16 / V;
+    u32x4 v[V] = {};
+#pragma unroll
+    for (int j = 0; j < K; j += R) {
+        u32x4 t[R][V];
+#pragma unroll
+        for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) t[q][u] = ld16<NT>(s[j + q] + lane + u * 64);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) v[u] ^= t[q][u];
+        }
     }
 #pragma unroll
     for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
@@ -115,7 +197,7 @@ __device__ __forceinline__ void move_uniform(const StreamArgs &a, const Owner &o
 template <int K>
 __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint64_t b, uint64_t p, uint32_t n)
 {
-    const uint64_t d = (a.dtab ? a.dtab[q] - b : a.vb) + p;
+    const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
     uint64_t s[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) s[j] = source_of<K>(a, j, q, b) + (p - b);
@@ -170,7 +252,7 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
         if (n < 64) break;
         base += 64;
         const uint64_t idx = base + 1 + lane < a.pt.T ? base + 1 + lane : a.pt.T;
-        ends = a.pt.off[idx];
+        ends = entry(a.pt.off, idx);
         j = 0;
     }
     // the end of span o.i + skip2, where no boundary in this KiB gave it
@@ -187,37 +269,48 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     const bool can = a.last != kLastDest || (one && hi - lo == 16);
     if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
         const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
-        const uint64_t d = (a.dtab ? a.dtab[q] - b : a.vb) + p;
-        gcptr16 s[K], s2[K];
-        uint64_t d2 = 0;
-        u32x4 v, v2;
+        const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
+        if constexpr (K <= 4) {                                // both at once, where registers allow
+            gcptr16 s[K], s2[K];
+            uint64_t d2 = 0;
+            u32x4 t[K], t2[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, q, b) + (p - b));
-        if (!one) {
-            d2 = a.dtab ? a.dtab[q2] : a.vb + w1;
+            for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, q, b) + (p - b));
+            if (!one) {
+                d2 = a.dtab ? entry(a.dtab, q2) : a.vb + w1;
 #pragma unroll
-            for (int j = 0; j < K; ++j) s2[j] = as_gc16(source_of<K>(a, j, q2, w1));
+                for (int j = 0; j < K; ++j) s2[j] = as_gc16(source_of<K>(a, j, q2, w1));
+            }
+#pragma unroll
+            for (int j = 0; j < K; ++j) t[j] = ld16<NT>(s[j]);
+            if (!one) {
+#pragma unroll
+                for (int j = 0; j < K; ++j) t2[j] = ld16<NT>(s2[j]);
+            }
+#pragma unroll
+            for (int j = 1; j < K; ++j) t[0] ^= t[j];
+            st16_any<NT>(d, t[0]);
+            if (!one) {
+#pragma unroll
+                for (int j = 1; j < K; ++j) t2[0] ^= t2[j];
+                st16_any<NT>(d2, t2[0]);
+            }
+        } else {
+            st16_any<NT>(d, xor_16<K, NT>([&](int j) { return source_of<K>(a, j, q, b) + (p - b); }));
+            if (!one)
+                st16_any<NT>(a.dtab ? entry(a.dtab, q2) : a.vb + w1,
+                             xor_16<K, NT>([&](int j) { return source_of<K>(a, j, q2, w1); }));
         }
-        v = ld16<NT>(s[0]);
-#pragma unroll
-        for (int j = 1; j < K; ++j) v ^= ld16<NT>(s[j]);
-        if (!one) {
-            v2 = ld16<NT>(s2[0]);
-#pragma unroll
-            for (int j = 1; j < K; ++j) v2 ^= ld16<NT>(s2[j]);
-        }
-        st16_any<NT>(d, v);
-        if (!one) st16_any<NT>(d2, v2);
         return;
     }
     // spans of less than 16 bytes
     uint64_t i = q, begin = b;
     for (uint64_t p = lo;;) {
-        const uint64_t e = a.pt.off[i + 1];
+        const uint64_t e = entry(a.pt.off, i + 1);
         move_bytes<K>(a, i, begin, p, (uint32_t)((e < hi ? e : hi) - p));
         if (e >= hi) break;
         p = begin = e;
-        do ++i; while (a.pt.off[i + 1] <= p);                  // p < hi <= L = off[T]
+        do ++i; while (entry(a.pt.off, i + 1) <= p);                  // p < hi <= L = off[T]
     }
 }
 
@@ -237,16 +330,14 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
         const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
         const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
         const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
-        const uint32_t first = a.pt.first_span[y0 >> a.pt.tile_shift];
+        const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
         if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
-            o.i = first & ~kWholeBlock;
-            o.b = a.pt.off[o.i];
-            move_uniform<K, U, NT>(a, o, x, lane);
+            move_unit<K, U, NT>(a, first & ~kWholeBlock, x, lane);
             continue;
         }
         locate(a.pt, o, first & ~kWholeBlock, y0, lane);
         if (y1 - y0 == S && y1 <= o.e) {
-            move_uniform<K, U, NT>(a, o, x, lane);
+            move_unit<K, U, NT>(a, o.i, x, lane);
             continue;
         }
 #pragma unroll 1
@@ -256,7 +347,7 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
             const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
             if ((int64_t)z0 >= (int64_t)z1) continue;
             if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
-            if (z1 - z0 == 1024 && z1 <= o.e) move_uniform<K, 1, NT>(a, o, xs, lane);
+            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT>(a, o, xs, lane);
             else move_shared<K, NT>(a, o, xs, z1, lane);
         }
     }
@@ -266,26 +357,27 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 // launch
 // ------------------------------------------------------------------------------------------------
 // Traffic (read and written) up to which a launch may find and leave its data in the 256 MB cache: it
-// then uses plain accesses (4 x 14.7 MB, 73 MB of traffic: 16 us, with streaming ones 18; from
-// 8 x 14.7 MB on streaming ones are as fast or faster), workgroups of four waves (16 against 17 us:
-// fewer to dispatch; long streams prefer single waves, 4.12 against 4.23 ms for 25.8 GB of copies)
-// and units of 1 KiB (16 against 19 and 20 us with 2 and 4 KiB).
+// then uses plain accesses (4 x 14.7 MB, 73 MB of traffic: 15.5 us, with streaming ones 16.9; from
+// 8 x 14.7 MB on streaming ones are as fast or faster) and workgroups of four waves (16 against 17 us:
+// fewer to dispatch; long streams prefer single waves, 4.12 against 4.23 ms for 25.8 GB of copies).
 constexpr uint64_t kCachedTraffic = 96ull << 20;
-// Spans of this size on average leave few units shared; if they also start at multiples of 16 the
-// sources' cache lines are not split between units.
-constexpr uint64_t kLongSpan = 1ull << 20;
 
-// KiB per wave and source for `nsrc` sources and long streams.  Enough must be in flight to cover the
-// look-ups in front of the data, but wider windows cost bandwidth (us for U = 1, 2, 4):
-//   long, even    1 source 5657, 4088, 4178 (25.8 GB); 2: 861, 769, 798 (4.9 GB); 3: 1026, 1034, 1071
-//                 (6.6 GB); 4: 1222, 1368, 1368 (8.2 GB); 6: 1835, 1939, 2008 (11.5 GB); 16: 2298, 2445
-//                 (14.3 GB)
-//   others        1 source 547, 411, 401 (2.1 GB); 4: 69, 66, 65 (0.3 GB); 8: 279, 265, 269 (1.2 GB);
-//                 15, at odd offsets: 2736, 2640 (14.4 GB)
-static uint32_t long_stream_unroll(int nsrc, bool long_even_spans)
+// KiB per wave and source.  Small units keep the windows narrow in which the chip moves through its
+// streams; one source alone needs two to cover the look-ups in front of the data.  us for 1 and 2 KiB:
+// 1 source 4.00 and 3.99 ms (25.8 GB in long spans), 418 and 377 us (2.1 GB in short ones); 2 sources
+// 745 and 776 (4.9 GB); 4: 1303 and 1418 (8.2 GB); 8: 2380 and 2595 (14.8 GB), 211 and 224 (1.2 GB,
+// short spans); 16: 2299 and 2405 (14.3 GB).
+static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
+
+// LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than have
+// about 96 KiB in flight between them (80 KiB beside the waves that look up): wider windows cost more
+// than they hide.  us, all that fit / so many: 4 sources 1303 / 1290 (22 waves), 6: 1848 / 1815 (15),
+// 8: 2380 / 2328 (12) and 3625 / 3565 (22.6 GB, into tensors), 16: 2299 / 2226 (8).
+static uint32_t crowd_limit(int nsrc)
 {
-    if (nsrc == 1) return long_even_spans ? 2 : 4;
-    return nsrc == 2 || !long_even_spans ? 2 : 1;
+    if (nsrc < 4) return 0;
+    const uint32_t waves = 80 / nsrc + 2 > 8 ? 80 / nsrc + 2 : 8;
+    return 160 * 1024 / waves / 512 * 512;
 }
 
 #define REFT_PICK_MANY(K)                                                                         \
@@ -297,7 +389,7 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, LaunchC
     void (*fn)(const StreamArgs) = nullptr;
     const bool cached = (uint64_t)(nsrc + 1) * (a.hi - a.lo) <= kCachedTraffic;
     // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
-    uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc, a.pt.even && a.pt.L / a.pt.T >= kLongSpan);
+    const uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc);
     if (unroll < cfg.unroll) cfg.unroll = unroll;
     if (cached && !cfg.capped) cfg.nontemporal = false;
     if (nsrc > kMaxSrc && cfg.unroll > 2) cfg.unroll = 2;    // 2 KiB of 9 sources and more: 18 loads a lane
@@ -321,7 +413,7 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, LaunchC
     uint64_t g = (a.nunits + waves - 1) / waves;
     if (cfg.capped && g > cfg.max_wgs) g = cfg.max_wgs;
     if (g > (1u << 30) / waves) g = (1u << 30) / waves;      // a wave takes more than one unit then
-    hipLaunchKernelGGL(fn, dim3((uint32_t)g), dim3(64 * waves), 0, stream, a);
+    hipLaunchKernelGGL(fn, dim3((uint32_t)g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
     return hipGetLastError();
 }
 
