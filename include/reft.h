@@ -240,10 +240,8 @@ int reft_parity_encode(reft_plan *plan, const void *const *shard_span_ptrs, uint
  * segments into parity data" while they are being gathered, section 3).  For a scheduler that
  * gathers and encodes in a bubble and lets two large copies (packed shard, parity) leave beside
  * computation, or where many small tensors would be gathered by a kernel anyway.
- * The single pass is taken where the write-burst kernel applies (see "burst"), with at most 8
- * shards, parity_dev and packed_dev aligned alike modulo 16, "unroll" 4 and "nontemporal" 1, and
- * "burst_stage_bytes" <= 36864 (two LDS images per half); otherwise the call runs the encode and
- * the pack as two launches, with the same result.
+ * The single pass takes up to 16 shards; with more the call runs the encode and the pack as separate
+ * launches, with the same result.
  * own < k; packed_cap >= L (REFT_ESIZE); neither buffer may overlap a span or the other.
  * Errors: REFT_EINVAL, REFT_ESIZE, REFT_EHIP.
  */
@@ -414,15 +412,14 @@ int reft_restore_wait(reft_plan *plan);
  *                  link in the other direction.
  *   "small_pieces" a tile in which at least this many spans start counts as dense in small spans
  *                  (default 1; 4294967295 = never, 0 = always): see "burst".
- *   "burst"        1 (default) = reft_parity_encode, reft_reconstruct_spans and the rotated calls use
- *                  the write-burst variant of the XOR kernel where it applies: a pass (up to 8 rows
- *                  each) of at least "burst_min_rows" rows (default 7), "burst_min_bytes" stream
- *                  bytes (default 8 MiB), at most one tile in eight dense in small spans (see
- *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
- *                  alike (mod 16) relative to its stream offset; reft_reconstruct uses it under
- *                  the first two conditions.  The variant keeps reads and writes apart in time: reader
- *                  waves XOR "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536)
- *                  of the stream at a time into LDS, and one writer wave per workgroup stores the
+ *   "burst"        1 (default) = reft_parity_encode and reft_parity_encode_rotated use the write-burst
+ *                  variant of the XOR kernel where it applies: at least "burst_min_rows" rows (default
+ *                  8; at most 8), "burst_min_bytes" stream bytes (default 2 GiB) and at most one tile
+ *                  in eight dense in small spans (see "small_pieces").  reft_reconstruct uses it from
+ *                  5 sources and 8 MiB on (or from those two values, where they are lower).  The
+ *                  variant keeps reads and writes apart in time: reader waves XOR
+ *                  "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536) of the
+ *                  stream at a time into LDS, and one writer wave per workgroup stores the
  *                  previous stage once all workgroups of the (persistent, "burst_wgs_per_cu" per
  *                  compute unit, default 2) grid have read theirs.  The writer waits by polling a
  *                  counter at most "burst_max_polls" times per round (default 6; 0 = never waits),

@@ -60,8 +60,8 @@ static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller piec
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
 static std::atomic<uint64_t> g_burst{1};         // parity encode may use the write-burst kernel
-static std::atomic<uint64_t> g_burst_min_rows{7};    // ... from this many sources on
-static std::atomic<uint64_t> g_burst_min_bytes{8ull << 20};  // ... and from this stream length on
+static std::atomic<uint64_t> g_burst_min_rows{8};    // ... from this many sources on
+static std::atomic<uint64_t> g_burst_min_bytes{2ull << 30};  // ... and from this stream length on
 static std::atomic<uint64_t> g_burst_stage{32768};   // stream bytes per workgroup and round
 static std::atomic<uint64_t> g_burst_wgs{2};         // resident workgroups per compute unit
 static std::atomic<uint64_t> g_burst_polls{6};       // bound on a writer wave's wait per round (0 = no waiting)
@@ -1401,25 +1401,16 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Seven and eight rows: reads and writes are separated in time with the burst kernel (6 rows,
-    // 11.5 GB: 1912 us against the stream kernel's 1835; 8 rows, 14.8 GB: 2338 against 2397) where
-    // spans are long.  More rows go through the stream kernel in one pass, up to kMaxStreamSrc.  Ragged destinations whose spans are not all aligned alike relative to their
-    // stream offsets, which the staging image cannot represent, keep the stream kernel.
-    uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
-    bool burst_ok = g_burst.load() && p->L >= g_burst_min_bytes.load() && nrows <= (uint32_t)kMaxSrc &&
-                    nrows >= g_burst_min_rows.load() && few_dense_tiles(p);
-    if (burst_ok && dst_row) {
-        bool have = false;
-        for (uint64_t t = 0; t < T && burst_ok; ++t) {
-            if (p->off[t + 1] == p->off[t]) continue;
-            const uint64_t c = ((uint64_t)(uintptr_t)dst_row[t] - p->off[t]) & 15u;
-            if (!have) { vb = c; have = true; }
-            else burst_ok = c == vb;
-        }
-    }
-    if (burst_ok) {
+    // Eight long rows into a contiguous destination: reads and writes are separated in time with the
+    // burst kernel.  TB/s, burst / stream kernel, 8 rows: 27.6 GB 6.38 / 6.29, 26.1 GB 6.38 / 6.31,
+    // 22.6 GB 6.28 / 6.32, 7.7 GB (0.9 GB a row) 6.03 / 6.14; 7 rows: 24.5 GB 6.28 / 6.31, 23.2 GB 6.43 /
+    // 6.38; into tensors 6.07 / 6.06 and less.  More rows go through the stream kernel in one pass, up
+    // to kMaxStreamSrc.
+    if (g_burst.load() && !dst_row && p->L >= g_burst_min_bytes.load() && nrows <= (uint32_t)kMaxSrc &&
+        nrows >= g_burst_min_rows.load() && few_dense_tiles(p)) {
         const BurstCfg bc = burst_cfg(ctr_ring, (*ctr_next)++ % ctr_blocks, p->num_cus);
-        HIPCHK(launch_gather_burst(pt, tab, (int)nrows, dtab, vb, 0, p->L, cfg, bc, s));
+        HIPCHK(launch_gather_burst(pt, tab, (int)nrows, (uint64_t)(uintptr_t)dst_contig, 0, p->L, cfg,
+                                   bc, s));
         return REFT_OK;
     }
     for (uint32_t done = 0; done < nrows;) {
@@ -1503,22 +1494,13 @@ extern "C" int reft_parity_encode_pack(reft_plan *p, const void *const *shard_sp
         }
     const LaunchCfg cfg = launch_cfg(p);
     const uint64_t vb = (uint64_t)(uintptr_t)parity_dev, vb2 = (uint64_t)(uintptr_t)packed_dev;
-    const uint64_t stage = g_burst_stage.load();
-    // The fused kernel applies where the burst kernel does (bytes, few span boundaries), from two rows
-    // fewer on since it saves a read of one, in one pass of at most kMaxSrc rows, with both
-    // destinations aligned alike and its one instantiation per row count (unroll 4, non-temporal); its
-    // two LDS images per half must fit a compute unit's LDS.  Otherwise: the encode and the pack as
-    // two launches.
-    const bool fused = g_burst.load() && p->L >= g_burst_min_bytes.load() && k <= (uint32_t)kMaxSrc &&
-                       k + 2 >= g_burst_min_rows.load() && few_dense_tiles(p) &&
-                       ((vb ^ vb2) & 15u) == 0 && cfg.unroll == 4 && cfg.nontemporal &&
-                       4 * (stage + 16) + 16 <= 160 * 1024;
     const uint64_t *tab = nullptr;
     int entry = 0;
     if ((rc = upload_ptrs(p, rows, k, s, &tab, &entry))) return rc;
-    if (fused) {
-        const BurstCfg bc = burst_cfg(p->burst_ctr, p->burst_next++ % kCtrBlocks, p->num_cus);
-        HIPCHK(launch_gather_burst_pack(p->tables(), tab, (int)k, vb, vb2, 0, p->L, cfg, bc, s));
+    if (k <= (uint32_t)kMaxStreamSrc) {
+        // TB/s over (k + 2) L bytes, this / a write-burst kernel with two images: 8 rows of 2.4 GB
+        // 6.24 / 6.14, of 0.6 GB 6.21 / 5.93; 5 rows 6.33 / 5.66; two launches 5.6
+        HIPCHK(launch_gather_pack(p->tables(), tab, (int)k, vb, vb2, 0, p->L, cfg, s));
     } else {
         if ((rc = xor_passes(p, tab, k, nullptr, nullptr, parity_dev, p->burst_ctr, kCtrBlocks,
                              &p->burst_next, s)))
@@ -1853,7 +1835,11 @@ extern "C" int reft_reconstruct(const void *const *shards, uint32_t k, const voi
     const uint32_t tile_shift = (uint32_t)g_tile_shift.load();
     hipStream_t st = (hipStream_t)stream;
     BurstCfg bc{};
-    const bool burst_ok = g_burst.load() && L >= g_burst_min_bytes.load();
+    // The ordinary kernel here (tiles, a persistent grid) mixes reads and writes worse than the one over
+    // span tables: the burst kernel pays from five sources and 8 MiB on (5 sources 6.05 / 6.16 TB/s,
+    // ordinary / burst, 8 sources 5.23 / 6.47), sooner only if the tunables say so.
+    const uint64_t min_rows = std::min<uint64_t>(g_burst_min_rows.load(), 5);
+    const bool burst_ok = g_burst.load() && L >= std::min<uint64_t>(g_burst_min_bytes.load(), 8ull << 20);
     uint32_t *ring = nullptr;
     int num_cus = 256;
     if (burst_ok) {
@@ -1871,7 +1857,7 @@ extern "C" int reft_reconstruct(const void *const *shards, uint32_t k, const voi
         int m = 0;
         if (done > 0) b.p[m++] = (uint64_t)(uintptr_t)out_dev;     // fold into the partial result
         while (m < kMaxSrc && done < n) b.p[m++] = src[done++];
-        if (burst_ok && (uint32_t)m >= g_burst_min_rows.load()) {
+        if (burst_ok && (uint32_t)m >= min_rows) {
             // reads and writes separated in time; folding in place is safe: a stage of the
             // output is read and, a round later, written by the same workgroup only
             bc = burst_cfg(ring, next_slot++ % kCtrBlocks, num_cus);

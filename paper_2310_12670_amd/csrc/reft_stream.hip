@@ -4,7 +4,9 @@
 //   place of stream byte o  <-  XOR over K sources of their byte o,    o in [lo, hi)
 //
 // A source is a row of span pointers or a contiguous buffer; the destination is a contiguous buffer
-// or a row of span pointers, and may itself be the last source.
+// or a row of span pointers, and may itself be the last source.  With PACK, the bytes of the first
+// source alone go to a second contiguous buffer as well (the packed stream of one shard beside the
+// parity of all), so that it is read once for both.
 //
 // The unit of work is one wavefront's: S = 1024 U consecutive stream bytes, U chunks of 16 bytes per
 // lane and source, all in flight at once.  A wave finds the span that owns its unit's first byte with
@@ -33,6 +35,7 @@ struct StreamArgs {
     const uint64_t *tab;     // rows of span pointers, row stride T
     const uint64_t *dtab;    // the destination's row, or null: contiguous
     uint64_t vb;             // contiguous destination: byte o lies at vb + o
+    uint64_t vb2;            // PACK: byte o of the first source goes to vb2 + o
     uint64_t cbase;          // kLastContig: byte o lies at cbase + o
     uint64_t lo, hi;         // stream range, lo < hi <= L
     uint64_t first_unit, nunits;
@@ -102,9 +105,10 @@ __device__ __forceinline__ void st16_any(uint64_t p, u32x4 v)
     else *(REFT_GLOBAL u32x4_any *)p = v;
 }
 
-// The XOR of the 16 bytes at address(j), j < K; all loads before the first use.
-template <int K, bool NT, class Address>
-__device__ __forceinline__ u32x4 xor_16(Address address)
+// The XOR of the 16 bytes at address(j), j < K; all loads before the first use.  With PACK the first
+// 16 go to pack.
+template <int K, bool NT, bool PACK, class Address>
+__device__ __forceinline__ u32x4 xor_16(Address address, uint64_t pack)
 {
     gcptr16 s[K];
 #pragma unroll
@@ -113,6 +117,7 @@ __device__ __forceinline__ u32x4 xor_16(Address address)
 #pragma unroll
     for (int j = 0; j < K; ++j) t[j] = ld16<NT>(s[j]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PACK) st16_any<NT>(pack, t[0]);
     u32x4 v = t[0];
 #pragma unroll
     for (int j = 1; j < K; ++j) v ^= t[j];
@@ -120,11 +125,12 @@ __device__ __forceinline__ u32x4 xor_16(Address address)
 }
 
 // 1 KiB of span o.i from stream byte x on, wholly inside the span and the range.
-template <int K, bool NT>
+template <int K, bool NT, bool PACK>
 __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, uint64_t x, uint32_t lane)
 {
     const uint64_t r = x - o.b + lane * 16;
-    const u32x4 v = xor_16<K, NT>([&](int j) { return source_of<K>(a, j, o.i, o.b) + r; });
+    const u32x4 v = xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, o.i, o.b) + r; },
+                                        a.vb2 + x + lane * 16);
     st16_any<NT>(a.dtab ? entry(a.dtab, o.i) + r : a.vb + x + lane * 16, v);
 }
 
@@ -136,7 +142,7 @@ __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, ui
 // is; the few bytes that come twice get the same value.  Where the destination is a source nothing may
 // come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
 // 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
-template <int K, int V, bool NT>
+template <int K, int V, bool NT, bool PACK>
 __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane)
 {
     constexpr uint32_t S = 1024 * V;
@@ -165,7 +171,8 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint6
     if (lead) {
         const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
         if ((int64_t)x - (int64_t)S < first && lane * 16 < lead) {
-            st16_any<NT>(d + lane * 16, xor_16<K, NT>([&](int j) { return (uint64_t)s[j] + lane * 16; }));
+            st16_any<NT>(d + lane * 16, xor_16<K, NT, PACK>([&](int j) { return (uint64_t)s[j] + lane * 16; },
+                                                            a.vb2 + x + lane * 16));
         }
         d += lead;
 #pragma unroll
@@ -183,6 +190,12 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint6
             for (int u = 0; u < V; ++u) t[q][u] = ld16<NT>(s[j + q] + lane + u * 64);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PACK) {
+            if (j == 0) {
+#pragma unroll
+                for (int u = 0; u < V; ++u) st16_any<NT>(a.vb2 + x + lead + (lane + u * 64) * 16, t[0][u]);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < R && j + q < K; ++q) {
 #pragma unroll
@@ -194,7 +207,7 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint6
 }
 
 // n bytes from stream byte p on, all inside span q (which starts at b), one by one.
-template <int K>
+template <int K, bool PACK>
 __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint64_t b, uint64_t p, uint32_t n)
 {
     const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
@@ -206,7 +219,11 @@ __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint
 #pragma unroll
         for (int j = 0; j < K; ++j) {
 #pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) v[c] ^= ld8(s[j] + (t + c < n ? t + c : n - 1));
+            for (uint32_t c = 0; c < 4; ++c) {
+                const uint8_t x = ld8(s[j] + (t + c < n ? t + c : n - 1));
+                if (PACK && j == 0 && t + c < n) st8(a.vb2 + p + t + c, x);
+                v[c] ^= x;
+            }
         }
 #pragma unroll
         for (uint32_t c = 0; c < 4; ++c)
@@ -222,7 +239,7 @@ __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint
 // then the next span's first 16: bytes that its neighbours move too are written twice, with the same
 // value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
 // the destination is a source (a byte must then be read and written once), in every straddling lane.
-template <int K, bool NT>
+template <int K, bool NT, bool PACK>
 __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
                                             uint32_t lane)
 {
@@ -287,6 +304,10 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
 #pragma unroll
                 for (int j = 0; j < K; ++j) t2[j] = ld16<NT>(s2[j]);
             }
+            if constexpr (PACK) {
+                st16_any<NT>(a.vb2 + p, t[0]);
+                if (!one) st16_any<NT>(a.vb2 + w1, t2[0]);
+            }
 #pragma unroll
             for (int j = 1; j < K; ++j) t[0] ^= t[j];
             st16_any<NT>(d, t[0]);
@@ -296,10 +317,11 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
                 st16_any<NT>(d2, t2[0]);
             }
         } else {
-            st16_any<NT>(d, xor_16<K, NT>([&](int j) { return source_of<K>(a, j, q, b) + (p - b); }));
+            st16_any<NT>(d, xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, q, b) + (p - b); },
+                                                a.vb2 + p));
             if (!one)
                 st16_any<NT>(a.dtab ? entry(a.dtab, q2) : a.vb + w1,
-                             xor_16<K, NT>([&](int j) { return source_of<K>(a, j, q2, w1); }));
+                             xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, q2, w1); }, a.vb2 + w1));
         }
         return;
     }
@@ -307,7 +329,7 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     uint64_t i = q, begin = b;
     for (uint64_t p = lo;;) {
         const uint64_t e = entry(a.pt.off, i + 1);
-        move_bytes<K>(a, i, begin, p, (uint32_t)((e < hi ? e : hi) - p));
+        move_bytes<K, PACK>(a, i, begin, p, (uint32_t)((e < hi ? e : hi) - p));
         if (e >= hi) break;
         p = begin = e;
         do ++i; while (entry(a.pt.off, i + 1) <= p);                  // p < hi <= L = off[T]
@@ -318,7 +340,7 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
 // there is one wave per unit, dispatched in order, so that the chip moves through its streams in
 // narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
 // workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
-template <int K, int U, bool NT>
+template <int K, int U, bool NT, bool PACK = false>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
     constexpr uint32_t S = 1024 * U;
@@ -332,12 +354,12 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
         const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
         const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
         if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
-            move_unit<K, U, NT>(a, first & ~kWholeBlock, x, lane);
+            move_unit<K, U, NT, PACK>(a, first & ~kWholeBlock, x, lane);
             continue;
         }
         locate(a.pt, o, first & ~kWholeBlock, y0, lane);
         if (y1 - y0 == S && y1 <= o.e) {
-            move_unit<K, U, NT>(a, o.i, x, lane);
+            move_unit<K, U, NT, PACK>(a, o.i, x, lane);
             continue;
         }
 #pragma unroll 1
@@ -347,8 +369,8 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
             const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
             if ((int64_t)z0 >= (int64_t)z1) continue;
             if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
-            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT>(a, o, xs, lane);
-            else move_shared<K, NT>(a, o, xs, z1, lane);
+            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, PACK>(a, o, xs, lane);
+            else move_shared<K, NT, PACK>(a, o, xs, z1, lane);
         }
     }
 }
@@ -384,16 +406,36 @@ static uint32_t crowd_limit(int nsrc)
     (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
                      : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
 
-static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, LaunchCfg cfg, hipStream_t stream)
+#define REFT_PICK_PACK(K) (cfg.nontemporal ? k_stream<K, 1, true, true> : k_stream<K, 1, false, true>)
+
+static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pack, LaunchCfg cfg,
+                                hipStream_t stream)
 {
     void (*fn)(const StreamArgs) = nullptr;
-    const bool cached = (uint64_t)(nsrc + 1) * (a.hi - a.lo) <= kCachedTraffic;
+    const bool cached = (uint64_t)(nsrc + (pack ? 2 : 1)) * (a.hi - a.lo) <= kCachedTraffic;
     // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
     const uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc);
     if (unroll < cfg.unroll) cfg.unroll = unroll;
     if (cached && !cfg.capped) cfg.nontemporal = false;
     if (nsrc > kMaxSrc && cfg.unroll > 2) cfg.unroll = 2;    // 2 KiB of 9 sources and more: 18 loads a lane
-    switch (nsrc) {
+    if (pack) cfg.unroll = 1;
+    switch (pack ? -nsrc : nsrc) {
+    case -1: fn = REFT_PICK_PACK(1); break;
+    case -2: fn = REFT_PICK_PACK(2); break;
+    case -3: fn = REFT_PICK_PACK(3); break;
+    case -4: fn = REFT_PICK_PACK(4); break;
+    case -5: fn = REFT_PICK_PACK(5); break;
+    case -6: fn = REFT_PICK_PACK(6); break;
+    case -7: fn = REFT_PICK_PACK(7); break;
+    case -8: fn = REFT_PICK_PACK(8); break;
+    case -9: fn = REFT_PICK_PACK(9); break;
+    case -10: fn = REFT_PICK_PACK(10); break;
+    case -11: fn = REFT_PICK_PACK(11); break;
+    case -12: fn = REFT_PICK_PACK(12); break;
+    case -13: fn = REFT_PICK_PACK(13); break;
+    case -14: fn = REFT_PICK_PACK(14); break;
+    case -15: fn = REFT_PICK_PACK(15); break;
+    case -16: fn = REFT_PICK_PACK(16); break;
     case 9: fn = REFT_PICK_MANY(9); break;
     case 10: fn = REFT_PICK_MANY(10); break;
     case 11: fn = REFT_PICK_MANY(11); break;
@@ -431,7 +473,24 @@ hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, b
     a.lo = lo;
     a.hi = hi;
     a.last = acc ? kLastDest : kLastTable;
-    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, cfg, stream);
+    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, false, cfg, stream);
+}
+
+hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
+                              uint64_t vb2, uint64_t lo, uint64_t hi, const LaunchCfg &cfg,
+                              hipStream_t stream)
+{
+    if (lo >= hi) return hipSuccess;
+    if (hi > pt.L) return hipErrorInvalidValue;
+    StreamArgs a{};
+    a.pt = pt;
+    a.tab = tab;
+    a.vb = vb;
+    a.vb2 = vb2;
+    a.lo = lo;
+    a.hi = hi;
+    a.last = kLastTable;
+    return launch_stream(a, nrows, vb, true, cfg, stream);
 }
 
 hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,
@@ -446,7 +505,7 @@ hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t sr
     a.lo = lo;
     a.hi = hi;
     a.last = kLastContig;
-    return launch_stream(a, 1, src_vbase, cfg, stream);
+    return launch_stream(a, 1, src_vbase, false, cfg, stream);
 }
 
 }  // namespace reft

@@ -43,7 +43,7 @@ def arena(sizes, phases, dev, gen):
 
 
 def check_all(dev, sizes, k, buckets, seed, align):
-    """Encode, decode, pack, unpack and a staged snapshot and restore that gather every byte."""
+    """Encode (also with pack), decode, pack, unpack and a staged snapshot and restore that gather every byte."""
     rng = np.random.default_rng(seed)
     gen = torch.Generator(device=dev)
     gen.manual_seed(seed)
@@ -86,6 +86,12 @@ def check_all(dev, sizes, k, buckets, seed, align):
         raw, par = guarded(phase)
         reft.reft_parity_encode(plan, [t for sh in shards for t in sh], k, par)
         check(raw, par, parity, "encode")
+        own = int(rng.integers(k))
+        raw, par = guarded(phase)
+        raw2, packed = guarded(int(rng.integers(0, 16)) // align * align)
+        reft.reft_parity_encode_pack(plan, [t for sh in shards for t in sh], k, own, par, packed)
+        check(raw, par, parity, "encode with pack")
+        check(raw2, packed, streams[own], "pack with encode")
         lost = int(rng.integers(k))
         raw2, outs = fresh()
         rows = [None if s == lost else t for s, sh in enumerate(shards) for t in sh]
