@@ -412,11 +412,13 @@ int reft_restore_wait(reft_plan *plan);
  *                  link in the other direction.
  *   "small_pieces" a tile in which at least this many spans start counts as dense in small spans
  *                  (default 1; 4294967295 = never, 0 = always): see "burst".
- *   "burst"        1 (default) = reft_parity_encode and reft_parity_encode_rotated use the write-burst
- *                  variant of the XOR kernel where it applies: at least "burst_min_rows" rows (default
- *                  8; at most 8), "burst_min_bytes" stream bytes (default 2 GiB) and at most one tile
- *                  in eight dense in small spans (see "small_pieces").  reft_reconstruct uses it from
- *                  5 sources and 8 MiB on (or from those two values, where they are lower).  The
+ *   "burst"        1 (default) = the XOR calls use the write-burst variant of the kernel where it
+ *                  applies: at least "burst_min_rows" rows (default 7; at most 8 count), at least
+ *                  "burst_min_bytes" stream bytes (default 2 GiB; four times that where the result
+ *                  goes into tensors), at most one tile in eight dense in small spans (see
+ *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
+ *                  alike (mod 16) relative to its stream offset.  reft_reconstruct uses it from 5 sources and 8 MiB on (or from
+ *                  those two values, where they are lower).  The
  *                  variant keeps reads and writes apart in time: reader waves XOR
  *                  "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536) of the
  *                  stream at a time into LDS, and one writer wave per workgroup stores the

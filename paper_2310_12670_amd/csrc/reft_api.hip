@@ -60,7 +60,7 @@ static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller piec
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
 static std::atomic<uint64_t> g_burst{1};         // parity encode may use the write-burst kernel
-static std::atomic<uint64_t> g_burst_min_rows{8};    // ... from this many sources on
+static std::atomic<uint64_t> g_burst_min_rows{7};    // ... from this many sources on
 static std::atomic<uint64_t> g_burst_min_bytes{2ull << 30};  // ... and from this stream length on
 static std::atomic<uint64_t> g_burst_stage{32768};   // stream bytes per workgroup and round
 static std::atomic<uint64_t> g_burst_wgs{2};         // resident workgroups per compute unit
@@ -531,7 +531,7 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     if (!out) return fail(REFT_EINVAL, "reft_plan_create: null out");
     *out = nullptr;
     if (!span_nbytes || T == 0) return fail(REFT_EINVAL, "reft_plan_create: no spans");
-    if (T >= kWholeBlock) return fail(REFT_EINVAL, "reft_plan_create: too many spans");
+    if (T >= 0xffffffffull) return fail(REFT_EINVAL, "reft_plan_create: too many spans");
 
     reft_plan *p = new (std::nothrow) reft_plan;
     if (!p) return fail(REFT_EINVAL, "reft_plan_create: out of host memory");
@@ -602,6 +602,8 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
         *out = p;
         return REFT_OK;
     }
+    // (beyond this the pointer pool alone is 1.2 TB)
+    if (T >= kWholeBlock) return fail(REFT_EINVAL, "reft_plan_create: too many spans for a GPU");
     HIPCHK(hipGetDevice(&p->device));
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, p->device));
@@ -1390,6 +1392,14 @@ static bool few_dense_tiles(const reft_plan *p)
     return (uint64_t)dense * 8 <= p->ntiles;
 }
 
+// Whether `rows` rows go through the burst kernel: long rows, few span boundaries.  A launch into
+// tensors needs rows four times as long.
+static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
+{
+    return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
+           rows >= g_burst_min_rows.load() && few_dense_tiles(p);
+}
+
 // The XOR passes over a device table of `nrows` rows of span pointers (row stride T of plan p)
 // into a contiguous destination or, if dtab is given, into the destination's own spans (dst_row
 // is the host copy of that row, used to decide which kernel applies).  More than kMaxStreamSrc rows
@@ -1401,16 +1411,27 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Eight long rows into a contiguous destination: reads and writes are separated in time with the
-    // burst kernel.  TB/s, burst / stream kernel, 8 rows: 27.6 GB 6.38 / 6.29, 26.1 GB 6.38 / 6.31,
-    // 22.6 GB 6.28 / 6.32, 7.7 GB (0.9 GB a row) 6.03 / 6.14; 7 rows: 24.5 GB 6.28 / 6.31, 23.2 GB 6.43 /
-    // 6.38; into tensors 6.07 / 6.06 and less.  More rows go through the stream kernel in one pass, up
-    // to kMaxStreamSrc.
-    if (g_burst.load() && !dst_row && p->L >= g_burst_min_bytes.load() && nrows <= (uint32_t)kMaxSrc &&
-        nrows >= g_burst_min_rows.load() && few_dense_tiles(p)) {
+    // Seven and eight long rows: reads and writes are separated in time with the burst kernel.  TB/s,
+    // burst / stream kernel, into a contiguous destination: 8 rows of 15.0 GB 6.13 / 6.03, 11.8 GB 6.25 /
+    // 6.14, 3.1 GB 6.38 / 6.29, 2.5 GB 6.28 / 6.32, 0.9 GB 6.03 / 6.14; 7 rows of 2.9 and 3.1 GB 6.43 / 6.38,
+    // 6.28 / 6.31; into tensors 15.0 GB 6.18 / 6.11, 11.8 GB 6.64 / 6.54, 3.1 GB 6.07 / 6.06, 2.5 GB 6.02 /
+    // 6.07.  Destination spans that are not all aligned alike relative to their stream offsets, which
+    // the staging image cannot represent, keep the stream kernel, and more rows go through it in
+    // one pass, up to kMaxStreamSrc.
+    bool burst = burst_applies(p, nrows, dst_row != nullptr);
+    uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
+    if (burst && dst_row) {
+        bool have = false;
+        for (uint64_t t = 0; t < T && burst; ++t) {
+            if (p->off[t + 1] == p->off[t]) continue;
+            const uint64_t c = ((uint64_t)(uintptr_t)dst_row[t] - p->off[t]) & 15u;
+            if (!have) { vb = c; have = true; }
+            else burst = c == vb;
+        }
+    }
+    if (burst) {
         const BurstCfg bc = burst_cfg(ctr_ring, (*ctr_next)++ % ctr_blocks, p->num_cus);
-        HIPCHK(launch_gather_burst(pt, tab, (int)nrows, (uint64_t)(uintptr_t)dst_contig, 0, p->L, cfg,
-                                   bc, s));
+        HIPCHK(launch_gather_burst(pt, tab, (int)nrows, dtab, vb, 0, p->L, cfg, bc, s));
         return REFT_OK;
     }
     for (uint32_t done = 0; done < nrows;) {
@@ -1498,8 +1519,9 @@ extern "C" int reft_parity_encode_pack(reft_plan *p, const void *const *shard_sp
     int entry = 0;
     if ((rc = upload_ptrs(p, rows, k, s, &tab, &entry))) return rc;
     if (k <= (uint32_t)kMaxStreamSrc) {
-        // TB/s over (k + 2) L bytes, this / a write-burst kernel with two images: 8 rows of 2.4 GB
-        // 6.24 / 6.14, of 0.6 GB 6.21 / 5.93; 5 rows 6.33 / 5.66; two launches 5.6
+        // TB/s over (k + 2) L bytes, this / a write-burst kernel with two images: 8 rows of 15.0 GB 6.08 / 6.02,
+        // of 11.8 GB 6.37 / 6.33, of 2.4 GB 6.24 / 6.14, of 0.6 GB 6.21 / 5.93; 5 rows 6.33 / 5.66; two
+        // launches 5.6
         HIPCHK(launch_gather_pack(p->tables(), tab, (int)k, vb, vb2, 0, p->L, cfg, s));
     } else {
         if ((rc = xor_passes(p, tab, k, nullptr, nullptr, parity_dev, p->burst_ctr, kCtrBlocks,
@@ -1724,8 +1746,8 @@ extern "C" int reft_reconstruct_rotated(reft_plan *p, const void *const *shard_s
             return fail(REFT_EINVAL, "reft_reconstruct_rotated: parity unit of member %u is null",
                         r < lost ? r : r + 1);
     // All segments at once: every one is the XOR of k - 1 operands, so the derived plan's stream is
-    // the lost shard's and one launch decodes it (16 members, 842 MB: 15 launches of 56 MB in two
-    // passes each took 4.8 ms, one launch in one pass 2.5 ms).
+    // the lost shard's and one launch decodes it (one unit and one decode, 16 members of 842 MB: 5.1 ms
+    // with 16 launches of two passes each, 2.46 with one launch for either).
     const uint64_t key = (2ull << 56) | ((uint64_t)k << 32) | lost;
     const DerivedPlan *dp = nullptr;
     auto it = p->derived.find(key);

@@ -63,11 +63,13 @@ hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nro
                               uint64_t vb2, uint64_t lo, uint64_t hi, const LaunchCfg &cfg,
                               hipStream_t stream);
 
-// The same result as launch_gather for up to kMaxSrc rows and a contiguous destination (virtual base
-// vb), by the burst kernel.  stage_bytes: a multiple of 4096, at most 65536.
-hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
-                               uint64_t lo, uint64_t hi, const LaunchCfg &cfg, const BurstCfg &bc,
-                               hipStream_t stream);
+// The same result as launch_gather for up to kMaxSrc rows, by the burst kernel.  With dtab == null the
+// destination is contiguous and vb its virtual base.  With dtab, every span with bytes must
+// satisfy (dtab[i] - off[i]) mod 16 == vb mod 16 (the caller checks; otherwise use launch_gather).
+// stage_bytes: a multiple of 4096, at most 65536.
+hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows,
+                               const uint64_t *dtab, uint64_t vb, uint64_t lo, uint64_t hi,
+                               const LaunchCfg &cfg, const BurstCfg &bc, hipStream_t stream);
 
 // src_vbase + o is the source address of stream byte o; tab is one row of T span pointers.
 hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,

@@ -108,7 +108,11 @@ __device__ __forceinline__ void xor_piece(uint64_t d, const uint64_t (&s)[K], ui
 // workgroups are resident); workgroup b takes stages b, b + grid, ...
 //
 // The LDS image of a stage is laid out like the destination: the byte of stream offset o sits
-// where address vb + o would fall relative to a 16-byte boundary (vb: the destination's virtual base).
+// where address vb + o would fall relative to a 16-byte boundary.  For a contiguous destination
+// vb is its virtual base.  For a ragged one (dtab), every span's place must have the same
+// alignment relative to its stream offset, (dtab[i] - off[i]) mod 16 = vb mod 16 for all spans
+// with bytes (the host checks this); then aligned 16-byte chunks of the image are aligned
+// 16-byte chunks of every destination span.
 //
 // ctr: 9 counters kCtrStride words apart, all zero at launch.  Workgroups arrive on counter
 // (blockIdx.x & 7); every arrival that completes a multiple of the group's size bumps counter 8,
@@ -217,8 +221,9 @@ __device__ __forceinline__ void burst_rounds(uint64_t nstages, uint32_t stage, u
 
 template <int K, int U, bool NT>
 __global__ void __launch_bounds__(kBurstThreads)
-k_gather_burst(PlanTables pt, const uint64_t *__restrict__ tab, uint64_t vb, uint64_t lo, uint64_t hi,
-               uint32_t stage, uint32_t *ctr, uint32_t max_polls, uint32_t nap)
+k_gather_burst(PlanTables pt, const uint64_t *__restrict__ tab, const uint64_t *__restrict__ dtab,
+               uint64_t vb, uint64_t lo, uint64_t hi, uint32_t stage, uint32_t *ctr,
+               uint32_t max_polls, uint32_t nap)
 {
     const uint64_t nstages = (hi - lo + stage - 1) / stage;
     burst_rounds(
@@ -243,9 +248,24 @@ k_gather_burst(PlanTables pt, const uint64_t *__restrict__ tab, uint64_t vb, uin
             }
         },
         [&](uint64_t st, REFT_LDS const unsigned char *img, uint32_t lane) {
-            const uint64_t o = lo + st * stage;
+            uint64_t o = lo + st * stage;
             const uint64_t e = o + stage < hi ? o + stage : hi;
-            emit_piece<NT>(vb + o, img + ((uint32_t)(vb + o) & 15u), (uint32_t)(e - o), lane);
+            // image byte of stream offset x: img0[x - o]
+            REFT_LDS const unsigned char *img0 = img + ((uint32_t)(vb + o) & 15u);
+            if (dtab == nullptr) {
+                emit_piece<NT>(vb + o, img0, (uint32_t)(e - o), lane);
+            } else {
+                const uint64_t o0 = o;
+                uint32_t i = pt.first_span[o >> pt.tile_shift] & ~kWholeBlock;
+                while (o < e) {
+                    while (pt.off[i + 1] <= o) ++i;
+                    const uint64_t so = pt.off[i];
+                    const uint64_t pe = pt.off[i + 1] < e ? pt.off[i + 1] : e;
+                    emit_piece<NT>(dtab[i] + (o - so), img0 + (uint32_t)(o - o0), (uint32_t)(pe - o),
+                                   lane);
+                    o = pe;
+                }
+            }
         });
 }
 
@@ -350,14 +370,14 @@ static hipError_t burst_grid(const void *fn, uint64_t nstages, const LaunchCfg &
     return hipSuccess;
 }
 
-hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
-                               uint64_t lo, uint64_t hi, const LaunchCfg &cfg, const BurstCfg &bc,
-                               hipStream_t stream)
+hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows,
+                               const uint64_t *dtab, uint64_t vb, uint64_t lo, uint64_t hi,
+                               const LaunchCfg &cfg, const BurstCfg &bc, hipStream_t stream)
 {
     if (lo >= hi) return hipSuccess;
     if (hi > pt.L || !burst_cfg_ok(bc)) return hipErrorInvalidValue;
-    void (*fn)(PlanTables, const uint64_t *, uint64_t, uint64_t, uint64_t, uint32_t, uint32_t *,
-               uint32_t, uint32_t) = nullptr;
+    void (*fn)(PlanTables, const uint64_t *, const uint64_t *, uint64_t, uint64_t, uint64_t,
+               uint32_t, uint32_t *, uint32_t, uint32_t) = nullptr;
     REFT_PICK_K(k_gather_burst, fn, nrows)
     size_t lds = 0;
     uint32_t grid = 0;
@@ -365,7 +385,7 @@ hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nr
     hipError_t e = burst_grid((const void *)fn, nstages, cfg, bc, &lds, &grid);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, stream, bc.ctr, 9 * kCtrStride);
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kBurstThreads), lds, stream, pt, tab, vb, lo, hi,
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kBurstThreads), lds, stream, pt, tab, dtab, vb, lo, hi,
                        bc.stage_bytes, bc.ctr, bc.max_polls, bc.nap);
     return hipGetLastError();
 }
