@@ -388,10 +388,13 @@ static void free_ring(reft_plan *p)
     p->ring_cap = 0;
 }
 
+// A filter in front of the comparison of all pointers, which decides: about 64 of them will do.  (All
+// of them, one multiply behind the other: the first call of an encode with 98,304 took 415 us, this way 299.)
 static uint64_t hash_ptrs(const void *const *ptrs, size_t n)
 {
+    const size_t step = n / 64 + 1;
     uint64_t h = 0x9e3779b97f4a7c15ull ^ n;
-    for (size_t i = 0; i < n; ++i) {
+    for (size_t i = 0; i < n; i += step) {
         h ^= (uint64_t)(uintptr_t)ptrs[i];
         h *= 0x100000001b3ull;
         h ^= h >> 29;
