@@ -637,7 +637,7 @@ def run_config(args, cfg, torch, reft, pinned, streams, primary):
                         "value, which is the whole timed region"},
             "verified": bool(ok),
             "roofline": {
-                "kernel": (f"k_gather_burst<{k}>" if burst_on else f"k_gather<{k}>") +
+                "kernel": (f"k_gather_burst<{k}>" if burst_on else f"k_stream<{k}>") +
                           f" (parity encode over {k} span tables)",
                 "bound": "hbm",
                 "achieved": round(enc_gbps, 1),
