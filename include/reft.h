@@ -295,7 +295,10 @@ int reft_reconstruct(const void *const *shards, uint32_t k, const void *parity, 
  *                  `lost` is ignored (its entries may be NULL).
  * lost             index of the lost shard, < k;  1 <= k <= REFT_MAX_K - 1.
  * parity_dev       device pointer to the L parity bytes.
- * out_span_ptrs    host array of T device pointers: the tensors that receive the lost shard.
+ * out_span_ptrs    host array of T device pointers: the tensors that receive the lost shard.  They may
+ *                  lie in place: span t at the address of its bytes in parity_dev, or of span t of a
+ *                  survivor (with more than 16 sources: of one of the first 16 survivors), whose
+ *                  contents are then replaced.  Any other overlap with a source is not allowed.
  * Errors: REFT_EINVAL (k or lost out of range, null pointers), REFT_EHIP.
  */
 int reft_reconstruct_spans(reft_plan *plan, const void *const *shard_span_ptrs, uint32_t k,
@@ -321,6 +324,10 @@ int reft_reconstruct_spans(reft_plan *plan, const void *const *shard_span_ptrs, 
  *                               that unit covers.  Row `lost` of shard_span_ptrs and entry `lost`
  *                               of parity_ptrs are ignored (they were on the lost node);
  *                               parity_ptrs[i] are device pointers to Lseg bytes each.
+ * The results may lie in place (with more than 16 sources: over one of the first 16): parity_dev at
+ * the address of one of the segments it covers, out_span_ptrs at the addresses of the bytes that
+ * their spans are decoded from, in the units or in a survivor; what they replace is then gone.
+ * Any other overlap with a source is not allowed.
  * 2 <= k <= REFT_MAX_K.  The first call for a given (k, member) or (k, lost) builds and caches
  * derived tables in the plan (allocates); later calls do not.
  * Errors: REFT_EINVAL (k, member or lost out of range, null pointers), REFT_EHIP.

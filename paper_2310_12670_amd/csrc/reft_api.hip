@@ -196,6 +196,7 @@ struct PieceLists {
 struct PtrEntry {
     bool live = false;
     uint64_t pos = 0, len = 0, hash = 0, tick = 0;
+    int in_place = -1;      // whether the last row is also a source (decode_in_place); -1: not looked at
     hipStream_t up_stream = nullptr;
     Event uploaded;
     hipStream_t user[kUsers] = {};
@@ -469,6 +470,7 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
     e.pos = pos;
     e.len = n;
     e.hash = h;
+    e.in_place = -1;
     e.tick = ++p->ring_tick;
     p->ring_head = pos + n;
     *dev_tab = p->d_ptr + pos;
@@ -1056,7 +1058,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         LaunchCfg cfg = link_cfg(p);
         cfg.max_wgs += cfg.max_wgs / 2;
         for (uint64_t b = bucket_begin; b < bucket_end; ++b)
-            HIPCHK(launch_gather(pt, tab, 1, false, nullptr, hview, p->bstart[b], p->bstart[b + 1],
+            HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, hview, p->bstart[b], p->bstart[b + 1],
                                  cfg, ps));
         if ((rc = release_ptrs(p, entry, ps))) return rc;
         return record_pack_done(p, ps);
@@ -1093,7 +1095,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
                 const uint64_t slot = (uint64_t)g * per_group + (r - r0);
                 const uint64_t slot_addr =
                     (uint64_t)(uintptr_t)staging + slot * stride + (runs[r].a & 255);
-                HIPCHK(launch_gather(pt, tab, 1, false, nullptr, slot_addr - runs[r].a, runs[r].a,
+                HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, slot_addr - runs[r].a, runs[r].a,
                                      runs[r].b, cfg, ps));
             }
             if ((rc = record(p->pack_filled[g], ps))) return rc;
@@ -1344,7 +1346,7 @@ extern "C" int reft_pack_device(reft_plan *p, const void *const *span_ptrs, void
     const uint64_t *tab = nullptr;
     int entry = 0;
     if ((rc = upload_ptrs(p, span_ptrs, 1, s, &tab, &entry))) return rc;
-    HIPCHK(launch_gather(p->tables(), tab, 1, false, nullptr, (uint64_t)(uintptr_t)dst_dev, 0, p->L,
+    HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, (uint64_t)(uintptr_t)dst_dev, 0, p->L,
                          launch_cfg(p), s));
     return release_ptrs(p, entry, s);
 }
@@ -1403,12 +1405,38 @@ static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
            rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
 
+// Whether some span's result goes to where a source row has that very span: `dst` is row `nrows` of
+// rows, or null for a contiguous destination at vb.
+static bool writes_a_source(const reft_plan *p, const uint64_t *rows, uint32_t nrows, const uint64_t *dst,
+                            uint64_t vb)
+{
+    for (uint32_t r = 0; r < nrows; ++r, rows += p->T)
+        for (uint64_t t = 0; t < p->T; ++t)
+            if (rows[t] == (dst ? dst[t] : vb + p->off[t]) && p->off[t + 1] != p->off[t]) return true;
+    return false;
+}
+
+// The same for a cached table whose last row is the destination: it depends on the table and the
+// plan alone, so it is looked at once per upload.
+static bool decode_in_place(reft_plan *p, int entry)
+{
+    PtrEntry &e = p->ring[entry];
+    if (e.in_place < 0) {
+        const uint64_t *rows = p->h_ptr + e.pos;
+        const uint32_t nrows = (uint32_t)(e.len / p->T) - 1;
+        e.in_place = writes_a_source(p, rows, nrows, rows + (uint64_t)nrows * p->T, 0);
+    }
+    return e.in_place != 0;
+}
+
 // The XOR passes over a device table of `nrows` rows of span pointers (row stride T of plan p)
 // into a contiguous destination or, if dtab is given, into the destination's own spans (dst_row
 // is the host copy of that row, used to decide which kernel applies).  More than kMaxStreamSrc rows
-// are folded in passes.  ctr_ring holds ctr_blocks blocks of burst counters; *ctr_next picks one.
+// are folded in passes.  in_place: the destination is one of the first kMaxStreamSrc rows (the burst
+// kernel needs no telling: a stage is read, and a round later written, by one workgroup, every byte
+// once).  ctr_ring holds ctr_blocks blocks of burst counters; *ctr_next picks one.
 static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const uint64_t *dtab,
-                      const void *const *dst_row, void *dst_contig, uint32_t *ctr_ring,
+                      const void *const *dst_row, void *dst_contig, bool in_place, uint32_t *ctr_ring,
                       uint32_t ctr_blocks, uint32_t *ctr_next, hipStream_t s)
 {
     const uint64_t T = p->T;
@@ -1441,7 +1469,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
         const bool acc = done > 0;
         const uint32_t cap = (uint32_t)kMaxStreamSrc - (acc ? 1u : 0u);
         const uint32_t n = nrows - done < cap ? nrows - done : cap;
-        HIPCHK(launch_gather(pt, tab + (uint64_t)done * T, (int)n, acc, dtab,
+        HIPCHK(launch_gather(pt, tab + (uint64_t)done * T, (int)n, acc, in_place, dtab,
                              (uint64_t)(uintptr_t)dst_contig, 0, p->L, cfg, s));
         done += n;
     }
@@ -1450,9 +1478,10 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
 
 // XOR of `nrows` host rows of span pointers into a contiguous destination or, if dst_row is
 // given, into the destination's own spans.  The rows are uploaded as one table through the
-// plan's cache (rows and dst_row may lie in the plan's row_buf).
+// plan's cache (rows and dst_row may lie in the plan's row_buf).  in_place: whether the contiguous
+// destination is a source; for a row this is found out here.
 static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const void *const *dst_row,
-                    void *dst_contig, hipStream_t s)
+                    void *dst_contig, bool in_place, hipStream_t s)
 {
     int rc;
     const uint64_t T = p->T;
@@ -1464,11 +1493,12 @@ static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const
         if (rows != all) std::copy(rows, rows + (size_t)nrows * T, all);
         if (dst_row != all + (size_t)nrows * T) std::copy(dst_row, dst_row + T, all + (size_t)nrows * T);
         if ((rc = upload_ptrs(p, all, nrows + 1, s, &tab, &entry))) return rc;
+        in_place = decode_in_place(p, entry);
     } else {
         if ((rc = upload_ptrs(p, rows, nrows, s, &tab, &entry))) return rc;
     }
     const uint64_t *dtab = dst_row ? tab + (uint64_t)nrows * T : nullptr;
-    if ((rc = xor_passes(p, tab, nrows, dtab, dst_row, dst_contig, p->burst_ctr, kCtrBlocks,
+    if ((rc = xor_passes(p, tab, nrows, dtab, dst_row, dst_contig, in_place, p->burst_ctr, kCtrBlocks,
                          &p->burst_next, s)))
         return rc;
     return release_ptrs(p, entry, s);
@@ -1485,7 +1515,7 @@ extern "C" int reft_parity_encode(reft_plan *p, const void *const *shard_span_pt
     if ((rc = check_span_ptrs(p, shard_span_ptrs, k, "reft_parity_encode"))) return rc;
     if (p->L == 0) return REFT_OK;
     if (!parity_dev) return fail(REFT_EINVAL, "reft_parity_encode: null parity buffer");
-    return xor_rows(p, shard_span_ptrs, k, nullptr, parity_dev, (hipStream_t)stream);
+    return xor_rows(p, shard_span_ptrs, k, nullptr, parity_dev, false, (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode")
 }
 
@@ -1527,10 +1557,10 @@ extern "C" int reft_parity_encode_pack(reft_plan *p, const void *const *shard_sp
         // launches 5.6
         HIPCHK(launch_gather_pack(p->tables(), tab, (int)k, vb, vb2, 0, p->L, cfg, s));
     } else {
-        if ((rc = xor_passes(p, tab, k, nullptr, nullptr, parity_dev, p->burst_ctr, kCtrBlocks,
-                             &p->burst_next, s)))
+        if ((rc = xor_passes(p, tab, k, nullptr, nullptr, parity_dev, false, p->burst_ctr,
+                             kCtrBlocks, &p->burst_next, s)))
             return rc;
-        HIPCHK(launch_gather(p->tables(), tab, 1, false, nullptr, vb2, 0, p->L, cfg, s));
+        HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, vb2, 0, p->L, cfg, s));
     }
     return release_ptrs(p, entry, s);
     REFT_GUARD_END("reft_parity_encode_pack")
@@ -1584,7 +1614,7 @@ extern "C" int reft_parity_encode_noalloc(reft_plan *p, const void *const *shard
         HIPCHK(hipGetLastError());
     }
     uint32_t next = 0;
-    return xor_passes(p, tab, k, nullptr, nullptr, parity_dev, ctr, 1, &next, s);
+    return xor_passes(p, tab, k, nullptr, nullptr, parity_dev, false, ctr, 1, &next, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1725,7 +1755,9 @@ extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard
     }
     reft_plan *d = dp->plan;
     if ((rc = derived_rows(p, *dp, shard_span_ptrs, nullptr, nullptr))) return rc;
-    return xor_rows(d, d->row_buf.data(), dp->nwin, nullptr, parity_dev, (hipStream_t)stream);
+    const bool in_place = writes_a_source(d, (const uint64_t *)d->row_buf.data(), dp->nwin, nullptr,
+                                          (uint64_t)(uintptr_t)parity_dev);
+    return xor_rows(d, d->row_buf.data(), dp->nwin, nullptr, parity_dev, in_place, (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode_rotated")
 }
 
@@ -1776,7 +1808,7 @@ extern "C" int reft_reconstruct_rotated(reft_plan *p, const void *const *shard_s
     if ((rc = derived_rows(p, *dp, shard_span_ptrs, parity_ptrs, (const void *const *)out_span_ptrs)))
         return rc;
     const void **rows = d->row_buf.data();
-    return xor_rows(d, rows, dp->nwin - 1, rows + (size_t)(dp->nwin - 1) * d->T, nullptr,
+    return xor_rows(d, rows, dp->nwin - 1, rows + (size_t)(dp->nwin - 1) * d->T, nullptr, false,
                     (hipStream_t)stream);
     REFT_GUARD_END("reft_reconstruct_rotated")
 }
@@ -1926,7 +1958,7 @@ extern "C" int reft_reconstruct_spans(reft_plan *p, const void *const *shard_spa
     for (uint64_t t = 0; t < T; ++t)
         rows[(size_t)r * T + t] = (const uint8_t *)parity_dev + p->off[t];
     ++r;                                                       // r == k source rows
-    return xor_rows(p, rows, k, (const void *const *)out_span_ptrs, nullptr, (hipStream_t)stream);
+    return xor_rows(p, rows, k, (const void *const *)out_span_ptrs, nullptr, false, (hipStream_t)stream);
     REFT_GUARD_END("reft_reconstruct_spans")
 }
 

@@ -52,8 +52,9 @@ struct SrcBases {
 // The destination address of stream byte o, for o in [lo, hi), is dst_vbase + o, or, when dtab
 // (one row of T span pointers) is not null, the byte's place in the destination's own span.
 // tab holds nrows rows of T span pointers (row stride T); the kernel XORs the rows' streams and,
-// if acc, the destination's current contents.  nrows + acc <= kMaxStreamSrc.
-hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc,
+// if acc, the destination's current contents.  nrows + acc <= kMaxStreamSrc.  in_place: a row has
+// spans at the very addresses that their results go to.
+hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc, bool in_place,
                          const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
                          const LaunchCfg &cfg, hipStream_t stream);
 

@@ -41,6 +41,7 @@ struct StreamArgs {
     uint64_t first_unit, nunits;
     uint32_t phase;          // unit u starts at stream byte u * S - phase
     uint32_t last;           // LastRow
+    uint32_t once;           // the destination is a source: every byte is read and written once only
 };
 
 // The tables do not change while the kernel runs; read through the constant address space, entries at
@@ -139,8 +140,8 @@ __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, ui
 // it, is read in whole cache lines, or, where it stands (nearly) alone, the destination is written in
 // such: a unit then starts where the one before it in the span ends, the span's first such unit moves
 // the bytes in front of it as well, and the last one, behind which there is no room, stays where it
-// is; the few bytes that come twice get the same value.  Where the destination is a source nothing may
-// come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
+// is; the few bytes that come twice get the same value.  Where the destination is a source (`once`)
+// nothing may come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
 // 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
 template <int K, int V, bool NT, bool PACK>
 __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane)
@@ -166,7 +167,7 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint6
     for (int j = 1; j < K; ++j) alike += (((uint32_t)(uint64_t)s[j] ^ (uint32_t)(uint64_t)s[0]) & 15u) == 0;
     uint32_t lead = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
     if (lead) {
-        if (a.last == kLastDest || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
+        if (a.once || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
     }
     if (lead) {
         const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
@@ -238,7 +239,7 @@ __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint
 // A lane whose 16 bytes reach over the end of its span moves the span's last 16 bytes instead, and
 // then the next span's first 16: bytes that its neighbours move too are written twice, with the same
 // value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
-// the destination is a source (a byte must then be read and written once), in every straddling lane.
+// the destination is a source (`once`), in every straddling lane.
 template <int K, bool NT, bool PACK>
 __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
                                             uint32_t lane)
@@ -283,7 +284,7 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     const uint64_t w0 = b < a.lo ? a.lo : b, w1 = to == kNone ? y1 : x + to;
     const uint64_t w2 = to2 != kNone ? x + to2 : end2 < a.hi ? end2 : a.hi;
     const bool one = w1 >= hi;                                 // all my bytes belong to span q
-    const bool can = a.last != kLastDest || (one && hi - lo == 16);
+    const bool can = !a.once || (one && hi - lo == 16);
     if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
         const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
         const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
@@ -459,7 +460,7 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pa
     return hipGetLastError();
 }
 
-hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc,
+hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc, bool in_place,
                          const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
                          const LaunchCfg &cfg, hipStream_t stream)
 {
@@ -473,6 +474,7 @@ hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, b
     a.lo = lo;
     a.hi = hi;
     a.last = acc ? kLastDest : kLastTable;
+    a.once = acc || in_place;
     return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, false, cfg, stream);
 }
 

@@ -13,7 +13,8 @@ import paper_2310_12670_amd as reft
 pytestmark = pytest.mark.gpu
 CANARY = 0x96
 GUARD = 512
-NAMES = ("unroll", "nontemporal", "max_wgs", "burst", "dma_min_bytes", "gather_min_pieces")
+NAMES = ("unroll", "nontemporal", "max_wgs", "burst", "burst_min_rows", "burst_min_bytes", "small_pieces", "dma_min_bytes",
+         "gather_min_pieces")
 
 
 @pytest.fixture(scope="module")
@@ -172,3 +173,91 @@ def test_more_spans_than_one_search_step(dev):
     rng = np.random.default_rng(5)
     sizes = [int(x) for x in rng.integers(0, 3, 20000)] + [100_000] + [0] * 500 + [int(x) for x in rng.integers(0, 40, 9000)]
     check_all(dev, sizes, 3, None, seed=11, align=1)
+
+
+def odd_sizes(rng):
+    """Boundaries around the KiB steps, then spans of several KiB at odd stream offsets (whose units
+    are moved to the sources' cache lines)."""
+    return boundary_sizes(rng) + [int(x) for x in rng.integers(3000, 90000, 12)]
+
+
+@pytest.mark.parametrize("burst", [0, 1])
+@pytest.mark.parametrize("k", [1, 2, 5, 8, 16])
+def test_decode_in_place(dev, k, burst):
+    """The lost shard decoded over the parity it comes from, and over a survivor: every byte of the
+    destination is a source, so it may be read and written once only."""
+    rng = np.random.default_rng(70 + k)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(70 + k)
+    sizes = odd_sizes(rng)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    L = int(off[-1])
+    reft.reft_set_tunable("burst", burst)
+    reft.reft_set_tunable("burst_min_rows", 1)
+    reft.reft_set_tunable("burst_min_bytes", 0)
+    reft.reft_set_tunable("small_pieces", 0xffffffff)
+    plan = reft.reft_plan_create(sizes)
+    try:
+        for align, phase, lost, over in ((1, 5, 0, None), (16, 0, k - 1, None), (1, 3, 0, k - 1), (4, 12, 0, k // 2)):
+            if over == lost:
+                continue
+            held = [arena(sizes, rng.integers(0, 16, len(sizes)) // align * align, dev, gen) for _ in range(k)]
+            streams = [oracle.pack([oracle.as_bytes(t.cpu()) for t in h[1]]) for h in held]
+            raw = torch.full((L + 2 * GUARD,), CANARY, dtype=torch.uint8, device=dev)
+            par = raw[GUARD + phase:GUARD + phase + L]
+            par.copy_(torch.from_numpy(oracle.encode(streams)))
+            outs = [par[a:b] for a, b in zip(off[:-1], off[1:])] if over is None else held[over][1]
+            rows = [None if s == lost else t for s, h in enumerate(held) for t in h[1]]
+            reft.reft_reconstruct_spans(plan, rows, k, lost, par, outs)
+            torch.cuda.synchronize()
+            got = np.concatenate([t.cpu().numpy() for t in outs])
+            assert np.array_equal(got, streams[lost]), (align, over)
+            r = raw.cpu().numpy()
+            assert np.all(r[:GUARD + phase] == CANARY) and np.all(r[GUARD + phase + L:] == CANARY)
+    finally:
+        reft.reft_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("k,phase", [(3, 0), (5, 7), (9, 2), (17, 5)])
+def test_rotated_in_place(dev, k, phase):
+    """A member's unit encoded over one of the segments it covers, and the lost shard decoded over the
+    units it comes from."""
+    rng = np.random.default_rng(80 + k)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(80 + k)
+    sizes = odd_sizes(rng)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    L = int(off[-1])
+    seg = -(-L // (k - 1))
+    packed = reft.reft_plan_create([L])
+    plan = reft.reft_plan_create(sizes)
+    try:
+        # encode: shards that are one span each, the unit of member 0 over segment 0 of the last
+        shards = [arena([L + seg], [phase], dev, gen)[1][0] for _ in range(k)]
+        streams = [s[:L].cpu().numpy() for s in shards]
+        units = [oracle.encode_rotated(streams, i) for i in range(k)]
+        reft.reft_parity_encode_rotated(packed, [s[:L] for s in shards], k, 0, shards[-1][:seg])
+        torch.cuda.synchronize()
+        assert np.array_equal(shards[-1][:seg].cpu().numpy(), units[0])
+        # decode: the units of the other members one behind the other, the tensors in the same place
+        held = [arena(sizes, rng.integers(0, 16, len(sizes)), dev, gen)[1] for _ in range(k)]
+        for h, s in zip(held, streams):
+            for t, a in zip(h, off[:-1]):
+                t.copy_(torch.from_numpy(s[a:a + t.numel()]))
+        lost = k // 2
+        raw = torch.zeros((k - 1) * seg + 64, dtype=torch.uint8, device=dev)
+        joined = raw[phase:phase + (k - 1) * seg]
+        ptrs, r = [None] * k, 0
+        for i in range(k):
+            if i != lost:
+                joined[r * seg:(r + 1) * seg].copy_(torch.from_numpy(units[i]))
+                ptrs[i] = joined[r * seg:(r + 1) * seg]
+                r += 1
+        outs = [joined[a:b] for a, b in zip(off[:-1], off[1:])]
+        rows = [None if s == lost else t for s, h in enumerate(held) for t in h]
+        reft.reft_reconstruct_rotated(plan, rows, ptrs, k, lost, outs)
+        torch.cuda.synchronize()
+        assert np.array_equal(joined[:L].cpu().numpy(), streams[lost])
+    finally:
+        reft.reft_plan_destroy(plan)
+        reft.reft_plan_destroy(packed)
