@@ -1,0 +1,19 @@
+// Grid sizes (host arithmetic alone, without HIP, so that it can be checked at any size).
+#pragma once
+#include <stdint.h>
+
+namespace reft {
+
+// Workgroups of 64 * waves threads for a launch of one wave per unit: as many as the units need, at most
+// `cap` (0: no cap), and so few that the work-items of the launch stay below 2^32, which is what HIP and
+// the 32-bit grid size of a dispatch packet take (one-wave workgroups on 1 KiB units get there at 64 GiB
+// of stream).  A wave takes more than one unit where there are fewer waves than units.
+inline uint32_t stream_grid(uint64_t nunits, uint32_t waves, uint32_t cap)
+{
+    const uint64_t most = 0xffffffffull / (64ull * waves);
+    uint64_t g = (nunits + waves - 1) / waves;
+    if (cap && g > cap) g = cap;
+    return (uint32_t)(g < most ? g : most);
+}
+
+}  // namespace reft

@@ -20,6 +20,7 @@
 // pointers, data: 2 - 4 us) of one wave hides behind the others, and short streams, which have few
 // units, spread over the whole chip.
 #include "reft_device.hpp"
+#include "reft_grid.hpp"
 
 namespace reft {
 
@@ -453,10 +454,8 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pa
     a.first_unit = (a.lo + a.phase) / S;
     a.nunits = (a.hi - 1 + a.phase) / S - a.first_unit + 1;
     const uint32_t waves = cached || cfg.capped ? 4 : 1;
-    uint64_t g = (a.nunits + waves - 1) / waves;
-    if (cfg.capped && g > cfg.max_wgs) g = cfg.max_wgs;
-    if (g > (1u << 30) / waves) g = (1u << 30) / waves;      // a wave takes more than one unit then
-    hipLaunchKernelGGL(fn, dim3((uint32_t)g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
+    const uint32_t g = stream_grid(a.nunits, waves, cfg.capped ? cfg.max_wgs : 0);
+    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
     return hipGetLastError();
 }
 

@@ -261,3 +261,30 @@ def test_rotated_in_place(dev, k, phase):
     finally:
         reft.reft_plan_destroy(plan)
         reft.reft_plan_destroy(packed)
+
+
+def test_stream_of_more_units_than_one_launch_has_waves(dev):
+    """64 GiB and more: a wave per KiB would be 2^32 work-items.  Two shards whose spans are all the
+    same few tensors (only the parity has its full length), every byte compared on the device."""
+    if torch.cuda.mem_get_info()[0] < 72 << 30:
+        pytest.skip("needs 70 GiB of free device memory")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(6)
+    n = (1 << 30) + 1000                     # spans begin at any place of a unit, the last unit is ragged
+    count = 65
+    a, b = (torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen) for _ in range(2))
+    c = torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen)
+    first = [a if i % 3 else c for i in range(count)]
+    raw = torch.full((n * count + 2 * GUARD,), CANARY, dtype=torch.uint8, device=dev)
+    par = raw[GUARD:GUARD + n * count]
+    plan = reft.reft_plan_create([n] * count)
+    try:
+        reft.reft_parity_encode(plan, first + [b] * count, 2, par)
+        torch.cuda.synchronize()
+    finally:
+        reft.reft_plan_destroy(plan)
+    for i in range(count):
+        assert torch.equal(par[i * n:(i + 1) * n], first[i] ^ b), i
+    assert (raw[:GUARD] == CANARY).all() and (raw[GUARD + n * count:] == CANARY).all()
+    del raw, par
+    torch.cuda.empty_cache()

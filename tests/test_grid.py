@@ -1,0 +1,43 @@
+"""Grid sizes of the kernels, compiled from the library's own header as a host program."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2310_12670_amd", "csrc")
+SOURCE = """
+#include "reft_grid.hpp"
+extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
+"""
+GiB = 1 << 30
+
+
+@pytest.fixture(scope="module")
+def grid(tmp_path_factory):
+    d = tmp_path_factory.mktemp("grid")
+    (d / "grid.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-I", CSRC, "-o", str(d / "grid.so"), str(d / "grid.cpp")], check=True)
+    lib = ctypes.CDLL(str(d / "grid.so"))
+    lib.stream.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32]
+    lib.stream.restype = ctypes.c_uint32
+    return lib
+
+
+@pytest.mark.parametrize("waves", [1, 4])
+@pytest.mark.parametrize("unit", [1024, 2048, 4096])
+@pytest.mark.parametrize("nbytes", [1, 1023, 1024, 5 << 20, 32 * GiB, 64 * GiB - 1024, 64 * GiB - 1, 64 * GiB, 64 * GiB + 1,
+                                    128 * GiB - 2048, 128 * GiB, 256 * GiB, 288 * 10**9, 1 << 45])
+def test_stream_launch_fits_a_dispatch(grid, nbytes, unit, waves):
+    """Fewer than 2^32 work-items whatever the stream's length, and a wave per unit where they are."""
+    units = -(-nbytes // unit)
+    g = grid.stream(units, waves, 0)
+    assert 1 <= g and g * 64 * waves < 1 << 32
+    assert g == min(-(-units // waves), (2**32 - 1) // (64 * waves))
+
+
+@pytest.mark.parametrize("waves", [1, 4])
+@pytest.mark.parametrize("cap", [1, 7, 48, 1 << 20])
+def test_stream_cap(grid, cap, waves):
+    for units in (1, 5, 100, 1 << 30, 1 << 35):
+        assert grid.stream(units, waves, cap) == min(-(-units // waves), cap, (2**32 - 1) // (64 * waves))
