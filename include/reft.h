@@ -398,7 +398,8 @@ int reft_restore_wait(reft_plan *plan);
  *   "unroll"       16-byte chunks in flight per thread and source, at most: 1, 2 or 4.  The pack,
  *                  unpack and ordinary XOR kernels take fewer where that is faster.
  *   "link_wgs"     cap on workgroups of kernels bound by the host link (default 32; kernels
- *                  that write host memory use half as many again, those that read it twice as many).
+ *                  that write host memory use half as many again, those that read it twice as many;
+ *                  none more than "max_wgs").
  *   "dma_min_bytes"     staged transport: spans of at least this size travel by DMA alone
  *                  (default 1 MiB; 0 = every span; a huge value = none, everything is gathered).
  *   "gather_min_pieces" staged transport: shortest run of pieces of smaller spans that is gathered

@@ -2,6 +2,7 @@
 // tables), the bucket pipelines that pair the gather / scatter kernels with chunked
 // hipMemcpyAsync transfers, and the XOR encode / decode entry points.
 #include "../../include/reft.h"
+#include "reft_grid.hpp"
 #include "reft_internal.hpp"
 
 #include <atomic>
@@ -287,11 +288,10 @@ static LaunchCfg launch_cfg(const reft_plan *p)
 }
 
 // Kernels whose rate is set by the host link need only a few workgroups to saturate it.
-static LaunchCfg link_cfg(const reft_plan *p)
+static LaunchCfg link_cfg(const reft_plan *p, uint32_t halves)
 {
     LaunchCfg c = launch_cfg(p);
-    const uint64_t w = g_link_wgs.load();
-    if (w < c.max_wgs) c.max_wgs = (uint32_t)w;
+    c.max_wgs = link_cap(g_link_wgs.load(), halves, c.max_wgs);
     c.capped = true;
     return c;
 }
@@ -1055,8 +1055,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         if ((rc = upload_ptrs(p, span_ptrs, 1, ps, &tab, &entry))) return rc;
         // Stores across the link: 32 / 48 / 64 workgroups move tensors of 8 MiB at 53.7 / 54.5 / 54.3
         // and of 10 KB at 51.6 / 53.5 / 53.9 GB/s.
-        LaunchCfg cfg = link_cfg(p);
-        cfg.max_wgs += cfg.max_wgs / 2;
+        const LaunchCfg cfg = link_cfg(p, 3);
         for (uint64_t b = bucket_begin; b < bucket_end; ++b)
             HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, hview, p->bstart[b], p->bstart[b + 1],
                                  cfg, ps));
@@ -1989,8 +1988,7 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
             return fail(REFT_EINVAL, "reft_restore: host buffer is not mapped for device access "
                                      "(not pinned); pass a staging ring to copy it by DMA");
         if ((rc = upload_ptrs(p, span_ptrs, 1, us, &tab, &entry))) return rc;
-        LaunchCfg cfg = link_cfg(p);
-        cfg.max_wgs *= 2;          // reads across the link need about twice the waves of writes
+        const LaunchCfg cfg = link_cfg(p, 4);   // reads across the link need about twice the waves of writes
         for (uint64_t b = 0; b < p->NB; ++b)
             HIPCHK(launch_scatter(pt, tab, hview, p->bstart[b], p->bstart[b + 1], cfg, us));
         if ((rc = release_ptrs(p, entry, us))) return rc;

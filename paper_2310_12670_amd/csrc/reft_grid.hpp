@@ -16,4 +16,12 @@ inline uint32_t stream_grid(uint64_t nunits, uint32_t waves, uint32_t cap)
     return (uint32_t)(g < most ? g : most);
 }
 
+// Cap on the workgroups of a kernel bound by the host link: `halves` halves of link_wgs, but never more
+// than the caller's (or the default) cap on any kernel.
+inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
+{
+    const uint64_t w = link_wgs * halves / 2;
+    return (uint32_t)(w < max_wgs ? w : max_wgs);
+}
+
 }  // namespace reft

@@ -9,6 +9,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "reft_grid.hpp"
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
+extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 """
 GiB = 1 << 30
 
@@ -21,6 +22,8 @@ def grid(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "grid.so"))
     lib.stream.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32]
     lib.stream.restype = ctypes.c_uint32
+    lib.link.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32]
+    lib.link.restype = ctypes.c_uint32
     return lib
 
 
@@ -41,3 +44,11 @@ def test_stream_launch_fits_a_dispatch(grid, nbytes, unit, waves):
 def test_stream_cap(grid, cap, waves):
     for units in (1, 5, 100, 1 << 30, 1 << 35):
         assert grid.stream(units, waves, cap) == min(-(-units // waves), cap, (2**32 - 1) // (64 * waves))
+
+
+@pytest.mark.parametrize("halves", [3, 4])
+def test_link_cap_keeps_to_max_wgs(grid, halves):
+    """Direct snapshot: half as many again as link_wgs; direct restore: twice; "max_wgs" bounds both."""
+    for link in (1, 2, 16, 32, 1 << 20):
+        for most in (1, 4, 16, 33, 4096, 1 << 20):
+            assert grid.link(link, halves, most) == min(link * halves // 2, most)
