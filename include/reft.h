@@ -121,7 +121,9 @@ int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *
  *       step are not disturbed.  Smaller spans are copied the same way when few lie together; a run
  *       of at least "gather_min_pieces" consecutive pieces of them within a bucket is gathered by
  *       one kernel launch on pack_stream into a slot of the staging ring and leaves as one copy
- *       (many small tensors would otherwise mean thousands of tiny transfers).  The ring's slots
+ *       (many small tensors would otherwise mean thousands of tiny transfers).  What is not gathered
+ *       is not cut at a bucket's end either: bytes of one span that are copied next to each other
+ *       leave in one copy.  The ring's slots
  *       form two groups used alternately; the two streams synchronise through events once per
  *       group.  pack_stream may equal copy_stream (fully in order).  The tensors are read in
  *       pack_stream's order: work queued on pack_stream before the call (say, the kernel that

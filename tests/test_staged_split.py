@@ -1,6 +1,7 @@
 """How a staged snapshot splits into gathered runs and copies: reft_plan_staged_work against the rule
-stated in plain Python (a span of at least dma_min bytes is one copy, runs of at least gather_min
-pieces of smaller ones within a bucket are gathered, shorter ones copied piece by piece)."""
+stated in plain Python (a span of at least dma_min bytes is one copy; of smaller ones, a run of at least
+gather_min pieces within a bucket is gathered, and the other pieces are copied, those of a span that
+lie one behind the other in one copy)."""
 import numpy as np
 import pytest
 
@@ -8,22 +9,26 @@ import paper_2310_12670_amd as reft
 
 
 def split(sizes, bucket, dma_min, gather_min):
-    gathers = copies = pending = at = 0
-    last = -1
-    for n in sizes:
-        if n == 0:
-            continue
-        if n >= dma_min:
-            gathers, copies, pending = gathers + (pending >= gather_min), copies + (pending if pending < gather_min else 1), 0
-            copies += 1
+    runs, at, last = [[]], 0, None           # runs of (span, offset, bytes); a large span is a run of its own
+    for i, n in enumerate(sizes):
+        if n >= dma_min and n:
+            runs += [[(i, at, n)], []]
         else:
-            for b in range(at // bucket, (at + n - 1) // bucket + 1):
-                if b != last and pending:
-                    gathers, copies, pending = gathers + (pending >= gather_min), copies + (pending if pending < gather_min else 1), 0
+            for b in range(at // bucket, (at + n - 1) // bucket + 1 if n else 0):
+                if b != last:
+                    runs.append([])
                 last = b
-                pending += 1
+                lo, hi = max(at, b * bucket), min(at + n, (b + 1) * bucket)
+                runs[-1].append((i, lo, hi - lo))
         at += n
-    gathers, copies = gathers + (pending >= gather_min), copies + (pending if pending < gather_min else 1)
+    gathers, copies, end = 0, 0, None
+    for run in runs:
+        if len(run) >= gather_min and sizes[run[0][0]] < dma_min:
+            gathers, copies, end = gathers + 1, copies + 1, None
+            continue
+        for i, lo, n in run:
+            copies += (i, lo) != end
+            end = (i, lo + n)
     return gathers, copies
 
 
@@ -51,3 +56,19 @@ def test_rule(bucket, dma_min, gather_min):
     finally:
         for n, v in saved.items():
             reft.reft_set_tunable(n, v)
+
+
+@pytest.mark.parametrize("size,count,bucket", [(900_000, 40, 65536), (900_000, 40, 4 << 20), (300_000, 60, 1 << 20),
+                                               (100_000, 80, 262144), (70_001, 50, 300_000)])
+def test_bucket_ends_split_no_copy(size, count, bucket):
+    """Fewer than eight spans per bucket: nothing is gathered, and every span leaves in one copy."""
+    saved = reft.reft_get_tunable("host_only_plans")
+    reft.reft_set_tunable("host_only_plans", 1)
+    try:
+        plan = reft.reft_plan_create([size] * count, None, bucket)
+        try:
+            assert reft.reft_plan_staged_work(plan) == (0, count)
+        finally:
+            reft.reft_plan_destroy(plan)
+    finally:
+        reft.reft_set_tunable("host_only_plans", saved)
