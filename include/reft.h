@@ -427,9 +427,9 @@ int reft_restore_wait(reft_plan *plan);
  *                  "burst_min_bytes" stream bytes (default 2 GiB; four times that where the result
  *                  goes into tensors), at most one tile in eight dense in small spans (see
  *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
- *                  alike (mod 16) relative to its stream offset.  reft_reconstruct uses it from 5 sources and 8 MiB on (or from
- *                  those two values, where they are lower).  The
- *                  variant keeps reads and writes apart in time: reader waves XOR
+ *                  alike (mod 16) relative to its stream offset.  reft_reconstruct goes by the same
+ *                  two values where they are set, and at their defaults uses the variant from 5
+ *                  sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader waves XOR
  *                  "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536) of the
  *                  stream at a time into LDS, and one writer wave per workgroup stores the
  *                  previous stage once all workgroups of the (persistent, "burst_wgs_per_cu" per

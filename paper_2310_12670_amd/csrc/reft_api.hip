@@ -2,7 +2,7 @@
 // tables), the bucket pipelines that pair the gather / scatter kernels with chunked
 // hipMemcpyAsync transfers, and the XOR encode / decode entry points.
 #include "../../include/reft.h"
-#include "reft_grid.hpp"
+#include "reft_rules.hpp"
 #include "reft_internal.hpp"
 
 #include <atomic>
@@ -61,8 +61,8 @@ static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller piec
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
 static std::atomic<uint64_t> g_burst{1};         // parity encode may use the write-burst kernel
-static std::atomic<uint64_t> g_burst_min_rows{7};    // ... from this many sources on
-static std::atomic<uint64_t> g_burst_min_bytes{2ull << 30};  // ... and from this stream length on
+static std::atomic<uint64_t> g_burst_min_rows{kBurstMinRows};    // ... from this many sources on
+static std::atomic<uint64_t> g_burst_min_bytes{kBurstMinBytes};  // ... and from this stream length on
 static std::atomic<uint64_t> g_burst_stage{32768};   // stream bytes per workgroup and round
 static std::atomic<uint64_t> g_burst_wgs{2};         // resident workgroups per compute unit
 static std::atomic<uint64_t> g_burst_polls{6};       // bound on a writer wave's wait per round (0 = no waiting)
@@ -1899,11 +1899,8 @@ extern "C" int reft_reconstruct(const void *const *shards, uint32_t k, const voi
     const uint32_t tile_shift = (uint32_t)g_tile_shift.load();
     hipStream_t st = (hipStream_t)stream;
     BurstCfg bc{};
-    // The ordinary kernel here (tiles, a persistent grid) mixes reads and writes worse than the one over
-    // span tables: the burst kernel pays from five sources and 8 MiB on (5 sources 6.05 / 6.16 TB/s,
-    // ordinary / burst, 8 sources 5.23 / 6.47), sooner only if the tunables say so.
-    const uint64_t min_rows = std::min<uint64_t>(g_burst_min_rows.load(), 5);
-    const bool burst_ok = g_burst.load() && L >= std::min<uint64_t>(g_burst_min_bytes.load(), 8ull << 20);
+    const uint64_t min_rows = contig_burst_min_rows(g_burst_min_rows.load());
+    const bool burst_ok = g_burst.load() && L >= contig_burst_min_bytes(g_burst_min_bytes.load());
     uint32_t *ring = nullptr;
     int num_cus = 256;
     if (burst_ok) {

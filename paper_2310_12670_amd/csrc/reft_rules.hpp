@@ -1,4 +1,4 @@
-// Grid sizes (host arithmetic alone, without HIP, so that it can be checked at any size).
+// Grid sizes and launch rules (host arithmetic alone, without HIP, so that it can be checked at any size).
 #pragma once
 #include <stdint.h>
 
@@ -23,5 +23,14 @@ inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
     const uint64_t w = link_wgs * halves / 2;
     return (uint32_t)(w < max_wgs ? w : max_wgs);
 }
+
+// "burst_min_rows" and "burst_min_bytes" where the caller has not set them, for the kernels over span tables.
+constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 2ull << 30;
+
+// The same two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes
+// worse than the one over span tables: there the burst kernel pays from five sources and 8 MiB on (5 sources
+// 6.05 / 6.16 TB/s, ordinary / burst, 8 sources 5.23 / 6.47).  What the caller sets holds for both.
+inline uint64_t contig_burst_min_rows(uint64_t rows) { return rows == kBurstMinRows ? 5 : rows; }
+inline uint64_t contig_burst_min_bytes(uint64_t bytes) { return bytes == kBurstMinBytes ? 8ull << 20 : bytes; }
 
 }  // namespace reft

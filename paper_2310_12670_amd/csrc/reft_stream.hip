@@ -20,7 +20,7 @@
 // pointers, data: 2 - 4 us) of one wave hides behind the others, and short streams, which have few
 // units, spread over the whole chip.
 #include "reft_device.hpp"
-#include "reft_grid.hpp"
+#include "reft_rules.hpp"
 
 namespace reft {
 

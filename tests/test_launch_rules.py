@@ -1,15 +1,19 @@
-"""Grid sizes of the kernels, compiled from the library's own header as a host program."""
+"""Grid sizes and launch rules of the kernels, compiled from the library's own header as a host program."""
 import ctypes
 import os
 import subprocess
 
 import pytest
 
+import paper_2310_12670_amd as reft
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2310_12670_amd", "csrc")
 SOURCE = """
-#include "reft_grid.hpp"
+#include "reft_rules.hpp"
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
+extern "C" uint64_t contig_rows(uint64_t rows) { return reft::contig_burst_min_rows(rows); }
+extern "C" uint64_t contig_bytes(uint64_t bytes) { return reft::contig_burst_min_bytes(bytes); }
 """
 GiB = 1 << 30
 
@@ -24,6 +28,9 @@ def grid(tmp_path_factory):
     lib.stream.restype = ctypes.c_uint32
     lib.link.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32]
     lib.link.restype = ctypes.c_uint32
+    for f in (lib.contig_rows, lib.contig_bytes):
+        f.argtypes = [ctypes.c_uint64]
+        f.restype = ctypes.c_uint64
     return lib
 
 
@@ -52,3 +59,14 @@ def test_link_cap_keeps_to_max_wgs(grid, halves):
     for link in (1, 2, 16, 32, 1 << 20):
         for most in (1, 4, 16, 33, 4096, 1 << 20):
             assert grid.link(link, halves, most) == min(link * halves // 2, most)
+
+
+def test_packed_decode_goes_by_the_callers_burst_limits(grid):
+    """reft_reconstruct takes "burst_min_rows" and "burst_min_bytes" as they are set, raised or lowered;
+    only at their defaults does it have limits of its own."""
+    rows, size = reft.reft_get_tunable("burst_min_rows"), reft.reft_get_tunable("burst_min_bytes")
+    assert grid.contig_rows(rows) == 5 and grid.contig_bytes(size) == 8 << 20
+    for r in (1, 2, 5, 6, 8, 9, 32, 1 << 40):
+        assert grid.contig_rows(r) == r
+    for b in (0, 1, 8 << 20, 9 << 20, 1 << 30, (2 << 30) + 1, 4 << 30, 1 << 62):
+        assert grid.contig_bytes(b) == b
