@@ -618,7 +618,7 @@ def run_config(args, cfg, torch, reft, pinned, streams, primary):
         value = 4 * L / t_step / 1e9
         enc_gbps = (k + 1) * L / (enc_ms * 1e-3) / 1e9
         dec_gbps = (k + 1) * L / (dec_ms * 1e-3) / 1e9
-        burst_on = reft.reft_get_tunable("burst") and k >= reft.reft_get_tunable("burst_min_rows")
+        kernel = encode_kernel(k, reft.reft_plan_burst_stats(b.plan), reft.reft_get_tunable("burst_max_polls"))
         traffic, source = measured_traffic(b.wl.cfg)
         out = {
             "workload": f"config {b.wl.cfg}: {b.wl.description}",
@@ -637,8 +637,7 @@ def run_config(args, cfg, torch, reft, pinned, streams, primary):
                         "value, which is the whole timed region"},
             "verified": bool(ok),
             "roofline": {
-                "kernel": (f"k_gather_burst<{k}>" if burst_on else f"k_stream<{k}>") +
-                          f" (parity encode over {k} span tables)",
+                "kernel": kernel + f" (parity encode over {k} span tables)",
                 "bound": "hbm",
                 "achieved": round(enc_gbps, 1),
                 "peak": HBM_PEAK_GBPS,
@@ -876,6 +875,15 @@ def has_demo(b, iterations=5):
         "overhead_pct": {p: round(100.0 * (v[0] - base) / base, 2) for p, v in res.items()},
         "fused_snapshot_verified": fused_ok,
     }
+
+
+def encode_kernel(k: int, burst_stats, polls: int) -> str:
+    """The kernel that a plan's encodes ran in, from what its write-burst launches left behind: rounds,
+    counted unless the writers do not wait (``polls`` 0).  (The decode takes the burst kernel only where
+    the encode of the same rows does.)"""
+    if any(burst_stats):
+        return f"k_gather_burst<{k}>"
+    return f"k_stream<{k}>" if polls else f"k_stream<{k}> or k_gather_burst<{k}> without waits"
 
 
 def measured_traffic(cfg: int):

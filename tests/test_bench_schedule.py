@@ -150,3 +150,10 @@ def test_the_pipelined_order_overlaps_the_two_directions():
     kernels = [o for o in lib.all if o.kind in ("encode", "decode")]
     for c, x in itertools.product(copies, kernels):
         assert not unordered(c, x), f"{c} may run beside {x}"
+
+
+def test_the_encode_kernel_is_named_by_what_ran():
+    """Not by the number of rows alone: eight rows of a short or many-span stream take k_stream."""
+    assert bench.encode_kernel(8, (457728, 0, 0, 894), 6) == "k_gather_burst<8>"
+    assert bench.encode_kernel(8, (0, 0, 0, 0), 6) == "k_stream<8>"
+    assert "k_stream<7>" in bench.encode_kernel(7, (0, 0, 0, 0), 0)
