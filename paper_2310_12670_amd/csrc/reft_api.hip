@@ -284,7 +284,7 @@ static LaunchCfg launch_cfg(const reft_plan *p)
 {
     const uint64_t cap = g_max_wgs;
     const uint64_t w = cap ? cap : 16ull * (uint64_t)(p ? p->num_cus : 256);
-    return LaunchCfg{(uint32_t)w, cap != 0, (uint32_t)g_unroll.load(), g_nontemporal.load() != 0};
+    return LaunchCfg{(uint32_t)w, cap != 0, cap != 0, (uint32_t)g_unroll.load(), g_nontemporal.load() != 0};
 }
 
 // Kernels whose rate is set by the host link need only a few workgroups to saturate it.
@@ -293,6 +293,7 @@ static LaunchCfg link_cfg(const reft_plan *p, uint32_t halves)
     LaunchCfg c = launch_cfg(p);
     c.max_wgs = link_cap(g_link_wgs.load(), halves, c.max_wgs);
     c.capped = true;
+    c.runs = false;
     return c;
 }
 

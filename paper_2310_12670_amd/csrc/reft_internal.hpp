@@ -14,6 +14,8 @@ struct LaunchCfg {
     uint32_t max_wgs;              // cap on the grid size (>= 1) in workgroups of kThreads
     bool capped;                   // the caller asked for that cap; if not, a kernel that does better
                                    // with a wave per unit of work may launch more
+    bool runs;                     // a capped grid may look up once for several units (pays where
+                                   // latency is the bound, not on the host link)
     uint32_t unroll;               // 1, 2 or 4 chunks of 16 B in flight per thread and source
     bool nontemporal;
 };

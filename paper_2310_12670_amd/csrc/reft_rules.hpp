@@ -16,6 +16,19 @@ inline uint32_t stream_grid(uint64_t nunits, uint32_t waves, uint32_t cap)
     return (uint32_t)(g < most ? g : most);
 }
 
+// Consecutive units that a wave of a capped grid takes together.  Runs pay where a wave waits on look-ups for
+// units inside long spans (spans of 70 KB by 8 workgroups: 46 us without, 51 with), with up to four sources
+// (5 by 64 workgroups: 224 us without, 240 with), and up to this many waves, beyond which more windows in
+// memory cost more than look-ups (1 GB copied by 192 / 256 workgroups: 445 / 361 us without, 367 / 382
+// with; parity of 2 by 96 / 128: 747 / 608 and 726 / 655).  Eight runs per wave keep the waves busy alike;
+// beyond 16 units nothing is gained.
+inline uint32_t run_of_units(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean_span)
+{
+    const uint64_t n = nunits / (8 * waves);
+    if (nsrc > 4 || waves > (nsrc == 1 ? 896u : 384u) || mean_span < 256 * 1024) return 1;
+    return n < 1 ? 1 : n < 16 ? (uint32_t)n : 16;
+}
+
 // Cap on the workgroups of a kernel bound by the host link: `halves` halves of link_wgs, but never more
 // than the caller's (or the default) cap on any kernel.
 inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)

@@ -40,8 +40,10 @@ struct StreamArgs {
     uint64_t cbase;          // kLastContig: byte o lies at cbase + o
     uint64_t lo, hi;         // stream range, lo < hi <= L
     uint64_t first_unit, nunits;
+    uint64_t nruns;          // runs of units
     uint32_t phase;          // unit u starts at stream byte u * S - phase
     uint32_t last;           // LastRow
+    uint32_t run;            // consecutive units that one wave takes together
     uint32_t once;           // the destination is a source: every byte is read and written once only
 };
 
@@ -144,8 +146,12 @@ __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, ui
 // is; the few bytes that come twice get the same value.  Where the destination is a source (`once`)
 // nothing may come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
 // 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
-template <int K, int V, bool NT, bool PACK>
-__device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane)
+//
+// RUN: the units behind it as well, up to `most` in all, as far as they lie wholly inside the span and the
+// range; returns how many.
+template <int K, int V, bool NT, bool PACK, bool RUN>
+__device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane,
+                                               uint32_t most)
 {
     constexpr uint32_t S = 1024 * V;
     // everything that is known of span i in one go, without branches between the loads (where there
@@ -166,46 +172,55 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, uint64_t i, uint6
     uint32_t alike = 0;
 #pragma unroll
     for (int j = 1; j < K; ++j) alike += (((uint32_t)(uint64_t)s[j] ^ (uint32_t)(uint64_t)s[0]) & 15u) == 0;
-    uint32_t lead = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
-    if (lead) {
-        if (a.once || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
-    }
-    if (lead) {
-        const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
-        if ((int64_t)x - (int64_t)S < first && lane * 16 < lead) {
-            st16_any<NT>(d + lane * 16, xor_16<K, NT, PACK>([&](int j) { return (uint64_t)s[j] + lane * 16; },
-                                                            a.vb2 + x + lane * 16));
+    const uint32_t to_line = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
+    for (uint32_t done = 1;; ++done) {
+        uint32_t lead = to_line;
+        if (lead) {
+            if (a.once || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
         }
-        d += lead;
+        if (lead) {
+            const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
+            if ((int64_t)x - (int64_t)S < first && lane * 16 < lead) {
+                st16_any<NT>(d + lane * 16, xor_16<K, NT, PACK>([&](int j) { return (uint64_t)s[j] + lane * 16; },
+                                                                a.vb2 + x + lane * 16));
+            }
+            d += lead;
 #pragma unroll
-        for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + lead);
-    }
-    // all loads of up to 16 chunks before the first use (left alone, the compiler alternates them)
-    constexpr int R = K * V <= 16 ? K : 16 / V;
-    u32x4 v[V] = {};
-#pragma unroll
-    for (int j = 0; j < K; j += R) {
-        u32x4 t[R][V];
-#pragma unroll
-        for (int q = 0; q < R && j + q < K; ++q) {
-#pragma unroll
-            for (int u = 0; u < V; ++u) t[q][u] = ld16<NT>(s[j + q] + lane + u * 64);
+            for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + lead);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (PACK) {
-            if (j == 0) {
+        // all loads of up to 16 chunks before the first use (left alone, the compiler alternates them)
+        constexpr int R = K * V <= 16 ? K : 16 / V;
+        u32x4 v[V] = {};
 #pragma unroll
-                for (int u = 0; u < V; ++u) st16_any<NT>(a.vb2 + x + lead + (lane + u * 64) * 16, t[0][u]);
+        for (int j = 0; j < K; j += R) {
+            u32x4 t[R][V];
+#pragma unroll
+            for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+                for (int u = 0; u < V; ++u) t[q][u] = ld16<NT>(s[j + q] + lane + u * 64);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (PACK) {
+                if (j == 0) {
+#pragma unroll
+                    for (int u = 0; u < V; ++u) st16_any<NT>(a.vb2 + x + lead + (lane + u * 64) * 16, t[0][u]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+                for (int u = 0; u < V; ++u) v[u] ^= t[q][u];
             }
         }
 #pragma unroll
-        for (int q = 0; q < R && j + q < K; ++q) {
+        for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
+        if constexpr (!RUN) return 1;
+        x += S;
+        if (done == most || x + S > (e < a.hi ? e : a.hi)) return done;
+        d += S - lead;
 #pragma unroll
-            for (int u = 0; u < V; ++u) v[u] ^= t[q][u];
-        }
+        for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + S - lead);
     }
-#pragma unroll
-    for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
 }
 
 // n bytes from stream byte p on, all inside span q (which starts at b), one by one.
@@ -338,41 +353,58 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     }
 }
 
+// Unit w of the launch or, in a RUN, as many from there on as can be done together, `most` at most; returns
+// how many.
+template <int K, int U, bool NT, bool PACK, bool RUN>
+__device__ __forceinline__ uint32_t move_next(const StreamArgs &a, uint64_t w, uint32_t most, uint32_t lane)
+{
+    constexpr uint32_t S = 1024 * U;
+    Owner o;
+    const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
+    const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
+    const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
+    const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
+    if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift)
+        return move_units<K, U, NT, PACK, RUN>(a, first & ~kWholeBlock, x, lane, most);
+    locate(a.pt, o, first & ~kWholeBlock, y0, lane);
+    if (y1 - y0 == S && y1 <= o.e) return move_units<K, U, NT, PACK, RUN>(a, o.i, x, lane, most);
+#pragma unroll 1
+    for (uint32_t u = 0; u < U; ++u) {
+        const uint64_t xs = x + u * 1024;
+        const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
+        const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
+        if ((int64_t)z0 >= (int64_t)z1) continue;
+        if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
+        if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, PACK>(a, o, xs, lane);
+        else move_shared<K, NT, PACK>(a, o, xs, z1, lane);
+    }
+    return 1;
+}
+
 // The workgroup (1 or 4 waves) has no meaning beyond the dispatch.  Unless the caller caps the grid
 // there is one wave per unit, dispatched in order, so that the chip moves through its streams in
 // narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
 // workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
-template <int K, int U, bool NT, bool PACK = false>
+//
+// RUN (a grid of few waves, each with many units): a wave takes a.run consecutive units together and
+// looks up once for those that lie in one span; without, look-ups and data of its units follow one
+// another.  126 MB in spans of 3 MB by 4 / 16 / 64 workgroups, us, without and with: packed 1867 / 479 / 134
+// and 1219 / 324 / 102 (tiles walked by workgroups: 1623 / 433 / 147), parity of 4: 3540 / 905 / 246 and
+// 2629 / 686 / 199 (3192 / 819 / 250).
+template <int K, int U, bool NT, bool PACK = false, bool RUN = false>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
-    constexpr uint32_t S = 1024 * U;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t waves = blockDim.x >> 6;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nunits; w += (uint64_t)gridDim.x * waves) {
-        Owner o;
-        const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
-        const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
-        const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
-        const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
-        if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
-            move_unit<K, U, NT, PACK>(a, first & ~kWholeBlock, x, lane);
-            continue;
-        }
-        locate(a.pt, o, first & ~kWholeBlock, y0, lane);
-        if (y1 - y0 == S && y1 <= o.e) {
-            move_unit<K, U, NT, PACK>(a, o.i, x, lane);
-            continue;
-        }
-#pragma unroll 1
-        for (uint32_t u = 0; u < U; ++u) {
-            const uint64_t xs = x + u * 1024;
-            const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
-            const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
-            if ((int64_t)z0 >= (int64_t)z1) continue;
-            if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
-            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, PACK>(a, o, xs, lane);
-            else move_shared<K, NT, PACK>(a, o, xs, z1, lane);
+    if constexpr (!RUN) {
+        for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nunits; w += (uint64_t)gridDim.x * waves)
+            (void)move_next<K, U, NT, PACK, false>(a, w, 1, lane);
+    } else {
+        for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nruns; w += (uint64_t)gridDim.x * waves) {
+            const uint64_t end = (w + 1) * a.run < a.nunits ? (w + 1) * a.run : a.nunits;
+            for (uint64_t v = w * a.run; v < end;)
+                v += move_next<K, U, NT, PACK, true>(a, v, (uint32_t)(end - v), lane);
         }
     }
 }
@@ -407,6 +439,16 @@ static uint32_t crowd_limit(int nsrc)
 #define REFT_PICK_MANY(K)                                                                         \
     (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
                      : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
+
+#define REFT_RUN(K) (cfg.nontemporal ? k_stream<K, 4, true, false, true> : k_stream<K, 4, false, false, true>)
+#define REFT_PICK_RUN(fn, nsrc)                                                                   \
+    switch (nsrc) {                                                                               \
+    case 1: fn = REFT_RUN(1); break;                                                              \
+    case 2: fn = REFT_RUN(2); break;                                                              \
+    case 3: fn = REFT_RUN(3); break;                                                              \
+    case 4: fn = REFT_RUN(4); break;                                                              \
+    default: return hipErrorInvalidValue;                                                         \
+    }
 
 #define REFT_PICK_PACK(K) (cfg.nontemporal ? k_stream<K, 1, true, true> : k_stream<K, 1, false, true>)
 
@@ -454,7 +496,11 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pa
     a.first_unit = (a.lo + a.phase) / S;
     a.nunits = (a.hi - 1 + a.phase) / S - a.first_unit + 1;
     const uint32_t waves = cached || cfg.capped ? 4 : 1;
-    const uint32_t g = stream_grid(a.nunits, waves, cfg.capped ? cfg.max_wgs : 0);
+    a.run = 1;
+    if (cfg.runs && cfg.unroll == 4) a.run = run_of_units(a.nunits, waves * (uint64_t)cfg.max_wgs, nsrc, a.pt.L / a.pt.T);
+    if (a.run > 1) REFT_PICK_RUN(fn, nsrc)
+    a.nruns = (a.nunits + a.run - 1) / a.run;
+    const uint32_t g = stream_grid(a.nruns, waves, cfg.capped ? cfg.max_wgs : 0);
     hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
     return hipGetLastError();
 }

@@ -175,24 +175,40 @@ def test_more_spans_than_one_search_step(dev):
     check_all(dev, sizes, 3, None, seed=11, align=1)
 
 
+# a grid of one or three workgroups, whose waves take up to 16 units together; 17 rows end with a pass
+# that accumulates into the destination
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 17])
+@pytest.mark.parametrize("max_wgs,align", [(1, 1), (3, 1), (1, 16)])
+def test_runs_of_units(dev, k, max_wgs, align):
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    rng = np.random.default_rng(k + 10 * max_wgs)
+    sizes = boundary_sizes(rng)[:6]                    # runs need a mean of 256 KiB
+    for n in [int(x) for x in rng.integers(4000, 400_000, 4)] + [0, 1, 3_000_000, 2_500_001]:
+        sizes.insert(int(rng.integers(0, len(sizes) + 1)), n)
+    sizes = [(n + align - 1) // align * align for n in sizes]
+    L = sum(sizes)
+    check_all(dev, sizes, k, [1_300_003, L - 1_300_003], seed=k, align=align)
+
+
 def odd_sizes(rng):
     """Boundaries around the KiB steps, then spans of several KiB at odd stream offsets (whose units
     are moved to the sources' cache lines)."""
     return boundary_sizes(rng) + [int(x) for x in rng.integers(3000, 90000, 12)]
 
 
-@pytest.mark.parametrize("burst", [0, 1])
+@pytest.mark.parametrize("burst,max_wgs", [(0, 0), (1, 0), (0, 1)])
 @pytest.mark.parametrize("k", [1, 2, 5, 8, 16])
-def test_decode_in_place(dev, k, burst):
+def test_decode_in_place(dev, k, burst, max_wgs):
     """The lost shard decoded over the parity it comes from, and over a survivor: every byte of the
     destination is a source, so it may be read and written once only."""
     rng = np.random.default_rng(70 + k)
     gen = torch.Generator(device=dev)
     gen.manual_seed(70 + k)
-    sizes = odd_sizes(rng)
+    sizes = odd_sizes(rng) if max_wgs == 0 else [int(x) for x in rng.integers(1, 700_000, 7)] + [0, 900_001, 15]
     off = np.concatenate([[0], np.cumsum(sizes)])
     L = int(off[-1])
     reft.reft_set_tunable("burst", burst)
+    reft.reft_set_tunable("max_wgs", max_wgs)
     reft.reft_set_tunable("burst_min_rows", 1)
     reft.reft_set_tunable("burst_min_bytes", 0)
     reft.reft_set_tunable("small_pieces", 0xffffffff)

@@ -12,6 +12,7 @@ SOURCE = """
 #include "reft_rules.hpp"
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
+extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
 extern "C" uint64_t contig_rows(uint64_t rows) { return reft::contig_burst_min_rows(rows); }
 extern "C" uint64_t contig_bytes(uint64_t bytes) { return reft::contig_burst_min_bytes(bytes); }
 """
@@ -28,6 +29,8 @@ def grid(tmp_path_factory):
     lib.stream.restype = ctypes.c_uint32
     lib.link.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32]
     lib.link.restype = ctypes.c_uint32
+    lib.run.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64]
+    lib.run.restype = ctypes.c_uint32
     for f in (lib.contig_rows, lib.contig_bytes):
         f.argtypes = [ctypes.c_uint64]
         f.restype = ctypes.c_uint64
@@ -70,3 +73,16 @@ def test_packed_decode_goes_by_the_callers_burst_limits(grid):
         assert grid.contig_rows(r) == r
     for b in (0, 1, 8 << 20, 9 << 20, 1 << 30, (2 << 30) + 1, 4 << 30, 1 << 62):
         assert grid.contig_bytes(b) == b
+
+
+def test_runs_leave_every_wave_eight(grid):
+    """1 to 16 units together; one at a time from five sources on, with many waves and in short spans."""
+    for waves in (4, 16, 256, 384, 896, 4096):
+        for units in (1, 100, 30720, 1 << 22, 1 << 36):
+            for nsrc in (1, 2, 4, 5, 16):
+                for mean in (10_000, 1 << 18, 1 << 30):
+                    n = grid.run(units, waves, nsrc, mean)
+                    assert n == 1 or (2 <= n <= 16 and n * 8 * waves <= units)
+                    if nsrc > 4 or waves > (896 if nsrc == 1 else 384) or mean < 1 << 18:
+                        assert n == 1
+    assert grid.run(30720, 16, 1, 1 << 20) == 16 and grid.run(30720, 512, 1, 1 << 20) == 7
