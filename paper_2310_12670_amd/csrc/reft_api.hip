@@ -632,9 +632,10 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     std::vector<uint64_t> tables((at_first + nblocks * sizeof(uint32_t) + 7) / 8, 0);
     std::copy(p->off.begin(), p->off.end(), tables.begin());
     uint32_t *lookup = (uint32_t *)((uint8_t *)tables.data() + at_first);
-    for (uint64_t t = 0, i = 0; t * block < p->L; ++t) {
-        while (p->off[i + 1] <= t * block) ++i;                      // t * block < L = off[T]
-        lookup[t] = (uint32_t)i | (p->off[i + 1] >= (t + 1) * block ? kWholeBlock : 0u);
+    for (uint64_t t = 0, i = 0; i < T; ++i) {                        // t: the first block without an entry
+        const uint64_t whole = p->off[i + 1] >> p->lookup_shift;
+        if (whole > t) std::fill(lookup + t, lookup + whole, (uint32_t)i | kWholeBlock), t = whole;
+        if (t * block < p->off[i + 1]) lookup[t++] = (uint32_t)i;
     }
     HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
     HIPCHK(hipMemcpy(p->d_tables, tables.data(), tables.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
