@@ -1,6 +1,10 @@
 """GPU test of reft_parity_encode_noalloc, the entry point for callers that cannot allocate: its
 output must equal reft_parity_encode's (and the CPU oracle's) byte for byte, on calls in a row that
-share the library's static scratch, the later ones on smaller inputs."""
+share the library's static scratch, the later ones on smaller inputs.  Every test runs with the
+write-burst kernel (its counters in the static scratch too, behind the pointers) and with the stream
+kernel; a captured call's kernel nodes tell which one it was."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -18,6 +22,32 @@ def dev():
     d = torch.device("cuda:0")
     torch.cuda.set_device(d)
     return d
+
+
+@pytest.fixture(autouse=True, params=["burst", "stream"])
+def kernel(request):
+    """The burst kernel from one row and one byte on, or never."""
+    names = ("burst", "burst_min_rows", "burst_min_bytes", "small_pieces")
+    saved = {n: reft.reft_get_tunable(n) for n in names}
+    for n, v in zip(names, (int(request.param == "burst"), 1, 0, 0xffffffff)):
+        reft.reft_set_tunable(n, v)
+    yield request.param
+    for n, v in saved.items():
+        reft.reft_set_tunable(n, v)
+
+
+def kernel_nodes(graph):
+    """Nodes of a captured graph (all of them kernels: the call records nothing else)."""
+    get = ctypes.CDLL(reft.lib_path()).hipGraphGetNodes
+    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    n = ctypes.c_size_t(0)
+    assert get(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def expected_nodes(kernel, k, T):
+    """Pointers 256 at a time, then the counters' clearing and the burst kernel, or the stream kernel."""
+    return -(-k * T // 256) + (2 if kernel == "burst" and k <= 8 else 1)
 
 
 def make_shards(dev, k, sizes, seed):
@@ -60,12 +90,13 @@ def encode_both_ways(dev, k, sizes, seed, stream):
 
 def test_noalloc_encode_equals_encode_on_calls_in_a_row(dev):
     s = torch.cuda.Stream()
-    # first call: eight shards of 24 MiB + 5 bytes in 300 spans (write-burst kernel, counters in the
-    # static scratch); then smaller ones that reuse the scratch: five shards of 9 MiB in 40 spans
-    # (burst kernel again, fewer pointers, fewer rounds), three shards of 70 KB (ordinary kernel),
-    # and twelve shards (two chained passes) of 10 MiB
+    # first call: eight shards of 24 MiB + 5 bytes in 300 spans; then smaller ones that reuse the
+    # scratch: five shards of 9 MiB in 40 spans (fewer pointers, fewer rounds), three shards of 70 KB,
+    # twelve shards of 10 MiB (more rows than the burst kernel takes: the stream kernel), and twenty
+    # (two chained passes of it)
     cases = [(8, sizes_for((24 << 20) + 5, 300, 1), 11), (5, sizes_for((9 << 20) + 16, 40, 2), 12),
              (3, [70001, 0, 33, 4096], 13), (12, sizes_for((10 << 20) + 48, 64, 3), 14),
+             (20, sizes_for((3 << 20) + 48, 64, 4), 16),
              (8, sizes_for((24 << 20) + 5, 300, 1), 15)]
     for k, sizes, seed in cases:
         got, ref, want = encode_both_ways(dev, k, sizes, seed, s)
@@ -116,9 +147,9 @@ def test_noalloc_encode_rejects_what_the_scratch_cannot_hold(dev):
         reft.reft_plan_destroy(plan)
 
 
-def test_noalloc_encode_replays_in_a_hip_graph(dev):
-    """Captured into a HIP graph once (the call allocates nothing and clears its counters with a
-    kernel, not a memset node) and replayed four times, the tensors' contents changed and eager
+def test_noalloc_encode_replays_in_a_hip_graph(dev, kernel):
+    """Captured into a HIP graph once (the call allocates nothing and clears the burst kernel's counters
+    with a kernel, not a memset node) and replayed four times, the tensors' contents changed and eager
     work and synchronisations between the replays: every replay gives the oracle's parity of the
     current contents."""
     k, sizes = 8, sizes_for((9 << 20) + 5, 12, 9)
@@ -132,9 +163,10 @@ def test_noalloc_encode_replays_in_a_hip_graph(dev):
         torch.cuda.synchronize()                                    # the shards are filled
         reft.reft_parity_encode_noalloc(plan, flat, k, out, s)      # first use outside the capture
         s.synchronize()
-        graph = torch.cuda.CUDAGraph()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
         with torch.cuda.graph(graph, stream=s):
             reft.reft_parity_encode_noalloc(plan, flat, k, out, torch.cuda.current_stream())
+        assert kernel_nodes(graph) == expected_nodes(kernel, k, len(sizes))
         for rep in range(4):
             for t in flat[rep::5]:
                 t.add_(rep + 1)                                      # new contents, same addresses
@@ -144,6 +176,29 @@ def test_noalloc_encode_replays_in_a_hip_graph(dev):
             torch.cuda.synchronize()
             want = oracle.encode([oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in shards])
             assert np.array_equal(out.cpu().numpy(), want), f"replay {rep}"
+        del graph
+    finally:
+        reft.reft_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("k", [1, 7, 8, 9])
+def test_noalloc_encode_takes_the_kernel_asked_for(dev, kernel, k):
+    """Up to eight rows the burst kernel where it applies, with its counters cleared in the same call."""
+    sizes = sizes_for((1 << 20) + 16, 300, 50 + k)
+    shards = make_shards(dev, k, sizes, 60 + k)
+    plan = reft.reft_plan_create(sizes, None, 0)
+    try:
+        out = torch.empty(sum(sizes), dtype=torch.uint8, device=dev)
+        s = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=s):
+            reft.reft_parity_encode_noalloc(plan, [t for sh in shards for t in sh], k, out, torch.cuda.current_stream())
+        assert kernel_nodes(graph) == expected_nodes(kernel, k, len(sizes))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(),
+                              oracle.encode([oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in shards]))
         del graph
     finally:
         reft.reft_plan_destroy(plan)
