@@ -1,8 +1,8 @@
 """GPU parity of the write-burst variant of the XOR kernel against the CPU oracle, bit-exact.
 
-reft_parity_encode and reft_reconstruct_spans switch to this variant by themselves for long
-streams with four or more rows; here the thresholds are lowered so that small, ragged cases run
-through it as well: every number of sources one launch takes, misaligned sources and
+reft_parity_encode and reft_reconstruct_spans switch to this variant by themselves for seven and eight
+rows of a long stream; here the thresholds are lowered so that small, ragged cases run
+through it as well, which the plan's burst statistics confirm: every number of sources one launch takes, misaligned sources and
 destinations, decode into tensors that are (and are not) aligned alike, stage sizes, grids from
 one workgroup up, and with the timing of the bursts switched off (the result must not depend on
 it)."""
@@ -50,6 +50,13 @@ def spans_in_arena(sizes, phases, dev, gen):
     return arena, [arena[s:s + n] for s, n in zip(starts, sizes)]
 
 
+def assert_burst(plan, rows):
+    """The plan's last XOR ran in the burst kernel (told by its rounds, which are counted only if the
+    writers wait; more than eight rows go through the stream kernel)."""
+    if rows <= 8 and reft.reft_get_tunable("burst_max_polls"):
+        assert any(reft.reft_plan_burst_stats(plan)), "not the burst kernel"
+
+
 def check_encode(dev, shards, sizes, out_phase=0):
     """Parity of the shards by the library against the oracle's byte loop; canaries around it."""
     k, L = len(shards), sum(sizes)
@@ -61,6 +68,7 @@ def check_encode(dev, shards, sizes, out_phase=0):
     try:
         reft.reft_parity_encode(plan, [t for sh in shards for t in sh], k, par)
         torch.cuda.synchronize()
+        assert_burst(plan, k)
     finally:
         reft.reft_plan_destroy(plan)
     r = raw.cpu().numpy()
@@ -70,9 +78,10 @@ def check_encode(dev, shards, sizes, out_phase=0):
     return par
 
 
-def check_decode(dev, shards, sizes, parity, lost, out_phases):
+def check_decode(dev, shards, sizes, parity, lost, out_phases, burst=True):
     """Single-loss decode straight into fresh tensors (each between canaries, span t starting
-    out_phases[t] bytes after a 256-byte boundary) against the oracle's subtraction decoder."""
+    out_phases[t] bytes after a 256-byte boundary) against the oracle's subtraction decoder.  burst:
+    the tensors are aligned alike relative to the stream, so that the burst kernel applies."""
     k, L = len(shards), sum(sizes)
     streams = [oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in shards]
     want = oracle.reconstruct([streams[s] for s in range(k) if s != lost], oracle.encode(streams))
@@ -88,6 +97,8 @@ def check_decode(dev, shards, sizes, parity, lost, out_phases):
     try:
         reft.reft_reconstruct_spans(plan, rows, k, lost, parity, outs)
         torch.cuda.synchronize()
+        if burst:
+            assert_burst(plan, k)
     finally:
         reft.reft_plan_destroy(plan)
     r = raw.cpu().numpy()
@@ -98,6 +109,11 @@ def check_decode(dev, shards, sizes, parity, lost, out_phases):
         mask[a:a + n] = False
     assert np.array_equal(np.concatenate(got) if got else np.zeros(0, np.uint8), want)
     assert np.all(r[mask] == CANARY), "wrote outside the output tensors"
+
+
+def alike(sizes, c=0):
+    """Places that are aligned alike relative to the stream, c bytes off."""
+    return [int((c + o) % 16) for o in np.cumsum([0] + list(sizes))[:-1]]
 
 
 SIZES = [
@@ -129,12 +145,10 @@ def test_edge_sizes_and_misalignment(dev, sizes, phase_mode):
     par = check_encode(dev, shards, sizes, out_phase=0 if phase_mode == "aligned" else int(rng.integers(1, 16)))
     # decode into tensors aligned alike relative to the stream (the burst kernel's case) ...
     lost = int(rng.integers(0, 4))
-    offs = np.concatenate([[0], np.cumsum(sizes)])
-    c = 0 if phase_mode == "aligned" else int(rng.integers(1, 16))
-    check_decode(dev, shards, sizes, par, lost, [int((c + o) % 16) for o in offs[:-1]])
+    check_decode(dev, shards, sizes, par, lost, alike(sizes, 0 if phase_mode == "aligned" else int(rng.integers(1, 16))))
     # ... and not alike (falls back to the ordinary kernel; same bytes)
     if phase_mode == "odd":
-        check_decode(dev, shards, sizes, par, lost, [int(x) for x in rng.integers(0, 16, size=len(sizes))])
+        check_decode(dev, shards, sizes, par, lost, [int(x) for x in rng.integers(0, 16, size=len(sizes))], burst=False)
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 15, 16, 23, 31])
@@ -142,7 +156,7 @@ def test_every_source_count_of_one_launch_and_chained_passes(dev, k):
     wl = make_workload(0)
     shards = [fill_shard(wl, s % wl.k, dev) for s in range(k)]
     par = check_encode(dev, shards, span_nbytes(wl))
-    check_decode(dev, shards, span_nbytes(wl), par, k // 2, [0] * len(wl.spans))
+    check_decode(dev, shards, span_nbytes(wl), par, k // 2, alike(span_nbytes(wl)))
 
 
 @pytest.mark.parametrize("stage,wgs,max_wgs,polls", [
@@ -159,7 +173,7 @@ def test_stage_sizes_grids_and_untimed_writes(dev, stage, wgs, max_wgs, polls):
     wl = make_workload(0)
     shards = [fill_shard(wl, s, dev) for s in range(wl.k)]
     par = check_encode(dev, shards, span_nbytes(wl), out_phase=stage % 7)
-    check_decode(dev, shards, span_nbytes(wl), par, wl.lost, [0] * len(wl.spans))
+    check_decode(dev, shards, span_nbytes(wl), par, wl.lost, alike(span_nbytes(wl), stage % 5))
 
 
 @pytest.mark.parametrize("unroll,nt", [(1, 1), (2, 0), (4, 1)])
@@ -184,15 +198,14 @@ def test_many_small_spans_through_the_piece_walk(dev):
         keep.append(arena)
         shards.append(spans)
     par = check_encode(dev, shards, sizes, out_phase=3)
-    offs = np.concatenate([[0], np.cumsum(sizes)])
-    check_decode(dev, shards, sizes, par, 2, [int((5 + o) % 16) for o in offs[:-1]])
+    check_decode(dev, shards, sizes, par, 2, alike(sizes, 5))
 
 
 def test_same_result_as_the_ordinary_kernel_and_back_to_back(dev):
-    """Default thresholds on a stream long enough to take the burst kernel by itself; several
-    launches in a row share the plan's ring of counter blocks."""
+    """Thresholds that the stream passes; several launches in a row share the plan's ring of counter
+    blocks."""
     reft.reft_set_tunable("burst_min_rows", 4)
-    reft.reft_set_tunable("burst_min_bytes", 8 << 20)
+    reft.reft_set_tunable("burst_min_bytes", 2 << 20)
     reft.reft_set_tunable("small_pieces", 8)
     wl = make_workload(2, shrink=4, layers=2)
     sizes = span_nbytes(wl)
@@ -212,7 +225,8 @@ def test_same_result_as_the_ordinary_kernel_and_back_to_back(dev):
         reft.reft_plan_destroy(plan)
     for o in outs:
         assert torch.equal(o, ref)
-    check_decode(dev, shards, sizes, ref, wl.lost, [0] * len(sizes))
+    reft.reft_set_tunable("burst", 1)
+    check_decode(dev, shards, sizes, ref, wl.lost, alike(sizes))
     streams = [oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in shards]
     assert np.array_equal(ref.cpu().numpy(), oracle.encode(streams))
 
@@ -245,8 +259,8 @@ def test_decode_from_packed_streams(dev, L, k, phase):
 
 
 def test_a_few_dense_tiles_among_large_spans(dev):
-    """Default thresholds: clusters of tiny tensors between large ones (fewer than one tile in a
-    hundred is dense in small spans, so the burst kernel walks those stages piece by piece)."""
+    """Clusters of tiny tensors between large ones (fewer than one tile in eight is dense in small
+    spans, so the burst kernel walks those stages piece by piece)."""
     reft.reft_set_tunable("burst_min_rows", 4)
     reft.reft_set_tunable("burst_min_bytes", 8 << 20)
     reft.reft_set_tunable("small_pieces", 8)
@@ -262,8 +276,7 @@ def test_a_few_dense_tiles_among_large_spans(dev):
         keep.append(arena)
         shards.append(spans)
     par = check_encode(dev, shards, sizes)
-    offs = np.concatenate([[0], np.cumsum(sizes)])
-    check_decode(dev, shards, sizes, par, 1, [int(o % 16) for o in offs[:-1]])
+    check_decode(dev, shards, sizes, par, 1, alike(sizes))
 
 
 def test_concurrent_launches_on_several_streams(dev):
@@ -328,12 +341,12 @@ def test_burst_statistics_add_up(dev):
         reft.reft_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("k", [1, 2, 5, 8, 11])
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 7, 8, 10, 11, 13, 14, 16, 17])
 @pytest.mark.parametrize("phases", ["alike", "apart"])
 def test_fused_pack_and_encode(dev, k, phases):
     """reft_parity_encode_pack: parity of k shards and the packed stream of each shard in turn,
-    against the oracle; ragged sizes, misaligned sources; destinations aligned alike (single pass
-    where k <= 8) and apart (two launches), canaries around both."""
+    against the oracle; ragged sizes, misaligned sources; destinations aligned alike and apart, one pass
+    up to 16 shards, separate launches beyond, canaries around both."""
     gen = torch.Generator(device=dev)
     gen.manual_seed(500 + k)
     rng = np.random.default_rng(k)
@@ -371,13 +384,14 @@ def test_fused_pack_and_encode(dev, k, phases):
         reft.reft_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("stage,wgs", [(4096, 2), (12288, 1), (36864, 2), (40960, 2)])
-def test_fused_pack_and_encode_stage_sizes(dev, stage, wgs):
-    """Stage sizes up to the largest whose two images fit the LDS, and one beyond (two launches)."""
-    reft.reft_set_tunable("burst_stage_bytes", stage)
-    reft.reft_set_tunable("burst_wgs_per_cu", wgs)
+@pytest.mark.parametrize("max_wgs,nt,unroll", [(0, 1, 4), (0, 0, 1), (3, 1, 4), (300, 0, 2)])
+def test_fused_pack_and_encode_back_to_back(dev, max_wgs, nt, unroll):
+    """Three calls in a row on one plan, under the launch parameters that the pass reads."""
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    reft.reft_set_tunable("nontemporal", nt)
+    reft.reft_set_tunable("unroll", unroll)
     gen = torch.Generator(device=dev)
-    gen.manual_seed(stage)
+    gen.manual_seed(max_wgs)
     sizes = [(5 << 20) + 48, 4096, 999]
     L, k = sum(sizes), 6
     shards = [[torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen) for n in sizes]
@@ -387,7 +401,7 @@ def test_fused_pack_and_encode_stage_sizes(dev, stage, wgs):
     try:
         par = torch.empty(L, dtype=torch.uint8, device=dev)
         pk = torch.empty(L, dtype=torch.uint8, device=dev)
-        for rep in range(3):                      # back to back on one plan
+        for rep in range(3):
             reft.reft_parity_encode_pack(plan, [t for sh in shards for t in sh], k, 2, par, pk)
         torch.cuda.synchronize()
         assert np.array_equal(par.cpu().numpy(), oracle.encode(streams))

@@ -29,16 +29,16 @@ def dev():
     return d
 
 
-@pytest.fixture(autouse=True, params=["direct", "staged", "staged-gather", "direct-lds",
-                                      "staged-gather-lds", "staged-tiny-dma", "staged-2streams",
+@pytest.fixture(autouse=True, params=["direct", "staged", "staged-gather", "direct-capped",
+                                      "staged-gather-capped", "staged-tiny-dma", "staged-2streams",
                                       "staged-tiny-dma-2streams"])
 def default_tunables(request):
     """Every case runs with each host transport: direct (kernels touch pinned host memory),
     staged (large pieces by DMA from the tensors, runs of small pieces through gather kernel and
     staging ring), staged-gather (every byte through the gather kernel and the ring) and
     staged-tiny-dma (every piece, however small, its own DMA copy); "-2streams" alternates the piece
-    copies between copy_stream and the plan's helper stream (dma_streams = 2); "-lds" forces the
-    kernels' LDS-staged small-piece path on for every tile.  Launch parameters are restored
+    copies between copy_stream and the plan's helper stream (dma_streams = 2); "-capped" keeps every
+    kernel to two workgroups, whose waves take many units each.  Launch parameters are restored
     afterwards."""
     global DIRECT
     names = ("max_wgs", "nontemporal", "unroll", "tile_shift", "link_wgs", "small_pieces",
@@ -51,8 +51,8 @@ def default_tunables(request):
     if "-tiny-dma" in request.param:
         reft.reft_set_tunable("dma_min_bytes", 0)
     reft.reft_set_tunable("dma_streams", 2 if request.param.endswith("-2streams") else 1)
-    if request.param.endswith("-lds"):
-        reft.reft_set_tunable("small_pieces", 0)
+    if request.param.endswith("-capped"):
+        reft.reft_set_tunable("max_wgs", 2)
     yield
     for n, v in saved.items():
         reft.reft_set_tunable(n, v)
@@ -303,8 +303,8 @@ def test_edge_sizes_and_misalignment(dev, sizes, phase_mode):
 
 @pytest.mark.parametrize("mean_size,tile_shift", [(100, 18), (700, 16), (3000, 18), (40, 14)])
 def test_thousands_of_tiny_spans(dev, mean_size, tile_shift):
-    """Many small tensors end to end: hundreds to thousands of spans per tile (several LDS passes
-    per tile), zero-length spans, odd sizes and odd addresses, next to a few large spans."""
+    """Many small tensors end to end: hundreds to thousands of spans per tile (dozens per block of the
+    kernels' look-up table), zero-length spans, odd sizes and odd addresses, next to a few large spans."""
     reft.reft_set_tunable("tile_shift", tile_shift)
     rng = np.random.default_rng(mean_size)
     gen = torch.Generator(device=dev)

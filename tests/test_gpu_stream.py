@@ -137,7 +137,7 @@ def boundary_sizes(rng):
 
 
 @pytest.mark.parametrize("unroll,max_wgs,nt", [(1, 0, 1), (1, 2, 0), (2, 3, 1), (4, 1, 1), (4, 64, 0)])
-@pytest.mark.parametrize("k", [1, 2, 5, 8, 9, 17])
+@pytest.mark.parametrize("k", [1, 2, 5, 8, 9, 12, 15, 16, 17])
 def test_boundaries(dev, k, unroll, max_wgs, nt):
     reft.reft_set_tunable("unroll", unroll)
     reft.reft_set_tunable("max_wgs", max_wgs)
