@@ -123,7 +123,7 @@ def parse_args():
                     help="tunable graph_copies: staged piece copies as a replayed hipGraph "
                          "(0 off, 1 independent nodes, 2 chain)")
     ap.add_argument("--no-burst", action="store_true",
-                    help="XOR kernels without write bursts (the ordinary gather kernel), for comparison")
+                    help="XOR kernels without write bursts (the stream kernel), for comparison")
     ap.add_argument("--burst-polls", type=int, default=-1,
                     help="tunable burst_max_polls (0 = write bursts are not timed)")
     ap.add_argument("--burst-nap", type=int, default=-1, help="tunable burst_nap")

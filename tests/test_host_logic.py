@@ -213,12 +213,12 @@ def test_build_refuses_burst_kernels_that_need_too_many_registers():
                 f"x.hip:1:1: remark:     SGPRs: 100 [-Rpass-analysis=kernel-resource-usage]\n"
                 f"x.hip:1:1: remark:     VGPRs: {vgprs} [-Rpass-analysis=kernel-resource-usage]\n")
 
-    ok = remarks("_ZN4reft14k_gather_burstILi8ELi4ELb1EEEvX", 121) + remarks("_ZN4reft8k_gatherILi8ELi4ELb1EEEvX", 167)
+    ok = remarks("_ZN4reft14k_gather_burstILi8ELi4ELb1EEEvX", 121) + remarks("_ZN4reft8k_streamILi8ELi1ELb1EEEvX", 167)
     assert check_burst_registers(ok) == {"_ZN4reft14k_gather_burstILi8ELi4ELb1EEEvX": 121}
     with pytest.raises(RuntimeError):
         check_burst_registers(ok + remarks("_ZN4reft18k_xor_contig_burstILi8ELi4ELb1EEEvX", 129))
     with pytest.raises(RuntimeError):
-        check_burst_registers(remarks("_ZN4reft8k_gatherILi8ELi4ELb1EEEvX", 167))   # no burst kernel reported
+        check_burst_registers(remarks("_ZN4reft8k_streamILi8ELi1ELb1EEEvX", 167))   # no burst kernel reported
 
 
 def test_header_is_plain_c(tmp_path):
