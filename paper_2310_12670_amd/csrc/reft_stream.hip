@@ -24,12 +24,15 @@
 
 namespace reft {
 
-// The last of a launch's K sources.
+// The last of a launch's K sources (bit 0: not a row of the table) and whether the destination is a source,
+// so that every byte is read and written once only (bit 1).
 enum LastRow : uint32_t {
     kLastTable = 0,      // an ordinary row of the table
-    kLastDest = 1,       // the destination's current bytes (accumulate)
-    kLastContig = 2,     // the contiguous buffer whose virtual base is cbase
+    kLastContig = 1,     // the contiguous buffer whose virtual base is cbase
+    kInPlace = 2,        // an ordinary row; that or another one is the destination
+    kLastDest = 3,       // the destination's current bytes (accumulate)
 };
+constexpr uint32_t kNoRow = 1, kOnce = 2;
 
 struct StreamArgs {
     PlanTables pt;
@@ -44,7 +47,6 @@ struct StreamArgs {
     uint32_t phase;          // unit u starts at stream byte u * S - phase
     uint32_t last;           // LastRow
     uint32_t run;            // consecutive units that one wave takes together
-    uint32_t once;           // the destination is a source: every byte is read and written once only
 };
 
 // The tables do not change while the kernel runs; read through the constant address space, entries at
@@ -95,7 +97,7 @@ __device__ __forceinline__ void locate(const PlanTables &pt, Owner &o, uint64_t 
 template <int K>
 __device__ __forceinline__ uint64_t source_of(const StreamArgs &a, int j, uint64_t q, uint64_t b)
 {
-    if (j == K - 1 && a.last != kLastTable) {
+    if (j == K - 1 && (a.last & kNoRow)) {
         if (a.last == kLastContig) return a.cbase + b;
         return a.dtab ? entry(a.dtab, q) : a.vb + b;
     }
@@ -143,7 +145,7 @@ __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, ui
 // it, is read in whole cache lines, or, where it stands (nearly) alone, the destination is written in
 // such: a unit then starts where the one before it in the span ends, the span's first such unit moves
 // the bytes in front of it as well, and the last one, behind which there is no room, stays where it
-// is; the few bytes that come twice get the same value.  Where the destination is a source (`once`)
+// is; the few bytes that come twice get the same value.  Where the destination is a source (kOnce)
 // nothing may come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
 // 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
 //
@@ -161,7 +163,7 @@ __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, 
     uint64_t p[K];
 #pragma unroll
     for (int j = 0; j < K - 1; ++j) p[j] = entry(a.tab, (uint64_t)j * a.pt.T + i);
-    p[K - 1] = entry(a.last == kLastTable ? a.tab + (uint64_t)(K - 1) * a.pt.T : a.pt.off, i);
+    p[K - 1] = entry(a.last & kNoRow ? a.pt.off : a.tab + (uint64_t)(K - 1) * a.pt.T, i);
     const uint64_t r = x - b;
     uint64_t d = (a.dtab ? dt : a.vb + b) + r;
     if (a.last == kLastContig) p[K - 1] = a.cbase + b;
@@ -173,10 +175,14 @@ __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, 
 #pragma unroll
     for (int j = 1; j < K; ++j) alike += (((uint32_t)(uint64_t)s[j] ^ (uint32_t)(uint64_t)s[0]) & 15u) == 0;
     const uint32_t to_line = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
+    // vmcnt(0), once in front of a run: the compiler may otherwise take registers for still in flight from
+    // before and wait for them in every round, and with them for the stores of the round before (2 sources,
+    // 126 MB by 4 workgroups: 2217 us so, 1583 with this)
+    if constexpr (RUN) __builtin_amdgcn_s_waitcnt(0x0f70);
     for (uint32_t done = 1;; ++done) {
         uint32_t lead = to_line;
         if (lead) {
-            if (a.once || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
+            if ((a.last & kOnce) || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
         }
         if (lead) {
             const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
@@ -255,7 +261,7 @@ __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint
 // A lane whose 16 bytes reach over the end of its span moves the span's last 16 bytes instead, and
 // then the next span's first 16: bytes that its neighbours move too are written twice, with the same
 // value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
-// the destination is a source (`once`), in every straddling lane.
+// the destination is a source (kOnce), in every straddling lane.
 template <int K, bool NT, bool PACK>
 __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
                                             uint32_t lane)
@@ -300,7 +306,7 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     const uint64_t w0 = b < a.lo ? a.lo : b, w1 = to == kNone ? y1 : x + to;
     const uint64_t w2 = to2 != kNone ? x + to2 : end2 < a.hi ? end2 : a.hi;
     const bool one = w1 >= hi;                                 // all my bytes belong to span q
-    const bool can = !a.once || (one && hi - lo == 16);
+    const bool can = !(a.last & kOnce) || (one && hi - lo == 16);
     if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
         const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
         const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
@@ -518,8 +524,7 @@ hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, b
     a.vb = dst_vbase;
     a.lo = lo;
     a.hi = hi;
-    a.last = acc ? kLastDest : kLastTable;
-    a.once = acc || in_place;
+    a.last = acc ? kLastDest : in_place ? kInPlace : kLastTable;
     return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, false, cfg, stream);
 }
 
