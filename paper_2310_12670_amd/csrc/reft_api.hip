@@ -197,7 +197,8 @@ struct PieceLists {
 struct PtrEntry {
     bool live = false;
     uint64_t pos = 0, len = 0, hash = 0, tick = 0;
-    int in_place = -1;      // whether the last row is also a source (decode_in_place); -1: not looked at
+    int in_place = -1;      // whether a source lies where the result for in_place_vb goes (see in_place());
+    uint64_t in_place_vb = 0;   // -1: not looked at
     hipStream_t up_stream = nullptr;
     Event uploaded;
     hipStream_t user[kUsers] = {};
@@ -1414,38 +1415,31 @@ static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
            rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
 
-// Whether some span's result goes to where a source row has that very span: `dst` is row `nrows` of
-// rows, or null for a contiguous destination at vb.
-static bool writes_a_source(const reft_plan *p, const uint64_t *rows, uint32_t nrows, const uint64_t *dst,
-                            uint64_t vb)
-{
-    for (uint32_t r = 0; r < nrows; ++r, rows += p->T)
-        for (uint64_t t = 0; t < p->T; ++t)
-            if (rows[t] == (dst ? dst[t] : vb + p->off[t]) && p->off[t + 1] != p->off[t]) return true;
-    return false;
-}
-
-// The same for a cached table whose last row is the destination: it depends on the table and the
-// plan alone, so it is looked at once per upload.
-static bool decode_in_place(reft_plan *p, int entry)
+// Whether some span's result goes to where a source row of the cached table has that very span.  The
+// destination is contiguous at vb or, with vb = 0, the table's last row.  The answer depends on these
+// addresses alone, so it is kept with the table.
+static bool in_place(reft_plan *p, int entry, uint64_t vb)
 {
     PtrEntry &e = p->ring[entry];
-    if (e.in_place < 0) {
-        const uint64_t *rows = p->h_ptr + e.pos;
-        const uint32_t nrows = (uint32_t)(e.len / p->T) - 1;
-        e.in_place = writes_a_source(p, rows, nrows, rows + (uint64_t)nrows * p->T, 0);
-    }
+    if (e.in_place >= 0 && e.in_place_vb == vb) return e.in_place != 0;
+    const uint64_t T = p->T, *row = p->h_ptr + e.pos;
+    const uint64_t *const end = row + e.len - (vb ? 0 : T), *const dst = vb ? nullptr : end;
+    e.in_place = 0;
+    e.in_place_vb = vb;
+    for (; row < end; row += T)
+        for (uint64_t t = 0; t < T; ++t)
+            if (row[t] == (dst ? dst[t] : vb + p->off[t]) && p->off[t + 1] != p->off[t]) e.in_place = 1;
     return e.in_place != 0;
 }
 
 // The XOR passes over a device table of `nrows` rows of span pointers (row stride T of plan p)
 // into a contiguous destination or, if dtab is given, into the destination's own spans (dst_row
 // is the host copy of that row, used to decide which kernel applies).  More than kMaxStreamSrc rows
-// are folded in passes.  in_place: the destination is one of the first kMaxStreamSrc rows (the burst
+// are folded in passes.  over_source: the destination is one of the first kMaxStreamSrc rows (the burst
 // kernel needs no telling: a stage is read, and a round later written, by one workgroup, every byte
 // once).  ctr_ring holds ctr_blocks blocks of burst counters; *ctr_next picks one.
 static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const uint64_t *dtab,
-                      const void *const *dst_row, void *dst_contig, bool in_place, uint32_t *ctr_ring,
+                      const void *const *dst_row, void *dst_contig, bool over_source, uint32_t *ctr_ring,
                       uint32_t ctr_blocks, uint32_t *ctr_next, hipStream_t s)
 {
     const uint64_t T = p->T;
@@ -1478,7 +1472,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
         const bool acc = done > 0;
         const uint32_t cap = (uint32_t)kMaxStreamSrc - (acc ? 1u : 0u);
         const uint32_t n = nrows - done < cap ? nrows - done : cap;
-        HIPCHK(launch_gather(pt, tab + (uint64_t)done * T, (int)n, acc, in_place, dtab,
+        HIPCHK(launch_gather(pt, tab + (uint64_t)done * T, (int)n, acc, over_source, dtab,
                              (uint64_t)(uintptr_t)dst_contig, 0, p->L, cfg, s));
         done += n;
     }
@@ -1487,10 +1481,10 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
 
 // XOR of `nrows` host rows of span pointers into a contiguous destination or, if dst_row is
 // given, into the destination's own spans.  The rows are uploaded as one table through the
-// plan's cache (rows and dst_row may lie in the plan's row_buf).  in_place: whether the contiguous
-// destination is a source; for a row this is found out here.
+// plan's cache (rows and dst_row may lie in the plan's row_buf).  apart: a contiguous destination overlaps
+// no source, by the entry point's rules.
 static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const void *const *dst_row,
-                    void *dst_contig, bool in_place, hipStream_t s)
+                    void *dst_contig, bool apart, hipStream_t s)
 {
     int rc;
     const uint64_t T = p->T;
@@ -1502,12 +1496,12 @@ static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const
         if (rows != all) std::copy(rows, rows + (size_t)nrows * T, all);
         if (dst_row != all + (size_t)nrows * T) std::copy(dst_row, dst_row + T, all + (size_t)nrows * T);
         if ((rc = upload_ptrs(p, all, nrows + 1, s, &tab, &entry))) return rc;
-        in_place = decode_in_place(p, entry);
     } else {
         if ((rc = upload_ptrs(p, rows, nrows, s, &tab, &entry))) return rc;
     }
     const uint64_t *dtab = dst_row ? tab + (uint64_t)nrows * T : nullptr;
-    if ((rc = xor_passes(p, tab, nrows, dtab, dst_row, dst_contig, in_place, p->burst_ctr, kCtrBlocks,
+    const bool over_source = (dst_row || !apart) && in_place(p, entry, (uint64_t)(uintptr_t)dst_contig);
+    if ((rc = xor_passes(p, tab, nrows, dtab, dst_row, dst_contig, over_source, p->burst_ctr, kCtrBlocks,
                          &p->burst_next, s)))
         return rc;
     return release_ptrs(p, entry, s);
@@ -1524,7 +1518,7 @@ extern "C" int reft_parity_encode(reft_plan *p, const void *const *shard_span_pt
     if ((rc = check_span_ptrs(p, shard_span_ptrs, k, "reft_parity_encode"))) return rc;
     if (p->L == 0) return REFT_OK;
     if (!parity_dev) return fail(REFT_EINVAL, "reft_parity_encode: null parity buffer");
-    return xor_rows(p, shard_span_ptrs, k, nullptr, parity_dev, false, (hipStream_t)stream);
+    return xor_rows(p, shard_span_ptrs, k, nullptr, parity_dev, true, (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode")
 }
 
@@ -1764,9 +1758,7 @@ extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard
     }
     reft_plan *d = dp->plan;
     if ((rc = derived_rows(p, *dp, shard_span_ptrs, nullptr, nullptr))) return rc;
-    const bool in_place = writes_a_source(d, (const uint64_t *)d->row_buf.data(), dp->nwin, nullptr,
-                                          (uint64_t)(uintptr_t)parity_dev);
-    return xor_rows(d, d->row_buf.data(), dp->nwin, nullptr, parity_dev, in_place, (hipStream_t)stream);
+    return xor_rows(d, d->row_buf.data(), dp->nwin, nullptr, parity_dev, false, (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode_rotated")
 }
 
