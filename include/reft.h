@@ -129,7 +129,7 @@ int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *
  *       pack_stream's order: work queued on pack_stream before the call (say, the kernel that
  *       produced a parity buffer) completes before any byte is read, also by the copies.
  *   direct (staging == NULL)  the gather kernel itself stores into the pinned host buffer across
- *       the host link: one launch per bucket on pack_stream, capped at "link_wgs" workgroups (a
+ *       the host link: one launch per bucket on pack_stream, of few workgroups (see "link_wgs"; a
  *       few dozen saturate the link).  No staging memory, no DMA, no second pass over HBM;
  *       copy_stream is not used.  Meant for times when the GPU is otherwise idle (pipeline
  *       bubbles, recovery): kernels that keep the link's write path full slow down kernels
@@ -380,9 +380,9 @@ int reft_recovery_plan(uint32_t k, const uint32_t *copy_offsets, uint32_t n_copi
 /* ---- S5 + S7: load a shard from pinned host memory back into its tensors (section 4.3, step 1) ---
  * The inverse of reft_snapshot_pack, with the same two transports: staged (staging != NULL:
  * large pieces by hipMemcpyAsync on copy_stream straight into their tensors, runs of small pieces
- * by hipMemcpyAsync into a staging slot and a scatter kernel on unpack_stream) or direct (staging == NULL: the scatter kernel reads the pinned host snapshot
- * across the link, per bucket, on unpack_stream).  host_bytes must equal L (REFT_ESIZE).  Other
- * arguments as for reft_snapshot_pack.
+ * by hipMemcpyAsync into a staging slot and a scatter kernel on unpack_stream) or direct (staging ==
+ * NULL: the scatter kernel reads the pinned host snapshot across the link, per bucket, on
+ * unpack_stream).  host_bytes must equal L (REFT_ESIZE).  Other arguments as for reft_snapshot_pack.
  */
 int reft_restore(reft_plan *plan, const void *host_src, uint64_t host_bytes,
                  void *staging, uint64_t staging_bytes,
@@ -429,9 +429,9 @@ int reft_restore_wait(reft_plan *plan);
  *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
  *                  alike (mod 16) relative to its stream offset.  reft_reconstruct goes by the same
  *                  two values where they are set, and at their defaults uses the variant from 5
- *                  sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader waves XOR
- *                  "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536) of the
- *                  stream at a time into LDS, and one writer wave per workgroup stores the
+ *                  sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader
+ *                  waves XOR "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536)
+ *                  of the stream at a time into LDS, and one writer wave per workgroup stores the
  *                  previous stage once all workgroups of the (persistent, "burst_wgs_per_cu" per
  *                  compute unit, default 2) grid have read theirs.  The writer waits by polling a
  *                  counter at most "burst_max_polls" times per round (default 6; 0 = never waits),

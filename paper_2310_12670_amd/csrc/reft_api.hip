@@ -49,7 +49,7 @@ static int fail(int code, const char *fmt, ...)
                         __FILE__, __LINE__);                                                      \
     } while (0)
 
-static std::atomic<uint64_t> g_max_wgs{0};       // 0 = 16 per compute unit
+static std::atomic<uint64_t> g_max_wgs{0};       // 0 = stream kernel: a wave per unit, others: 16 per compute unit
 static std::atomic<uint64_t> g_nontemporal{1};
 static std::atomic<uint64_t> g_unroll{4};
 static std::atomic<uint64_t> g_tile_shift{18};   // read at plan creation
@@ -1445,13 +1445,13 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Seven and eight long rows: reads and writes are separated in time with the burst kernel.  TB/s,
-    // burst / stream kernel, into a contiguous destination: 8 rows of 15.0 GB 6.13 / 6.03, 11.8 GB 6.25 /
-    // 6.14, 3.1 GB 6.38 / 6.29, 2.5 GB 6.28 / 6.32, 0.9 GB 6.03 / 6.14; 7 rows of 2.9 and 3.1 GB 6.43 / 6.38,
-    // 6.28 / 6.31; into tensors 15.0 GB 6.18 / 6.11, 11.8 GB 6.64 / 6.54, 3.1 GB 6.07 / 6.06, 2.5 GB 6.02 /
-    // 6.07.  Destination spans that are not all aligned alike relative to their stream offsets, which
-    // the staging image cannot represent, keep the stream kernel, and more rows go through it in
-    // one pass, up to kMaxStreamSrc.
+    // Seven and eight long rows: reads and writes are separated in time with the burst kernel.  Its rate
+    // over the stream kernel's, both in turn, medians of five over two allocations: into a contiguous
+    // destination 8 rows of 2.9 to 15.4 GB +0.3 to +2.8 %, 7 rows -0.9 to +0.9 % up to 6.4 GB and +0.2 to
+    // +2.4 % from 11.4 GB on; 8 rows of 0.9 GB 6.03 / 6.14 TB/s.  Into tensors, 11.4 to 15.4 GB: 8 rows +0.2 to
+    // +1.4 %, 7 rows -0.3 to +0.8 %; 8 rows of 3.1 and 2.5 GB 6.07 / 6.06, 6.02 / 6.07.  Destination spans that
+    // are not all aligned alike relative to their stream offsets, which the staging image cannot
+    // represent, keep the stream kernel, and more rows go through it in one pass, up to kMaxStreamSrc.
     bool burst = burst_applies(p, nrows, dst_row != nullptr);
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     if (burst && dst_row) {

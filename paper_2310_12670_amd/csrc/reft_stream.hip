@@ -432,9 +432,10 @@ constexpr uint64_t kCachedTraffic = 96ull << 20;
 static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 
 // LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than have
-// about 96 KiB in flight between them (80 KiB beside the waves that look up): wider windows cost more
-// than they hide.  us, all that fit / so many: 4 sources 1303 / 1290 (22 waves), 6: 1848 / 1815 (15),
-// 8: 2380 / 2328 (12) and 3625 / 3565 (22.6 GB, into tensors), 16: 2299 / 2226 (8).
+// about 96 KiB in flight between them (80 KiB beside the waves that look up), but at least 8 (128 KiB with
+// 16 sources): wider windows cost more than they hide.  us, all that fit / so many: 4 sources 1303 / 1290
+// (22 waves), 6: 1848 / 1815 (15), 8: 2380 / 2328 (12) and 3625 / 3565 (22.6 GB, into tensors), 16: 2299 /
+// 2226 (8).
 static uint32_t crowd_limit(int nsrc)
 {
     if (nsrc < 4) return 0;
