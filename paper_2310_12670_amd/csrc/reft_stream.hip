@@ -4,7 +4,7 @@
 //   place of stream byte o  <-  XOR over K sources of their byte o,    o in [lo, hi)
 //
 // A source is a row of span pointers or a contiguous buffer; the destination is a contiguous buffer
-// or a row of span pointers, and may itself be the last source.  With PACK, the bytes of the first
+// or a row of span pointers, and may itself be the last source.  With kPacked, the bytes of the first
 // source alone go to a second contiguous buffer as well (the packed stream of one shard beside the
 // parity of all), so that it is read once for both.
 //
@@ -24,29 +24,34 @@
 
 namespace reft {
 
-// The last of a launch's K sources (bit 0: not a row of the table) and whether the destination is a source,
-// so that every byte is read and written once only (bit 1).
+// The last of a launch's K sources.
 enum LastRow : uint32_t {
     kLastTable = 0,      // an ordinary row of the table
-    kLastContig = 1,     // the contiguous buffer whose virtual base is cbase
-    kInPlace = 2,        // an ordinary row; that or another one is the destination
-    kLastDest = 3,       // the destination's current bytes (accumulate)
+    kLastDest = 1,       // the destination's current bytes (accumulate)
+    kLastContig = 2,     // the contiguous buffer whose virtual base is cbase
 };
-constexpr uint32_t kNoRow = 1, kOnce = 2;
+
+// Forms of the kernel.
+enum Form {
+    kPlain,
+    kPacked,             // with the packed stream of the first source
+    kRuns,               // a wave takes several units together (see k_stream)
+    kInPlace,            // a row of the table is the destination: as with kLastDest, every byte is read and
+                         // written once only.  (As an argument of the plain form it costs that 1 to 5 %.)
+};
 
 struct StreamArgs {
     PlanTables pt;
     const uint64_t *tab;     // rows of span pointers, row stride T
     const uint64_t *dtab;    // the destination's row, or null: contiguous
     uint64_t vb;             // contiguous destination: byte o lies at vb + o
-    uint64_t vb2;            // PACK: byte o of the first source goes to vb2 + o
+    uint64_t vb2;            // kPacked: byte o of the first source goes to vb2 + o
     uint64_t cbase;          // kLastContig: byte o lies at cbase + o
     uint64_t lo, hi;         // stream range, lo < hi <= L
     uint64_t first_unit, nunits;
-    uint64_t nruns;          // runs of units
     uint32_t phase;          // unit u starts at stream byte u * S - phase
     uint32_t last;           // LastRow
-    uint32_t run;            // consecutive units that one wave takes together
+    uint32_t run;            // kRuns: consecutive units that one wave takes together
 };
 
 // The tables do not change while the kernel runs; read through the constant address space, entries at
@@ -97,7 +102,7 @@ __device__ __forceinline__ void locate(const PlanTables &pt, Owner &o, uint64_t 
 template <int K>
 __device__ __forceinline__ uint64_t source_of(const StreamArgs &a, int j, uint64_t q, uint64_t b)
 {
-    if (j == K - 1 && (a.last & kNoRow)) {
+    if (j == K - 1 && a.last != kLastTable) {
         if (a.last == kLastContig) return a.cbase + b;
         return a.dtab ? entry(a.dtab, q) : a.vb + b;
     }
@@ -145,16 +150,17 @@ __device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, ui
 // it, is read in whole cache lines, or, where it stands (nearly) alone, the destination is written in
 // such: a unit then starts where the one before it in the span ends, the span's first such unit moves
 // the bytes in front of it as well, and the last one, behind which there is no room, stays where it
-// is; the few bytes that come twice get the same value.  Where the destination is a source (kOnce)
+// is; the few bytes that come twice get the same value.  Where the destination is a source
 // nothing may come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
 // 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
 //
-// RUN: the units behind it as well, up to `most` in all, as far as they lie wholly inside the span and the
+// kRuns: the units behind it as well, up to `most` in all, as far as they lie wholly inside the span and the
 // range; returns how many.
-template <int K, int V, bool NT, bool PACK, bool RUN>
+template <int K, int V, bool NT, Form F>
 __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane,
                                                uint32_t most)
 {
+    constexpr bool PACK = F == kPacked;
     constexpr uint32_t S = 1024 * V;
     // everything that is known of span i in one go, without branches between the loads (where there
     // is no such table, an entry of another one is loaded and not used)
@@ -163,7 +169,7 @@ __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, 
     uint64_t p[K];
 #pragma unroll
     for (int j = 0; j < K - 1; ++j) p[j] = entry(a.tab, (uint64_t)j * a.pt.T + i);
-    p[K - 1] = entry(a.last & kNoRow ? a.pt.off : a.tab + (uint64_t)(K - 1) * a.pt.T, i);
+    p[K - 1] = entry(a.last == kLastTable ? a.tab + (uint64_t)(K - 1) * a.pt.T : a.pt.off, i);
     const uint64_t r = x - b;
     uint64_t d = (a.dtab ? dt : a.vb + b) + r;
     if (a.last == kLastContig) p[K - 1] = a.cbase + b;
@@ -178,11 +184,11 @@ __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, 
     // vmcnt(0), once in front of a run: the compiler may otherwise take registers for still in flight from
     // before and wait for them in every round, and with them for the stores of the round before (2 sources,
     // 126 MB by 4 workgroups: 2217 us so, 1583 with this)
-    if constexpr (RUN) __builtin_amdgcn_s_waitcnt(0x0f70);
+    if constexpr (F == kRuns) __builtin_amdgcn_s_waitcnt(0x0f70);
     for (uint32_t done = 1;; ++done) {
-        uint32_t lead = to_line;
+        uint32_t lead = F == kInPlace ? 0 : to_line;
         if (lead) {
-            if ((a.last & kOnce) || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
+            if (a.last == kLastDest || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
         }
         if (lead) {
             const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
@@ -220,7 +226,7 @@ __device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, 
         }
 #pragma unroll
         for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
-        if constexpr (!RUN) return 1;
+        if constexpr (F != kRuns) return 1;
         x += S;
         if (done == most || x + S > (e < a.hi ? e : a.hi)) return done;
         d += S - lead;
@@ -261,11 +267,12 @@ __device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint
 // A lane whose 16 bytes reach over the end of its span moves the span's last 16 bytes instead, and
 // then the next span's first 16: bytes that its neighbours move too are written twice, with the same
 // value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
-// the destination is a source (kOnce), in every straddling lane.
-template <int K, bool NT, bool PACK>
+// the destination is a source (a byte must then be read and written once), in every straddling lane.
+template <int K, bool NT, Form F>
 __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
                                             uint32_t lane)
 {
+    constexpr bool PACK = F == kPacked;
     constexpr uint32_t kNone = 0xffffffffu;
     const uint32_t at = lane * 16;
     // my span: `skip` spans behind o's, from byte `from` of this KiB on (if skip), up to byte `to`;
@@ -306,7 +313,8 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     const uint64_t w0 = b < a.lo ? a.lo : b, w1 = to == kNone ? y1 : x + to;
     const uint64_t w2 = to2 != kNone ? x + to2 : end2 < a.hi ? end2 : a.hi;
     const bool one = w1 >= hi;                                 // all my bytes belong to span q
-    const bool can = !(a.last & kOnce) || (one && hi - lo == 16);
+    bool can = a.last != kLastDest || (one && hi - lo == 16);
+    if constexpr (F == kInPlace) can = one && hi - lo == 16;
     if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
         const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
         const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
@@ -359,58 +367,52 @@ __device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o,
     }
 }
 
-// Unit w of the launch or, in a RUN, as many from there on as can be done together, `most` at most; returns
-// how many.
-template <int K, int U, bool NT, bool PACK, bool RUN>
-__device__ __forceinline__ uint32_t move_next(const StreamArgs &a, uint64_t w, uint32_t most, uint32_t lane)
-{
-    constexpr uint32_t S = 1024 * U;
-    Owner o;
-    const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
-    const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
-    const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
-    const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
-    if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift)
-        return move_units<K, U, NT, PACK, RUN>(a, first & ~kWholeBlock, x, lane, most);
-    locate(a.pt, o, first & ~kWholeBlock, y0, lane);
-    if (y1 - y0 == S && y1 <= o.e) return move_units<K, U, NT, PACK, RUN>(a, o.i, x, lane, most);
-#pragma unroll 1
-    for (uint32_t u = 0; u < U; ++u) {
-        const uint64_t xs = x + u * 1024;
-        const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
-        const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
-        if ((int64_t)z0 >= (int64_t)z1) continue;
-        if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
-        if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, PACK>(a, o, xs, lane);
-        else move_shared<K, NT, PACK>(a, o, xs, z1, lane);
-    }
-    return 1;
-}
-
 // The workgroup (1 or 4 waves) has no meaning beyond the dispatch.  Unless the caller caps the grid
 // there is one wave per unit, dispatched in order, so that the chip moves through its streams in
 // narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
 // workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
 //
-// RUN (a grid of few waves, each with many units): a wave takes a.run consecutive units together and
+// kRuns (a grid of few waves, each with many units): a wave takes a.run consecutive units together and
 // looks up once for those that lie in one span; without, look-ups and data of its units follow one
-// another.  126 MB in spans of 3 MB by 4 / 16 / 64 workgroups, us, without and with: packed 1867 / 479 / 134
-// and 1219 / 324 / 102 (tiles walked by workgroups: 1623 / 433 / 147), parity of 4: 3540 / 905 / 246 and
-// 2629 / 686 / 199 (3192 / 819 / 250).
-template <int K, int U, bool NT, bool PACK = false, bool RUN = false>
+// another.  126 MB in spans of 3 MB by 4 / 16 / 64 workgroups, us, without and with: packed 1869 / 479 / 134
+// and 1186 / 315 / 102 (tiles walked by workgroups: 1620 / 432 / 145), parity of 4: 3563 / 906 / 247 and
+// 2593 / 677 / 196 (3168 / 817 / 253).
+template <int K, int U, bool NT, Form F = kPlain>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
+    constexpr uint32_t S = 1024 * U;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t waves = blockDim.x >> 6;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if constexpr (!RUN) {
-        for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nunits; w += (uint64_t)gridDim.x * waves)
-            (void)move_next<K, U, NT, PACK, false>(a, w, 1, lane);
-    } else {
-        for (uint64_t w = (uint64_t)blockIdx.x * waves + wave; w < a.nruns; w += (uint64_t)gridDim.x * waves) {
-            const uint64_t end = (w + 1) * a.run < a.nunits ? (w + 1) * a.run : a.nunits;
-            for (uint64_t v = w * a.run; v < end;)
-                v += move_next<K, U, NT, PACK, true>(a, v, (uint32_t)(end - v), lane);
+    const uint64_t stride = (uint64_t)gridDim.x * waves;
+    // kRuns: units left of this run, and how many of them the last step moved
+    uint32_t left = F == kRuns ? a.run : 1, done = 1;
+    for (uint64_t w = ((uint64_t)blockIdx.x * waves + wave) * (F == kRuns ? a.run : 1); w < a.nunits;
+         w += F != kRuns ? stride : (left -= done) ? done : done + (stride - 1) * (left = a.run)) {
+        Owner o;
+        const uint64_t x = (a.first_unit + w) * S - a.phase;   // below 0 (wraps) in the first unit
+        const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
+        const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
+        const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
+        if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
+            done = move_units<K, U, NT, F>(a, first & ~kWholeBlock, x, lane, left);
+            continue;
+        }
+        locate(a.pt, o, first & ~kWholeBlock, y0, lane);
+        if (y1 - y0 == S && y1 <= o.e) {
+            done = move_units<K, U, NT, F>(a, o.i, x, lane, left);
+            continue;
+        }
+        done = 1;
+#pragma unroll 1
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint64_t xs = x + u * 1024;
+            const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
+            const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
+            if ((int64_t)z0 >= (int64_t)z1) continue;
+            if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
+            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, F == kPacked>(a, o, xs, lane);
+            else move_shared<K, NT, F>(a, o, xs, z1, lane);
         }
     }
 }
@@ -447,56 +449,45 @@ static uint32_t crowd_limit(int nsrc)
     (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
                      : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
 
-#define REFT_RUN(K) (cfg.nontemporal ? k_stream<K, 4, true, false, true> : k_stream<K, 4, false, false, true>)
-#define REFT_PICK_RUN(fn, nsrc)                                                                   \
-    switch (nsrc) {                                                                               \
-    case 1: fn = REFT_RUN(1); break;                                                              \
-    case 2: fn = REFT_RUN(2); break;                                                              \
-    case 3: fn = REFT_RUN(3); break;                                                              \
-    case 4: fn = REFT_RUN(4); break;                                                              \
-    default: return hipErrorInvalidValue;                                                         \
-    }
+#define REFT_PICK_PACK(K) (cfg.nontemporal ? k_stream<K, 1, true, kPacked> : k_stream<K, 1, false, kPacked>)
 
-#define REFT_PICK_PACK(K) (cfg.nontemporal ? k_stream<K, 1, true, true> : k_stream<K, 1, false, true>)
+#define REFT_PICK_RUNS(K) (cfg.nontemporal ? k_stream<K, 4, true, kRuns> : k_stream<K, 4, false, kRuns>)
 
-static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pack, LaunchCfg cfg,
+#define REFT_PICK_IN_PLACE(K) k_stream<K, 1, true, kInPlace>
+
+#define REFT_CASES_4(PICK)                                                                        \
+    case 1: fn = PICK(1); break;                                                                  \
+    case 2: fn = PICK(2); break;                                                                  \
+    case 3: fn = PICK(3); break;                                                                  \
+    case 4: fn = PICK(4); break;
+
+#define REFT_CASES_5_8(PICK)                                                                      \
+    case 5: fn = PICK(5); break;                                                                  \
+    case 6: fn = PICK(6); break;                                                                  \
+    case 7: fn = PICK(7); break;                                                                  \
+    case 8: fn = PICK(8); break;
+
+#define REFT_CASES_9_16(PICK)                                                                     \
+    case 9: fn = PICK(9); break;                                                                  \
+    case 10: fn = PICK(10); break;                                                                \
+    case 11: fn = PICK(11); break;                                                                \
+    case 12: fn = PICK(12); break;                                                                \
+    case 13: fn = PICK(13); break;                                                                \
+    case 14: fn = PICK(14); break;                                                                \
+    case 15: fn = PICK(15); break;                                                                \
+    case 16: fn = PICK(16); break;
+
+static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, Form form, LaunchCfg cfg,
                                 hipStream_t stream)
 {
     void (*fn)(const StreamArgs) = nullptr;
-    const bool cached = (uint64_t)(nsrc + (pack ? 2 : 1)) * (a.hi - a.lo) <= kCachedTraffic;
+    const bool cached = (uint64_t)(nsrc + (form == kPacked ? 2 : 1)) * (a.hi - a.lo) <= kCachedTraffic;
     // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
     const uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc);
     if (unroll < cfg.unroll) cfg.unroll = unroll;
     if (cached && !cfg.capped) cfg.nontemporal = false;
     if (nsrc > kMaxSrc && cfg.unroll > 2) cfg.unroll = 2;    // 2 KiB of 9 sources and more: 18 loads a lane
-    if (pack) cfg.unroll = 1;
-    switch (pack ? -nsrc : nsrc) {
-    case -1: fn = REFT_PICK_PACK(1); break;
-    case -2: fn = REFT_PICK_PACK(2); break;
-    case -3: fn = REFT_PICK_PACK(3); break;
-    case -4: fn = REFT_PICK_PACK(4); break;
-    case -5: fn = REFT_PICK_PACK(5); break;
-    case -6: fn = REFT_PICK_PACK(6); break;
-    case -7: fn = REFT_PICK_PACK(7); break;
-    case -8: fn = REFT_PICK_PACK(8); break;
-    case -9: fn = REFT_PICK_PACK(9); break;
-    case -10: fn = REFT_PICK_PACK(10); break;
-    case -11: fn = REFT_PICK_PACK(11); break;
-    case -12: fn = REFT_PICK_PACK(12); break;
-    case -13: fn = REFT_PICK_PACK(13); break;
-    case -14: fn = REFT_PICK_PACK(14); break;
-    case -15: fn = REFT_PICK_PACK(15); break;
-    case -16: fn = REFT_PICK_PACK(16); break;
-    case 9: fn = REFT_PICK_MANY(9); break;
-    case 10: fn = REFT_PICK_MANY(10); break;
-    case 11: fn = REFT_PICK_MANY(11); break;
-    case 12: fn = REFT_PICK_MANY(12); break;
-    case 13: fn = REFT_PICK_MANY(13); break;
-    case 14: fn = REFT_PICK_MANY(14); break;
-    case 15: fn = REFT_PICK_MANY(15); break;
-    case 16: fn = REFT_PICK_MANY(16); break;
-    default: REFT_PICK_K(k_stream, fn, nsrc)
-    }
+    if (form == kPacked || form == kInPlace) cfg.unroll = 1;
     // units start where the contiguous operand is 16-byte aligned
     const uint64_t S = 1024ull * cfg.unroll;
     a.phase = (uint32_t)contig & 15u;
@@ -504,10 +495,38 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, bool pa
     a.nunits = (a.hi - 1 + a.phase) / S - a.first_unit + 1;
     const uint32_t waves = cached || cfg.capped ? 4 : 1;
     a.run = 1;
-    if (cfg.runs && cfg.unroll == 4) a.run = run_of_units(a.nunits, waves * (uint64_t)cfg.max_wgs, nsrc, a.pt.L / a.pt.T);
-    if (a.run > 1) REFT_PICK_RUN(fn, nsrc)
-    a.nruns = (a.nunits + a.run - 1) / a.run;
-    const uint32_t g = stream_grid(a.nruns, waves, cfg.capped ? cfg.max_wgs : 0);
+    if (form == kPlain && cfg.runs && cfg.unroll == 4) {
+        a.run = run_of_units(a.nunits, waves * (uint64_t)cfg.max_wgs, nsrc, a.pt.L / a.pt.T);
+        if (a.run > 1) form = kRuns;
+    }
+    switch (form) {
+    case kPlain:
+        switch (nsrc) {
+            REFT_CASES_9_16(REFT_PICK_MANY)
+        default: REFT_PICK_K(k_stream, fn, nsrc)
+        }
+        break;
+    case kPacked:
+        switch (nsrc) {
+            REFT_CASES_4(REFT_PICK_PACK) REFT_CASES_5_8(REFT_PICK_PACK) REFT_CASES_9_16(REFT_PICK_PACK)
+        default: return hipErrorInvalidValue;
+        }
+        break;
+    case kRuns:
+        switch (nsrc) {
+            REFT_CASES_4(REFT_PICK_RUNS)
+        default: return hipErrorInvalidValue;
+        }
+        break;
+    case kInPlace:
+        switch (nsrc) {
+            REFT_CASES_4(REFT_PICK_IN_PLACE) REFT_CASES_5_8(REFT_PICK_IN_PLACE)
+            REFT_CASES_9_16(REFT_PICK_IN_PLACE)
+        default: return hipErrorInvalidValue;
+        }
+        break;
+    }
+    const uint32_t g = stream_grid((a.nunits + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
     hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
     return hipGetLastError();
 }
@@ -525,8 +544,9 @@ hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, b
     a.vb = dst_vbase;
     a.lo = lo;
     a.hi = hi;
-    a.last = acc ? kLastDest : in_place ? kInPlace : kLastTable;
-    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, false, cfg, stream);
+    a.last = acc ? kLastDest : kLastTable;
+    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, in_place && !acc ? kInPlace : kPlain, cfg,
+                         stream);
 }
 
 hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
@@ -543,7 +563,7 @@ hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nro
     a.lo = lo;
     a.hi = hi;
     a.last = kLastTable;
-    return launch_stream(a, nrows, vb, true, cfg, stream);
+    return launch_stream(a, nrows, vb, kPacked, cfg, stream);
 }
 
 hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,
@@ -558,7 +578,7 @@ hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t sr
     a.lo = lo;
     a.hi = hi;
     a.last = kLastContig;
-    return launch_stream(a, 1, src_vbase, false, cfg, stream);
+    return launch_stream(a, 1, src_vbase, kPlain, cfg, stream);
 }
 
 }  // namespace reft
