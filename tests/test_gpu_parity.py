@@ -70,6 +70,7 @@ class Guarded:
             self.raw = torch.full((total,), CANARY, dtype=torch.uint8, pin_memory=True)
         else:
             self.raw = torch.full((total,), CANARY, dtype=torch.uint8, device=device)
+            torch.cuda.synchronize()         # the fill runs on another stream than the call under test
         self.n = n
         self.start = GUARD + phase
         self.view = self.raw[self.start:self.start + n]
@@ -92,6 +93,7 @@ def arena_spans(sizes, phases, dev, gen):
         pos += ((n + ph + 255) // 256 + 1) * 256
     arena = torch.randint(0, 256, (max(pos, 256),), dtype=torch.uint8, device=dev, generator=gen)
     assert arena.data_ptr() % 256 == 0
+    torch.cuda.synchronize()                 # the fill runs on another stream than the call under test
     return arena, [arena[s:s + n] for s, n in zip(starts, sizes)]
 
 
