@@ -168,6 +168,16 @@ def test_sizes_around_the_launch_rule(dev, k, mean, traffic):
     check_all(dev, sizes, k, None, seed=k, align=1)
 
 
+# uncached launches of 32 n - 1, 32 n and 32 n + 1 units of 1 KiB (one source: of 2 KiB), and a few bytes to either side
+@pytest.mark.parametrize("k", [1, 15, 16])
+@pytest.mark.parametrize("units,more", [(-1, 0), (0, -5), (0, 0), (0, 9), (1, 0)])
+def test_units_change_places_inside_32_kib(dev, k, units, more):
+    unit = 2048 if k == 1 else 1024
+    L = (128 << 20) // (k + 1) // (32 * unit) * 32 * unit + units * unit + more
+    sizes = [L // 3 + 1, 70_001, 16, 33, 1 << 20]
+    check_all(dev, sizes + [L - sum(sizes)], k, None, seed=k, align=1)
+
+
 def test_more_spans_than_one_search_step(dev):
     """Blocks of the look-up table that own several hundred spans, and wide gaps of empty ones."""
     rng = np.random.default_rng(5)

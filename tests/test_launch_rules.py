@@ -13,6 +13,7 @@ SOURCE = """
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
+extern "C" uint64_t unit(uint32_t kib, uint64_t w, uint64_t n) { return kib == 1 ? reft::unit_of_wave<1>(w, n) : reft::unit_of_wave<2>(w, n); }
 extern "C" uint64_t contig_rows(uint64_t rows) { return reft::contig_burst_min_rows(rows); }
 extern "C" uint64_t contig_bytes(uint64_t bytes) { return reft::contig_burst_min_bytes(bytes); }
 """
@@ -31,6 +32,8 @@ def grid(tmp_path_factory):
     lib.link.restype = ctypes.c_uint32
     lib.run.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64]
     lib.run.restype = ctypes.c_uint32
+    lib.unit.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64]
+    lib.unit.restype = ctypes.c_uint64
     for f in (lib.contig_rows, lib.contig_bytes):
         f.argtypes = [ctypes.c_uint64]
         f.restype = ctypes.c_uint64
@@ -86,3 +89,18 @@ def test_runs_leave_every_wave_eight(grid):
                     if nsrc > 4 or waves > (896 if nsrc == 1 else 384) or mean < 1 << 18:
                         assert n == 1
     assert grid.run(30720, 16, 1, 1 << 20) == 16 and grid.run(30720, 512, 1, 1 << 20) == 7
+
+
+@pytest.mark.parametrize("kib", [1, 2])
+def test_every_unit_has_one_wave(grid, kib):
+    """The order of units is a permutation inside 32 KiB, each XCD on its own bits; what is left stays in order."""
+    for n in (1, 31, 32, 33, 63, 64, 65, 1000, 4097):
+        units = [grid.unit(kib, w, n) for w in range(n)]
+        assert sorted(units) == list(range(n))
+        assert all(u // 32 == w // 32 for w, u in enumerate(units)) and units[n // 32 * 32:] == list(range(n // 32 * 32, n))
+        own = 0b10011 if kib == 1 else 0b01011
+        for x in range(8):
+            assert len({u & own for u in units[x:n // 32 * 32:8]}) <= 1
+    for n in (1 << 33, (1 << 40) + 5):                # beyond 32 bits
+        at = n // 32 * 32 - 64
+        assert sorted(grid.unit(kib, w, n) for w in range(at, n)) == list(range(at, n))
