@@ -22,6 +22,8 @@
 #include "reft_device.hpp"
 #include "reft_rules.hpp"
 
+#include <algorithm>
+
 namespace reft {
 
 // The last of a launch's K sources.
@@ -436,15 +438,16 @@ constexpr uint64_t kCachedTraffic = 96ull << 20;
 // short spans); 16: 2299 and 2405 (14.3 GB).
 static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 
-// LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than have
-// about 96 KiB in flight between them (80 KiB beside the waves that look up), but at least 8 (128 KiB with
-// 16 sources): wider windows cost more than they hide.  us, all that fit / so many: 4 sources 1303 / 1290
-// (22 waves), 6: 1848 / 1815 (15), 8: 2380 / 2328 (12) and 3625 / 3565 (22.6 GB, into tensors), 16: 2299 /
-// 2226 (8).
+// LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than its streams
+// want: the more there are, the wider the windows in which the chip moves through memory.  Swept from 8 to 20 waves
+// on 0.5 to 14 GB (encode, decode, with packed stream, rotated): the best is 14 to 16 with 4 sources, 14 with 5 and
+// 6, 13, 12 with 8, 12, 11, 11, 10 with 12, 9, 9, 8 with 15 and 16, and one more or less costs 0.2 to 1 %.  us, with 80
+// KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4 sources 738 / 720,
+// 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713 and, in spans of 10 KB, 309 / 302.
 static uint32_t crowd_limit(int nsrc)
 {
     if (nsrc < 4) return 0;
-    const uint32_t waves = 80 / nsrc + 2 > 8 ? 80 / nsrc + 2 : 8;
+    const uint32_t waves = std::max({20 - nsrc, 17 - 5 * nsrc / 8, 8});
     return 160 * 1024 / waves / 512 * 512;
 }
 
