@@ -1399,7 +1399,7 @@ static BurstCfg burst_cfg(uint32_t *ring, uint32_t slot, int num_cus)
 // The burst kernel walks a stage piece by piece, the stream kernel spreads pieces over its waves: the
 // former pays where at most one tile in eight holds a span boundary ("small_pieces" of them).
 // Measured for 8 rows, burst / stream kernel: 0.5 GB in spans of 0.2 MB 134 / 107 us, 2 GB in spans
-// of 0.9 MB 431 / 405 us, 14.8 GB in spans of 10 MB 2338 / 2397 us.
+// of 0.9 MB 431 / 405 us.
 static bool few_dense_tiles(const reft_plan *p)
 {
     const auto &v = p->tile_spans_sorted;
@@ -1407,11 +1407,11 @@ static bool few_dense_tiles(const reft_plan *p)
     return (uint64_t)dense * 8 <= p->ntiles;
 }
 
-// Whether `rows` rows go through the burst kernel: long rows, few span boundaries.  A launch into
-// tensors needs rows four times as long.
+// Whether `rows` rows go through the burst kernel: never by default, else long rows with few span boundaries.  A
+// launch into tensors needs rows four times as long.
 static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
 {
-    return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
+    return g_burst.load() && span_burst(g_burst_min_rows.load(), g_burst_min_bytes.load()) && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
            rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
 
@@ -1445,13 +1445,9 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Seven and eight long rows: reads and writes are separated in time with the burst kernel.  Its rate
-    // over the stream kernel's, both in turn, medians of five over two allocations: into a contiguous
-    // destination 8 rows of 2.9 to 15.4 GB +0.3 to +2.8 %, 7 rows -0.9 to +0.9 % up to 6.4 GB and +0.2 to
-    // +2.4 % from 11.4 GB on; 8 rows of 0.9 GB 6.03 / 6.14 TB/s.  Into tensors, 11.4 to 15.4 GB: 8 rows +0.2 to
-    // +1.4 %, 7 rows -0.3 to +0.8 %; 8 rows of 3.1 and 2.5 GB 6.07 / 6.06, 6.02 / 6.07.  Destination spans that
-    // are not all aligned alike relative to their stream offsets, which the staging image cannot
-    // represent, keep the stream kernel, and more rows go through it in one pass, up to kMaxStreamSrc.
+    // The burst kernel where the caller asks for it.  Destination spans that are not all aligned alike relative to
+    // their stream offsets, which its staging image cannot represent, keep the stream kernel, and more rows go
+    // through it in one pass, up to kMaxStreamSrc.
     bool burst = burst_applies(p, nrows, dst_row != nullptr);
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     if (burst && dst_row) {
