@@ -228,14 +228,16 @@ struct reft_plan {
     int num_cus = 256;
     uint64_t T = 0, NB = 0, L = 0, max_bucket = 0;
     uint32_t tile_shift = 16;
-    uint32_t lookup_shift = 16;       // blocks of the device's look-up table
+    uint32_t unit_shift = 0;          // blocks of the device's look-up table of units
+    uint32_t grid = 0;                // see head_of
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
+    std::vector<uint64_t> unit_off;   // [T+1] (of plans with device tables)
     std::vector<uint64_t> bstart;     // [NB+1]
     std::vector<uint32_t> first;      // [ntiles] host copy of the tile table
-    uint8_t *d_tables = nullptr;      // device memory of the plan; the next four point into it
-    uint64_t *d_off = nullptr;
-    uint32_t *d_first = nullptr;
+    uint8_t *d_tables = nullptr;      // device memory of the plan; the pointers below point into it
+    uint64_t *d_off = nullptr, *d_unit_off = nullptr;
+    uint32_t *d_unit_span = nullptr, *d_tile_span = nullptr;
     // cache of pointer tables: a pool of ring_cap pointers (pinned host mirror and device copy)
     // handed out front to back, and the tables that currently live in it
     uint64_t ring_cap = 0, ring_head = 0, ring_tick = 0;
@@ -278,7 +280,26 @@ struct reft_plan {
     uint32_t *burst_ctr = nullptr;
     uint32_t burst_next = 0;
 
-    PlanTables tables() const { return PlanTables{d_off, d_first, T, L, lookup_shift}; }
+    PlanTables tables() const
+    {
+        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, tile_shift, grid};
+    }
+
+    // lo < hi <= L
+    StreamRange range(uint64_t lo, uint64_t hi) const
+    {
+        StreamRange r{lo, hi, 0, unit_off[T] - 1};
+        if (lo > 0) {
+            const uint64_t i = (uint64_t)(std::upper_bound(off.begin(), off.end() - 1, lo) - off.begin()) - 1;
+            r.first = unit_off[i] + first_unit_at(lo - off[i], head_of(off[i], grid));
+        }
+        if (hi < L) {
+            const uint64_t i = (uint64_t)(std::upper_bound(off.begin(), off.end() - 1, hi - 1) - off.begin()) - 1;
+            r.last = unit_off[i] + last_unit_at(hi - 1 - off[i], head_of(off[i], grid));
+        }
+        return r;
+    }
+    StreamRange all() const { return range(0, L); }
 };
 
 static LaunchCfg launch_cfg(const reft_plan *p)
@@ -615,33 +636,48 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, p->device));
     p->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    // The kernels' look-up table: blocks of 4 KiB where 65,536 of them cover the stream (a finer
-    // table has more blocks inside one span, which need no search), else larger ones up to the tile;
-    // but no more than 16 spans per block on average, since a search goes 64 spans at a time.
-    p->lookup_shift = p->tile_shift;
-    while (p->lookup_shift > 12 && ((p->L >> (p->lookup_shift - 1)) <= 65536 ||
-                                    T > 16 * ((p->L >> p->lookup_shift) + 1)))
-        --p->lookup_shift;
-    const uint64_t block = 1ull << p->lookup_shift;
-    const uint64_t nblocks = (p->L + block - 1) / block + 1;
-    // One allocation and one copy for the tables: span offsets, look-up table; behind them the burst
-    // counters and the device half of the pointer pool.
-    const size_t at_first = ((T + 1) * sizeof(uint64_t) + 255) & ~(size_t)255;
-    const size_t at_ctr = (at_first + nblocks * sizeof(uint32_t) + 255) & ~(size_t)255;
-    const size_t at_ptr = (at_ctr + kCtrBlocks * kBurstCtrBytes + 255) & ~(size_t)255;
+    // The stream kernel's look-up table: an entry per unit (a look-up then needs no search) as long as that is
+    // no more than 65,536 entries or 16 per span, else blocks of units.
+    p->grid = p->L / T >= kGridMeanSpan ? (uint32_t)kUnit - 1 : 0;
+    p->unit_off.resize(T + 1);
+    uint64_t number = 0;
+    for (uint64_t t = 0; t < T; ++t) {
+        const uint64_t n = p->off[t + 1] - p->off[t];
+        if (n) number = first_number(number, p->off[t], p->grid);
+        p->unit_off[t] = number;
+        number += units_of(n, head_of(p->off[t], p->grid));
+    }
+    p->unit_off[T] = number;
+    const uint64_t units = p->unit_off[T], most = std::max<uint64_t>(65536, 16 * T);
+    p->unit_shift = 0;
+    while ((units >> p->unit_shift) > most) ++p->unit_shift;
+    const uint64_t nblocks = (units >> p->unit_shift) + 1;
+    // One allocation and one copy for the tables: span offsets, unit offsets, units' and tiles' spans; behind them
+    // the burst counters and the device half of the pointer pool.
+    auto behind = [](size_t at, size_t bytes) { return (at + bytes + 255) & ~(size_t)255; };
+    const size_t at_unit_off = behind(0, (T + 1) * sizeof(uint64_t));
+    const size_t at_unit_span = behind(at_unit_off, (T + 1) * sizeof(uint64_t));
+    const size_t at_tile_span = behind(at_unit_span, nblocks * sizeof(uint32_t));
+    const size_t at_ctr = behind(at_tile_span, first.size() * sizeof(uint32_t));
+    const size_t at_ptr = behind(at_ctr, kCtrBlocks * kBurstCtrBytes);
     p->ring_cap = (uint64_t)kRingRows * T;
-    std::vector<uint64_t> tables((at_first + nblocks * sizeof(uint32_t) + 7) / 8, 0);
+    std::vector<uint64_t> tables(at_ctr / sizeof(uint64_t), 0);
+    uint8_t *const image = (uint8_t *)tables.data();
     std::copy(p->off.begin(), p->off.end(), tables.begin());
-    uint32_t *lookup = (uint32_t *)((uint8_t *)tables.data() + at_first);
+    std::copy(p->unit_off.begin(), p->unit_off.end(), (uint64_t *)(image + at_unit_off));
+    std::copy(first.begin(), first.end(), (uint32_t *)(image + at_tile_span));
+    uint32_t *const lookup = (uint32_t *)(image + at_unit_span);
     for (uint64_t t = 0, i = 0; i < T; ++i) {                        // t: the first block without an entry
-        const uint64_t whole = p->off[i + 1] >> p->lookup_shift;
+        const uint64_t whole = p->unit_off[i + 1] >> p->unit_shift;
         if (whole > t) std::fill(lookup + t, lookup + whole, (uint32_t)i | kWholeBlock), t = whole;
-        if (t * block < p->off[i + 1]) lookup[t++] = (uint32_t)i;
+        if (t << p->unit_shift < p->unit_off[i + 1]) lookup[t++] = (uint32_t)i;
     }
     HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
     HIPCHK(hipMemcpy(p->d_tables, tables.data(), tables.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
     p->d_off = (uint64_t *)p->d_tables;
-    p->d_first = (uint32_t *)(p->d_tables + at_first);
+    p->d_unit_off = (uint64_t *)(p->d_tables + at_unit_off);
+    p->d_unit_span = (uint32_t *)(p->d_tables + at_unit_span);
+    p->d_tile_span = (uint32_t *)(p->d_tables + at_tile_span);
     p->burst_ctr = (uint32_t *)(p->d_tables + at_ctr);
     p->d_ptr = (uint64_t *)(p->d_tables + at_ptr);
     int rc;
@@ -1068,7 +1104,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         // and of 10 KB at 51.6 / 53.5 / 53.9 GB/s.
         const LaunchCfg cfg = link_cfg(p, 3);
         for (uint64_t b = bucket_begin; b < bucket_end; ++b)
-            HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, hview, p->bstart[b], p->bstart[b + 1],
+            HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, hview, p->range(p->bstart[b], p->bstart[b + 1]),
                                  cfg, ps));
         if ((rc = release_ptrs(p, entry, ps))) return rc;
         return record_pack_done(p, ps);
@@ -1105,8 +1141,8 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
                 const uint64_t slot = (uint64_t)g * per_group + (r - r0);
                 const uint64_t slot_addr =
                     (uint64_t)(uintptr_t)staging + slot * stride + (runs[r].a & 255);
-                HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, slot_addr - runs[r].a, runs[r].a,
-                                     runs[r].b, cfg, ps));
+                HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, slot_addr - runs[r].a,
+                                     p->range(runs[r].a, runs[r].b), cfg, ps));
             }
             if ((rc = record(p->pack_filled[g], ps))) return rc;
             if ((rc = wait_on(cs, p->pack_filled[g]))) return rc;
@@ -1356,7 +1392,7 @@ extern "C" int reft_pack_device(reft_plan *p, const void *const *span_ptrs, void
     const uint64_t *tab = nullptr;
     int entry = 0;
     if ((rc = upload_ptrs(p, span_ptrs, 1, s, &tab, &entry))) return rc;
-    HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, (uint64_t)(uintptr_t)dst_dev, 0, p->L,
+    HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, (uint64_t)(uintptr_t)dst_dev, p->all(),
                          launch_cfg(p), s));
     return release_ptrs(p, entry, s);
 }
@@ -1376,7 +1412,7 @@ extern "C" int reft_unpack_device(reft_plan *p, const void *src_dev, uint64_t sr
     const uint64_t *tab = nullptr;
     int entry = 0;
     if ((rc = upload_ptrs(p, span_ptrs, 1, s, &tab, &entry))) return rc;
-    HIPCHK(launch_scatter(p->tables(), tab, (uint64_t)(uintptr_t)src_dev, 0, p->L, launch_cfg(p),
+    HIPCHK(launch_scatter(p->tables(), tab, (uint64_t)(uintptr_t)src_dev, p->all(), launch_cfg(p),
                           s));
     return release_ptrs(p, entry, s);
 }
@@ -1469,7 +1505,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
         const uint32_t cap = (uint32_t)kMaxStreamSrc - (acc ? 1u : 0u);
         const uint32_t n = nrows - done < cap ? nrows - done : cap;
         HIPCHK(launch_gather(pt, tab + (uint64_t)done * T, (int)n, acc, over_source, dtab,
-                             (uint64_t)(uintptr_t)dst_contig, 0, p->L, cfg, s));
+                             (uint64_t)(uintptr_t)dst_contig, p->all(), cfg, s));
         done += n;
     }
     return REFT_OK;
@@ -1554,12 +1590,12 @@ extern "C" int reft_parity_encode_pack(reft_plan *p, const void *const *shard_sp
         // TB/s over (k + 2) L bytes, this / a write-burst kernel with two images: 8 rows of 15.0 GB 6.08 / 6.02,
         // of 11.8 GB 6.37 / 6.33, of 2.4 GB 6.24 / 6.14, of 0.6 GB 6.21 / 5.93; 5 rows 6.33 / 5.66; two
         // launches 5.6
-        HIPCHK(launch_gather_pack(p->tables(), tab, (int)k, vb, vb2, 0, p->L, cfg, s));
+        HIPCHK(launch_gather_pack(p->tables(), tab, (int)k, vb, vb2, p->all(), cfg, s));
     } else {
         if ((rc = xor_passes(p, tab, k, nullptr, nullptr, parity_dev, false, p->burst_ctr,
                              kCtrBlocks, &p->burst_next, s)))
             return rc;
-        HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, vb2, 0, p->L, cfg, s));
+        HIPCHK(launch_gather(p->tables(), tab, 1, false, false, nullptr, vb2, p->all(), cfg, s));
     }
     return release_ptrs(p, entry, s);
     REFT_GUARD_END("reft_parity_encode_pack")
@@ -1985,7 +2021,7 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
         if ((rc = upload_ptrs(p, span_ptrs, 1, us, &tab, &entry))) return rc;
         const LaunchCfg cfg = link_cfg(p, 4);   // reads across the link need about twice the waves of writes
         for (uint64_t b = 0; b < p->NB; ++b)
-            HIPCHK(launch_scatter(pt, tab, hview, p->bstart[b], p->bstart[b + 1], cfg, us));
+            HIPCHK(launch_scatter(pt, tab, hview, p->range(p->bstart[b], p->bstart[b + 1]), cfg, us));
         if ((rc = release_ptrs(p, entry, us))) return rc;
         return record(p->rest_done, us);
     }
@@ -2038,7 +2074,7 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
                 const uint64_t slot = (uint64_t)g * per_group + (r - r0);
                 const uint64_t slot_addr =
                     (uint64_t)(uintptr_t)staging + slot * stride + (runs[r].a & 255);
-                HIPCHK(launch_scatter(pt, tab, slot_addr - runs[r].a, runs[r].a, runs[r].b, cfg, us));
+                HIPCHK(launch_scatter(pt, tab, slot_addr - runs[r].a, p->range(runs[r].a, runs[r].b), cfg, us));
             }
             if ((rc = record(p->rest_free[g], us))) return rc;
         }

@@ -25,11 +25,20 @@ constexpr uint32_t kWholeBlock = 0x80000000u;
 // Device-side tables of a plan.
 struct PlanTables {
     const uint64_t *off;           // [T+1] prefix sums of the span sizes (stream offsets)
-    const uint32_t *first_span;    // first span that owns a byte of block t of the stream, with
-                                   // kWholeBlock set if that span owns all of the block's bytes
+    const uint64_t *unit_off;      // [T+1] number of each span's first unit, and of the last one's end
+    const uint32_t *unit_span;     // first span that owns a unit of block t of 1 << unit_shift units, with
+                                   // kWholeBlock set if that span owns all of the block's units
+    const uint32_t *tile_span;     // first span that owns a byte of tile t of 1 << tile_shift bytes
     uint64_t T;
     uint64_t L;
-    uint32_t tile_shift;           // block = 1 << tile_shift stream bytes
+    uint32_t unit_shift;
+    uint32_t tile_shift;
+    uint32_t grid;                 // see head_of
+};
+
+// Stream bytes [lo, hi) and the units first .. last that may move some of them.
+struct StreamRange {
+    uint64_t lo, hi, first, last;
 };
 
 // Parameters of the gather variant that writes in chip-wide bursts (see k_gather_burst).
@@ -57,13 +66,13 @@ struct SrcBases {
 // if acc, the destination's current contents.  nrows + acc <= kMaxStreamSrc.  in_place: a row has
 // spans at the very addresses that their results go to.
 hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc, bool in_place,
-                         const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
+                         const uint64_t *dtab, uint64_t dst_vbase, const StreamRange &range,
                          const LaunchCfg &cfg, hipStream_t stream);
 
 // Fused pack + encode: the XOR of the nrows rows (contiguous, virtual base vb) and, in the same pass,
 // the packed stream of row 0 (contiguous, virtual base vb2).  nrows <= kMaxStreamSrc.
 hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
-                              uint64_t vb2, uint64_t lo, uint64_t hi, const LaunchCfg &cfg,
+                              uint64_t vb2, const StreamRange &range, const LaunchCfg &cfg,
                               hipStream_t stream);
 
 // The same result as launch_gather for up to kMaxSrc rows, by the burst kernel.  With dtab == null the
@@ -76,7 +85,7 @@ hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nr
 
 // src_vbase + o is the source address of stream byte o; tab is one row of T span pointers.
 hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,
-                          uint64_t lo, uint64_t hi, const LaunchCfg &cfg, hipStream_t stream);
+                          const StreamRange &range, const LaunchCfg &cfg, hipStream_t stream);
 
 // dst[i] = XOR over s < nsrc of src.p[s][i], i in [0, L); any alignment.  The _burst form gives the
 // same bytes with reads and writes separated in time (see k_gather_burst).

@@ -233,7 +233,7 @@ k_gather_burst(PlanTables pt, const uint64_t *__restrict__ tab, const uint64_t *
             uint64_t e = o + stage;
             if (e > hi) e = hi;
             const ToImage sink{img, (vb + o) & ~15ull};
-            uint32_t i = pt.first_span[o >> pt.tile_shift] & ~kWholeBlock;
+            uint32_t i = pt.tile_span[o >> pt.tile_shift];
             while (o < e) {
                 // o < e <= L = off[T], so a span with off[i+1] > o exists at or after i
                 while (pt.off[i + 1] <= o) ++i;
@@ -256,7 +256,7 @@ k_gather_burst(PlanTables pt, const uint64_t *__restrict__ tab, const uint64_t *
                 emit_piece<NT>(vb + o, img0, (uint32_t)(e - o), lane);
             } else {
                 const uint64_t o0 = o;
-                uint32_t i = pt.first_span[o >> pt.tile_shift] & ~kWholeBlock;
+                uint32_t i = pt.tile_span[o >> pt.tile_shift];
                 while (o < e) {
                     while (pt.off[i + 1] <= o) ++i;
                     const uint64_t so = pt.off[i];

@@ -8,17 +8,17 @@
 // source alone go to a second contiguous buffer as well (the packed stream of one shard beside the
 // parity of all), so that it is read once for both.
 //
-// The unit of work is one wavefront's: S = 1024 U consecutive stream bytes, U chunks of 16 bytes per
-// lane and source, all in flight at once.  A wave finds the span that owns its unit's first byte with
-// one look-up in the plan's table and one coalesced load of 64 span ends (locate), and from there
-//   - a unit inside one span, the usual case, needs K span pointers and then only vector accesses at
-//     uniform bases;
-//   - a unit that spans share is done 1 KiB at a time, and where a boundary falls into that KiB
-//     every lane finds its own span by comparing with the boundaries, which the wave broadcasts one
-//     by one.
-// Waves do not meet: no LDS, no barrier, so the chain of dependent loads (table, span ends,
-// pointers, data: 2 - 4 us) of one wave hides behind the others, and short streams, which have few
-// units, spread over the whole chip.
+// The unit of work is one wavefront's: a KiB of one span (units_of), 16 bytes per lane and source, all in flight
+// at once.  A wave looks up its unit's span (a table with an entry per unit, or per block of units in long
+// streams), loads what is known of the span, K span pointers among it, and then has only vector accesses at uniform
+// bases; the span's last unit differs in nothing but the lanes that store.  No unit has bytes of two spans, so
+// there is nothing to search and nothing for lanes to decide, whatever the spans' sizes.
+//
+// Waves do not meet: no LDS, no barrier, so the chain of dependent loads (table, span, data: 2 - 3 us) of one wave
+// hides behind the others, and short streams, which have few units, spread over the whole chip.
+//
+// Before, the units were KiB of the stream: a wave whose KiB held a boundary broadcast the boundaries, every lane
+// found its own span, and straddling lanes moved 16 bytes of either.
 #include "reft_device.hpp"
 #include "reft_rules.hpp"
 
@@ -43,18 +43,24 @@ enum Form {
 };
 
 struct StreamArgs {
-    PlanTables pt;
+    const uint64_t *off, *unit_off;   // of the plan's tables (PlanTables)
+    const uint32_t *unit_span;
+    uint64_t T;
     const uint64_t *tab;     // rows of span pointers, row stride T
-    const uint64_t *dtab;    // the destination's row, or null: contiguous
+    const uint64_t *last_row, *dest_row;   // of the last source and the destination, or any table (not used)
     uint64_t vb;             // contiguous destination: byte o lies at vb + o
     uint64_t vb2;            // kPacked: byte o of the first source goes to vb2 + o
     uint64_t cbase;          // kLastContig: byte o lies at cbase + o
-    uint64_t lo, hi;         // stream range, lo < hi <= L
-    uint64_t first_unit, nunits;
-    uint32_t phase;          // unit u starts at stream byte u * S - phase
+    StreamRange range;       // lo < hi <= L
+    uint64_t first_step, nsteps;   // a wave's step is U units: step x has units x U .. x U + U - 1
+    uint64_t stride;         // waves of the grid
+    uint32_t waves;          // waves per workgroup
+    uint32_t unit_shift;
+    uint32_t grid;           // see head_of
     uint32_t last;           // LastRow
-    uint32_t spread;         // units in the order of unit_of_wave
-    uint32_t run;            // kRuns: consecutive units that one wave takes together
+    uint32_t ragged;         // the destination has a row
+    uint32_t spread;         // steps in the order of unit_of_wave
+    uint32_t run;            // kRuns: consecutive steps that one wave takes together
 };
 
 // The tables do not change while the kernel runs; read through the constant address space, entries at
@@ -77,39 +83,59 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l)
     return (uint64_t)b << 32 | a;
 }
 
-// Span i owns stream bytes [b, e), and lane l holds the end of span base + l, where i = base + c.
-// All but `ends` are the same in every lane.
-struct Owner {
-    uint64_t i, b, e, base, ends;
-    uint32_t c;
-};
-
-// The span that owns byte x < L; span i is that one or an earlier one.  64 span ends per step: the
-// number of them at or below x says how far to go on.
-__device__ __forceinline__ void locate(const PlanTables &pt, Owner &o, uint64_t i, uint64_t x, uint32_t lane)
+// The span that owns unit u; all lanes get the same answer.  Where a block of units is shared by spans, 64 ends per
+// step: the number of them at or below u says how far to go on.
+__device__ __forceinline__ uint64_t span_of(const StreamArgs &a, uint64_t u, uint32_t lane)
 {
-    o.b = entry(pt.off, i);
+    const uint32_t first = entry(a.unit_span, u >> a.unit_shift);
+    uint64_t i = first & ~kWholeBlock;
+    if (first & kWholeBlock) return i;
     for (;; i += 64) {
-        const uint64_t at = i + 1 + lane < pt.T ? i + 1 + lane : pt.T;
-        o.ends = entry(pt.off, at);                                   // off[T] = L > x ends the search
-        o.c = (uint32_t)__popcll(__ballot(o.ends <= x));
-        if (o.c) o.b = readlane64(o.ends, o.c - 1);
-        if (o.c < 64) break;
+        const uint64_t at = i + 1 + lane < a.T ? i + 1 + lane : a.T;
+        const uint32_t c = (uint32_t)__popcll(__ballot(entry(a.unit_off, at) <= u));   // unit_off[T] > u ends the search
+        if (c < 64) return i + c;
     }
-    o.base = i;
-    o.i = i + o.c;
-    o.e = readlane64(o.ends, o.c);
 }
 
-// The address of the first byte of span q (which starts at stream byte b) in source row j.
+// What a wave knows of a span.
 template <int K>
-__device__ __forceinline__ uint64_t source_of(const StreamArgs &a, int j, uint64_t q, uint64_t b)
+struct Span {
+    uint64_t u0, u1;         // its units
+    int64_t lo, hi;          // its bytes in the range, from its first one on (lo may lie below 0)
+    uint64_t s[K], d, d2;    // where its first byte lies in the sources, the destination and the packed stream
+    uint32_t head, lead;     // see piece_of
+};
+
+// Span i, everything in one go (what the last source and the destination have no table for comes from another one
+// and is not used: a branch there costs the wave another wait).
+//
+// The lead: a span's units lie so that the first source, and with it those that are aligned like it, is read in
+// whole cache lines, or, where it stands (nearly) alone, the destination is written in such.  (Shards of tensors at
+// odd stream offsets are aligned alike: 8 x 56 MB encoded in 87 instead of 108 us.)
+template <int K>
+__device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
 {
-    if (j == K - 1 && a.last != kLastTable) {
-        if (a.last == kLastContig) return a.cbase + b;
-        return a.dtab ? entry(a.dtab, q) : a.vb + b;
-    }
-    return entry(a.tab, (uint64_t)j * a.pt.T + q);
+    Span<K> o;
+    const uint64_t b = entry(a.off, i), e = entry(a.off, i + 1);
+    o.u0 = entry(a.unit_off, i);
+    o.u1 = entry(a.unit_off, i + 1);
+    const uint64_t dt = entry(a.dest_row, i);
+#pragma unroll
+    for (int j = 0; j < K - 1; ++j) o.s[j] = entry(a.tab, (uint64_t)j * a.T + i);
+    o.s[K - 1] = entry(a.last_row, i);
+    __builtin_amdgcn_sched_barrier(0);       // (the compiler waits for the first before it asks for the last)
+    o.d = a.ragged ? dt : a.vb + b;
+    o.d2 = a.vb2 + b;
+    if (a.last == kLastContig) o.s[K - 1] = a.cbase + b;
+    if (a.last == kLastDest) o.s[K - 1] = o.d;
+    o.head = (uint32_t)head_of((uint32_t)b, a.grid);
+    o.lo = (int64_t)(a.range.lo - b);
+    o.hi = (int64_t)((e < a.range.hi ? e : a.range.hi) - b);
+    uint32_t alike = 0;
+#pragma unroll
+    for (int j = 1; j < K; ++j) alike += (((uint32_t)o.s[j] ^ (uint32_t)o.s[0]) & 15u) == 0;
+    o.lead = (uint32_t)(0 - (2 * alike >= K ? o.s[0] : o.d) - o.head) & (kMaxLead - 1);
+    return o;
 }
 
 template <bool NT>
@@ -119,305 +145,162 @@ __device__ __forceinline__ void st16_any(uint64_t p, u32x4 v)
     else *(REFT_GLOBAL u32x4_any *)p = v;
 }
 
-// The XOR of the 16 bytes at address(j), j < K; all loads before the first use.  With PACK the first
-// 16 go to pack.
-template <int K, bool NT, bool PACK, class Address>
-__device__ __forceinline__ u32x4 xor_16(Address address, uint64_t pack)
+// Loads of the 16 bytes `at` bytes (at least 0) behind p.
+template <bool NT>
+__device__ __forceinline__ u32x4 ld16_at(uint64_t p, uint32_t at)
 {
-    gcptr16 s[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) s[j] = as_gc16(address(j));
+    return ld16<NT>((gcptr16)((const REFT_GLOBAL char *)p + at));
+}
+
+// The XOR of the sources' 16 bytes at byte `from` + `at` of the span, all loads before the first use (left alone,
+// the compiler alternates them); stored if `store`.
+template <int K, bool NT, bool PACK>
+__device__ __forceinline__ void move_16(const Span<K> &o, int64_t from, uint32_t at, bool store)
+{
     u32x4 t[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) t[j] = ld16<NT>(s[j]);
+    for (int j = 0; j < K; ++j) t[j] = ld16_at<NT>(o.s[j] + from, at);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (PACK) st16_any<NT>(pack, t[0]);
     u32x4 v = t[0];
 #pragma unroll
     for (int j = 1; j < K; ++j) v ^= t[j];
-    return v;
+    if (store) {
+        if constexpr (PACK) st16_any<NT>(o.d2 + from + at, t[0]);
+        st16_any<NT>(o.d + from + at, v);
+    }
 }
 
-// 1 KiB of span o.i from stream byte x on, wholly inside the span and the range.
-template <int K, bool NT, bool PACK>
-__device__ __forceinline__ void move_kib(const StreamArgs &a, const Owner &o, uint64_t x, uint32_t lane)
+// Byte x of the span.
+template <int K, bool PACK>
+__device__ __forceinline__ void move_byte(const Span<K> &o, int64_t x)
 {
-    const uint64_t r = x - o.b + lane * 16;
-    const u32x4 v = xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, o.i, o.b) + r; },
-                                        a.vb2 + x + lane * 16);
-    st16_any<NT>(a.dtab ? entry(a.dtab, o.i) + r : a.vb + x + lane * 16, v);
+    uint8_t t[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) t[j] = ld8(o.s[j] + x);
+    if constexpr (PACK) st8(o.d2 + x, t[0]);
+#pragma unroll
+    for (int j = 1; j < K; ++j) t[0] ^= t[j];
+    st8(o.d + x, t[0]);
 }
 
-// The unit of V KiB at stream byte x, wholly inside span i and the range.  Inside a span the units
-// move together by up to 127 bytes so that the first source, and with it those that are aligned like
-// it, is read in whole cache lines, or, where it stands (nearly) alone, the destination is written in
-// such: a unit then starts where the one before it in the span ends, the span's first such unit moves
-// the bytes in front of it as well, and the last one, behind which there is no room, stays where it
-// is; the few bytes that come twice get the same value.  Where the destination is a source
-// nothing may come twice, and nothing is moved.  (Shards of tensors at odd stream offsets are aligned alike:
-// 8 x 56 MB encoded in 87 instead of 108 us, 8 x 132 MB of small tensors in 221 instead of 262.)
-//
-// kRuns: the units behind it as well, up to `most` in all, as far as they lie wholly inside the span and the
-// range; returns how many.
-template <int K, int V, bool NT, Form F>
-__device__ __forceinline__ uint32_t move_units(const StreamArgs &a, uint64_t i, uint64_t x, uint32_t lane,
+// Unit u of span o.  All lanes load, those behind the piece's end its last 16 bytes, and one of them stores these: a
+// few bytes come twice, with the same value.  Only where fewer than 16 bytes of the span lie in the range up to
+// the piece's end, and where the destination is a source (a byte must then be read and written once), the bytes
+// behind the last whole 16 go one per lane.
+template <int K, bool NT, Form F>
+__device__ __forceinline__ void move_unit(const StreamArgs &a, const Span<K> &o, uint64_t u, uint32_t lane)
+{
+    constexpr bool PACK = F == kPacked;
+    const bool once = F == kInPlace || a.last == kLastDest;
+    const int64_t lo = o.lo > 0 ? o.lo : 0;
+    const Piece p = piece_of(u - o.u0, o.head, once ? 0 : o.lead, lo, o.hi);
+    if (p.s >= p.t) return;
+    const int32_t len = (int32_t)(p.t - p.s);                  // at most kUnit + kMaxLead - 1
+    if (!once && p.t - lo >= 16) {
+        const int64_t from = len < 16 ? p.t - 16 : p.s;        // a short piece takes bytes in front of it along
+        const int32_t n = len < 16 ? 16 : len;
+        move_16<K, NT, PACK>(o, from, (uint32_t)lane_place((int32_t)lane * 16, n), (int32_t)lane * 16 < n);
+        if (n > (int32_t)kUnit && (int32_t)lane * 16 < n - (int32_t)kUnit)
+            move_16<K, NT, PACK>(o, from, (uint32_t)lane_place((int32_t)(kUnit + lane * 16), n), true);
+        return;
+    }
+    if ((int32_t)lane * 16 + 16 <= len) move_16<K, NT, PACK>(o, p.s, lane * 16, true);
+    const int32_t whole = len & ~15;
+    if ((int32_t)lane < len - whole) move_byte<K, PACK>(o, p.s + whole + lane);
+}
+
+// The U units from u on, and kRuns the steps behind them, up to `most` in all, as far as all their bytes are
+// of span o and in the range; returns how many steps.
+template <int K, int U, bool NT, Form F>
+__device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K> &o, uint64_t u, uint32_t lane,
                                                uint32_t most)
 {
     constexpr bool PACK = F == kPacked;
-    constexpr uint32_t S = 1024 * V;
-    // everything that is known of span i in one go, without branches between the loads (where there
-    // is no such table, an entry of another one is loaded and not used)
-    const uint64_t b = entry(a.pt.off, i), e = entry(a.pt.off, i + 1);
-    const uint64_t dt = entry(a.dtab ? a.dtab : a.pt.off, i);
-    uint64_t p[K];
-#pragma unroll
-    for (int j = 0; j < K - 1; ++j) p[j] = entry(a.tab, (uint64_t)j * a.pt.T + i);
-    p[K - 1] = entry(a.last == kLastTable ? a.tab + (uint64_t)(K - 1) * a.pt.T : a.pt.off, i);
-    const uint64_t r = x - b;
-    uint64_t d = (a.dtab ? dt : a.vb + b) + r;
-    if (a.last == kLastContig) p[K - 1] = a.cbase + b;
-    if (a.last == kLastDest) p[K - 1] = d - r;
-    gcptr16 s[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) s[j] = as_gc16(p[j] + r);
-    uint32_t alike = 0;
-#pragma unroll
-    for (int j = 1; j < K; ++j) alike += (((uint32_t)(uint64_t)s[j] ^ (uint32_t)(uint64_t)s[0]) & 15u) == 0;
-    const uint32_t to_line = (uint32_t)(0 - (2 * alike >= K ? (uint64_t)s[0] : d)) & 127u;
+    constexpr int64_t S = U * (int64_t)kUnit;
+    const bool once = F == kInPlace || a.last == kLastDest;
+    const uint32_t lead = once ? 0 : o.lead;
+    int64_t x = (int64_t)((u - o.u0) * kUnit + o.head + lead - kUnit);
+    const bool whole = (u > o.u0 || x == 0) && x >= o.lo && x + S <= o.hi;
+    if (!whole) return 0;
     // vmcnt(0), once in front of a run: the compiler may otherwise take registers for still in flight from
     // before and wait for them in every round, and with them for the stores of the round before (2 sources,
     // 126 MB by 4 workgroups: 2217 us so, 1583 with this)
     if constexpr (F == kRuns) __builtin_amdgcn_s_waitcnt(0x0f70);
     for (uint32_t done = 1;; ++done) {
-        uint32_t lead = F == kInPlace ? 0 : to_line;
-        if (lead) {
-            if (a.last == kLastDest || x + S + 128 > (e < a.hi ? e : a.hi)) lead = 0;
-        }
-        if (lead) {
-            const int64_t first = (int64_t)(b > a.lo ? b : a.lo);
-            if ((int64_t)x - (int64_t)S < first && lane * 16 < lead) {
-                st16_any<NT>(d + lane * 16, xor_16<K, NT, PACK>([&](int j) { return (uint64_t)s[j] + lane * 16; },
-                                                                a.vb2 + x + lane * 16));
-            }
-            d += lead;
-#pragma unroll
-            for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + lead);
-        }
-        // all loads of up to 16 chunks before the first use (left alone, the compiler alternates them)
-        constexpr int R = K * V <= 16 ? K : 16 / V;
-        u32x4 v[V] = {};
+        // all loads of up to 16 chunks before the first use
+        constexpr int R = K * U <= 16 ? K : 16 / U;
+        u32x4 v[U] = {};
 #pragma unroll
         for (int j = 0; j < K; j += R) {
-            u32x4 t[R][V];
+            u32x4 t[R][U];
 #pragma unroll
             for (int q = 0; q < R && j + q < K; ++q) {
 #pragma unroll
-                for (int u = 0; u < V; ++u) t[q][u] = ld16<NT>(s[j + q] + lane + u * 64);
+                for (int c = 0; c < U; ++c) t[q][c] = ld16_at<NT>(o.s[j + q] + x, lane * 16 + c * (uint32_t)kUnit);
             }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (PACK) {
                 if (j == 0) {
 #pragma unroll
-                    for (int u = 0; u < V; ++u) st16_any<NT>(a.vb2 + x + lead + (lane + u * 64) * 16, t[0][u]);
+                    for (int c = 0; c < U; ++c) st16_any<NT>(o.d2 + x + lane * 16 + c * kUnit, t[0][c]);
                 }
             }
 #pragma unroll
             for (int q = 0; q < R && j + q < K; ++q) {
 #pragma unroll
-                for (int u = 0; u < V; ++u) v[u] ^= t[q][u];
+                for (int c = 0; c < U; ++c) v[c] ^= t[q][c];
             }
         }
 #pragma unroll
-        for (int u = 0; u < V; ++u) st16_any<NT>(d + (uint64_t)(lane + u * 64) * 16, v[u]);
+        for (int c = 0; c < U; ++c) st16_any<NT>(o.d + x + lane * 16 + c * kUnit, v[c]);
         if constexpr (F != kRuns) return 1;
         x += S;
-        if (done == most || x + S > (e < a.hi ? e : a.hi)) return done;
-        d += S - lead;
-#pragma unroll
-        for (int j = 0; j < K; ++j) s[j] = as_gc16((uint64_t)s[j] + S - lead);
-    }
-}
-
-// n bytes from stream byte p on, all inside span q (which starts at b), one by one.
-template <int K, bool PACK>
-__device__ __forceinline__ void move_bytes(const StreamArgs &a, uint64_t q, uint64_t b, uint64_t p, uint32_t n)
-{
-    const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
-    uint64_t s[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) s[j] = source_of<K>(a, j, q, b) + (p - b);
-    for (uint32_t t = 0; t < n; t += 4) {                      // 4 K bytes in flight
-        uint32_t v[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-#pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) {
-                const uint8_t x = ld8(s[j] + (t + c < n ? t + c : n - 1));
-                if (PACK && j == 0 && t + c < n) st8(a.vb2 + p + t + c, x);
-                v[c] ^= x;
-            }
-        }
-#pragma unroll
-        for (uint32_t c = 0; c < 4; ++c)
-            if (t + c < n) st8(d + t + c, (uint8_t)v[c]);
-    }
-}
-
-// 1 KiB from stream byte x on that several spans share or that reaches out of the range.  o owns the
-// first of its bytes that lies in the range, y1 is the end of them; lane l holds the end of span
-// base + l (ends), span o.i is base + c.
-//
-// A lane whose 16 bytes reach over the end of its span moves the span's last 16 bytes instead, and
-// then the next span's first 16: bytes that its neighbours move too are written twice, with the same
-// value.  Bytes are moved one by one only in spans that have fewer than 16 in the range, and, where
-// the destination is a source (a byte must then be read and written once), in every straddling lane.
-template <int K, bool NT, Form F>
-__device__ __forceinline__ void move_shared(const StreamArgs &a, const Owner &o, uint64_t x, uint64_t y1,
-                                            uint32_t lane)
-{
-    constexpr bool PACK = F == kPacked;
-    constexpr uint32_t kNone = 0xffffffffu;
-    const uint32_t at = lane * 16;
-    // my span: `skip` spans behind o's, from byte `from` of this KiB on (if skip), up to byte `to`;
-    // the next one with bytes: `skip2` spans behind o's, up to byte `to2`
-    uint32_t skip = 0, from = 0, to = kNone, skip2 = 0, to2 = kNone;
-    uint64_t base = o.base, ends = o.ends;
-    uint32_t j = o.c;
-    for (;;) {
-        const uint32_t rel = (uint32_t)(ends - x);
-        const uint32_t n = (uint32_t)__popcll(__ballot(ends < y1));   // ends ascend: lanes 0 .. n - 1
-        for (; j < n; ++j) {
-            const uint32_t bnd = __builtin_amdgcn_readlane(rel, j);
-            const uint32_t s = (uint32_t)(base - o.i) + j + 1;
-            if (at >= bnd) {
-                skip = s;
-                from = bnd;
-            } else if (to == kNone || bnd == to) {
-                to = bnd;
-                skip2 = s;
-            } else if (to2 == kNone) {
-                to2 = bnd;
-            }
-        }
-        if (n < 64) break;
-        base += 64;
-        const uint64_t idx = base + 1 + lane < a.pt.T ? base + 1 + lane : a.pt.T;
-        ends = entry(a.pt.off, idx);
-        j = 0;
-    }
-    // the end of span o.i + skip2, where no boundary in this KiB gave it
-    const uint64_t end2 = __shfl(ends, (int)((uint32_t)(o.i - base) + skip2) & 63);
-    const uint64_t me = x + at;                                // may wrap below 0 in the first unit
-    const uint64_t lo = (int64_t)me < (int64_t)a.lo ? a.lo : me;
-    const uint64_t hi = (int64_t)(me + 16) > (int64_t)y1 ? y1 : me + 16;
-    if ((int64_t)lo >= (int64_t)hi) return;
-    // the parts of the two spans that lie in the range (of the first, as far as it is known): [w0, w1), [w1, w2)
-    const uint64_t q = o.i + skip, b = skip ? x + from : o.b, q2 = o.i + skip2;
-    const uint64_t w0 = b < a.lo ? a.lo : b, w1 = to == kNone ? y1 : x + to;
-    const uint64_t w2 = to2 != kNone ? x + to2 : end2 < a.hi ? end2 : a.hi;
-    const bool one = w1 >= hi;                                 // all my bytes belong to span q
-    bool can = a.last != kLastDest || (one && hi - lo == 16);
-    if constexpr (F == kInPlace) can = one && hi - lo == 16;
-    if (can && w1 - w0 >= 16 && (one || (w2 - w1 >= 16 && w2 >= hi))) {
-        const uint64_t p = lo < w1 - 16 ? lo : w1 - 16;
-        const uint64_t d = (a.dtab ? entry(a.dtab, q) - b : a.vb) + p;
-        if constexpr (K <= 4) {                                // both at once, where registers allow
-            gcptr16 s[K], s2[K];
-            uint64_t d2 = 0;
-            u32x4 t[K], t2[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j) s[j] = as_gc16(source_of<K>(a, j, q, b) + (p - b));
-            if (!one) {
-                d2 = a.dtab ? entry(a.dtab, q2) : a.vb + w1;
-#pragma unroll
-                for (int j = 0; j < K; ++j) s2[j] = as_gc16(source_of<K>(a, j, q2, w1));
-            }
-#pragma unroll
-            for (int j = 0; j < K; ++j) t[j] = ld16<NT>(s[j]);
-            if (!one) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) t2[j] = ld16<NT>(s2[j]);
-            }
-            if constexpr (PACK) {
-                st16_any<NT>(a.vb2 + p, t[0]);
-                if (!one) st16_any<NT>(a.vb2 + w1, t2[0]);
-            }
-#pragma unroll
-            for (int j = 1; j < K; ++j) t[0] ^= t[j];
-            st16_any<NT>(d, t[0]);
-            if (!one) {
-#pragma unroll
-                for (int j = 1; j < K; ++j) t2[0] ^= t2[j];
-                st16_any<NT>(d2, t2[0]);
-            }
-        } else {
-            st16_any<NT>(d, xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, q, b) + (p - b); },
-                                                a.vb2 + p));
-            if (!one)
-                st16_any<NT>(a.dtab ? entry(a.dtab, q2) : a.vb + w1,
-                             xor_16<K, NT, PACK>([&](int j) { return source_of<K>(a, j, q2, w1); }, a.vb2 + w1));
-        }
-        return;
-    }
-    // spans of less than 16 bytes
-    uint64_t i = q, begin = b;
-    for (uint64_t p = lo;;) {
-        const uint64_t e = entry(a.pt.off, i + 1);
-        move_bytes<K, PACK>(a, i, begin, p, (uint32_t)((e < hi ? e : hi) - p));
-        if (e >= hi) break;
-        p = begin = e;
-        do ++i; while (entry(a.pt.off, i + 1) <= p);                  // p < hi <= L = off[T]
+        if (done == most || x + S > o.hi) return done;
     }
 }
 
 // The workgroup (1 or 4 waves) has no meaning beyond the dispatch.  Unless the caller caps the grid
-// there is one wave per unit, dispatched in order, so that the chip moves through its streams in
+// there is one wave per step, dispatched in order, so that the chip moves through its streams in
 // narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
 // workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
 //
-// kRuns (a grid of few waves, each with many units): a wave takes a.run consecutive units together and
-// looks up once for those that lie in one span; without, look-ups and data of its units follow one
+// kRuns (a grid of few waves, each with many units): a wave takes a.run consecutive steps together and
+// looks up once for those that lie in one span; without, look-ups and data of its steps follow one
 // another.  126 MB in spans of 3 MB by 4 / 16 / 64 workgroups, us, without and with: packed 1869 / 479 / 134
 // and 1186 / 315 / 102 (tiles walked by workgroups: 1620 / 432 / 145), parity of 4: 3563 / 906 / 247 and
 // 2593 / 677 / 196 (3168 / 817 / 253).
 template <int K, int U, bool NT, Form F = kPlain>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
-    constexpr uint32_t S = 1024 * U;
     const uint32_t lane = threadIdx.x & 63;
-    const uint32_t waves = blockDim.x >> 6;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t stride = (uint64_t)gridDim.x * waves;
-    // kRuns: units left of this run, and how many of them the last step moved
+    // all arguments at once: left alone, the compiler loads a few, looks whether there is work, and then loads the
+    // others, and the first wave on a die waits for host memory twice
+    asm volatile("" ::"s"(a.off), "s"(a.unit_off), "s"(a.unit_span), "s"(a.T), "s"(a.tab), "s"(a.last_row), "s"(a.dest_row), "s"(a.vb),
+                 "s"(a.cbase), "s"(a.range.lo), "s"(a.range.hi), "s"(a.first_step), "s"(a.nsteps), "s"(a.waves),
+                 "s"(a.unit_shift), "s"(a.grid), "s"(a.last), "s"(a.ragged), "s"(a.stride), "s"(a.spread));
+    // kRuns: steps left of this run, and how many of them the last round moved
     uint32_t left = F == kRuns ? a.run : 1, done = 1;
-    for (uint64_t w = ((uint64_t)blockIdx.x * waves + wave) * (F == kRuns ? a.run : 1); w < a.nunits;
-         w += F != kRuns ? stride : (left -= done) ? done : done + (stride - 1) * (left = a.run)) {
-        Owner o;
+    for (uint64_t w = ((uint64_t)blockIdx.x * a.waves + wave) * (F == kRuns ? a.run : 1); w < a.nsteps;
+         w += F != kRuns ? a.stride : (left -= done) ? done : done + (a.stride - 1) * (left = a.run)) {
         // streaming launches only: the few instructions more delay a short one by 0.2 us
-        const uint64_t un = NT && F != kRuns && U <= 2 && a.spread ? unit_of_wave<U>(w, a.nunits) : w;
-        const uint64_t x = (a.first_unit + un) * S - a.phase;  // below 0 (wraps) in the first unit
-        const uint64_t y0 = (int64_t)x < (int64_t)a.lo ? a.lo : x;
-        const uint64_t y1 = (int64_t)(x + S) > (int64_t)a.hi ? a.hi : x + S;
-        const uint32_t first = entry(a.pt.first_span, y0 >> a.pt.tile_shift);
-        if ((first & kWholeBlock) && y1 - y0 == S && y1 <= ((y0 >> a.pt.tile_shift) + 1) << a.pt.tile_shift) {
-            done = move_units<K, U, NT, F>(a, first & ~kWholeBlock, x, lane, left);
-            continue;
-        }
-        locate(a.pt, o, first & ~kWholeBlock, y0, lane);
-        if (y1 - y0 == S && y1 <= o.e) {
-            done = move_units<K, U, NT, F>(a, o.i, x, lane, left);
-            continue;
-        }
-        done = 1;
-#pragma unroll 1
-        for (uint32_t u = 0; u < U; ++u) {
-            const uint64_t xs = x + u * 1024;
-            const uint64_t z0 = (int64_t)xs < (int64_t)a.lo ? a.lo : xs;
-            const uint64_t z1 = (int64_t)(xs + 1024) > (int64_t)y1 ? y1 : xs + 1024;
-            if ((int64_t)z0 >= (int64_t)z1) continue;
-            if (z0 >= o.e) locate(a.pt, o, o.i, z0, lane);
-            if (z1 - z0 == 1024 && z1 <= o.e) move_kib<K, NT, F == kPacked>(a, o, xs, lane);
-            else move_shared<K, NT, F>(a, o, xs, z1, lane);
+        const uint64_t step = NT && F != kRuns && U <= 2 && a.spread ? unit_of_wave<U>(w, a.nsteps) : w;
+        uint64_t u = (a.first_step + step) * U;
+        if (U > 1 && u < a.range.first) u = a.range.first;
+        uint64_t end = (a.first_step + step + 1) * U;
+        if (U > 1 && end > a.range.last + 1) end = a.range.last + 1;
+        Span<K> o = load_span<K>(a, span_of(a, u, lane));
+        if constexpr (U == 1 && F != kRuns) {
+            move_unit<K, NT, F>(a, o, u, lane);
+        } else {
+            done = end - u == U && end <= o.u1 ? move_steps<K, U, NT, F>(a, o, u, lane, left) : 0;
+            if (done) continue;
+            done = 1;
+            for (;;) {
+                move_unit<K, NT, F>(a, o, u, lane);
+                if (++u == end) break;
+                if (u >= o.u1) o = load_span<K>(a, span_of(a, u, lane));
+            }
         }
     }
 }
@@ -439,16 +322,20 @@ constexpr uint64_t kCachedTraffic = 96ull << 20;
 static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 
 // LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than its streams
-// want: the more there are, the wider the windows in which the chip moves through memory.  Swept from 8 to 20 waves
-// on 0.5 to 14 GB (encode, decode, with packed stream, rotated): the best is 14 to 16 with 4 sources, 14 with 5 and
-// 6, 13, 12 with 8, 12, 11, 11, 10 with 12, 9, 9, 8 with 15 and 16, and one more or less costs 0.2 to 1 %.  us, with 80
-// KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4 sources 738 / 720,
-// 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713 and, in spans of 10 KB, 309 / 302.
-static uint32_t crowd_limit(int nsrc)
+// want: the more there are, the wider the windows in which the chip moves through memory.  Swept from 8 to 30 waves
+// on 0.1 to 14 GB, in spans of 10 KB to 10 MB (encode, decode, with packed stream, rotated, copies): with 4 sources and
+// more the best is 16, 14, 14, 13, 12 (8 sources), 12, 11, 11, 10 (12), 9, 9, 8, 8, and one more or less costs 0.2 to 1
+// %.  us, with 80 KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4
+// sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713.  All that fit / so many: 3 sources
+// 582 / 575 in long spans, 370 / 342 (0.5 GB each) in short ones; 2 sources 273 / 263 in spans below a MiB, but 425 /
+// 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369.
+static uint32_t crowd_limit(int nsrc, uint64_t mean_span)
 {
-    if (nsrc < 4) return 0;
-    const uint32_t waves = std::max({20 - nsrc, 17 - 5 * nsrc / 8, 8});
-    return 160 * 1024 / waves / 512 * 512;
+    const uint32_t waves = nsrc == 1   ? (mean_span >= 64 * 1024 ? 24 : 32)
+                           : nsrc == 2 ? (mean_span < 1024 * 1024 ? 28 : 32)
+                           : nsrc == 3 ? 24
+                                       : std::max({20 - nsrc, 17 - 5 * nsrc / 8, 8});
+    return waves == 32 ? 0 : 160 * 1024 / waves / 512 * 512;
 }
 
 #define REFT_PICK_MANY(K)                                                                         \
@@ -483,29 +370,36 @@ static uint32_t crowd_limit(int nsrc)
     case 15: fn = PICK(15); break;                                                                \
     case 16: fn = PICK(16); break;
 
-static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, Form form, LaunchCfg cfg,
-                                hipStream_t stream)
+static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64_t *dtab, int nsrc, Form form,
+                                LaunchCfg cfg, hipStream_t stream)
 {
     void (*fn)(const StreamArgs) = nullptr;
-    const bool cached = (uint64_t)(nsrc + (form == kPacked ? 2 : 1)) * (a.hi - a.lo) <= kCachedTraffic;
+    const bool cached = (uint64_t)(nsrc + (form == kPacked ? 2 : 1)) * (a.range.hi - a.range.lo) <= kCachedTraffic;
     // a capped grid (few waves, say on the host link) wants all that a wave may have in flight
     const uint32_t unroll = cfg.capped ? 4 : cached ? 1 : long_stream_unroll(nsrc);
     if (unroll < cfg.unroll) cfg.unroll = unroll;
     if (cached && !cfg.capped) cfg.nontemporal = false;
     if (nsrc > kMaxSrc && cfg.unroll > 2) cfg.unroll = 2;    // 2 KiB of 9 sources and more: 18 loads a lane
     if (form == kPacked || form == kInPlace) cfg.unroll = 1;
-    // units start where the contiguous operand is 16-byte aligned
-    const uint64_t S = 1024ull * cfg.unroll;
-    a.phase = (uint32_t)contig & 15u;
-    a.first_unit = (a.lo + a.phase) / S;
-    a.nunits = (a.hi - 1 + a.phase) / S - a.first_unit + 1;
+    a.first_step = a.range.first / cfg.unroll;
+    a.nsteps = a.range.last / cfg.unroll - a.first_step + 1;
     const uint32_t waves = cached || cfg.capped ? 4 : 1;
+    a.off = pt.off;
+    a.unit_off = pt.unit_off;
+    a.unit_span = pt.unit_span;
+    a.T = pt.T;
+    a.unit_shift = pt.unit_shift;
+    a.grid = pt.grid;
+    if (a.last == kLastTable) a.last_row = a.tab + (uint64_t)(nsrc - 1) * pt.T;
+    else a.last_row = pt.unit_off;
+    a.ragged = dtab != nullptr;
+    a.dest_row = dtab ? dtab : pt.unit_off;
     a.run = 1;
-    // (in short spans the tensors' places have little to do with the stream's: 8 x 132 MB in spans of 10 KB 204.6
-    // us in plain order, 206.2 so)
-    a.spread = waves == 1 && a.first_unit % 32 == 0 && a.pt.L / a.pt.T >= 64 * 1024;
+    // (in short spans the tensors' places have little to do with the units' numbers: 8 x 132 MB in spans of 10 KB
+    // 204.6 us in plain order, 206.2 so)
+    a.spread = waves == 1 && a.first_step % 32 == 0 && pt.L / pt.T >= 64 * 1024;
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
-        a.run = run_of_units(a.nunits, waves * (uint64_t)cfg.max_wgs, nsrc, a.pt.L / a.pt.T);
+        a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, pt.L / pt.T);
         if (a.run > 1) form = kRuns;
     }
     switch (form) {
@@ -535,59 +429,53 @@ static hipError_t launch_stream(StreamArgs a, int nsrc, uint64_t contig, Form fo
         }
         break;
     }
-    const uint32_t g = stream_grid((a.nunits + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
-    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc) : 0, stream, a);
+    const uint32_t g = stream_grid((a.nsteps + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
+    a.waves = waves;
+    a.stride = (uint64_t)g * waves;
+    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc, pt.L / pt.T) : 0, stream, a);
     return hipGetLastError();
 }
 
 hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc, bool in_place,
-                         const uint64_t *dtab, uint64_t dst_vbase, uint64_t lo, uint64_t hi,
+                         const uint64_t *dtab, uint64_t dst_vbase, const StreamRange &range,
                          const LaunchCfg &cfg, hipStream_t stream)
 {
-    if (lo >= hi) return hipSuccess;
-    if (hi > pt.L) return hipErrorInvalidValue;
+    if (range.lo >= range.hi) return hipSuccess;
+    if (range.hi > pt.L) return hipErrorInvalidValue;
     StreamArgs a{};
-    a.pt = pt;
     a.tab = tab;
-    a.dtab = dtab;
     a.vb = dst_vbase;
-    a.lo = lo;
-    a.hi = hi;
+    a.range = range;
     a.last = acc ? kLastDest : kLastTable;
-    return launch_stream(a, nrows + (acc ? 1 : 0), dtab ? 0 : dst_vbase, in_place && !acc ? kInPlace : kPlain, cfg,
+    return launch_stream(pt, a, dtab, nrows + (acc ? 1 : 0), in_place && !acc ? kInPlace : kPlain, cfg,
                          stream);
 }
 
 hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t vb,
-                              uint64_t vb2, uint64_t lo, uint64_t hi, const LaunchCfg &cfg,
+                              uint64_t vb2, const StreamRange &range, const LaunchCfg &cfg,
                               hipStream_t stream)
 {
-    if (lo >= hi) return hipSuccess;
-    if (hi > pt.L) return hipErrorInvalidValue;
+    if (range.lo >= range.hi) return hipSuccess;
+    if (range.hi > pt.L) return hipErrorInvalidValue;
     StreamArgs a{};
-    a.pt = pt;
     a.tab = tab;
     a.vb = vb;
     a.vb2 = vb2;
-    a.lo = lo;
-    a.hi = hi;
+    a.range = range;
     a.last = kLastTable;
-    return launch_stream(a, nrows, vb, kPacked, cfg, stream);
+    return launch_stream(pt, a, nullptr, nrows, kPacked, cfg, stream);
 }
 
 hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t src_vbase,
-                          uint64_t lo, uint64_t hi, const LaunchCfg &cfg, hipStream_t stream)
+                          const StreamRange &range, const LaunchCfg &cfg, hipStream_t stream)
 {
-    if (lo >= hi) return hipSuccess;
-    if (hi > pt.L) return hipErrorInvalidValue;
+    if (range.lo >= range.hi) return hipSuccess;
+    if (range.hi > pt.L) return hipErrorInvalidValue;
     StreamArgs a{};
-    a.pt = pt;
-    a.dtab = tab;
     a.cbase = src_vbase;
-    a.lo = lo;
-    a.hi = hi;
+    a.range = range;
     a.last = kLastContig;
-    return launch_stream(a, 1, src_vbase, kPlain, cfg, stream);
+    return launch_stream(pt, a, tab, 1, kPlain, cfg, stream);
 }
 
 }  // namespace reft

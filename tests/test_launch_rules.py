@@ -14,6 +14,16 @@ extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { retu
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
 extern "C" int span_burst(uint64_t rows, uint64_t bytes) { return reft::span_burst(rows, bytes); }
+extern "C" uint64_t units_of(uint64_t n, uint64_t head) { return reft::units_of(n, head); }
+extern "C" uint64_t first_unit_at(uint64_t r, uint64_t head) { return reft::first_unit_at(r, head); }
+extern "C" uint64_t last_unit_at(uint64_t r, uint64_t head) { return reft::last_unit_at(r, head); }
+extern "C" void piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, int64_t hi, int64_t *st)
+{
+    const reft::Piece p = reft::piece_of(j, head, lead, lo, hi);
+    st[0] = p.s;
+    st[1] = p.t;
+}
+extern "C" int32_t lane_place(int32_t at, int32_t len) { return reft::lane_place(at, len); }
 extern "C" uint64_t unit(uint32_t kib, uint64_t w, uint64_t n) { return kib == 1 ? reft::unit_of_wave<1>(w, n) : reft::unit_of_wave<2>(w, n); }
 extern "C" uint64_t contig_rows(uint64_t rows) { return reft::contig_burst_min_rows(rows); }
 extern "C" uint64_t contig_bytes(uint64_t bytes) { return reft::contig_burst_min_bytes(bytes); }
@@ -33,6 +43,10 @@ def grid(tmp_path_factory):
     lib.link.restype = ctypes.c_uint32
     lib.run.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64]
     lib.run.restype = ctypes.c_uint32
+    for f in (lib.units_of, lib.first_unit_at, lib.last_unit_at):
+        f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
+        f.restype = ctypes.c_uint64
+    lib.piece_of.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
     lib.span_burst.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
     lib.unit.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64]
     lib.unit.restype = ctypes.c_uint64
@@ -113,3 +127,45 @@ def test_every_unit_has_one_wave(grid, kib):
     for n in (1 << 33, (1 << 40) + 5):                # beyond 32 bits
         at = n // 32 * 32 - 64
         assert sorted(grid.unit(kib, w, n) for w in range(at, n)) == list(range(at, n))
+
+
+def moved(grid, n, head, lead, lo, hi, once):
+    """How often each byte of a span of n bytes is written by the units that a launch over its bytes lo .. hi - 1
+    has, as the kernel's lanes do it."""
+    count = [0] * n
+    st = (ctypes.c_int64 * 2)()
+    low, high = max(lo, 0), min(hi, n)
+    for j in range(grid.first_unit_at(low, head), grid.last_unit_at(high - 1, head) + 1):
+        assert j < grid.units_of(n, head)
+        grid.piece_of(j, head, 0 if once else lead, low, high, st)
+        a, b = st
+        if a >= b:
+            continue
+        size = b - a
+        assert size < 1024 + 128
+        if not once and b - low >= 16:
+            start, size = (b - 16, 16) if size < 16 else (a, size)
+            at = [start + grid.lane_place(16 * x, size) for x in range(-(-size // 16))]
+            assert all(start <= x and x + 16 <= b for x in at)
+            places = [x + i for x in at for i in range(16)]
+        else:
+            places = range(a, b)                       # 16 bytes a lane, what is left one byte a lane
+        for x in places:
+            assert low <= x < high
+            count[x] += 1
+    return count
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 100, 127, 128, 129, 1023, 1024, 1025, 1040, 1151, 1152, 1153, 2047, 2048,
+                               2049, 2200, 5000])
+def test_units_cover_a_span(grid, n):
+    cuts = sorted({x for x in (0, 1, 5, 15, 16, 100, 127, 128, 500, 1008, 1023, 1024, 1025, 1100, 2040, n - 17, n - 1, n)
+                   if 0 <= x <= n})
+    for head, lead in [(1024, x) for x in (0, 1, 15, 16, 64, 127)] + [(1, 0), (1, 127), (17, 3), (600, 120), (1023, 127)]:
+        for lo in cuts:
+            for hi in cuts:
+                if lo < hi:
+                    for once in (False, True):
+                        count = moved(grid, n, head, lead, -70 if lo == 0 else lo, hi + 90 if hi == n else hi, once)
+                        assert not any(count[:lo]) and not any(count[hi:])
+                        assert all(c == 1 if once else c >= 1 for c in count[lo:hi])
