@@ -230,6 +230,7 @@ struct reft_plan {
     uint32_t tile_shift = 16;
     uint32_t unit_shift = 0;          // blocks of the device's look-up table of units
     uint32_t grid = 0;                // see head_of
+    uint32_t burst_shift = 16;        // tiles of the burst kernel's look-up table
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
     std::vector<uint64_t> unit_off;   // [T+1] (of plans with device tables)
@@ -282,7 +283,7 @@ struct reft_plan {
 
     PlanTables tables() const
     {
-        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, tile_shift, grid};
+        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid};
     }
 
     // lo < hi <= L
@@ -648,38 +649,40 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
         number += units_of(n, head_of(p->off[t], p->grid));
     }
     p->unit_off[T] = number;
-    const uint64_t units = p->unit_off[T], most = std::max<uint64_t>(65536, 16 * T);
+    const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(65536, 16 * T), 1ull << 31);
     p->unit_shift = 0;
     while ((units >> p->unit_shift) > most) ++p->unit_shift;
     const uint64_t nblocks = (units >> p->unit_shift) + 1;
-    // One allocation and one copy for the tables: span offsets, unit offsets, units' and tiles' spans; behind them
-    // the burst counters and the device half of the pointer pool.
+    // One allocation, and one copy for span offsets, unit offsets and the burst kernel's spans of tiles (4096 of them
+    // at most, it walks on from there); behind them the units' spans, which the device fills in (528 MB in 49,152
+    // spans: 540,000 entries), the burst counters and the device half of the pointer pool.
+    p->burst_shift = p->tile_shift;
+    while ((p->L >> p->burst_shift) >= 4096) ++p->burst_shift;
+    const size_t burst_tiles = (size_t)(p->L >> p->burst_shift) + 1;
     auto behind = [](size_t at, size_t bytes) { return (at + bytes + 255) & ~(size_t)255; };
     const size_t at_unit_off = behind(0, (T + 1) * sizeof(uint64_t));
-    const size_t at_unit_span = behind(at_unit_off, (T + 1) * sizeof(uint64_t));
-    const size_t at_tile_span = behind(at_unit_span, nblocks * sizeof(uint32_t));
-    const size_t at_ctr = behind(at_tile_span, first.size() * sizeof(uint32_t));
+    const size_t at_tile_span = behind(at_unit_off, (T + 1) * sizeof(uint64_t));
+    const size_t at_unit_span = behind(at_tile_span, burst_tiles * sizeof(uint32_t));
+    const size_t at_ctr = behind(at_unit_span, nblocks * sizeof(uint32_t));
     const size_t at_ptr = behind(at_ctr, kCtrBlocks * kBurstCtrBytes);
     p->ring_cap = (uint64_t)kRingRows * T;
-    std::vector<uint64_t> tables(at_ctr / sizeof(uint64_t), 0);
-    uint8_t *const image = (uint8_t *)tables.data();
+    std::vector<uint64_t> tables(at_unit_span / sizeof(uint64_t), 0);
     std::copy(p->off.begin(), p->off.end(), tables.begin());
-    std::copy(p->unit_off.begin(), p->unit_off.end(), (uint64_t *)(image + at_unit_off));
-    std::copy(first.begin(), first.end(), (uint32_t *)(image + at_tile_span));
-    uint32_t *const lookup = (uint32_t *)(image + at_unit_span);
-    for (uint64_t t = 0, i = 0; i < T; ++i) {                        // t: the first block without an entry
-        const uint64_t whole = p->unit_off[i + 1] >> p->unit_shift;
-        if (whole > t) std::fill(lookup + t, lookup + whole, (uint32_t)i | kWholeBlock), t = whole;
-        if (t << p->unit_shift < p->unit_off[i + 1]) lookup[t++] = (uint32_t)i;
+    std::copy(p->unit_off.begin(), p->unit_off.end(), tables.begin() + (ptrdiff_t)(at_unit_off / sizeof(uint64_t)));
+    uint32_t *const tile_span = (uint32_t *)((uint8_t *)tables.data() + at_tile_span);
+    for (size_t t = 0; t < burst_tiles; ++t) {
+        const size_t at = t << (p->burst_shift - p->tile_shift);
+        if (at < p->ntiles) tile_span[t] = first[at];
     }
     HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
     HIPCHK(hipMemcpy(p->d_tables, tables.data(), tables.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
     p->d_off = (uint64_t *)p->d_tables;
     p->d_unit_off = (uint64_t *)(p->d_tables + at_unit_off);
-    p->d_unit_span = (uint32_t *)(p->d_tables + at_unit_span);
     p->d_tile_span = (uint32_t *)(p->d_tables + at_tile_span);
+    p->d_unit_span = (uint32_t *)(p->d_tables + at_unit_span);
     p->burst_ctr = (uint32_t *)(p->d_tables + at_ctr);
     p->d_ptr = (uint64_t *)(p->d_tables + at_ptr);
+    HIPCHK(launch_unit_spans(p->tables(), p->d_unit_span, nblocks, nullptr));
     int rc;
     const DeviceStatics *ds = nullptr;
     if ((rc = device_statics(&ds))) return rc;
@@ -715,6 +718,7 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->row_buf.resize((size_t)(REFT_MAX_K + 1) * T);
     p->pieces.reserve(kPieceLists);
     (void)pieces_of(p, 0, p->NB);
+    HIPCHK(hipStreamSynchronize(nullptr));             // the units' spans are there (other streams read them)
 
     guard.p = nullptr;
     *out = p;
