@@ -59,6 +59,33 @@ def test_forty_pointer_sets_on_two_streams(dev):
         reft.reft_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("order", ["null last", "null first", "null only"])
+def test_tables_read_on_the_null_stream_are_retired(dev, order):
+    """Uses on the null stream leave no event: a table that it may still read is overwritten on that stream itself, or
+    on another one (which knows nothing of the null stream) only when they have ended.  120 tables for 9 places."""
+    sizes = [1 << 20, 17, 65536 + 3, 300_000]
+    L, k = sum(sizes), 8
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(10)
+    pool = [[torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen) for n in sizes] for _ in range(40)]
+    cpu = [oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in pool]
+    side = torch.cuda.Stream()
+    streams = {"null last": [side, None], "null first": [None, side], "null only": [None]}[order]
+    outs = [torch.empty(L, dtype=torch.uint8, device=dev) for _ in range(120)]
+    plan = reft.reft_plan_create(sizes, None, 0)
+    torch.cuda.synchronize()
+    try:
+        for i, o in enumerate(outs):
+            rows = [t for j in range(k) for t in pool[(i + j * (1 + i // 40)) % 40]]
+            reft.reft_parity_encode(plan, rows, k, o, streams[i % len(streams)])
+    finally:
+        reft.reft_plan_destroy(plan)
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        want = oracle.encode([cpu[(i + j * (1 + i // 40)) % 40] for j in range(k)])
+        assert np.array_equal(o.cpu().numpy(), want), i
+
+
 def test_one_table_shared_by_many_streams(dev):
     """The same pointer array on six streams in turn (more than a table tracks), then retired by
     forty new ones while its last readers may still run."""
