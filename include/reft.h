@@ -422,10 +422,9 @@ int reft_restore_wait(reft_plan *plan);
  *                  link in the other direction.
  *   "small_pieces" a tile in which at least this many spans start counts as dense in small spans
  *                  (default 1; 4294967295 = never, 0 = always): see "burst".
- *   "burst"        1 (default) = the XOR calls may use the write-burst variant of the kernel.  The
- *                  calls over span tables do where "burst_min_rows" or "burst_min_bytes" is set to
- *                  another value than its default (7, 2 GiB) and it applies: at least that many rows
- *                  (at most 8 count), at least that many stream bytes (four times that where the result
+ *   "burst"        1 (default) = the XOR calls use the write-burst variant of the kernel where it
+ *                  applies: at least "burst_min_rows" rows (default 7; at most 8 count), at least
+ *                  "burst_min_bytes" stream bytes (default 13 GiB; four times that where the result
  *                  goes into tensors), at most one tile in eight dense in small spans (see
  *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
  *                  alike (mod 16) relative to its stream offset.  reft_reconstruct goes by the same

@@ -1469,11 +1469,11 @@ static bool few_dense_tiles(const reft_plan *p)
     return (uint64_t)dense * 8 <= p->ntiles;
 }
 
-// Whether `rows` rows go through the burst kernel: never by default, else long rows with few span boundaries.  A
-// launch into tensors needs rows four times as long.
+// Whether `rows` rows go through the burst kernel: very long rows, few span boundaries.  A launch into tensors
+// needs rows four times as long.
 static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
 {
-    return g_burst.load() && span_burst(g_burst_min_rows.load(), g_burst_min_bytes.load()) && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
+    return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
            rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
 
@@ -1507,7 +1507,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // The burst kernel where the caller asks for it.  Destination spans that are not all aligned alike relative to
+    // Very long rows: reads and writes are separated in time with the burst kernel.  Destination spans that are not all aligned alike relative to
     // their stream offsets, which its staging image cannot represent, keep the stream kernel, and more rows go
     // through it in one pass, up to kMaxStreamSrc.
     bool burst = burst_applies(p, nrows, dst_row != nullptr);

@@ -98,16 +98,15 @@ inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
     return (uint32_t)(w < max_wgs ? w : max_wgs);
 }
 
-// "burst_min_rows" and "burst_min_bytes" where the caller has not set them.
-constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 2ull << 30;
+// "burst_min_rows" and "burst_min_bytes" where the caller has not set them, for the kernels over span tables.  Since its
+// units lie in the order of unit_of_wave the stream kernel is as good or better up to about 12 GB a row.  Parity, burst /
+// stream kernel: 8 rows of 3.1 GB 4290 / 4172 us and, in other memory, 4319 / 4265, 7 of 3.1 GB 3958 / 3893; TB/s, 8
+// rows of 11.4 GB 6.38 / 6.41, 11.8 GB 6.63 / 6.74 and 6.12 / 6.08, 15.0 GB 6.26 / 6.17, 15.4 GB 6.15 / 6.07 and 6.35 /
+// 6.21.  Into tensors (from four times the bytes on, so in practice never): 8 rows of 11.4 to 15.4 GB 6.18 / 6.19, 6.49 /
+// 6.50, 6.11 / 6.13, 6.27 / 6.22.
+constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 13ull << 30;
 
-// Whether launches over span tables go by the two: only where one of them is set.  By itself the stream kernel
-// is as good or better since its units lie in the order of unit_of_wave; us, burst / stream: 8 sources of 3.1 GB 4290 /
-// 4172 and, in other memory, 4319 / 4265, of 11.8 GB 16664 / 16665 and 15694 / 15657, 7 of 3.1 GB 3958 / 3893;
-// into tensors 8 of 3.1 GB 4287 / 4285, of 11.8 GB 16583 / 16459.
-inline bool span_burst(uint64_t rows, uint64_t bytes) { return rows != kBurstMinRows || bytes != kBurstMinBytes; }
-
-// The two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes
+// The same two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes
 // worse than the one over span tables: there the burst kernel pays from five sources and 8 MiB on (5 sources
 // 6.05 / 6.16 TB/s, ordinary / burst, 8 sources 5.23 / 6.47).  What the caller sets holds for both.
 inline uint64_t contig_burst_min_rows(uint64_t rows) { return rows == kBurstMinRows ? 5 : rows; }

@@ -1,5 +1,5 @@
 """GPU parity at the full sizes of configurations 1-4, in the launch configuration bench.py times
-(staged snapshot, staged restore, the XOR kernels it takes by default), plus the direct restore.
+(staged snapshot, staged restore, XOR kernels), plus the direct restore.
 
 At 11-15 GB per shard the oracle cannot recompute everything in seconds, so each case checks
   * sampled windows of every output against the oracle, byte for byte: random windows, windows

@@ -13,7 +13,6 @@ SOURCE = """
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
-extern "C" int span_burst(uint64_t rows, uint64_t bytes) { return reft::span_burst(rows, bytes); }
 extern "C" uint64_t units_of(uint64_t n, uint64_t head) { return reft::units_of(n, head); }
 extern "C" uint64_t first_unit_at(uint64_t r, uint64_t head) { return reft::first_unit_at(r, head); }
 extern "C" uint64_t last_unit_at(uint64_t r, uint64_t head) { return reft::last_unit_at(r, head); }
@@ -47,7 +46,6 @@ def grid(tmp_path_factory):
         f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
         f.restype = ctypes.c_uint64
     lib.piece_of.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
-    lib.span_burst.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
     lib.unit.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64]
     lib.unit.restype = ctypes.c_uint64
     for f in (lib.contig_rows, lib.contig_bytes):
@@ -92,13 +90,6 @@ def test_packed_decode_goes_by_the_callers_burst_limits(grid):
         assert grid.contig_rows(r) == r
     for b in (0, 1, 8 << 20, 9 << 20, 1 << 30, (2 << 30) + 1, 4 << 30, 1 << 62):
         assert grid.contig_bytes(b) == b
-
-
-def test_burst_kernel_over_spans_is_asked_for(grid):
-    """By default the calls over span tables take the stream kernel; either value set brings the burst kernel back."""
-    rows, size = reft.reft_get_tunable("burst_min_rows"), reft.reft_get_tunable("burst_min_bytes")
-    assert not grid.span_burst(rows, size)
-    assert grid.span_burst(rows - 1, size) and grid.span_burst(rows, size + 1) and grid.span_burst(1, 0)
 
 
 def test_runs_leave_every_wave_eight(grid):
