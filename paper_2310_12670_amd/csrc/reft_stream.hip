@@ -138,11 +138,12 @@ __device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
     return o;
 }
 
-template <bool NT>
-__device__ __forceinline__ void st16_any(uint64_t p, u32x4 v)
+// A lane's offset from a uniform base.  (Hidden from the compiler, which otherwise widens it to 64 bits outside of the
+// loop and then adds it to every base in vector registers, where a load takes base and 32-bit offset as they are.)
+__device__ __forceinline__ uint32_t lane_offset(uint32_t at)
 {
-    if constexpr (NT) __builtin_nontemporal_store(v, (REFT_GLOBAL u32x4_any *)p);
-    else *(REFT_GLOBAL u32x4_any *)p = v;
+    asm volatile("" : "+v"(at));
+    return at;
 }
 
 // Loads of the 16 bytes `at` bytes (at least 0) behind p.
@@ -152,12 +153,21 @@ __device__ __forceinline__ u32x4 ld16_at(uint64_t p, uint32_t at)
     return ld16<NT>((gcptr16)((const REFT_GLOBAL char *)p + at));
 }
 
+template <bool NT>
+__device__ __forceinline__ void st16_at(uint64_t p, uint32_t at, u32x4 v)
+{
+    REFT_GLOBAL u32x4_any *const q = (REFT_GLOBAL u32x4_any *)((REFT_GLOBAL char *)p + at);
+    if constexpr (NT) __builtin_nontemporal_store(v, q);
+    else *q = v;
+}
+
 // The XOR of the sources' 16 bytes at byte `from` + `at` of the span, all loads before the first use (left alone,
 // the compiler alternates them); stored if `store`.
 template <int K, bool NT, bool PACK>
 __device__ __forceinline__ void move_16(const Span<K> &o, int64_t from, uint32_t at, bool store)
 {
     u32x4 t[K];
+    at = lane_offset(at);
 #pragma unroll
     for (int j = 0; j < K; ++j) t[j] = ld16_at<NT>(o.s[j] + from, at);
     __builtin_amdgcn_sched_barrier(0);
@@ -165,8 +175,9 @@ __device__ __forceinline__ void move_16(const Span<K> &o, int64_t from, uint32_t
 #pragma unroll
     for (int j = 1; j < K; ++j) v ^= t[j];
     if (store) {
-        if constexpr (PACK) st16_any<NT>(o.d2 + from + at, t[0]);
-        st16_any<NT>(o.d + from + at, v);
+        at = lane_offset(at);
+        if constexpr (PACK) st16_at<NT>(o.d2 + from, at, t[0]);
+        st16_at<NT>(o.d + from, at, v);
     }
 }
 
@@ -227,22 +238,23 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
     // 126 MB by 4 workgroups: 2217 us so, 1583 with this)
     if constexpr (F == kRuns) __builtin_amdgcn_s_waitcnt(0x0f70);
     for (uint32_t done = 1;; ++done) {
-        // all loads of up to 16 chunks before the first use
-        constexpr int R = K * U <= 16 ? K : 16 / U;
+        // all loads of up to 32 chunks before the first use
+        constexpr int R = K * U <= 32 ? K : 32 / U;
         u32x4 v[U] = {};
+        const uint32_t at = lane_offset(lane * 16);
 #pragma unroll
         for (int j = 0; j < K; j += R) {
             u32x4 t[R][U];
 #pragma unroll
             for (int q = 0; q < R && j + q < K; ++q) {
 #pragma unroll
-                for (int c = 0; c < U; ++c) t[q][c] = ld16_at<NT>(o.s[j + q] + x, lane * 16 + c * (uint32_t)kUnit);
+                for (int c = 0; c < U; ++c) t[q][c] = ld16_at<NT>(o.s[j + q] + x + c * kUnit, at);
             }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (PACK) {
                 if (j == 0) {
 #pragma unroll
-                    for (int c = 0; c < U; ++c) st16_any<NT>(o.d2 + x + lane * 16 + c * kUnit, t[0][c]);
+                    for (int c = 0; c < U; ++c) st16_at<NT>(o.d2 + x + c * kUnit, at, t[0][c]);
                 }
             }
 #pragma unroll
@@ -252,7 +264,7 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
             }
         }
 #pragma unroll
-        for (int c = 0; c < U; ++c) st16_any<NT>(o.d + x + lane * 16 + c * kUnit, v[c]);
+        for (int c = 0; c < U; ++c) st16_at<NT>(o.d + x + c * kUnit, at, v[c]);
         if constexpr (F != kRuns) return 1;
         x += S;
         if (done == most || x + S > o.hi) return done;
