@@ -81,12 +81,12 @@ constexpr uint64_t unit_of_wave(uint64_t w, uint64_t n)
 // units inside long spans (spans of 70 KB by 8 workgroups: 46 us without, 51 with), with up to four sources
 // (5 by 64 workgroups: 224 us without, 240 with), and up to this many waves, beyond which more windows in
 // memory cost more than look-ups (1 GB copied by 192 / 256 workgroups: 445 / 361 us without, 367 / 382
-// with; parity of 2 by 96 / 128: 747 / 608 and 726 / 655).  Eight runs per wave keep the waves busy alike;
+// with; parity of 2 by 128 / 192: 804 / 590 without, 613 / 539 with).  Eight runs per wave keep the waves busy alike;
 // beyond 16 units nothing is gained.
 inline uint32_t run_of_units(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean_span)
 {
     const uint64_t n = nunits / (8 * waves);
-    if (nsrc > 4 || waves > (nsrc == 1 ? 896u : 384u) || mean_span < 256 * 1024) return 1;
+    if (nsrc > 4 || waves > (nsrc == 1 ? 896u : nsrc == 2 ? 768u : 384u) || mean_span < 256 * 1024) return 1;
     return n < 1 ? 1 : n < 16 ? (uint32_t)n : 16;
 }
 
