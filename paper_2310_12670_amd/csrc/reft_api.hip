@@ -443,8 +443,13 @@ static int retire_entry(PtrEntry &e, hipStream_t s)
         e.user[i] = nullptr;
     }
     if (e.null_used && s != nullptr) {
-        HIPCHK(hipEventRecord(e.used[0].ev, nullptr));
-        HIPCHK(hipEventSynchronize(e.used[0].ev));
+        // (s may be capturing: this is no part of what it captures)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+        hipError_t err = hipEventRecord(e.used[0].ev, nullptr);
+        if (err == hipSuccess) err = hipEventSynchronize(e.used[0].ev);
+        HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+        HIPCHK(err);
     }
     e.null_used = false;
     e.live = false;

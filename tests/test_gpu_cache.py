@@ -86,6 +86,38 @@ def test_tables_read_on_the_null_stream_are_retired(dev, order):
         assert np.array_equal(o.cpu().numpy(), want), i
 
 
+def test_capture_that_takes_the_place_of_a_null_stream_table(dev):
+    """Nine tables of eight rows fill the plan's pool on the null stream; the captured call needs the place of one."""
+    sizes = [70_000, 33, 1 << 16]
+    L, k = sum(sizes), 8
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    pool = [[torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen) for n in sizes] for _ in range(20)]
+    rows = [[t for j in range(k) for t in pool[(i + j) % 20]] for i in range(12)]
+    want = [oracle.encode([oracle.pack([oracle.as_bytes(t.cpu()) for t in pool[(i + j) % 20]]) for j in range(k)])
+            for i in range(12)]
+    out = torch.empty(L, dtype=torch.uint8, device=dev)
+    plan = reft.reft_plan_create(sizes, None, 0)
+    try:
+        for i in range(11):
+            reft.reft_parity_encode(plan, rows[i], k, out)
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            reft.reft_parity_encode(plan, rows[11], k, out, torch.cuda.current_stream())
+        for _ in range(3):
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want[11])
+        del graph
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)
+
+
 def test_one_table_shared_by_many_streams(dev):
     """The same pointer array on six streams in turn (more than a table tracks), then retired by
     forty new ones while its last readers may still run."""
