@@ -656,7 +656,8 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     HIPCHK(hipGetDeviceProperties(&prop, p->device));
     p->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     // The stream kernel's look-up table: an entry per unit (a look-up then needs no search) as long as that is
-    // no more than 65,536 entries or 16 per span, else blocks of units.
+    // no more than 16,384 entries or 8 per span, else blocks of units.  (Made here and not by a kernel: that would wait
+    // behind whatever the null stream still has to do, and plan creation with it.)
     p->grid = p->L / T >= kGridMeanSpan ? (uint32_t)kUnit - 1 : 0;
     p->unit_off.resize(T + 1);
     uint64_t number = 0;
@@ -667,13 +668,13 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
         number += units_of(n, head_of(p->off[t], p->grid));
     }
     p->unit_off[T] = number;
-    const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(65536, 16 * T), 1ull << 31);
+    const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(16384, 8 * T), 1ull << 31);
     p->unit_shift = 0;
     while ((units >> p->unit_shift) > most) ++p->unit_shift;
     const uint64_t nblocks = (units >> p->unit_shift) + 1;
-    // One allocation, and one copy for span offsets, unit offsets and the burst kernel's spans of tiles (4096 of them
-    // at most, it walks on from there); behind them the units' spans, which the device fills in (528 MB in 49,152
-    // spans: 540,000 entries), the burst counters and the device half of the pointer pool.
+    // One allocation and one copy for the tables: span offsets, unit offsets, the burst kernel's spans of tiles (4096 of
+    // them at most, it walks on from there) and the units' spans; behind them the burst counters and the device half
+    // of the pointer pool.
     p->burst_shift = p->tile_shift;
     while ((p->L >> p->burst_shift) >= 4096) ++p->burst_shift;
     const size_t burst_tiles = (size_t)(p->L >> p->burst_shift) + 1;
@@ -684,13 +685,19 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     const size_t at_ctr = behind(at_unit_span, nblocks * sizeof(uint32_t));
     const size_t at_ptr = behind(at_ctr, kCtrBlocks * kBurstCtrBytes);
     p->ring_cap = (uint64_t)kRingRows * T;
-    std::vector<uint64_t> tables(at_unit_span / sizeof(uint64_t), 0);
+    std::vector<uint64_t> tables(at_ctr / sizeof(uint64_t), 0);
     std::copy(p->off.begin(), p->off.end(), tables.begin());
     std::copy(p->unit_off.begin(), p->unit_off.end(), tables.begin() + (ptrdiff_t)(at_unit_off / sizeof(uint64_t)));
     uint32_t *const tile_span = (uint32_t *)((uint8_t *)tables.data() + at_tile_span);
     for (size_t t = 0; t < burst_tiles; ++t) {
         const size_t at = t << (p->burst_shift - p->tile_shift);
         if (at < p->ntiles) tile_span[t] = first[at];
+    }
+    uint32_t *const lookup = (uint32_t *)((uint8_t *)tables.data() + at_unit_span);
+    for (uint64_t t = 0, i = 0; i < T; ++i) {                        // t: the first block without an entry
+        const uint64_t whole = p->unit_off[i + 1] >> p->unit_shift;
+        if (whole > t) std::fill(lookup + t, lookup + whole, (uint32_t)i | kWholeBlock), t = whole;
+        if (t << p->unit_shift < p->unit_off[i + 1]) lookup[t++] = (uint32_t)i;
     }
     HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
     HIPCHK(hipMemcpy(p->d_tables, tables.data(), tables.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
@@ -700,7 +707,6 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->d_unit_span = (uint32_t *)(p->d_tables + at_unit_span);
     p->burst_ctr = (uint32_t *)(p->d_tables + at_ctr);
     p->d_ptr = (uint64_t *)(p->d_tables + at_ptr);
-    HIPCHK(launch_unit_spans(p->tables(), p->d_unit_span, nblocks, nullptr));
     int rc;
     const DeviceStatics *ds = nullptr;
     if ((rc = device_statics(&ds))) return rc;
@@ -736,7 +742,6 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->row_buf.resize((size_t)(REFT_MAX_K + 1) * T);
     p->pieces.reserve(kPieceLists);
     (void)pieces_of(p, 0, p->NB);
-    HIPCHK(hipStreamSynchronize(nullptr));             // the units' spans are there (other streams read them)
 
     guard.p = nullptr;
     *out = p;

@@ -60,9 +60,6 @@ struct SrcBases {
     uint64_t p[kMaxSrc];
 };
 
-// Fills the n entries of unit_span from unit_off (pt.unit_span is not read).
-hipError_t launch_unit_spans(const PlanTables &pt, uint32_t *unit_span, uint64_t n, hipStream_t stream);
-
 // The destination address of stream byte o, for o in [lo, hi), is dst_vbase + o, or, when dtab
 // (one row of T span pointers) is not null, the byte's place in the destination's own span.
 // tab holds nrows rows of T span pointers (row stride T); the kernel XORs the rows' streams and,

@@ -451,28 +451,6 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     return hipGetLastError();
 }
 
-// Entry t is the last span that starts at unit t << unit_shift or before; n entries, of which the last may lie behind
-// all units.
-__global__ void __launch_bounds__(256) k_unit_spans(PlanTables pt, uint32_t *unit_span, uint64_t n)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    uint64_t lo = 0, hi = pt.T;                        // unit_off[lo] <= u, and hi = T or unit_off[hi] > u
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) / 2;
-        if (pt.unit_off[mid] <= t << pt.unit_shift) lo = mid;
-        else hi = mid;
-    }
-    unit_span[t] = (uint32_t)lo | ((t + 1) << pt.unit_shift <= pt.unit_off[lo + 1] ? kWholeBlock : 0);
-}
-
-hipError_t launch_unit_spans(const PlanTables &pt, uint32_t *unit_span, uint64_t n, hipStream_t stream)
-{
-    if (n > 0xffffffffull) return hipErrorInvalidValue;      // 32-bit grids; a plan has 2^31 entries at most
-    hipLaunchKernelGGL(k_unit_spans, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, stream, pt, unit_span, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool acc, bool in_place,
                          const uint64_t *dtab, uint64_t dst_vbase, const StreamRange &range,
                          const LaunchCfg &cfg, hipStream_t stream)
