@@ -80,7 +80,8 @@ typedef void *reft_stream;
  * stream, and a cache for the callers' pointer arrays (72 rows of T pointers, pinned host mirror
  * and device copy).  A call that passes pointers the cache already holds uploads nothing; up to
  * 32 tables are kept, each remembering the streams (up to 4) that last read it, and a new table
- * takes the room of the oldest ones after waiting for exactly those readers.
+ * takes the room of the oldest ones after waiting for exactly those readers.  Up to 39 of the 72 rows
+ * belong to the null stream once calls on it have read tables there; other streams keep the rest.
  * Errors: REFT_EINVAL (null out/span_nbytes, T == 0, a zero-length bucket), REFT_ESIZE (bucket
  * lengths do not sum to L), REFT_EHIP.
  */

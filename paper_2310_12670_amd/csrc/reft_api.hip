@@ -168,6 +168,7 @@ namespace {
 constexpr int kRing = 32;       // pointer tables the plan's cache holds at once
 constexpr int kUsers = 4;       // streams per cached table whose most recent use is tracked
 constexpr uint32_t kRingRows = 72;  // capacity of the cache, in rows of T pointers (>= 2 * (REFT_MAX_K + 1))
+constexpr uint32_t kNullRows = kRingRows - (REFT_MAX_K + 1);  // see null_end
 constexpr int kMaxSlots = 64;   // staging slots used by the staged bucket pipelines
 constexpr int kGroups = 2;      // the slots form two groups that alternate (double buffering)
 constexpr uint32_t kCtrBlocks = 8;  // burst launches that may be in flight on one ring of counters
@@ -194,9 +195,8 @@ struct PieceLists {
 
 // One cached pointer table: `len` pointers at position `pos` of the plan's pool (pinned host
 // mirror and device copy).  `uploaded` is recorded behind the host-to-device copy; used[i] behind
-// the last kernel that read the table on stream user[i].  Readers on the null stream are not recorded
-// but noted: that stream exists as long as the device, so an event may be recorded when one is needed (4 x 0.9 MB
-// encoded call after call 6.6 us with an event behind each, 4.4 without; 4 x 14.7 MB 13.9, 12.85).
+// the last kernel that read the table on stream user[i], but for readers on the null stream in the
+// pool's first rows (see null_end).
 struct PtrEntry {
     bool live = false;
     uint64_t pos = 0, len = 0, hash = 0, tick = 0;
@@ -206,7 +206,6 @@ struct PtrEntry {
     Event uploaded;
     hipStream_t user[kUsers] = {};
     Event used[kUsers];
-    bool null_used = false;
 };
 
 // A plan derived from a base plan for the rotated placement, with the recipe that turns the
@@ -246,6 +245,11 @@ struct reft_plan {
     // cache of pointer tables: a pool of ring_cap pointers (pinned host mirror and device copy)
     // handed out front to back, and the tables that currently live in it
     uint64_t ring_cap = 0, ring_head = 0, ring_tick = 0;
+    // Room below null_end is left to the null stream: kernels on it may have read tables there without an event
+    // behind them, so that only what comes behind them on that stream may overwrite that room.  It ends within the first
+    // kNullRows rows; the others, enough for the widest table, are everyone's, and there each reader leaves its event.
+    // (4 x 0.9 MB encoded call after call 6.6 us with an event behind each, 4.4 without; 4 x 14.7 MB 13.9, 12.85.)
+    uint64_t null_end = 0;
     uint64_t *h_ptr = nullptr;
     uint64_t *d_ptr = nullptr;
     PtrEntry ring[kRing];
@@ -431,10 +435,9 @@ static uint64_t hash_ptrs(const void *const *ptrs, size_t n)
     return h;
 }
 
-// The host waits for exactly the work that may still read the entry's table (its upload and the
-// kernels behind which a use was recorded): never for the whole device.  s is the stream that will write the
-// table's place next; it waits by itself for what it has read.
-static int retire_entry(PtrEntry &e, hipStream_t s)
+// The host waits for exactly the work behind which an event was recorded that may still read the entry's table (its
+// upload and kernels): never for the whole device.
+static int retire_entry(PtrEntry &e)
 {
     if (e.uploaded.recorded) HIPCHK(hipEventSynchronize(e.uploaded.ev));
     e.uploaded.recorded = false;
@@ -443,16 +446,6 @@ static int retire_entry(PtrEntry &e, hipStream_t s)
         e.used[i].recorded = false;
         e.user[i] = nullptr;
     }
-    if (e.null_used && s != nullptr) {
-        // (s may be capturing: this is no part of what it captures)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-        hipError_t err = hipEventRecord(e.used[0].ev, nullptr);
-        if (err == hipSuccess) err = hipEventSynchronize(e.used[0].ev);
-        HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-        HIPCHK(err);
-    }
-    e.null_used = false;
     e.live = false;
     return REFT_OK;
 }
@@ -467,8 +460,8 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
                        const uint64_t **dev_tab, int *entry)
 {
     static_assert(sizeof(void *) == sizeof(uint64_t), "pointers are 64-bit");
-    const uint64_t n = (uint64_t)rows * p->T;
-    if (n > p->ring_cap)
+    const uint64_t n = (uint64_t)rows * p->T, least = s == nullptr ? 0 : p->null_end;
+    if (n > p->ring_cap - least)
         return fail(REFT_ESIZE, "pointer table of %u rows exceeds the plan's cache (%llu pointers)",
                     rows, (unsigned long long)p->ring_cap);
     const uint64_t h = hash_ptrs(ptrs, n);
@@ -485,18 +478,18 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
             return REFT_OK;
         }
     }
-    const uint64_t pos = p->ring_head + n > p->ring_cap ? 0 : p->ring_head;
+    const uint64_t pos = p->ring_head + n > p->ring_cap || p->ring_head < least ? least : p->ring_head;
     int slot = -1;
     for (int i = 0; i < kRing; ++i) {
         PtrEntry &e = p->ring[i];
-        if (e.live && e.pos < pos + n && pos < e.pos + e.len && (rc = retire_entry(e, s))) return rc;
+        if (e.live && e.pos < pos + n && pos < e.pos + e.len && (rc = retire_entry(e))) return rc;
         if (!e.live && slot < 0) slot = i;
     }
     if (slot < 0) {                                    // every slot is live: the oldest goes
         slot = 0;
         for (int i = 1; i < kRing; ++i)
             if (p->ring[i].tick < p->ring[slot].tick) slot = i;
-        if ((rc = retire_entry(p->ring[slot], s))) return rc;
+        if ((rc = retire_entry(p->ring[slot]))) return rc;
     }
     PtrEntry &e = p->ring[slot];
     memcpy(p->h_ptr + pos, ptrs, n * sizeof(uint64_t));
@@ -517,12 +510,13 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
     return REFT_OK;
 }
 
-// Record, on stream s, that the kernels queued so far were the last ones to read entry's table.
+// Record, on stream s, that the kernels queued so far were the last ones to read entry's table (or
+// leave its room to the null stream).
 static int release_ptrs(reft_plan *p, int entry, hipStream_t s)
 {
     PtrEntry &e = p->ring[entry];
-    if (s == nullptr) {
-        e.null_used = true;
+    if (s == nullptr && e.pos + e.len <= (uint64_t)kNullRows * p->T) {
+        if (p->null_end < e.pos + e.len) p->null_end = e.pos + e.len;
         return REFT_OK;
     }
     int i = -1;
@@ -762,13 +756,11 @@ extern "C" void reft_plan_destroy(reft_plan *p)
             e.ev = nullptr;
         }
     };
-    bool null_used = false;
     for (int i = 0; i < kRing; ++i) {
         drain(p->ring[i].uploaded);
         for (int u = 0; u < kUsers; ++u) drain(p->ring[i].used[u]);
-        null_used = null_used || p->ring[i].null_used;
     }
-    if (null_used) {                                   // the plan's GPU need not be the current one
+    if (p->null_end) {                                 // the plan's GPU need not be the current one
         int dev = p->device;
         (void)hipGetDevice(&dev);
         if (dev != p->device) (void)hipSetDevice(p->device);

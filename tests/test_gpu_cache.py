@@ -61,8 +61,8 @@ def test_forty_pointer_sets_on_two_streams(dev):
 
 @pytest.mark.parametrize("order", ["null last", "null first", "null only"])
 def test_tables_read_on_the_null_stream_are_retired(dev, order):
-    """Uses on the null stream leave no event: a table that it may still read is overwritten on that stream itself, or
-    on another one (which knows nothing of the null stream) only when they have ended.  120 tables for 9 places."""
+    """Uses on the null stream leave no event in the pool's first rows: a table there is overwritten on that stream
+    itself; other streams, which know nothing of it, take the other rows.  120 tables for 9 places."""
     sizes = [1 << 20, 17, 65536 + 3, 300_000]
     L, k = sum(sizes), 8
     gen = torch.Generator(device=dev)
@@ -86,8 +86,40 @@ def test_tables_read_on_the_null_stream_are_retired(dev, order):
         assert np.array_equal(o.cpu().numpy(), want), i
 
 
+@pytest.mark.parametrize("rows,then", [([8] * 9, [(1, False), (1, True)]), ([1] * 33, [(2, True)] * 20),
+                                       ([4, 8, 1, 8, 8, 8, 2, 4], [(1, False), (8, True), (2, False), (1, True), (8, True)] * 4)])
+def test_shorter_tables_beside_those_of_the_null_stream(dev, rows, then):
+    """Tables of different lengths, `rows` on the null stream behind a kernel that keeps it busy, then (rows, whether on a side
+    stream): no upload on the side stream may change what a waiting kernel of the null stream will read."""
+    sizes = [70_000, 33, 1 << 16]
+    L = sum(sizes)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(12)
+    pool = [[torch.randint(0, 256, (n,), dtype=torch.uint8, device=dev, generator=gen) for n in sizes] for _ in range(50)]
+    cpu = [oracle.pack([oracle.as_bytes(t.cpu()) for t in sh]) for sh in pool]
+    calls = [(k, False) for k in rows] + then
+    outs = [torch.zeros(L, dtype=torch.uint8, device=dev) for _ in calls]
+    side = torch.cuda.Stream()
+    plan = reft.reft_plan_create(sizes, None, 0)
+    torch.cuda.synchronize()
+    try:
+        torch.cuda._sleep(20_000_000)
+        for i, ((k, on_side), o) in enumerate(zip(calls, outs)):
+            spans = [t for j in range(k) for t in pool[(i + j) % 50]]
+            if k == 1:
+                reft.reft_pack_device(plan, spans, o, side if on_side else None)
+            else:
+                reft.reft_parity_encode(plan, spans, k, o, side if on_side else None)
+    finally:
+        reft.reft_plan_destroy(plan)
+    torch.cuda.synchronize()
+    for i, ((k, _), o) in enumerate(zip(calls, outs)):
+        assert np.array_equal(o.cpu().numpy(), oracle.encode([cpu[(i + j) % 50] for j in range(k)])), i
+
+
 def test_capture_that_takes_the_place_of_a_null_stream_table(dev):
-    """Nine tables of eight rows fill the plan's pool on the null stream; the captured call needs the place of one."""
+    """Nine tables of eight rows fill the plan's pool on the null stream; the captured call needs the place of one that
+    left an event."""
     sizes = [70_000, 33, 1 << 16]
     L, k = sum(sizes), 8
     gen = torch.Generator(device=dev)
