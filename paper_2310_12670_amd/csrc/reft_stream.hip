@@ -223,6 +223,60 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, const Span<K> &o,
     if ((int32_t)lane < len - whole) move_byte<K, PACK>(o, p.s + whole + lane);
 }
 
+// The first M KiB at most of the `len` bytes (at least 16) at byte `from` of the span, all loads of up to 32 chunks
+// before the first use.
+template <int K, int M, bool NT>
+__device__ __forceinline__ void move_chunks(const Span<K> &o, int64_t from, int32_t len, bool twice, uint32_t lane)
+{
+    constexpr int R = K * M <= 32 ? K : 32 / M;
+    u32x4 v[M] = {};
+    uint32_t at[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) at[c] = lane_offset((uint32_t)lane_place((int32_t)(c * kUnit + lane * 16), len));
+#pragma unroll
+    for (int j = 0; j < K; j += R) {
+        u32x4 t[R][M];
+#pragma unroll
+        for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+            for (int c = 0; c < M; ++c) t[q][c] = ld16_at<NT>(o.s[j + q] + from, at[c]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < R && j + q < K; ++q) {
+#pragma unroll
+            for (int c = 0; c < M; ++c) v[c] ^= t[q][c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < M; ++c)
+        if ((int32_t)(c * kUnit + lane * 16) + (twice ? 0 : 15) < len) st16_at<NT>(o.d + from, at[c], v[c]);
+}
+
+// `n` units (at most U) of span o from u on together; as move_unit, where it says which bytes come twice.
+template <int K, int U, bool NT>
+__device__ __forceinline__ void move_units(const StreamArgs &a, const Span<K> &o, uint64_t u, uint32_t n, uint32_t lane)
+{
+    const bool once = a.last == kLastDest;
+    const int64_t lo = o.lo > 0 ? o.lo : 0;
+    const uint32_t lead = once ? 0 : o.lead;
+    const Piece p = {piece_of(u - o.u0, o.head, lead, lo, o.hi).s, piece_of(u - o.u0 + n - 1, o.head, lead, lo, o.hi).t};
+    if (p.s >= p.t) return;
+    const bool twice = !once && p.t - lo >= 16;
+    int32_t len = (int32_t)(p.t - p.s);                        // at most U * kUnit + kMaxLead - 1
+    if (twice && len < 16) len = 16;
+    const int64_t from = p.t - len;
+    if (len >= 16) {
+        if (U > 3 && len > 3 * (int32_t)kUnit) move_chunks<K, U, NT>(o, from, len, twice, lane);
+        else if (U > 2 && len > 2 * (int32_t)kUnit) move_chunks<K, 3, NT>(o, from, len, twice, lane);
+        else if (len > (int32_t)kUnit) move_chunks<K, 2, NT>(o, from, len, twice, lane);
+        else move_chunks<K, 1, NT>(o, from, len, twice, lane);
+        if (len > U * (int32_t)kUnit && (int32_t)lane * 16 < len - U * (int32_t)kUnit)
+            move_16<K, NT, false>(o, from, (uint32_t)lane_place((int32_t)(U * kUnit + lane * 16), len), true);
+    }
+    if (!twice && (int32_t)lane < (len & 15)) move_byte<K, false>(o, p.s + (len & ~15) + lane);
+}
+
 // The U units from u on, and kRuns the steps behind them, up to `most` in all, as far as all their bytes are
 // of span o and in the range; returns how many steps.
 template <int K, int U, bool NT, Form F>
@@ -238,7 +292,7 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
     if (!whole) return 0;
     // vmcnt(0), once in front of a run: the compiler may otherwise take registers for still in flight from
     // before and wait for them in every round, and with them for the stores of the round before (2 sources,
-    // 126 MB by 4 workgroups: 2217 us so, 1583 with this)
+    // 126 MB by 4 workgroups: 2217 us so, 1583 with this; with 3 and 4 sources it takes 0.3 to 1 % itself)
     if constexpr (F == kRuns) __builtin_amdgcn_s_waitcnt(0x0f70);
     for (uint32_t done = 1;; ++done) {
         // all loads of up to 32 chunks before the first use
@@ -312,9 +366,10 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
             if (done) continue;
             done = 1;
             for (;;) {
-                move_unit<K, NT, F>(a, o, u, lane);
-                if (++u == end) break;
-                if (u >= o.u1) o = load_span<K>(a, span_of(a, u, lane));
+                const uint64_t part = end < o.u1 ? end : o.u1;
+                move_units<K, U, NT>(a, o, u, (uint32_t)(part - u), lane);
+                if ((u = part) == end) break;
+                o = load_span<K>(a, span_of(a, u, lane));
             }
         }
     }

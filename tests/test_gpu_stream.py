@@ -154,6 +154,23 @@ def test_boundaries(dev, k, unroll, max_wgs, nt):
         check_all(dev, sizes, k, buckets, seed=k * 64 + unroll * 8 + align, align=align)
 
 
+# the same boundaries in a stream whose spans are longer on average, so that a unit is a KiB
+@pytest.mark.parametrize("unroll,max_wgs", [(1, 0), (2, 3), (4, 1), (4, 64)])
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 8, 9, 16, 17])
+def test_boundaries_of_spans_beside_long_ones(dev, k, unroll, max_wgs):
+    reft.reft_set_tunable("unroll", unroll)
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    rng = np.random.default_rng(31 * k + unroll + max_wgs)
+    for align in (1, 4, 16):
+        sizes = [(n + align - 1) // align * align for n in boundary_sizes(rng)]
+        sizes.insert(int(rng.integers(0, len(sizes))), 512 * (len(sizes) + 1))
+        L, buckets = sum(sizes), []
+        while L:
+            buckets.append(min(L, int(rng.integers(1, 50_000))))
+            L -= buckets[-1]
+        check_all(dev, sizes, k, buckets, seed=k * 64 + unroll * 8 + align, align=align)
+
+
 # one launch below and one above the traffic at which the launch changes, for every number of
 # sources whose rule differs, with short and with long spans
 @pytest.mark.parametrize("k", [1, 2, 3, 6, 8])

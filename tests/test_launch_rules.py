@@ -160,3 +160,60 @@ def test_units_cover_a_span(grid, n):
                         count = moved(grid, n, head, lead, -70 if lo == 0 else lo, hi + 90 if hi == n else hi, once)
                         assert not any(count[:lo]) and not any(count[hi:])
                         assert all(c == 1 if once else c >= 1 for c in count[lo:hi])
+
+
+def moved_in_steps(grid, n, head, lead, lo, hi, once, steps, before):
+    """The same where a wave takes `steps` units of a span together (the span's first unit is the before-th of one)."""
+    count = [0] * n
+    st, en = (ctypes.c_int64 * 2)(), (ctypes.c_int64 * 2)()
+    low, high = max(lo, 0), min(hi, n)
+    first, last = grid.first_unit_at(low, head), grid.last_unit_at(high - 1, head)
+    j = first
+    while j <= last:
+        end = min((j + before) // steps * steps + steps - before, last + 1)
+        grid.piece_of(j, head, 0 if once else lead, low, high, st)
+        grid.piece_of(end - 1, head, 0 if once else lead, low, high, en)
+        j, a, b = end, st[0], en[1]
+        if a >= b:
+            continue
+        twice, size = not once and b - low >= 16, b - a
+        assert size < 1024 * steps + 128
+        if twice and size < 16:
+            size = 16
+        start, places = b - size, []
+        if size >= 16:
+            chunks = min(-(-size // 1024), steps)
+            for x in range(chunks * 64):
+                place = start + grid.lane_place(16 * x, size)
+                assert start <= place and place + 16 <= b
+                if 16 * x + (0 if twice else 15) < size:
+                    places.append(place)
+            if size > steps * 1024:
+                places += [start + grid.lane_place(steps * 1024 + 16 * x, size) for x in range(64) if 16 * x < size - steps * 1024]
+        places = [x + i for x in places for i in range(16)]
+        if not twice:
+            places += range(a + (size & ~15), a + size)
+        for x in places:
+            assert low <= x < high
+            count[x] += 1
+    return count
+
+
+def cuts_of(n):
+    return sorted({x for x in (0, 1, 5, 15, 16, 100, 127, 128, 255, 256, 257, 271, 272, 500, 1008, 1024, 1025, 1100, 2040, 4096,
+                               n - 17, n - 1, n) if 0 <= x <= n})
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 129, 1023, 1024, 1025, 1151, 1153, 2048, 2200, 4095, 4097, 4224, 5000])
+@pytest.mark.parametrize("steps", [2, 4])
+def test_steps_of_units_cover_a_span(grid, n, steps):
+    for head, lead, before in [(1024, 0, 0), (1024, 127, 1), (1, 0, 0), (1, 127, 3), (17, 3, 2), (600, 120, 1), (1023, 127, 0)]:
+        cuts = cuts_of(n)
+        for lo in cuts:
+            for hi in cuts[::2] + [n]:
+                if lo < hi:
+                    for once in (False, True):
+                        count = moved_in_steps(grid, n, head, lead, -70 if lo == 0 else lo, hi + 90 if hi == n else hi, once, steps,
+                                               before % steps)
+                        assert not any(count[:lo]) and not any(count[hi:])
+                        assert all(c == 1 if once else c >= 1 for c in count[lo:hi])
