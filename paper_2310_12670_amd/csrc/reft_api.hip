@@ -654,12 +654,12 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     // no more than 16,384 entries or 4 per span, else blocks of units (with 8 per span 0.3 % faster at 10 KB a span,
     // but plans of 49,152 spans take 1.9 ms to make instead of 1.0).  (Made here and not by a kernel: that would wait
     // behind whatever the null stream still has to do, and plan creation with it.)
-    p->grid = p->L / T >= kGridMeanSpan ? (uint32_t)kUnit - 1 : 0;
+    p->grid = grid_of(p->L, T);
     p->unit_off.resize(T + 1);
     uint64_t number = 0;
     for (uint64_t t = 0; t < T; ++t) {
         const uint64_t n = p->off[t + 1] - p->off[t];
-        if (n) number = first_number(number, p->off[t], p->grid);
+        if (n) number = first_number(number, p->off[t], align_of(p->L, T));
         p->unit_off[t] = number;
         number += units_of(n, head_of(p->off[t], p->grid));
     }

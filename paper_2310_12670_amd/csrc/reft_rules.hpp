@@ -24,16 +24,27 @@ constexpr uint64_t units_of(uint64_t span_bytes, uint64_t head)
     return span_bytes == 0 ? 0 : span_bytes <= head ? 1 : 1 + (span_bytes - head + kUnit - 1) / kUnit;
 }
 
-// In streams of long spans (a MiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
-// their numbers are the KiB's, but for multiples of 32 (some numbers between spans have no bytes): where a shard's
-// tensors lie in memory in order, an XCD then keeps to the same address bits from span to span (unit_of_wave; a
-// rotated unit and decode, 16 x 842 MB in pieces of 1.3 MB: 2481 us without, 2406 with).  `grid` is kUnit - 1 there and
-// 0 in other streams, where one more piece per span would cost more.
-constexpr uint64_t kGridMeanSpan = 1 << 20;
-constexpr uint64_t head_of(uint64_t off, uint64_t grid) { return kUnit - (off & grid); }
-constexpr uint64_t first_number(uint64_t least, uint64_t off, uint64_t grid)
+// In streams of long spans (64 KiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
+// their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie in
+// memory in order, an XCD then keeps to the same address bits from span to span (unit_of_wave, which is taken in these
+// streams alone).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few waves
+// look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256 KiB modulo 8, that is
+// for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain order / spread / on the grid
+// modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x 2030 / 1889 / 1825 / 1815; of
+// 300 KB, 8 x 961 / 952 / 969 / 929, 12 x 1420 / 1384 / 1397 / 1356, 16 with the packed stream 2087 / 2015 / 2037 / 1983; a rotated
+// unit and decode, 16 x 842 MB in pieces of 1.3 MB, 2481 spread, 2406 on the grid.  In other streams one more piece per
+// span would cost more, and the spans' places have little to do with the units' numbers (8 x 132 MB in spans of 10 KB
+// 204.6 us in plain order, 206.2 spread).
+constexpr uint64_t kGridMeanSpan = 64 * 1024, kWideMeanSpan = 256 * 1024;
+constexpr uint32_t align_of(uint64_t L, uint64_t T)
 {
-    return grid ? least + ((off / kUnit - least) & 31) : least;
+    return L / T >= kWideMeanSpan ? 31 : L / T >= kGridMeanSpan ? 7 : 0;
+}
+constexpr uint32_t grid_of(uint64_t L, uint64_t T) { return align_of(L, T) ? (uint32_t)kUnit - 1 : 0; }
+constexpr uint64_t head_of(uint64_t off, uint64_t grid) { return kUnit - (off & grid); }
+constexpr uint64_t first_number(uint64_t least, uint64_t off, uint64_t align)
+{
+    return align ? least + ((off / kUnit - least) & align) : least;
 }
 
 // Unit j of a span moves its bytes [s, t), none if s >= t, as far as they lie in [lo, hi), which may reach below 0 or

@@ -465,9 +465,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.ragged = dtab != nullptr;
     a.dest_row = dtab ? dtab : pt.unit_off;
     a.run = 1;
-    // (in short spans the tensors' places have little to do with the units' numbers: 8 x 132 MB in spans of 10 KB
-    // 204.6 us in plain order, 206.2 so)
-    a.spread = waves == 1 && a.first_step % 32 == 0 && pt.L / pt.T >= 64 * 1024;
+    a.spread = waves == 1 && a.first_step % 32 == 0 && pt.grid;
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
         a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, pt.L / pt.T);
         if (a.run > 1) form = kRuns;

@@ -14,6 +14,10 @@ extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { retu
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
 extern "C" uint64_t units_of(uint64_t n, uint64_t head) { return reft::units_of(n, head); }
+extern "C" uint32_t align_of(uint64_t L, uint64_t T) { return reft::align_of(L, T); }
+extern "C" uint32_t grid_of(uint64_t L, uint64_t T) { return reft::grid_of(L, T); }
+extern "C" uint64_t first_number(uint64_t least, uint64_t off, uint64_t align) { return reft::first_number(least, off, align); }
+extern "C" uint64_t head_of(uint64_t off, uint64_t grid) { return reft::head_of(off, grid); }
 extern "C" uint64_t first_unit_at(uint64_t r, uint64_t head) { return reft::first_unit_at(r, head); }
 extern "C" uint64_t last_unit_at(uint64_t r, uint64_t head) { return reft::last_unit_at(r, head); }
 extern "C" void piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, int64_t hi, int64_t *st)
@@ -42,7 +46,9 @@ def grid(tmp_path_factory):
     lib.link.restype = ctypes.c_uint32
     lib.run.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64]
     lib.run.restype = ctypes.c_uint32
-    for f in (lib.units_of, lib.first_unit_at, lib.last_unit_at):
+    lib.first_number.argtypes = [ctypes.c_uint64] * 3
+    lib.first_number.restype = ctypes.c_uint64
+    for f in (lib.units_of, lib.first_unit_at, lib.last_unit_at, lib.grid_of, lib.align_of, lib.head_of):
         f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
         f.restype = ctypes.c_uint64
     lib.piece_of.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
@@ -118,6 +124,24 @@ def test_every_unit_has_one_wave(grid, kib):
     for n in (1 << 33, (1 << 40) + 5):                # beyond 32 bits
         at = n // 32 * 32 - 64
         assert sorted(grid.unit(kib, w, n) for w in range(at, n)) == list(range(at, n))
+
+
+@pytest.mark.parametrize("mean", [1 << 16, 70_001, 300_000, 1 << 20, 3 << 20])
+def test_units_that_are_spread_have_the_numbers_of_their_kib(grid, mean):
+    """From a mean of 64 KiB on, where a launch spreads them: modulo 8, from 256 KiB on modulo the 32 KiB inside which they
+    change places."""
+    sizes = [mean + (-1) ** i * (7 * i % 61) * 100 for i in range(64)]
+    sizes[-1] += 64 * mean - sum(sizes)
+    mask, align = grid.grid_of(sum(sizes), len(sizes)), grid.align_of(sum(sizes), len(sizes))
+    assert mask == 1023 and grid.grid_of(64 * 65536 - 1, 64) == 0 and align == (31 if mean >= 1 << 18 else 7)
+    off = number = 0
+    for n in sizes:
+        number = grid.first_number(number, off, align)
+        for j in (0, 1, grid.units_of(n, grid.head_of(off, mask)) - 1):
+            start = off if j == 0 else off + grid.head_of(off, mask) + (j - 1) * 1024
+            assert (number + j - start // 1024) & align == 0
+        number += grid.units_of(n, grid.head_of(off, mask))
+        off += n
 
 
 def moved(grid, n, head, lead, lo, hi, once):
