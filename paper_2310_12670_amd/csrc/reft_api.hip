@@ -233,6 +233,7 @@ struct reft_plan {
     uint32_t tile_shift = 16;
     uint32_t unit_shift = 0;          // blocks of the device's look-up table of units
     uint32_t grid = 0;                // see head_of
+    uint32_t unit = 1024;             // see unit_bytes
     uint32_t burst_shift = 16;        // tiles of the burst kernel's look-up table
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
@@ -291,7 +292,7 @@ struct reft_plan {
 
     PlanTables tables() const
     {
-        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid};
+        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid, unit};
     }
 
     // lo < hi <= L
@@ -300,11 +301,11 @@ struct reft_plan {
         StreamRange r{lo, hi, 0, unit_off[T] - 1};
         if (lo > 0) {
             const uint64_t i = (uint64_t)(std::upper_bound(off.begin(), off.end() - 1, lo) - off.begin()) - 1;
-            r.first = unit_off[i] + first_unit_at(lo - off[i], head_of(off[i], grid));
+            r.first = unit_off[i] + first_unit_at(lo - off[i], head_of(off[i], grid, unit), unit);
         }
         if (hi < L) {
             const uint64_t i = (uint64_t)(std::upper_bound(off.begin(), off.end() - 1, hi - 1) - off.begin()) - 1;
-            r.last = unit_off[i] + last_unit_at(hi - 1 - off[i], head_of(off[i], grid));
+            r.last = unit_off[i] + last_unit_at(hi - 1 - off[i], head_of(off[i], grid, unit), unit);
         }
         return r;
     }
@@ -655,13 +656,14 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     // but plans of 49,152 spans take 1.9 ms to make instead of 1.0).  (Made here and not by a kernel: that would wait
     // behind whatever the null stream still has to do, and plan creation with it.)
     p->grid = grid_of(p->L, T);
+    p->unit = (uint32_t)unit_bytes(p->L, T);
     p->unit_off.resize(T + 1);
     uint64_t number = 0;
     for (uint64_t t = 0; t < T; ++t) {
         const uint64_t n = p->off[t + 1] - p->off[t];
         if (n) number = first_number(number, p->off[t], align_of(p->L, T));
         p->unit_off[t] = number;
-        number += units_of(n, head_of(p->off[t], p->grid));
+        number += p->unit == kUnit ? units_of(n, head_of(p->off[t], p->grid)) : units_of(n, kSmallUnit, kSmallUnit);
     }
     p->unit_off[T] = number;
     const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(16384, 4 * T), 1ull << 31);

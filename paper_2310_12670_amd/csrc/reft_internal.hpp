@@ -34,6 +34,7 @@ struct PlanTables {
     uint32_t unit_shift;
     uint32_t tile_shift;
     uint32_t grid;                 // see head_of
+    uint32_t unit;                 // bytes of a unit (see unit_bytes)
 };
 
 // Stream bytes [lo, hi) and the units first .. last that may move some of them.

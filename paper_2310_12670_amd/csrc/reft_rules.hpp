@@ -16,13 +16,19 @@ inline uint32_t stream_grid(uint64_t nunits, uint32_t waves, uint32_t cap)
     return (uint32_t)(g < most ? g : most);
 }
 
-// The stream kernel's units: every span is cut into pieces of kUnit bytes of its own.  The first one ends `head`
-// bytes into the span (1 to kUnit), the last one with the span.
-constexpr uint64_t kUnit = 1024;
-constexpr uint64_t units_of(uint64_t span_bytes, uint64_t head)
+// The stream kernel's units: every span is cut into pieces of `unit` bytes of its own.  The first one ends `head`
+// bytes into the span (1 to `unit`), the last one with the span.  A unit has kUnit bytes, or, in streams of tiny spans
+// (kSmallMeanSpan), kSmallUnit.
+constexpr uint64_t kUnit = 1024, kSmallUnit = 256;
+constexpr uint64_t units_of(uint64_t span_bytes, uint64_t head, uint64_t unit = kUnit)
 {
-    return span_bytes == 0 ? 0 : span_bytes <= head ? 1 : 1 + (span_bytes - head + kUnit - 1) / kUnit;
+    return span_bytes == 0 ? 0 : span_bytes <= head ? 1 : 1 + (span_bytes - head + unit - 1) / unit;
 }
+
+// At 700 bytes a span both kinds of units are as fast (parity of 8 x 70 MB 123 us), below the small ones win (see
+// k_stream_small).  At 512 their numbers stay below 4 per span, so that each has its entry in the look-up table.
+constexpr uint64_t kSmallMeanSpan = 512;
+constexpr uint64_t unit_bytes(uint64_t L, uint64_t T) { return L / T < kSmallMeanSpan && T < (1u << 29) ? kSmallUnit : kUnit; }
 
 // In streams of long spans (64 KiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
 // their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie in
@@ -41,7 +47,7 @@ constexpr uint32_t align_of(uint64_t L, uint64_t T)
     return L / T >= kWideMeanSpan ? 31 : L / T >= kGridMeanSpan ? 7 : 0;
 }
 constexpr uint32_t grid_of(uint64_t L, uint64_t T) { return align_of(L, T) ? (uint32_t)kUnit - 1 : 0; }
-constexpr uint64_t head_of(uint64_t off, uint64_t grid) { return kUnit - (off & grid); }
+constexpr uint64_t head_of(uint64_t off, uint64_t grid, uint64_t unit = kUnit) { return unit - (off & grid); }
 constexpr uint64_t first_number(uint64_t least, uint64_t off, uint64_t align)
 {
     return align ? least + ((off / kUnit - least) & align) : least;
@@ -54,17 +60,17 @@ constexpr uint32_t kMaxLead = 128;
 struct Piece {
     int64_t s, t;
 };
-constexpr Piece piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, int64_t hi)
+constexpr Piece piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, int64_t hi, uint64_t unit = kUnit)
 {
-    const int64_t t = (int64_t)(head + lead + j * kUnit), s = j ? t - (int64_t)kUnit : 0;
+    const int64_t t = (int64_t)(head + lead + j * unit), s = j ? t - (int64_t)unit : 0;
     return Piece{s < lo ? lo : s, t > hi ? hi : t};
 }
 
 // The first and the last of a span's units that may move its byte r, whatever its lead.
-constexpr uint64_t last_unit_at(uint64_t r, uint64_t head) { return r < head ? 0 : 1 + (r - head) / kUnit; }
-constexpr uint64_t first_unit_at(uint64_t r, uint64_t head)
+constexpr uint64_t last_unit_at(uint64_t r, uint64_t head, uint64_t unit = kUnit) { return r < head ? 0 : 1 + (r - head) / unit; }
+constexpr uint64_t first_unit_at(uint64_t r, uint64_t head, uint64_t unit = kUnit)
 {
-    return last_unit_at(r < kMaxLead ? 0 : r - (kMaxLead - 1), head);
+    return last_unit_at(r < kMaxLead ? 0 : r - (kMaxLead - 1), head, unit);
 }
 
 // Where the 16 bytes lie that the lane at byte `at` (a multiple of 16) of a piece of `len` bytes moves: behind the

@@ -12,7 +12,8 @@
 // at once.  A wave looks up its unit's span (a table with an entry per unit, or per block of units in long
 // streams), loads what is known of the span, K span pointers among it, and then has only vector accesses at uniform
 // bases; the span's last unit differs in nothing but the lanes that store.  No unit has bytes of two spans, so
-// there is nothing to search and nothing for lanes to decide, whatever the spans' sizes.
+// there is nothing to search and nothing for lanes to decide.  Only in streams of spans of a few hundred bytes, where most
+// of a wave would stay empty, several units share one (k_stream_small).
 //
 // Waves do not meet: no LDS, no barrier, so the chain of dependent loads (table, span, data: 2 - 3 us) of one wave
 // hides behind the others, and short streams, which have few units, spread over the whole chip.
@@ -64,6 +65,7 @@ struct StreamArgs {
     uint32_t ragged;         // the destination has a row
     uint32_t spread;         // steps in the order of unit_of_wave
     uint32_t run;            // kRuns: consecutive steps that one wave takes together
+    uint32_t once, pack;     // k_stream_small: the destination is a source; with the packed stream
 };
 
 // The tables do not change while the kernel runs; read through the constant address space, entries at
@@ -375,6 +377,82 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
     }
 }
 
+// Streams of tiny spans (kSmallMeanSpan): units of kSmallUnit bytes, each one's by 16 lanes, so that a wave moves four of
+// them, U times over; what a wave knows of its span in k_stream, each lane loads here for its own.  Bound by the rate at
+// which waves start (about 4 per ns) and by that chain of loads.  us, units of the stream (see above) / a wave per span
+// / so: 100,000 spans of 40 bytes packed 8.8 / 24.4 / 7.5, parity of 8 32.3 / 40.7 / 19.9; of 300 bytes 19.9 / 26.0 / 16.7 and
+// 91.8 / 102 / 58; 4 MB in 300 by 16 workgroups, two units per lane in flight, 108 / 128 / 47 and 246 / 269 / 91.
+template <int K, int U>
+__global__ void __launch_bounds__(256) k_stream_small(const StreamArgs a)
+{
+    constexpr uint32_t G = kSmallUnit / 16, N = 64 / G;
+    const uint32_t lane = threadIdx.x & 63, me = lane % G;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint64_t w = (uint64_t)blockIdx.x * a.waves + wave; w < a.nsteps; w += a.stride) {
+        uint64_t u[U], i[U];
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+            u[c] = a.range.first + (w * U + c) * N + lane / G;
+            i[c] = entry(a.unit_span, u[c] < a.range.last ? u[c] : a.range.last) & ~kWholeBlock;
+        }
+        uint64_t b[U], e[U], u0[U], d[U], s[U][K];
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+            b[c] = entry(a.off, i[c]);
+            e[c] = entry(a.off, i[c] + 1);
+            u0[c] = entry(a.unit_off, i[c]);
+            d[c] = entry(a.dest_row, i[c]);
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) s[c][j] = entry(a.tab, (uint64_t)j * a.T + i[c]);
+            s[c][K - 1] = entry(a.last_row, i[c]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        int64_t from[U], byte[U];              // where a lane's 16 bytes begin, and where its single byte lies
+        bool wide[U], narrow[U];               // whether it has them
+        u32x4 t[U][K];
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+            if (!a.ragged) d[c] = a.vb + b[c];
+            if (a.last == kLastContig) s[c][K - 1] = a.cbase + b[c];
+            if (a.last == kLastDest) s[c][K - 1] = d[c];
+            const int64_t first = (int64_t)(a.range.lo - b[c]), lo = first > 0 ? first : 0;
+            const int64_t hi = (int64_t)((e[c] < a.range.hi ? e[c] : a.range.hi) - b[c]);
+            const Piece p = piece_of(u[c] - u0[c], kSmallUnit, 0, lo, hi, kSmallUnit);
+            const int32_t len = u[c] <= a.range.last && p.s < p.t ? (int32_t)(p.t - p.s) : 0;
+            const int32_t at = (int32_t)me * 16, whole = len & ~15;
+            // as in move_unit
+            const bool twice = !a.once && p.t - lo >= 16;
+            const int32_t n = twice && len < 16 ? 16 : len;
+            from[c] = p.t - n + (twice ? lane_place(at, n) : at);
+            wide[c] = len && at + (twice ? 0 : 15) < n;
+            byte[c] = p.s + whole + me;
+            narrow[c] = !twice && (int32_t)me < len - whole;
+#pragma unroll
+            for (int j = 0; j < K; ++j)        // (16 bytes that are there, where none are wanted)
+                t[c][j] = ld16<false>(as_gc16(wide[c] ? s[c][j] + from[c] : (uint64_t)a.off));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+            if (wide[c]) {
+                if (a.pack) st16_at<false>(a.vb2 + b[c] + from[c], 0, t[c][0]);
+#pragma unroll
+                for (int j = 1; j < K; ++j) t[c][0] ^= t[c][j];
+                st16_at<false>(d[c] + from[c], 0, t[c][0]);
+            }
+            if (narrow[c]) {
+                uint8_t x[K];
+#pragma unroll
+                for (int j = 0; j < K; ++j) x[j] = ld8(s[c][j] + byte[c]);
+                if (a.pack) st8(a.vb2 + b[c] + byte[c], x[0]);
+#pragma unroll
+                for (int j = 1; j < K; ++j) x[0] ^= x[j];
+                st8(d[c] + byte[c], x[0]);
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // launch
 // ------------------------------------------------------------------------------------------------
@@ -418,6 +496,10 @@ static uint32_t crowd_limit(int nsrc, uint64_t mean_span)
 
 #define REFT_PICK_IN_PLACE(K) k_stream<K, 1, true, kInPlace>
 
+#define REFT_PICK_SMALL(K) (two ? k_stream_small<K, 2> : k_stream_small<K, 1>)
+
+#define REFT_PICK_SMALL_MANY(K) k_stream_small<K, 1>
+
 #define REFT_CASES_4(PICK)                                                                        \
     case 1: fn = PICK(1); break;                                                                  \
     case 2: fn = PICK(2); break;                                                                  \
@@ -439,6 +521,25 @@ static uint32_t crowd_limit(int nsrc, uint64_t mean_span)
     case 14: fn = PICK(14); break;                                                                \
     case 15: fn = PICK(15); break;                                                                \
     case 16: fn = PICK(16); break;
+
+static hipError_t launch_small(StreamArgs a, int nsrc, Form form, const LaunchCfg &cfg, hipStream_t stream)
+{
+    void (*fn)(const StreamArgs) = nullptr;
+    const bool two = cfg.capped && nsrc <= kMaxSrc;
+    switch (nsrc) {
+        REFT_CASES_4(REFT_PICK_SMALL) REFT_CASES_5_8(REFT_PICK_SMALL) REFT_CASES_9_16(REFT_PICK_SMALL_MANY)
+    default: return hipErrorInvalidValue;
+    }
+    const uint64_t units = (two ? 2 : 1) * 64 / (kSmallUnit / 16);
+    a.once = form == kInPlace || a.last == kLastDest;
+    a.pack = form == kPacked;
+    a.nsteps = (a.range.last - a.range.first) / units + 1;
+    a.waves = 4;
+    const uint32_t g = stream_grid(a.nsteps, a.waves, cfg.capped ? cfg.max_wgs : 0);
+    a.stride = (uint64_t)g * a.waves;
+    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * a.waves), 0, stream, a);
+    return hipGetLastError();
+}
 
 static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64_t *dtab, int nsrc, Form form,
                                 LaunchCfg cfg, hipStream_t stream)
@@ -464,6 +565,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     else a.last_row = pt.unit_off;
     a.ragged = dtab != nullptr;
     a.dest_row = dtab ? dtab : pt.unit_off;
+    if (pt.unit == kSmallUnit) return launch_small(a, nsrc, form, cfg, stream);
     a.run = 1;
     a.spread = waves == 1 && a.first_step % 32 == 0 && pt.grid;
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {

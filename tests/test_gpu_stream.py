@@ -171,6 +171,63 @@ def test_boundaries_of_spans_beside_long_ones(dev, k, unroll, max_wgs):
         check_all(dev, sizes, k, buckets, seed=k * 64 + unroll * 8 + align, align=align)
 
 
+def tiny_sizes(rng, n, mean):
+    """n spans around the ends of 16-byte chunks and of units of 256 bytes, their mean exactly `mean`."""
+    edges = [0, 1, 2, 15, 16, 17, 31, 100, 239, 240, 241, 255, 256, 257, 271, 272, 273, 511, 512, 513, 767, 768, 769]
+    sizes = [int(x) for x in rng.choice(edges, n - 1)]
+    short = n * mean - sum(sizes)
+    return sizes + [short] if short >= 0 else tiny_sizes(rng, n, mean)
+
+
+# the largest mean of streams of tiny spans and the one behind it
+@pytest.mark.parametrize("mean", [511, 512])
+@pytest.mark.parametrize("max_wgs", [0, 2])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 17])
+def test_tiny_spans(dev, k, max_wgs, mean):
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    rng = np.random.default_rng(37 * k + max_wgs)
+    for align in (1, 16):
+        sizes = tiny_sizes(rng, 333, mean)
+        L, buckets = sum(sizes), []
+        while L:
+            buckets.append(min(L, int(rng.integers(1, 20_000))))
+            L -= buckets[-1]
+        check_all(dev, sizes, k, buckets, seed=k, align=align)
+
+
+@pytest.mark.parametrize("k", [1, 2, 8, 16])
+@pytest.mark.parametrize("max_wgs", [0, 2])
+def test_tiny_spans_in_place(dev, k, max_wgs):
+    """Decoded over the parity, and over a survivor: every byte is read and written once only."""
+    reft.reft_set_tunable("max_wgs", max_wgs)
+    rng = np.random.default_rng(90 + k)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(90 + k)
+    sizes = tiny_sizes(rng, 501, 300)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    L = int(off[-1])
+    plan = reft.reft_plan_create(sizes)
+    try:
+        for lost, over in ((0, None), (0, k - 1), (k - 1, None)):
+            if over == lost:
+                continue
+            held = [arena(sizes, rng.integers(0, 16, len(sizes)), dev, gen) for _ in range(k)]
+            streams = [oracle.pack([oracle.as_bytes(t.cpu()) for t in h[1]]) for h in held]
+            raw = torch.full((L + 2 * GUARD,), CANARY, dtype=torch.uint8, device=dev)
+            par = raw[GUARD + 3:GUARD + 3 + L]
+            par.copy_(torch.from_numpy(oracle.encode(streams)))
+            outs = [par[a:b] for a, b in zip(off[:-1], off[1:])] if over is None else held[over][1]
+            rows = [None if s == lost else t for s, h in enumerate(held) for t in h[1]]
+            reft.reft_reconstruct_spans(plan, rows, k, lost, par, outs)
+            torch.cuda.synchronize()
+            assert np.array_equal(np.concatenate([t.cpu().numpy() for t in outs]), streams[lost]), (lost, over)
+            r = raw.cpu().numpy()
+            assert np.all(r[:GUARD + 3] == CANARY) and np.all(r[GUARD + 3 + L:] == CANARY)
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)
+
+
 # one launch below and one above the traffic at which the launch changes, for every number of
 # sources whose rule differs, with short and with long spans
 @pytest.mark.parametrize("k", [1, 2, 3, 6, 8])

@@ -26,6 +26,16 @@ extern "C" void piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, i
     st[0] = p.s;
     st[1] = p.t;
 }
+extern "C" uint64_t unit_bytes(uint64_t L, uint64_t T) { return reft::unit_bytes(L, T); }
+extern "C" uint64_t small_units_of(uint64_t n) { return reft::units_of(n, reft::kSmallUnit, reft::kSmallUnit); }
+extern "C" uint64_t small_first_at(uint64_t r) { return reft::first_unit_at(r, reft::kSmallUnit, reft::kSmallUnit); }
+extern "C" uint64_t small_last_at(uint64_t r) { return reft::last_unit_at(r, reft::kSmallUnit, reft::kSmallUnit); }
+extern "C" void small_piece_of(uint64_t j, int64_t lo, int64_t hi, int64_t *st)
+{
+    const reft::Piece p = reft::piece_of(j, reft::kSmallUnit, 0, lo, hi, reft::kSmallUnit);
+    st[0] = p.s;
+    st[1] = p.t;
+}
 extern "C" int32_t lane_place(int32_t at, int32_t len) { return reft::lane_place(at, len); }
 extern "C" uint64_t unit(uint32_t kib, uint64_t w, uint64_t n) { return kib == 1 ? reft::unit_of_wave<1>(w, n) : reft::unit_of_wave<2>(w, n); }
 extern "C" uint64_t contig_rows(uint64_t rows) { return reft::contig_burst_min_rows(rows); }
@@ -51,6 +61,12 @@ def grid(tmp_path_factory):
     for f in (lib.units_of, lib.first_unit_at, lib.last_unit_at, lib.grid_of, lib.align_of, lib.head_of):
         f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
         f.restype = ctypes.c_uint64
+    lib.unit_bytes.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
+    for f in (lib.small_units_of, lib.small_first_at, lib.small_last_at):
+        f.argtypes = [ctypes.c_uint64]
+    for f in (lib.unit_bytes, lib.small_units_of, lib.small_first_at, lib.small_last_at):
+        f.restype = ctypes.c_uint64
+    lib.small_piece_of.argtypes = [ctypes.c_uint64, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
     lib.piece_of.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
     lib.unit.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64]
     lib.unit.restype = ctypes.c_uint64
@@ -223,6 +239,32 @@ def moved_in_steps(grid, n, head, lead, lo, hi, once, steps, before):
     return count
 
 
+def moved_small(grid, n, lo, hi, once):
+    """The same for units of 256 bytes, 16 lanes each."""
+    count = [0] * n
+    st = (ctypes.c_int64 * 2)()
+    low, high = max(lo, 0), min(hi, n)
+    for j in range(grid.small_first_at(low), grid.small_last_at(high - 1) + 1):
+        assert j < grid.small_units_of(n)
+        grid.small_piece_of(j, low, high, st)
+        a, b = st
+        if a >= b:
+            continue
+        twice, size = not once and b - low >= 16, b - a
+        assert size <= 256
+        whole, k = size & ~15, 16 if twice and size < 16 else size
+        for me in range(16):
+            at = 16 * me
+            place = b - k + (grid.lane_place(at, k) if twice else at)
+            mine = list(range(place, place + 16)) if at + (0 if twice else 15) < k else []
+            if not twice and me < size - whole:
+                mine.append(a + whole + me)
+            for x in mine:
+                assert low <= x < high
+                count[x] += 1
+    return count
+
+
 def cuts_of(n):
     return sorted({x for x in (0, 1, 5, 15, 16, 100, 127, 128, 255, 256, 257, 271, 272, 500, 1008, 1024, 1025, 1100, 2040, 4096,
                                n - 17, n - 1, n) if 0 <= x <= n})
@@ -241,3 +283,22 @@ def test_steps_of_units_cover_a_span(grid, n, steps):
                                                before % steps)
                         assert not any(count[:lo]) and not any(count[hi:])
                         assert all(c == 1 if once else c >= 1 for c in count[lo:hi])
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 100, 239, 240, 241, 255, 256, 257, 270, 272, 273, 511, 512, 513, 1000])
+def test_small_units_cover_a_span(grid, n):
+    for lo in cuts_of(n):
+        for hi in cuts_of(n):
+            if lo < hi:
+                for once in (False, True):
+                    count = moved_small(grid, n, -70 if lo == 0 else lo, hi + 90 if hi == n else hi, once)
+                    assert not any(count[:lo]) and not any(count[hi:])
+                    assert all(c == 1 if once else c >= 1 for c in count[lo:hi])
+
+
+def test_small_units_have_an_entry_each(grid):
+    """At most 4 a span, which is what the look-up table has room for."""
+    assert grid.unit_bytes(511 * 1000, 1000) == 256 and grid.unit_bytes(512 * 1000, 1000) == 1024
+    for sizes in ([511] * 999, [1] * 998 + [509_000], [257, 765] * 500):
+        assert grid.unit_bytes(sum(sizes), len(sizes)) == 256
+        assert sum(grid.small_units_of(n) for n in sizes) <= 4 * len(sizes)
