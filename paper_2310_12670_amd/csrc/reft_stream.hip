@@ -476,10 +476,11 @@ static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 // %.  us, with 80 KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4
 // sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713.  All that fit / so many: 3 sources
 // 582 / 575 in long spans, 370 / 342 (0.5 GB each) in short ones; 2 sources 273 / 263 in spans below a MiB, but 425 /
-// 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369.
-static uint32_t crowd_limit(int nsrc, uint64_t mean_span)
+// 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369; two copies of one source (with
+// the packed stream) 319 / 328 (0.6 GB in spans of 70 KB).
+static uint32_t crowd_limit(int nsrc, uint64_t mean_span, bool packed)
 {
-    const uint32_t waves = nsrc == 1   ? (mean_span >= 64 * 1024 ? 24 : 32)
+    const uint32_t waves = nsrc == 1   ? (mean_span >= 64 * 1024 && !packed ? 24 : 32)
                            : nsrc == 2 ? (mean_span < 1024 * 1024 ? 28 : 32)
                            : nsrc == 3 ? 24
                                        : std::max({20 - nsrc, 17 - 5 * nsrc / 8, 8});
@@ -602,7 +603,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     const uint32_t g = stream_grid((a.nsteps + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
     a.waves = waves;
     a.stride = (uint64_t)g * waves;
-    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc, pt.L / pt.T) : 0, stream, a);
+    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc, pt.L / pt.T, form == kPacked) : 0, stream, a);
     return hipGetLastError();
 }
 
