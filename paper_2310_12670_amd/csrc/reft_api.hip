@@ -284,7 +284,7 @@ struct reft_plan {
     };
     std::vector<CopyGraph> graphs;
     uint64_t graph_tick = 0;
-    // write-burst kernel: spans that start in each tile, sorted (plans with many span boundaries keep
+    // write-burst kernel: spans that start in each tile where any do, sorted (plans with many span boundaries keep
     // the stream kernel), and a ring of counter blocks, one per launch in flight
     std::vector<uint32_t> tile_spans_sorted;
     uint32_t *burst_ctr = nullptr;
@@ -631,10 +631,9 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
             while (p->off[i + 1] <= o) ++i;      // o < L = off[T] keeps i < T
             first[t] = (uint32_t)i;
         }
-        p->tile_spans_sorted.resize(p->ntiles);
         for (uint64_t t = 0; t < p->ntiles; ++t) {
             const uint64_t nxt = t + 1 < p->ntiles ? first[t + 1] : T - 1;
-            p->tile_spans_sorted[t] = (uint32_t)(nxt - first[t]);
+            if (nxt > first[t]) p->tile_spans_sorted.push_back((uint32_t)(nxt - first[t]));
         }
         std::sort(p->tile_spans_sorted.begin(), p->tile_spans_sorted.end());
     }
@@ -659,11 +658,12 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->unit = (uint32_t)unit_bytes(p->L, T);
     p->unit_off.resize(T + 1);
     uint64_t number = 0;
+    const uint64_t align = align_of(p->L, T);
     for (uint64_t t = 0; t < T; ++t) {
-        const uint64_t n = p->off[t + 1] - p->off[t];
-        if (n) number = first_number(number, p->off[t], align_of(p->L, T));
+        const uint64_t b = p->off[t], n = p->off[t + 1] - b;
+        if (n) number = first_number(number, b, align);
         p->unit_off[t] = number;
-        number += p->unit == kUnit ? units_of(n, head_of(p->off[t], p->grid)) : units_of(n, kSmallUnit, kSmallUnit);
+        number += p->unit == kUnit ? units_of(n, head_of(b, p->grid)) : units_of(n, kSmallUnit, kSmallUnit);
     }
     p->unit_off[T] = number;
     const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(16384, 4 * T), 1ull << 31);
@@ -680,25 +680,33 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     const size_t at_unit_off = behind(0, (T + 1) * sizeof(uint64_t));
     const size_t at_tile_span = behind(at_unit_off, (T + 1) * sizeof(uint64_t));
     const size_t at_unit_span = behind(at_tile_span, burst_tiles * sizeof(uint32_t));
-    const size_t at_ctr = behind(at_unit_span, nblocks * sizeof(uint32_t));
+    const size_t at_ctr = behind(at_unit_span, (nblocks + 3) * sizeof(uint32_t));
     const size_t at_ptr = behind(at_ctr, kCtrBlocks * kBurstCtrBytes);
     p->ring_cap = (uint64_t)kRingRows * T;
-    std::unique_ptr<uint64_t[]> tables(new uint64_t[at_ctr / sizeof(uint64_t)]);  // gaps are not read
-    std::copy(p->off.begin(), p->off.end(), tables.get());
-    std::copy(p->unit_off.begin(), p->unit_off.end(), tables.get() + at_unit_off / sizeof(uint64_t));
-    uint32_t *const tile_span = (uint32_t *)((uint8_t *)tables.get() + at_tile_span);
+    HIPCHK(hipHostMalloc((void **)&p->h_ptr, p->ring_cap * sizeof(uint64_t), hipHostMallocDefault));
+    // Made in the pinned mirror of the pool, which is not in use yet, where they fit (256 spans of 60 KB: 91 us for all of
+    // this function from other memory, 66 so).  Gaps are not read.
+    std::unique_ptr<uint64_t[]> heap;
+    if (at_ctr > p->ring_cap * sizeof(uint64_t)) heap.reset(new uint64_t[at_ctr / sizeof(uint64_t)]);
+    uint64_t *const tables = heap ? heap.get() : p->h_ptr;
+    std::copy(p->off.begin(), p->off.end(), tables);
+    std::copy(p->unit_off.begin(), p->unit_off.end(), tables + at_unit_off / sizeof(uint64_t));
+    uint32_t *const tile_span = (uint32_t *)((uint8_t *)tables + at_tile_span);
     for (size_t t = 0; t < burst_tiles; ++t) {
         const size_t at = t << (p->burst_shift - p->tile_shift);
         tile_span[t] = at < p->ntiles ? first[at] : 0;
     }
-    uint32_t *const lookup = (uint32_t *)((uint8_t *)tables.get() + at_unit_span);
+    uint32_t *const lookup = (uint32_t *)((uint8_t *)tables + at_unit_span);
     for (uint64_t t = 0, i = 0; i < T; ++i) {                        // t: the first block without an entry
-        const uint64_t whole = p->unit_off[i + 1] >> p->unit_shift;
-        if (whole > t) std::fill(lookup + t, lookup + whole, (uint32_t)i | kWholeBlock), t = whole;
-        if (t << p->unit_shift < p->unit_off[i + 1]) lookup[t++] = (uint32_t)i;
+        const uint64_t end = p->unit_off[i + 1], whole = end >> p->unit_shift;
+        if (whole > t) {                       // (four at a time: up to three too many, for the spans behind)
+            for (; t < whole; t += 4) std::fill_n(lookup + t, 4, (uint32_t)i | kWholeBlock);
+            t = whole;
+        }
+        if (t << p->unit_shift < end) lookup[t++] = (uint32_t)i;
     }
     HIPCHK(hipMalloc((void **)&p->d_tables, at_ptr + p->ring_cap * sizeof(uint64_t)));
-    HIPCHK(hipMemcpy(p->d_tables, tables.get(), at_ctr, hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(p->d_tables, tables, at_ctr, hipMemcpyHostToDevice));
     p->d_off = (uint64_t *)p->d_tables;
     p->d_unit_off = (uint64_t *)(p->d_tables + at_unit_off);
     p->d_tile_span = (uint32_t *)(p->d_tables + at_tile_span);
@@ -734,9 +742,8 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     // idle helper streams made here were enough to push a snapshot and a restore, on streams
     // created after them, onto one queue, where they took turns on the link).
     if (g_dma_streams.load() == 2) HIPCHK(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
-    // everything a data-moving call needs is made here: the pointer-table pool, the host scratch
-    // for row tables, and the whole stream's piece lists for the staged transport
-    HIPCHK(hipHostMalloc((void **)&p->h_ptr, p->ring_cap * sizeof(uint64_t), hipHostMallocDefault));
+    // everything else a data-moving call needs is made here too: the host scratch for row tables, and
+    // the whole stream's piece lists for the staged transport
     p->row_buf.resize((size_t)(REFT_MAX_K + 1) * T);
     p->pieces.reserve(kPieceLists);
     (void)pieces_of(p, 0, p->NB);
@@ -1471,8 +1478,9 @@ static BurstCfg burst_cfg(uint32_t *ring, uint32_t slot, int num_cus)
 static bool few_dense_tiles(const reft_plan *p)
 {
     const auto &v = p->tile_spans_sorted;
-    const auto dense = v.end() - std::lower_bound(v.begin(), v.end(), (uint32_t)g_small_pieces.load());
-    return (uint64_t)dense * 8 <= p->ntiles;
+    const uint32_t most = (uint32_t)g_small_pieces.load();
+    const uint64_t dense = most ? (uint64_t)(v.end() - std::lower_bound(v.begin(), v.end(), most)) : p->ntiles;
+    return dense * 8 <= p->ntiles;
 }
 
 // Whether `rows` rows go through the burst kernel: very long rows, few span boundaries.  A launch into tensors
