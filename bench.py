@@ -619,7 +619,7 @@ def run_config(args, cfg, torch, reft, pinned, streams, primary):
         enc_gbps = (k + 1) * L / (enc_ms * 1e-3) / 1e9
         dec_gbps = (k + 1) * L / (dec_ms * 1e-3) / 1e9
         kernel = encode_kernel(k, reft.reft_plan_burst_stats(b.plan), reft.reft_get_tunable("burst_max_polls"))
-        traffic, source = measured_traffic(b.wl.cfg)
+        traffic, source = measured_traffic(b.wl.cfg, kernel)
         out = {
             "workload": f"config {b.wl.cfg}: {b.wl.description}",
             "k": k, "spans": b.T, "stream_bytes": L, "buckets": len(b.wl.bucket_nbytes),
@@ -886,11 +886,11 @@ def encode_kernel(k: int, burst_stats, polls: int) -> str:
     return f"k_stream<{k}>" if polls else f"k_stream<{k}> or k_gather_burst<{k}> without waits"
 
 
-def measured_traffic(cfg: int):
+def measured_traffic(cfg: int, kernel: str):
     """(HBM bytes per launch of the encode kernel, the tracked file they come from): FETCH_SIZE and
     WRITE_SIZE of a committed rocprofv3 counter run, each scaled by a copy of known size.  A
     calibrated figure from an earlier run of the same command, not measured by this run.
-    (None, None) if no such profile exists for this configuration."""
+    (None, None) if no such profile exists for this configuration and the kernel that ran."""
     name = f"config{cfg}_kernels_hbm_traffic.txt"
     try:
         kv = {}
@@ -898,7 +898,7 @@ def measured_traffic(cfg: int):
             if "=" in line and line.split("=")[0].strip().startswith("traffic_"):
                 key, _, val = line.partition("=")
                 kv[key.strip()] = val.strip()
-        if int(kv.get("traffic_config", -1)) == cfg:
+        if int(kv.get("traffic_config", -1)) == cfg and kv.get("traffic_kernel") == kernel:
             return int(kv["traffic_bytes"]), f"profiles/{name} (rocprofv3 --pmc run of this command)"
     except (OSError, ValueError, KeyError):
         pass

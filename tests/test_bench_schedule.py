@@ -157,3 +157,15 @@ def test_the_encode_kernel_is_named_by_what_ran():
     assert bench.encode_kernel(8, (457728, 0, 0, 894), 6) == "k_gather_burst<8>"
     assert bench.encode_kernel(8, (0, 0, 0, 0), 6) == "k_stream<8>"
     assert "k_stream<7>" in bench.encode_kernel(7, (0, 0, 0, 0), 0)
+
+
+@pytest.mark.parametrize("cfg", [1, 2, 3, 4])
+def test_the_traffic_in_the_record_is_that_of_the_kernel_that_ran(cfg):
+    """A profile names its kernel; beside another one its bytes are not given."""
+    given = {kernel: bench.measured_traffic(cfg, kernel) for kernel in ("k_stream<8>", "k_gather_burst<8>")}
+    assert sorted(v == (None, None) for v in given.values()) == [False, True]
+    text = open(f"{bench.ROOT}/profiles/config{cfg}_kernels_hbm_traffic.txt").read()
+    for kernel, (traffic, source) in given.items():
+        if traffic:
+            assert f"traffic_kernel = {kernel}\n" in text and f"traffic_bytes = {traffic}\n" in text and source
+    assert bench.measured_traffic(cfg, "k_stream<7>") == (None, None)
