@@ -1,7 +1,7 @@
 """GPU parity of the write-burst variant of the XOR kernel against the CPU oracle, bit-exact.
 
-reft_parity_encode and reft_reconstruct_spans switch to this variant by themselves for seven and eight
-rows of a long stream; here the thresholds are lowered so that small, ragged cases run
+reft_parity_encode switches to this variant by itself for seven and eight rows of 13 GiB and more (a decode
+into tensors would from four times that on); here the thresholds are lowered so that small, ragged cases run
 through it as well, which the plan's burst statistics confirm: every number of sources one launch takes, misaligned sources and
 destinations, decode into tensors that are (and are not) aligned alike, stage sizes, grids from
 one workgroup up, and with the timing of the bursts switched off (the result must not depend on
@@ -199,6 +199,28 @@ def test_many_small_spans_through_the_piece_walk(dev):
         shards.append(spans)
     par = check_encode(dev, shards, sizes, out_phase=3)
     check_decode(dev, shards, sizes, par, 2, alike(sizes, 5))
+
+
+@pytest.mark.parametrize("k", [2, 8])
+def test_tiles_of_the_look_up_table_larger_than_the_plans(dev, k):
+    """4096 tiles at most: streams of more have larger ones, in which the kernel walks on, here over many small spans."""
+    saved = reft.reft_get_tunable("tile_shift")
+    reft.reft_set_tunable("tile_shift", 12)
+    try:
+        rng = np.random.default_rng(k)
+        gen = torch.Generator(device=dev)
+        gen.manual_seed(k)
+        sizes = [9_000_001] + [int(x) for x in rng.integers(0, 90, 400)] + [18_500_000, 0, 7, 8_000_003]
+        assert sum(sizes) >> 13 >= 4096
+        shards, keep = [], []
+        for s in range(k):
+            arena, spans = spans_in_arena(sizes, [int(x) for x in rng.integers(0, 16, len(sizes))], dev, gen)
+            keep.append(arena)
+            shards.append(spans)
+        par = check_encode(dev, shards, sizes, out_phase=9)
+        check_decode(dev, shards, sizes, par, k - 1, alike(sizes, 3))
+    finally:
+        reft.reft_set_tunable("tile_shift", saved)
 
 
 def test_same_result_as_the_ordinary_kernel_and_back_to_back(dev):
