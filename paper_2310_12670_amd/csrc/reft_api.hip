@@ -1521,9 +1521,9 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     const uint64_t T = p->T;
     const LaunchCfg cfg = launch_cfg(p);
     const PlanTables pt = p->tables();
-    // Very long rows: reads and writes are separated in time with the burst kernel.  Destination spans that are not all aligned alike relative to
-    // their stream offsets, which its staging image cannot represent, keep the stream kernel, and more rows go
-    // through it in one pass, up to kMaxStreamSrc.
+    // Very long rows: reads and writes are separated in time with the burst kernel.  Destination spans that are not
+    // all aligned alike relative to their stream offsets, which its staging image cannot represent, keep the stream
+    // kernel, and more rows go through it in one pass, up to kMaxStreamSrc.
     bool burst = burst_applies(p, nrows, dst_row != nullptr);
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     if (burst && dst_row) {

@@ -94,6 +94,26 @@ constexpr uint64_t unit_of_wave(uint64_t w, uint64_t n)
     return (w & ~12ull) | (w >> 1 & 4) | (w & 4) << 1;
 }
 
+// LDS for one-wave workgroups to ask for, which they do not use, so that no more of them share a compute unit than its
+// streams want (0: as many as fit): the more there are, the wider the windows in which the chip moves through memory.
+// Swept from 8 to 30 requested waves on 0.1 to 14 GB, in spans of 10 KB to 10 MB (encode, decode, with packed stream,
+// rotated, copies): with 4 sources and more the best is 16, 15, 14, 13, 12 (8 sources), 12, 11, 11, 10 (12), 9, 9, 8, 8,
+// and one more or less costs 0.2 to 1 %.  (These are requests; in the blocks of 1280 bytes in which LDS is handed out
+// 28, 24, 15, 13, 12, 11 and 10 come to 25, 21, 14, 12, 11, 10 and 9 waves.)  us, with 80 KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8
+// from 12 on) / with this one: 4 sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713.  All
+// that fit / so many: 3 sources 582 / 575 in long spans, 370 / 342 (0.5 GB each) in short ones; 2 sources 273 / 263 in
+// spans below a MiB, but 425 / 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369; two
+// copies of one source (with the packed stream) 319 / 328 (0.6 GB in spans of 70 KB).
+constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
+{
+    if (nsrc == 1) return mean_span >= 64 * 1024 && !packed ? 24 : 32;
+    if (nsrc == 2) return mean_span < 1024 * 1024 ? 28 : 32;
+    if (nsrc == 3) return 24;
+    const uint32_t some = nsrc < 12 ? 20 - nsrc : 8, many = 17 - 5 * nsrc / 8;
+    return some > many ? some : many > 8 ? many : 8;
+}
+constexpr uint32_t crowd_lds(uint32_t waves) { return waves == 32 ? 0 : 160 * 1024 / waves / 512 * 512; }
+
 // Consecutive units that a wave of a capped grid takes together.  Runs pay where a wave waits on look-ups for
 // units inside long spans (spans of 70 KB by 8 workgroups: 46 us without, 51 with), with up to four sources
 // (5 by 64 workgroups: 224 us without, 240 with), and up to this many waves, beyond which more windows in

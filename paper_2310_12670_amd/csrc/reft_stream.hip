@@ -26,8 +26,6 @@
 #include "reft_device.hpp"
 #include "reft_rules.hpp"
 
-#include <algorithm>
-
 namespace reft {
 
 // The last of a launch's K sources.
@@ -79,13 +77,6 @@ __device__ __forceinline__ uint64_t entry(const uint64_t *tab, uint64_t i)
 __device__ __forceinline__ uint32_t entry(const uint32_t *tab, uint64_t i)
 {
     return ((const REFT_CONST uint32_t *)(uint64_t)tab)[i];
-}
-
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l)
-{
-    const uint32_t a = __builtin_amdgcn_readlane((uint32_t)v, l);
-    const uint32_t b = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
-    return (uint64_t)b << 32 | a;
 }
 
 // The span that owns unit u; all lanes get the same answer.  Where a block of units is shared by spans, 64 ends per
@@ -347,8 +338,8 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // all arguments at once: left alone, the compiler loads a few, looks whether there is work, and then loads the
     // others, and the first wave on a die waits for host memory twice
-    asm volatile("" ::"s"(a.off), "s"(a.unit_off), "s"(a.unit_span), "s"(a.T), "s"(a.tab), "s"(a.last_row), "s"(a.dest_row), "s"(a.vb),
-                 "s"(a.cbase), "s"(a.range.lo), "s"(a.range.hi), "s"(a.first_step), "s"(a.nsteps), "s"(a.waves),
+    asm volatile("" ::"s"(a.off), "s"(a.unit_off), "s"(a.unit_span), "s"(a.T), "s"(a.tab), "s"(a.last_row),
+                 "s"(a.dest_row), "s"(a.vb), "s"(a.cbase), "s"(a.range.lo), "s"(a.range.hi), "s"(a.first_step), "s"(a.nsteps), "s"(a.waves),
                  "s"(a.unit_shift), "s"(a.grid), "s"(a.last), "s"(a.ragged), "s"(a.stride), "s"(a.spread));
     // kRuns: steps left of this run, and how many of them the last round moved
     uint32_t left = F == kRuns ? a.run : 1, done = 1;
@@ -469,24 +460,6 @@ constexpr uint64_t kCachedTraffic = 96ull << 20;
 // short spans); 16: 2299 and 2405 (14.3 GB).
 static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 
-// LDS to ask for, which the kernel does not use, so that no more waves share a compute unit than its streams
-// want: the more there are, the wider the windows in which the chip moves through memory.  Swept from 8 to 30 waves
-// on 0.1 to 14 GB, in spans of 10 KB to 10 MB (encode, decode, with packed stream, rotated, copies): with 4 sources and
-// more the best is 16, 14, 14, 13, 12 (8 sources), 12, 11, 11, 10 (12), 9, 9, 8, 8, and one more or less costs 0.2 to 1
-// %.  us, with 80 KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4
-// sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713.  All that fit / so many: 3 sources
-// 582 / 575 in long spans, 370 / 342 (0.5 GB each) in short ones; 2 sources 273 / 263 in spans below a MiB, but 425 /
-// 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369; two copies of one source (with
-// the packed stream) 319 / 328 (0.6 GB in spans of 70 KB).
-static uint32_t crowd_limit(int nsrc, uint64_t mean_span, bool packed)
-{
-    const uint32_t waves = nsrc == 1   ? (mean_span >= 64 * 1024 && !packed ? 24 : 32)
-                           : nsrc == 2 ? (mean_span < 1024 * 1024 ? 28 : 32)
-                           : nsrc == 3 ? 24
-                                       : std::max({20 - nsrc, 17 - 5 * nsrc / 8, 8});
-    return waves == 32 ? 0 : 160 * 1024 / waves / 512 * 512;
-}
-
 #define REFT_PICK_MANY(K)                                                                         \
     (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
                      : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
@@ -603,7 +576,8 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     const uint32_t g = stream_grid((a.nsteps + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
     a.waves = waves;
     a.stride = (uint64_t)g * waves;
-    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), waves == 1 ? crowd_limit(nsrc, pt.L / pt.T, form == kPacked) : 0, stream, a);
+    const uint32_t lds = waves == 1 ? crowd_lds(crowd_waves((uint32_t)nsrc, pt.L / pt.T, form == kPacked)) : 0;
+    hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), lds, stream, a);
     return hipGetLastError();
 }
 

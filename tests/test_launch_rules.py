@@ -13,6 +13,8 @@ SOURCE = """
 extern "C" uint32_t stream(uint64_t nunits, uint32_t waves, uint32_t cap) { return reft::stream_grid(nunits, waves, cap); }
 extern "C" uint32_t link(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs) { return reft::link_cap(link_wgs, halves, max_wgs); }
 extern "C" uint32_t run(uint64_t nunits, uint64_t waves, uint32_t nsrc, uint64_t mean) { return reft::run_of_units(nunits, waves, nsrc, mean); }
+extern "C" uint32_t crowd_waves(uint32_t nsrc, uint64_t mean, bool packed) { return reft::crowd_waves(nsrc, mean, packed); }
+extern "C" uint32_t crowd_lds(uint32_t waves) { return reft::crowd_lds(waves); }
 extern "C" uint64_t units_of(uint64_t n, uint64_t head) { return reft::units_of(n, head); }
 extern "C" uint32_t align_of(uint64_t L, uint64_t T) { return reft::align_of(L, T); }
 extern "C" uint32_t grid_of(uint64_t L, uint64_t T) { return reft::grid_of(L, T); }
@@ -56,6 +58,9 @@ def grid(tmp_path_factory):
     lib.link.restype = ctypes.c_uint32
     lib.run.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64]
     lib.run.restype = ctypes.c_uint32
+    lib.crowd_waves.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool]
+    lib.crowd_lds.argtypes = [ctypes.c_uint32]
+    lib.crowd_waves.restype = lib.crowd_lds.restype = ctypes.c_uint32
     lib.first_number.argtypes = [ctypes.c_uint64] * 3
     lib.first_number.restype = ctypes.c_uint64
     for f in (lib.units_of, lib.first_unit_at, lib.last_unit_at, lib.grid_of, lib.align_of, lib.head_of):
@@ -110,21 +115,37 @@ def test_packed_decode_goes_by_the_callers_burst_limits(grid):
     assert grid.contig_rows(rows) == 5 and grid.contig_bytes(size) == 8 << 20
     for r in (1, 2, 5, 6, 8, 9, 32, 1 << 40):
         assert grid.contig_rows(r) == r
-    for b in (0, 1, 8 << 20, 9 << 20, 1 << 30, (2 << 30) + 1, 4 << 30, 1 << 62):
+    for b in (0, 1, 8 << 20, 9 << 20, 1 << 30, 2 << 30, (2 << 30) + 1, 4 << 30, (13 << 30) - 1, (13 << 30) + 1, 1 << 62):
         assert grid.contig_bytes(b) == b
 
 
 def test_runs_leave_every_wave_eight(grid):
     """1 to 16 units together; one at a time from five sources on, with many waves and in short spans."""
-    for waves in (4, 16, 256, 384, 896, 4096):
+    most = {1: 896, 2: 768, 3: 384, 4: 384}
+    for waves in (4, 16, 256, 384, 385, 512, 768, 769, 896, 897, 4096):
         for units in (1, 100, 30720, 1 << 22, 1 << 36):
-            for nsrc in (1, 2, 4, 5, 16):
-                for mean in (10_000, 1 << 18, 1 << 30):
+            for nsrc in (1, 2, 3, 4, 5, 16):
+                for mean in (10_000, (1 << 18) - 1, 1 << 18, 1 << 30):
                     n = grid.run(units, waves, nsrc, mean)
                     assert n == 1 or (2 <= n <= 16 and n * 8 * waves <= units)
-                    if nsrc > 4 or waves > (896 if nsrc == 1 else 384) or mean < 1 << 18:
+                    if nsrc > 4 or waves > most[nsrc] or mean < 1 << 18:
                         assert n == 1
+                    elif units == 1 << 36:
+                        assert n == 16
     assert grid.run(30720, 16, 1, 1 << 20) == 16 and grid.run(30720, 512, 1, 1 << 20) == 7
+
+
+def test_waves_that_share_a_compute_unit(grid):
+    """As swept, the more sources the fewer; and LDS for no more of them, in blocks as the device hands it out."""
+    swept = [24, 32, 24, 16, 15, 14, 13, 12, 12, 11, 11, 10, 9, 9, 8, 8]
+    assert [grid.crowd_waves(k, 1 << 20, False) for k in range(1, 17)] == swept
+    assert [grid.crowd_waves(k, (1 << 20) - 1, False) for k in range(1, 17)] == [24, 28] + swept[2:]
+    assert [grid.crowd_waves(k, 65535, False) for k in (1, 2, 3)] == [32, 28, 24]
+    assert [grid.crowd_waves(k, 1 << 16, True) for k in (1, 2, 3, 8)] == [32, 28, 24, 12]
+    assert grid.crowd_lds(32) == 0
+    for waves in {28, *swept} - {32}:
+        asked = grid.crowd_lds(waves)
+        assert asked <= 64 << 10 and waves - 3 <= (160 << 10) // (-(-asked // 1280) * 1280) <= waves
 
 
 @pytest.mark.parametrize("kib", [1, 2])
