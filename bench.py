@@ -889,7 +889,7 @@ def encode_kernel(k: int, burst_stats, polls: int) -> str:
 def measured_traffic(cfg: int, kernel: str):
     """(HBM bytes per launch of the encode kernel, the tracked file they come from): FETCH_SIZE and
     WRITE_SIZE of a committed rocprofv3 counter run, each scaled by a copy of known size.  A
-    calibrated figure from an earlier run of the same command, not measured by this run.
+    calibrated figure from an earlier run at the same sizes, not measured by this run.
     (None, None) if no such profile exists for this configuration and the kernel that ran."""
     name = f"config{cfg}_kernels_hbm_traffic.txt"
     try:
@@ -899,7 +899,7 @@ def measured_traffic(cfg: int, kernel: str):
                 key, _, val = line.partition("=")
                 kv[key.strip()] = val.strip()
         if int(kv.get("traffic_config", -1)) == cfg and kv.get("traffic_kernel") == kernel:
-            return int(kv["traffic_bytes"]), f"profiles/{name} (rocprofv3 --pmc run of this command)"
+            return int(kv["traffic_bytes"]), f"profiles/{name} (rocprofv3 --pmc)"
     except (OSError, ValueError, KeyError):
         pass
     return None, None
