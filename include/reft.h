@@ -77,11 +77,12 @@ typedef void *reft_stream;
  * out               receives the plan; destroy it with reft_plan_destroy.
  * Allocates on the current GPU everything the data-moving calls will need: the device tables, the
  * events, the burst kernels' counters, the piece lists of the staged transport for the whole
- * stream, and a cache for the callers' pointer arrays (72 rows of T pointers, pinned host mirror
- * and device copy).  A call that passes pointers the cache already holds uploads nothing; up to
- * 32 tables are kept, each remembering the streams (up to 4) that last read it, and a new table
- * takes the room of the oldest ones after waiting for exactly those readers.  Up to 39 of the 72 rows
- * belong to the null stream once calls on it have read tables there; other streams keep the rest.
+ * stream, and a cache for the callers' pointer arrays (105 rows of T pointers, 72 from 65,536
+ * spans on; pinned host mirror and device copy).  A call that passes pointers the cache already
+ * holds uploads nothing; up to 32 tables are kept, each remembering the streams (up to 4) that last
+ * read it, and a new table takes the room of the oldest ones after waiting for exactly those
+ * readers.  What calls on the null stream have read in all but the last 33 rows stays that
+ * stream's; other streams use the rest.
  * Errors: REFT_EINVAL (null out/span_nbytes, T == 0, a zero-length bucket), REFT_ESIZE (bucket
  * lengths do not sum to L), REFT_EHIP.
  */

@@ -167,8 +167,13 @@ extern "C" const char *reft_version(void) { return "libreft 0.1 (gfx950)"; }
 namespace {
 constexpr int kRing = 32;       // pointer tables the plan's cache holds at once
 constexpr int kUsers = 4;       // streams per cached table whose most recent use is tracked
-constexpr uint32_t kRingRows = 72;  // capacity of the cache, in rows of T pointers (>= 2 * (REFT_MAX_K + 1))
-constexpr uint32_t kNullRows = kRingRows - (REFT_MAX_K + 1);  // see null_end
+// Capacity of the cache, in rows of T pointers: kCacheRows for the null stream's tables and kSideRows, enough for the widest
+// table, that these leave to other streams (see null_end).  Of many spans there are kCacheRows in all, those for the null
+// stream among them, and its tables may lie in the others as well (where a call on 65,536 spans leaves an event, 2 us,
+// it has spent more than ten times that on comparing pointers).
+constexpr uint32_t kCacheRows = 72, kSideRows = REFT_MAX_K + 1;
+constexpr uint64_t kManySpans = 65536;
+static_assert(kCacheRows >= 2 * kSideRows, "the widest table must fit on either side");
 constexpr int kMaxSlots = 64;   // staging slots used by the staged bucket pipelines
 constexpr int kGroups = 2;      // the slots form two groups that alternate (double buffering)
 constexpr uint32_t kCtrBlocks = 8;  // burst launches that may be in flight on one ring of counters
@@ -247,10 +252,11 @@ struct reft_plan {
     // handed out front to back, and the tables that currently live in it
     uint64_t ring_cap = 0, ring_head = 0, ring_tick = 0;
     // Room below null_end is left to the null stream: kernels on it may have read tables there without an event
-    // behind them, so that only what comes behind them on that stream may overwrite that room.  It ends within the first
-    // kNullRows rows; the others, enough for the widest table, are everyone's, and there each reader leaves its event.
-    // (4 x 0.9 MB encoded call after call 6.6 us with an event behind each, 4.4 without; 4 x 14.7 MB 13.9, 12.85.)
-    uint64_t null_end = 0;
+    // behind them, so that only what comes behind them on that stream may overwrite that room.  The null stream's tables
+    // lie in the first null_cap pointers' room as far as null_most allows; the rest is other streams' in any case, and
+    // there each reader leaves its event.  (4 x 0.9 MB encoded call after call 6.6 us with an event behind each, 4.4
+    // without; 4 x 14.7 MB 13.9, 12.85.)
+    uint64_t null_end = 0, null_cap = 0, null_most = 0;
     uint64_t *h_ptr = nullptr;
     uint64_t *d_ptr = nullptr;
     PtrEntry ring[kRing];
@@ -461,8 +467,9 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
                        const uint64_t **dev_tab, int *entry)
 {
     static_assert(sizeof(void *) == sizeof(uint64_t), "pointers are 64-bit");
-    const uint64_t n = (uint64_t)rows * p->T, least = s == nullptr ? 0 : p->null_end;
-    if (n > p->ring_cap - least)
+    const uint64_t n = (uint64_t)rows * p->T;
+    const uint64_t least = s == nullptr ? 0 : p->null_end, most = s == nullptr ? p->null_most : p->ring_cap;
+    if (n > most - least)
         return fail(REFT_ESIZE, "pointer table of %u rows exceeds the plan's cache (%llu pointers)",
                     rows, (unsigned long long)p->ring_cap);
     const uint64_t h = hash_ptrs(ptrs, n);
@@ -479,7 +486,7 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
             return REFT_OK;
         }
     }
-    const uint64_t pos = p->ring_head + n > p->ring_cap || p->ring_head < least ? least : p->ring_head;
+    const uint64_t pos = p->ring_head + n > most || p->ring_head < least ? least : p->ring_head;
     int slot = -1;
     for (int i = 0; i < kRing; ++i) {
         PtrEntry &e = p->ring[i];
@@ -516,7 +523,7 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
 static int release_ptrs(reft_plan *p, int entry, hipStream_t s)
 {
     PtrEntry &e = p->ring[entry];
-    if (s == nullptr && e.pos + e.len <= (uint64_t)kNullRows * p->T) {
+    if (s == nullptr && e.pos + e.len <= p->null_cap) {
         if (p->null_end < e.pos + e.len) p->null_end = e.pos + e.len;
         return REFT_OK;
     }
@@ -682,7 +689,9 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     const size_t at_unit_span = behind(at_tile_span, burst_tiles * sizeof(uint32_t));
     const size_t at_ctr = behind(at_unit_span, (nblocks + 3) * sizeof(uint32_t));
     const size_t at_ptr = behind(at_ctr, kCtrBlocks * kBurstCtrBytes);
-    p->ring_cap = (uint64_t)kRingRows * T;
+    p->ring_cap = (T < kManySpans ? kCacheRows + kSideRows : kCacheRows) * T;
+    p->null_cap = p->ring_cap - kSideRows * T;
+    p->null_most = T < kManySpans ? p->null_cap : p->ring_cap;
     HIPCHK(hipHostMalloc((void **)&p->h_ptr, p->ring_cap * sizeof(uint64_t), hipHostMallocDefault));
     // Made in the pinned mirror of the pool, which is not in use yet, where they fit (256 spans of 60 KB: 91 us for all of
     // this function from other memory, 66 so).  Gaps are not read.

@@ -7,6 +7,7 @@ import os
 import random
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -203,13 +204,15 @@ class Calls:
     """A plan and calls on it; set `i` of pointers differs from every other set."""
 
     def __init__(self, lib, sizes=SIZES):
-        self.lib, self.plan = lib, ctypes.c_void_p()
+        self.lib, self.plan, self.spans = lib, ctypes.c_void_p(), len(sizes)
         lib.sim_end()
         sizes = (ctypes.c_uint64 * len(sizes))(*sizes)
         assert lib.reft_plan_create(sizes, len(sizes), None, 0, 0, ctypes.byref(self.plan)) == 0, lib.reft_last_error()
 
     def pointers(self, rows, i):
-        return (ctypes.c_void_p * (rows * T))(*[(1 << 44) + (i << 32) + (r << 24) + (t << 21) for r in range(rows) for t in range(T)])
+        row = np.zeros((rows, self.spans), np.uint64)      # (empty spans have null pointers)
+        row[:, :T] = (1 << 44) + (i << 32) + (np.arange(rows)[:, None] << 24) + (np.arange(T) << 21)
+        return (ctypes.c_void_p * row.size).from_buffer(row)
 
     def rows(self, n, i, stream):
         """A call whose table has n rows: a pack, an encode of n shards or, from 34 on, a decode of n - 33 into tensors."""
@@ -252,26 +255,35 @@ def test_the_oldest_of_many_tables_gives_up_its_slot(lib):
 
 
 def test_a_known_table_on_the_null_stream_records_nothing(lib):
+    """However many tables there are room for (72 rows), and whatever other streams do in between."""
     c = Calls(lib)
-    for n in (1, 8, 33 + 8):
+    mine = (1, 8, 33 + 8, 16, 32, 33 + 4)
+    for n in mine:
         c.rows(n, n, None)
     before = lib.sim_events()
     for _ in range(5):
-        for n in (1, 8, 33 + 8):
+        for n in mine:
             c.rows(n, n, None)
+    assert lib.sim_events() == before
+    for i in range(20):
+        c.rows(16, 50 + i, 1)
+    before = lib.sim_events()
+    for n in mine:
+        c.rows(n, n, None)
     assert lib.sim_events() == before
     c.end()
 
 
-@pytest.mark.parametrize("null", [0.0, 0.2, 0.5, 0.9])
+@pytest.mark.parametrize("spans", [T, 65_536])
+@pytest.mark.parametrize("null", [0.0, 0.2, 0.5, 0.9, 1.0])
 @pytest.mark.parametrize("seed", [1, 2, 3])
-def test_calls_of_all_sizes_on_three_streams(lib, seed, null):
+def test_calls_of_all_sizes_on_three_streams(lib, seed, null, spans):
     """The widest tables (32 rows) among them, old and new pointers, a second phase on side streams alone."""
     rng = random.Random(seed)
-    c = Calls(lib)
-    for step in range(600):
+    c = Calls(lib, SIZES + [0] * (spans - T))
+    for step in range(600 if spans == T else 60):
         n = rng.choice((1, 1, 1, 2, 4, 8, 8, 16, 32, 33 + 4, 33 + 8, 33 + 31))
-        stream = None if step < 500 and rng.random() < null else rng.choice((1, 2))
+        stream = None if step < (500 if spans == T else 50) and rng.random() < null else rng.choice((1, 2))
         c.rows(n, rng.choice((n, n, rng.randrange(50), 1000 + step)), stream)
     c.end()
 
