@@ -25,26 +25,31 @@ constexpr uint64_t units_of(uint64_t span_bytes, uint64_t head, uint64_t unit = 
     return span_bytes == 0 ? 0 : span_bytes <= head ? 1 : 1 + (span_bytes - head + unit - 1) / unit;
 }
 
-// At 700 bytes a span both kinds of units are as fast (parity of 8 x 70 MB 123 us), below the small ones win (see
-// k_stream_small).  At 512 their numbers stay below 4 per span, so that each has its entry in the look-up table.
+// At 700 bytes a span small units are better with few sources and worse with many (us, kUnit / kSmallUnit: packed 33.3 /
+// 26.0, parity of 3 60 / 50, of 8 123 / 127, with the packed stream 133 / 143), below they win (k_stream_small).  At 512
+// their numbers stay below 4 per span, so that each has its entry in the look-up table.
 constexpr uint64_t kSmallMeanSpan = 512;
-constexpr uint64_t unit_bytes(uint64_t L, uint64_t T) { return L / T < kSmallMeanSpan && T < (1u << 29) ? kSmallUnit : kUnit; }
+constexpr uint64_t unit_bytes(uint64_t L, uint64_t T)
+{
+    return L / T < kSmallMeanSpan && T < (1u << 29) ? kSmallUnit : kUnit;
+}
 
 // In streams of long spans (64 KiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
-// their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie in
-// memory in order, an XCD then keeps to the same address bits from span to span (unit_of_wave, which is taken in these
-// streams alone).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few waves
-// look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256 KiB modulo 8, that is
-// for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain order / spread / on the grid
-// modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x 2030 / 1889 / 1825 / 1815; of
-// 300 KB, 8 x 961 / 952 / 969 / 929, 12 x 1420 / 1384 / 1397 / 1356, 16 with the packed stream 2087 / 2015 / 2037 / 1983; a rotated
-// unit and decode, 16 x 842 MB in pieces of 1.3 MB, 2481 spread, 2406 on the grid.  In other streams one more piece per
-// span would cost more, and the spans' places have little to do with the units' numbers (8 x 132 MB in spans of 10 KB
-// 204.6 us in plain order, 206.2 spread).
-constexpr uint64_t kGridMeanSpan = 64 * 1024, kWideMeanSpan = 256 * 1024;
+// their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie
+// in memory in order, an XCD then keeps to the same address bits from span to span (unit_of_wave, which is taken in
+// these streams alone).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few
+// waves look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256 KiB modulo 8, that
+// is for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain order / spread /
+// on the grid modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x 2030 / 1889 /
+// 1825 / 1815; of 300 KB, 8 x 961 / 952 / 969 / 929, 12 x 1420 / 1384 / 1397 / 1356, 16 with the packed stream 2087 / 2015
+// / 2037 / 1983; a rotated unit and decode, 16 x 842 MB in pieces of 1.3 MB, 2481 spread, 2406 on the grid.  In other
+// streams one more piece per span would cost more, and the spans' places have little to do with the units' numbers (8 x
+// 132 MB in spans of 10 KB 204.6 us in plain order, 206.2 spread); and below 5 MiB no launch of 16 sources and two
+// results at most leaves the cache, so that none would spread them (2 MB in spans of 300 KB 2.9 us, 3.1 on the grid).
+constexpr uint64_t kGridMeanSpan = 64 * 1024, kWideMeanSpan = 256 * 1024, kGridMinBytes = 5 << 20;
 constexpr uint32_t align_of(uint64_t L, uint64_t T)
 {
-    return L / T >= kWideMeanSpan ? 31 : L / T >= kGridMeanSpan ? 7 : 0;
+    return L < kGridMinBytes || L / T < kGridMeanSpan ? 0 : L / T < kWideMeanSpan ? 7 : 31;
 }
 constexpr uint32_t grid_of(uint64_t L, uint64_t T) { return align_of(L, T) ? (uint32_t)kUnit - 1 : 0; }
 constexpr uint64_t head_of(uint64_t off, uint64_t grid, uint64_t unit = kUnit) { return unit - (off & grid); }
@@ -67,7 +72,10 @@ constexpr Piece piece_of(uint64_t j, uint64_t head, uint32_t lead, int64_t lo, i
 }
 
 // The first and the last of a span's units that may move its byte r, whatever its lead.
-constexpr uint64_t last_unit_at(uint64_t r, uint64_t head, uint64_t unit = kUnit) { return r < head ? 0 : 1 + (r - head) / unit; }
+constexpr uint64_t last_unit_at(uint64_t r, uint64_t head, uint64_t unit = kUnit)
+{
+    return r < head ? 0 : 1 + (r - head) / unit;
+}
 constexpr uint64_t first_unit_at(uint64_t r, uint64_t head, uint64_t unit = kUnit)
 {
     return last_unit_at(r < kMaxLead ? 0 : r - (kMaxLead - 1), head, unit);
@@ -136,11 +144,12 @@ inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
 }
 
 // "burst_min_rows" and "burst_min_bytes" where the caller has not set them, for the kernels over span tables.  Since its
-// units lie in the order of unit_of_wave the stream kernel is as good or better up to about 12 GB a row.  Parity, burst /
-// stream kernel: 8 rows of 3.1 GB 4290 / 4172 us and, in other memory, 4319 / 4265, 7 of 3.1 GB 3958 / 3893; TB/s, 8
-// rows of 11.4 GB 6.38 / 6.41, 11.8 GB 6.63 / 6.74 and 6.12 / 6.08, 15.0 GB 6.26 / 6.17, 15.4 GB 6.15 / 6.07 and 6.35 /
-// 6.21.  Into tensors (from four times the bytes on, so in practice never): 8 rows of 11.4 to 15.4 GB 6.18 / 6.19, 6.49 /
-// 6.50, 6.11 / 6.13, 6.27 / 6.22.
+// units lie in the order of unit_of_wave the stream kernel is as good or better up to about 12 GB a row.  Time of the
+// burst kernel over the stream kernel's, in turn in one process, four places of memory each: parity of 8 rows of 3.1 GB
+// 1.03, 1.01, 7 of 3.1 GB 1.02; 8 of 11.8 GB 1.025, 1.011, 1.000, 1.003, of 11.4 GB 0.999, 1.006, 0.996, 0.998, of 15.0 GB
+// 1.001, 0.993, 0.998, 0.991, of 15.4 GB 1.003, 0.996, 0.994, 0.997; 7 of 11.8 GB 1.028 to 1.005, of 15.0 GB 1.004, 1.000,
+// 0.998, 0.996, of 15.4 GB 1.010, 0.999, 0.993, 0.997.  Into tensors, 7 and 8 rows of 11.4 to 15.4 GB, 1.002 to 1.024 (so
+// only from four times the bytes on, more than the memory holds).
 constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 13ull << 30;
 
 // The same two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes

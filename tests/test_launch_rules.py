@@ -167,10 +167,11 @@ def test_every_unit_has_one_wave(grid, kib):
 def test_units_that_are_spread_have_the_numbers_of_their_kib(grid, mean):
     """From a mean of 64 KiB on, where a launch spreads them: modulo 8, from 256 KiB on modulo the 32 KiB inside which they
     change places."""
-    sizes = [mean + (-1) ** i * (7 * i % 61) * 100 for i in range(64)]
-    sizes[-1] += 64 * mean - sum(sizes)
+    sizes = [mean + (-1) ** i * (7 * i % 61) * 100 for i in range(96)]
+    sizes[-1] += 96 * mean - sum(sizes)
     mask, align = grid.grid_of(sum(sizes), len(sizes)), grid.align_of(sum(sizes), len(sizes))
-    assert mask == 1023 and grid.grid_of(64 * 65536 - 1, 64) == 0 and align == (31 if mean >= 1 << 18 else 7)
+    assert mask == 1023 and grid.grid_of(96 * 65536 - 1, 96) == 0 and align == (31 if mean >= 1 << 18 else 7)
+    assert grid.align_of((5 << 20) - 1, 2) == grid.grid_of((5 << 20) - 1, 2) == 0 and grid.align_of(5 << 20, 2) == 31
     off = number = 0
     for n in sizes:
         number = grid.first_number(number, off, align)
