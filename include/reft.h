@@ -398,7 +398,8 @@ int reft_restore_wait(reft_plan *plan);
  *                  ordinary XOR kernels, 16 workgroups per compute unit in the others.  A small cap
  *                  keeps a snapshot kernel on few compute units while training kernels run beside it.
  *   "nontemporal"  1 = streaming (non-temporal) loads and stores in the kernels, 0 = plain.  (Launches
- *                  whose traffic fits the cache, up to 96 MiB, use plain ones with either.)
+ *                  whose traffic fits the cache, up to 96 MiB, and streams of spans of fewer than 512
+ *                  bytes on average use plain ones with either.)
  *   "unroll"       16-byte chunks in flight per thread and source, at most: 1, 2 or 4.  The pack,
  *                  unpack and ordinary XOR kernels take fewer where that is faster.
  *   "link_wgs"     cap on workgroups of kernels bound by the host link (default 32; kernels
@@ -430,8 +431,8 @@ int reft_restore_wait(reft_plan *plan);
  *                  goes into tensors), at most one tile in eight dense in small spans (see
  *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
  *                  alike (mod 16) relative to its stream offset.  reft_reconstruct goes by the same
- *                  two values where they are set, and at their defaults uses the variant from 5
- *                  sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader
+ *                  two values where they are set, and at their defaults (7 and 13 GiB exactly) uses
+ *                  the variant from 5 sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader
  *                  waves XOR "burst_stage_bytes" (default 32768; a multiple of 4096, at most 65536)
  *                  of the stream at a time into LDS, and one writer wave per workgroup stores the
  *                  previous stage once all workgroups of the (persistent, "burst_wgs_per_cu" per
