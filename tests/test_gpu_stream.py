@@ -228,6 +228,39 @@ def test_tiny_spans_in_place(dev, k, max_wgs):
         reft.reft_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("k", [3, 17])
+def test_tiny_spans_captured(dev, k):
+    """The call that allocates nothing, in a graph replayed over changed contents."""
+    rng = np.random.default_rng(k)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(k)
+    sizes = tiny_sizes(rng, 400, 400)
+    held = [arena(sizes, rng.integers(0, 16, len(sizes)), dev, gen) for _ in range(k)]
+    spans = [t for h in held for t in h[1]]
+    out = torch.empty(sum(sizes), dtype=torch.uint8, device=dev)
+    plan = reft.reft_plan_create(sizes)
+    try:
+        s = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        reft.reft_parity_encode_noalloc(plan, spans, k, out, s)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            reft.reft_parity_encode_noalloc(plan, spans, k, out, torch.cuda.current_stream())
+        for rep in range(3):
+            held[rep][0].add_(rep + 1)
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            want = oracle.encode([oracle.pack([oracle.as_bytes(t.cpu()) for t in h[1]]) for h in held])
+            assert np.array_equal(out.cpu().numpy(), want), rep
+        del graph
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)
+
+
 # one launch below and one above the traffic at which the launch changes, for every number of
 # sources whose rule differs, with short and with long spans
 @pytest.mark.parametrize("k", [1, 2, 3, 6, 8])
