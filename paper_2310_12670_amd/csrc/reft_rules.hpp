@@ -36,8 +36,8 @@ constexpr uint64_t unit_bytes(uint64_t L, uint64_t T)
 
 // In streams of long spans (64 KiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
 // their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie
-// in memory in order, an XCD then keeps to the same address bits from span to span (unit_of_wave, which is taken in
-// these streams alone).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few
+// in memory in order, an XCD then keeps to the same address bits from span to span (see unit_of_wave; where they do not,
+// turn_of sees to it inside each span).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few
 // waves look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256 KiB modulo 8, that
 // is for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain order / spread /
 // on the grid modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x 2030 / 1889 /
@@ -60,8 +60,9 @@ constexpr uint64_t first_number(uint64_t least, uint64_t off, uint64_t align)
 
 // Unit j of a span moves its bytes [s, t), none if s >= t, as far as they lie in [lo, hi), which may reach below 0 or
 // lie behind the span.  All units but the first start `lead` (below kMaxLead) bytes later than they otherwise would,
-// the first moves those bytes as well.
-constexpr uint32_t kMaxLead = 128;
+// the first moves those bytes as well.  Launches that spread their units move them to the KiB of the addresses, others,
+// where the first unit's wave should not take twice as long as the rest, to the cache lines.
+constexpr uint32_t kMaxLead = 1024, kLineLead = 128;
 struct Piece {
     int64_t s, t;
 };
@@ -100,6 +101,35 @@ constexpr uint64_t unit_of_wave(uint64_t w, uint64_t n)
     if ((w | 31) >= n) return w;
     if (U == 1) return (w & ~28ull) | (w >> 1 & 12) | (w & 4) << 2;
     return (w & ~12ull) | (w >> 1 & 4) | (w & 4) << 1;
+}
+
+// How far the units of a span are turned where steps are dealt in one of these orders: number x of the span (from 0) moves
+// its unit x + turn, and behind the last one the first ones follow.  `number` is that of x = 0, `kib` the KiB of memory in
+// which unit 0 would begin were it whole.  So a unit's number is its KiB's modulo 32 whatever the span's place in the stream,
+// and an XCD keeps to its address bits.  In streams of odd sizes the numbers had nothing to do with the addresses: us,
+// before and so, with the lead up to a whole KiB, in spans of 200 KB (log-uniform 50 : 65536) decode of 8 x 0.5 GB 741 / 707,
+// of 4 409 / 400, parity of 8 754 / 743, copies 325 / 322; 1024 spans of 64 to 128 KiB, decode of 8 x 0.2 GB 341 / 337.
+// Where the tensors lie in order already: 4139 / 4143 (8 x 3.1 GB), in shuffled order 3489 / 3463 (decode of 8 x 2.5 GB).
+constexpr uint32_t kTurned = 32;                 // spans of as many units or fewer are not turned
+constexpr uint32_t turn_of(uint64_t number, uint64_t kib) { return (uint32_t)(number - kib) & (kTurned - 1); }
+
+// The unit from which on a step of U units is moved whose numbers u .. u + U - 1 are all of the span with the numbers u0 ..
+// u1 - 1.  Whole steps change places among themselves (and turn by an even number where U is 2).
+template <uint32_t U>
+constexpr uint64_t turned(uint64_t u, uint64_t u0, uint64_t u1, uint32_t turn)
+{
+    const uint64_t first = (u0 + U - 1) / U * U, units = (u1 - first) / U * U;
+    u += turn / U * U;
+    return u < first + units ? u : u - units;
+}
+
+// Whether a launch that streams (see kCachedTraffic) deals its steps to waves in the order of unit_of_wave.  In spans
+// below 20 KiB on average the numbers of units mean too little (4 KB: 0 to +2 %, 7 KB 0 %, 14 KB -1 to +1 %, 28 KB -2 to -4 %),
+// and copies, two units a wave, gain from 32 KiB on only (14 KB +1 %, 43 KB -2 %).
+constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024;
+constexpr bool spread_of(uint32_t nsrc, uint64_t mean_span, bool packed)
+{
+    return mean_span >= (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan);
 }
 
 // LDS for one-wave workgroups to ask for, which they do not use, so that no more of them share a compute unit than its

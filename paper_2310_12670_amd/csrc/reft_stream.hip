@@ -100,6 +100,7 @@ struct Span {
     int64_t lo, hi;          // its bytes in the range, from its first one on (lo may lie below 0)
     uint64_t s[K], d, d2;    // where its first byte lies in the sources, the destination and the packed stream
     uint32_t head, lead;     // see piece_of
+    uint32_t turn;           // see turn_of (0 where some of the span is not in the range)
 };
 
 // Span i, everything in one go (what the last source and the destination have no table for comes from another one
@@ -108,7 +109,7 @@ struct Span {
 // The lead: a span's units lie so that the first source, and with it those that are aligned like it, is read in
 // whole cache lines, or, where it stands (nearly) alone, the destination is written in such.  (Shards of tensors at
 // odd stream offsets are aligned alike: 8 x 56 MB encoded in 87 instead of 108 us.)
-template <int K>
+template <int K, bool SPREAD>
 __device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
 {
     Span<K> o;
@@ -130,7 +131,10 @@ __device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
     uint32_t alike = 0;
 #pragma unroll
     for (int j = 1; j < K; ++j) alike += (((uint32_t)o.s[j] ^ (uint32_t)o.s[0]) & 15u) == 0;
-    o.lead = (uint32_t)(0 - (2 * alike >= K ? o.s[0] : o.d) - o.head) & (kMaxLead - 1);
+    const uint64_t ref = (2 * alike >= K ? o.s[0] : o.d) + o.head;
+    const bool wide = SPREAD && a.spread && o.u1 - o.u0 > kTurned;
+    o.lead = (uint32_t)(0 - ref) & ((wide ? kMaxLead : kLineLead) - 1);
+    o.turn = wide && b >= a.range.lo && e <= a.range.hi ? turn_of(o.u0, (ref + o.lead - kUnit) / kUnit) : 0;
     return o;
 }
 
@@ -334,7 +338,10 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
 // another.  126 MB in spans of 3 MB by 4 / 16 / 64 workgroups, us, without and with: packed 1869 / 479 / 134
 // and 1186 / 315 / 102 (tiles walked by workgroups: 1620 / 432 / 145), parity of 4: 3563 / 906 / 247 and
 // 2593 / 677 / 196 (3168 / 817 / 253).
-template <int K, int U, bool NT, Form F = kPlain>
+//
+// SPREAD: for launches that may deal their steps in an order other than a.first_step, a.first_step + 1, ...  (Where short
+// spans are copied, what the kernel would have to ask and to work out for that costs 1 to 6 %.)
+template <int K, int U, bool NT, Form F = kPlain, bool SPREAD = false>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
     const uint32_t lane = threadIdx.x & 63;
@@ -349,16 +356,21 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
     for (uint64_t w = ((uint64_t)blockIdx.x * a.waves + wave) * (F == kRuns ? a.run : 1); w < a.nsteps;
          w += F != kRuns ? a.stride : (left -= done) ? done : done + (a.stride - 1) * (left = a.run)) {
         // streaming launches only: the few instructions more delay a short one by 0.2 us
-        const uint64_t step = NT && F != kRuns && U <= 2 && a.spread ? unit_of_wave<U>(w, a.nsteps) : w;
+        const uint64_t step = SPREAD && a.spread ? unit_of_wave<U>(w, a.nsteps) : w;
         uint64_t u = (a.first_step + step) * U;
         if (U > 1 && u < a.range.first) u = a.range.first;
         uint64_t end = (a.first_step + step + 1) * U;
         if (U > 1 && end > a.range.last + 1) end = a.range.last + 1;
-        Span<K> o = load_span<K>(a, span_of(a, u, lane));
+        Span<K> o = load_span<K, SPREAD>(a, span_of(a, u, lane));
+        const bool one = end - u == U && end <= o.u1;
+        if (SPREAD && one) {
+            u = turned<U>(u, o.u0, o.u1, o.turn);
+            end = u + U;
+        }
         if constexpr (U == 1 && F != kRuns) {
             move_unit<K, NT, F>(a, o, u, lane);
         } else {
-            done = end - u == U && end <= o.u1 ? move_steps<K, U, NT, F>(a, o, u, lane, left) : 0;
+            done = one ? move_steps<K, U, NT, F>(a, o, u, lane, left) : 0;
             if (done) continue;
             done = 1;
             for (;;) {
@@ -371,7 +383,7 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
                     u = part;
                 }
                 if (u == end) break;
-                o = load_span<K>(a, span_of(a, u, lane));
+                o = load_span<K, SPREAD>(a, span_of(a, u, lane));
             }
         }
     }
@@ -473,11 +485,17 @@ static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
     (cfg.nontemporal ? (cfg.unroll == 1 ? k_stream<K, 1, true> : k_stream<K, 2, true>)            \
                      : (cfg.unroll == 1 ? k_stream<K, 1, false> : k_stream<K, 2, false>))
 
-#define REFT_PICK_PACK(K) (cfg.nontemporal ? k_stream<K, 1, true, kPacked> : k_stream<K, 1, false, kPacked>)
+// (only one source has two units a step in a launch that spreads them)
+#define REFT_PICK_SPREAD(K)                                                                       \
+    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, true> : k_stream<K, K == 1 ? 2 : 1, true, kPlain, true>)
+
+#define REFT_PICK_PACK(K)                                                                         \
+    (a.spread ? k_stream<K, 1, true, kPacked, true>                                               \
+              : cfg.nontemporal ? k_stream<K, 1, true, kPacked> : k_stream<K, 1, false, kPacked>)
 
 #define REFT_PICK_RUNS(K) (cfg.nontemporal ? k_stream<K, 4, true, kRuns> : k_stream<K, 4, false, kRuns>)
 
-#define REFT_PICK_IN_PLACE(K) k_stream<K, 1, true, kInPlace>
+#define REFT_PICK_IN_PLACE(K) k_stream<K, 1, true, kInPlace, true>
 
 #define REFT_PICK_SMALL(K) (two ? k_stream_small<K, 2> : k_stream_small<K, 1>)
 
@@ -537,6 +555,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     if (form == kPacked || form == kInPlace) cfg.unroll = 1;
     a.first_step = a.range.first / cfg.unroll;
     a.nsteps = a.range.last / cfg.unroll - a.first_step + 1;
+    const uint64_t mean = pt.L / pt.T;
     const uint32_t waves = cached || cfg.capped ? 4 : 1;
     a.off = pt.off;
     a.unit_off = pt.unit_off;
@@ -550,13 +569,20 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.dest_row = dtab ? dtab : pt.unit_off;
     if (pt.unit == kSmallUnit) return launch_small(a, nsrc, form, cfg, stream);
     a.run = 1;
-    a.spread = waves == 1 && a.first_step % 32 == 0 && pt.grid;
+    a.spread = waves == 1 && cfg.nontemporal && a.first_step % 32 == 0 && spread_of(nsrc, mean, form == kPacked);
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
-        a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, pt.L / pt.T);
+        a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, mean);
         if (a.run > 1) form = kRuns;
     }
     switch (form) {
     case kPlain:
+        if (a.spread) {
+            switch (nsrc) {
+                REFT_CASES_4(REFT_PICK_SPREAD) REFT_CASES_5_8(REFT_PICK_SPREAD) REFT_CASES_9_16(REFT_PICK_SPREAD)
+            default: return hipErrorInvalidValue;
+            }
+            break;
+        }
         switch (nsrc) {
             REFT_CASES_9_16(REFT_PICK_MANY)
         default: REFT_PICK_K(k_stream, fn, nsrc)
@@ -585,7 +611,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     const uint32_t g = stream_grid((a.nsteps + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
     a.waves = waves;
     a.stride = (uint64_t)g * waves;
-    const uint32_t lds = waves == 1 ? crowd_lds(crowd_waves((uint32_t)nsrc, pt.L / pt.T, form == kPacked)) : 0;
+    const uint32_t lds = waves == 1 ? crowd_lds(crowd_waves((uint32_t)nsrc, mean, form == kPacked)) : 0;
     hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), lds, stream, a);
     return hipGetLastError();
 }

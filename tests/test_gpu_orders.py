@@ -1,0 +1,67 @@
+"""GPU parity of launches that deal their units in another order than the stream's (more traffic than the cache holds, spans of
+20 KiB and more on average): spans of about the units that are turned, odd sizes and such as the tensors' alignment, every
+call over span tables, and windows of other members' streams.  Bytes: equal to the oracle or wrong."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_12670_amd as reft
+from test_gpu_rotated import check_rotated
+from test_gpu_stream import arena, check_all, dev, stream_kernel_only  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+TRAFFIC = 110 << 20
+
+
+def sizes_of(kib, total, odd, seed):
+    """Spans of a few bytes to either side of 31 to 35 KiB and of 63 to 66, or of `kib` KiB on average, a few small ones between."""
+    rng = np.random.default_rng(seed)
+    sizes = []
+    while sum(sizes) < total:
+        if kib == 0:
+            sizes.append(int(rng.choice([31, 32, 33, 34, 35, 63, 64, 65, 66])) * 1024 + (int(rng.integers(-17, 18)) if odd else 0))
+        else:
+            n = int(rng.integers(kib * 512, kib * 1536))
+            sizes.append(n | 1 if odd else n // 512 * 512)
+        if len(sizes) % 50 == 0:
+            sizes += [0, 5 if odd else 512]
+    return sizes
+
+
+@pytest.mark.parametrize("odd", [True, False])
+@pytest.mark.parametrize("kib", [0, 21, 70])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 8, 9, 13, 16])
+def test_every_call(dev, k, kib, odd):  # noqa: F811
+    check_all(dev, sizes_of(kib, TRAFFIC // (k + 1), odd, k), k, None, seed=k + kib, align=1 if odd else 16)
+
+
+@pytest.mark.parametrize("odd", [True, False])
+@pytest.mark.parametrize("k", [3, 8, 14, 16])
+def test_windows(dev, k, odd):  # noqa: F811
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(k)
+    # the decode's k - 1 rows and result are what leaves the cache, the unit's k - 1 windows are a part of that
+    sizes = sizes_of(300, TRAFFIC // k, odd, k)
+    shards = [arena(sizes, [0] * len(sizes), dev, gen)[1] for _ in range(k)]
+    check_rotated(dev, shards, sizes, losts=[0, k - 1])
+
+
+@pytest.mark.parametrize("odd", [True, False])
+@pytest.mark.parametrize("k", [2, 3, 4, 9])
+def test_in_place(dev, k, odd):  # noqa: F811
+    """The lost shard decoded over the parity: every byte read and written once."""
+    sizes = sizes_of(70, TRAFFIC // (k + 1), odd, k)
+    off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(k)
+    shards = [arena(sizes, [0] * len(sizes), dev, gen)[1] for _ in range(k)]
+    plan = reft.reft_plan_create(sizes)
+    try:
+        par = torch.empty(off[-1], dtype=torch.uint8, device=dev)
+        reft.reft_parity_encode(plan, [t for sh in shards for t in sh], k, par)
+        rows = [None if s == 1 else t for s, sh in enumerate(shards) for t in sh]
+        reft.reft_reconstruct_spans(plan, rows, k, 1, par, [par[a:b] for a, b in zip(off, off[1:])])
+        torch.cuda.synchronize()
+        assert torch.equal(par, torch.cat(shards[1]))
+    finally:
+        reft.reft_plan_destroy(plan)
