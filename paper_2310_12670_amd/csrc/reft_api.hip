@@ -239,6 +239,7 @@ struct reft_plan {
     uint32_t unit_shift = 0;          // blocks of the device's look-up table of units
     uint32_t grid = 0;                // see head_of
     uint32_t unit = 1024;             // see unit_bytes
+    bool odd = false, windows = false;   // see PlanTables
     uint32_t burst_shift = 16;        // tiles of the burst kernel's look-up table
     uint64_t ntiles = 0;
     std::vector<uint64_t> off;        // [T+1]
@@ -298,7 +299,7 @@ struct reft_plan {
 
     PlanTables tables() const
     {
-        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid, unit};
+        return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid, unit, odd, windows};
     }
 
     // lo < hi <= L
@@ -664,15 +665,17 @@ extern "C" int reft_plan_create(const uint64_t *span_nbytes, uint64_t T,
     p->grid = grid_of(p->L, T);
     p->unit = (uint32_t)unit_bytes(p->L, T);
     p->unit_off.resize(T + 1);
-    uint64_t number = 0;
+    uint64_t number = 0, apart = 0;
     const uint64_t align = align_of(p->L, T);
     for (uint64_t t = 0; t < T; ++t) {
         const uint64_t b = p->off[t], n = p->off[t + 1] - b;
+        if (b % 64) apart += n;
         if (n) number = first_number(number, b, align);
         p->unit_off[t] = number;
         number += p->unit == kUnit ? units_of(n, head_of(b, p->grid)) : units_of(n, kSmallUnit, kSmallUnit);
     }
     p->unit_off[T] = number;
+    p->odd = odd_stream(apart, p->L);
     const uint64_t units = p->unit_off[T], most = std::min<uint64_t>(std::max<uint64_t>(16384, 4 * T), 1ull << 31);
     p->unit_shift = 0;
     while ((units >> p->unit_shift) > most) ++p->unit_shift;
@@ -1767,6 +1770,7 @@ static int derived_plan(reft_plan *p, uint64_t key, const std::vector<Segment> &
         reft_plan *d;
         ~Guard() { if (d) reft_plan_destroy(d); }
     } guard{dp.plan};
+    dp.plan->windows = true;
     dp.nwin = (uint32_t)segs[0].wins.size();
     dp.recipe.resize((size_t)dp.nwin * sizes.size());
     for (uint32_t q = 0; q < dp.nwin; ++q)

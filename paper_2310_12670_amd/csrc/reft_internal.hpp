@@ -35,6 +35,8 @@ struct PlanTables {
     uint32_t tile_shift;
     uint32_t grid;                 // see head_of
     uint32_t unit;                 // bytes of a unit (see unit_bytes)
+    bool odd;                      // see odd_stream
+    bool windows;                  // the rows are windows of streams, at different offsets
 };
 
 // Stream bytes [lo, hi) and the units first .. last that may move some of them.

@@ -103,6 +103,21 @@ constexpr uint64_t unit_of_wave(uint64_t w, uint64_t n)
     return (w & ~12ull) | (w >> 1 & 4) | (w & 4) << 1;
 }
 
+// The same for odd streams (odd_stream): neighbouring steps that share cache lines meet in one L2 every second time, as the
+// XCD keeps bits 1, 2 and 4 of the step.
+constexpr uint64_t near_step_of_wave(uint64_t w, uint64_t n)
+{
+    if ((w | 31) >= n) return w;
+    return (w & ~31ull) | (w << 1 & 6) | (w << 2 & 16) | (w >> 3 & 1) | (w >> 1 & 8);
+}
+
+// And where workgroups of two waves take neighbouring units (bit 0 of w is the wave), with the same bits the workgroup's.
+constexpr uint64_t pair_step_of_wave(uint64_t w, uint64_t n)
+{
+    if ((w | 31) >= n) return w;
+    return (w & ~24ull) | (w << 1 & 16) | (w >> 1 & 8);
+}
+
 // How far the units of a span are turned where steps are dealt in one of these orders: number x of the span (from 0) moves
 // its unit x + turn, and behind the last one the first ones follow.  `number` is that of x = 0, `kib` the KiB of memory in
 // which unit 0 would begin were it whole.  So a unit's number is its KiB's modulo 32 whatever the span's place in the stream,
@@ -123,13 +138,42 @@ constexpr uint64_t turned(uint64_t u, uint64_t u0, uint64_t u1, uint32_t turn)
     return u < first + units ? u : u - units;
 }
 
-// Whether a launch that streams (see kCachedTraffic) deals its steps to waves in the order of unit_of_wave.  In spans
-// below 20 KiB on average the numbers of units mean too little (4 KB: 0 to +2 %, 7 KB 0 %, 14 KB -1 to +1 %, 28 KB -2 to -4 %),
-// and copies, two units a wave, gain from 32 KiB on only (14 KB +1 %, 43 KB -2 %).
-constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024;
-constexpr bool spread_of(uint32_t nsrc, uint64_t mean_span, bool packed)
+// Whether a stream is odd: most of its bytes (`bytes` of L) lie in spans whose places in it are no multiples of 64 bytes,
+// which tensors' addresses are, so that the rows of a launch mostly do not lie alike.  Where a result lies otherwise than the
+// sources, neighbouring units write parts of the same 64 bytes, and where a source does, they both read its line between
+// them (8 x 132 MB in one span 187 us, the result 64 bytes off 190, 1 byte off 195, all eight sources apart 203).
+constexpr bool odd_stream(uint64_t bytes, uint64_t L) { return bytes > L / 2; }
+
+// The order in which a launch that streams (see kCachedTraffic) deals its steps to waves.
+//
+// In spans below 20 KiB on average the numbers of units mean too little (4 KB: 0 to +2 %, 7 KB 0 %, 14 KB -1 to +1 %,
+// 28 KB -2 to -4 %), and copies, two units a wave, gain from 32 KiB on only (14 KB +1 %, 43 KB -2 %).
+//
+// Odd streams: two results, or two or three sources, in pairs, a wave's neighbour in its own workgroup, so that both
+// parts of a line that they share are in the same L2 at once.  Time of kFar / kNear / pairs, in spans of 14, 43 and 200 KB and
+// 2 MB: with the packed stream, 2 sources 1 / .93 / .90, 1 / .92 / .92, 1 / .92 / .93 and 1 / .99 / .95, 5 sources 1 / .97 / .95,
+// 1 / .97 / .95, 1 / .95 / .93 and 1 / .98 / .97, 8 sources 1 / .97 / .96, .97 / .97, .98 / .98, .98 / .99, 12 sources 1 / 1 /
+// 1.06, .99 / .99, .99 / .96, .99 / .95; parity of 2 1 / 1 / .96, .95 / .97, .94 / .96, .97 / .96.  One result and more
+// sources, all alike but for the result: near, from 64 KiB and up to 12 sources (4 sources .99, .97, .98 of kFar in 43 and 200
+// KB and 2 MB, 8 .99, .98, .98, 16 1.04, 1.05, .99); alike but for one source (decodes): far (near 0 to 2 % more).  Rows that
+// are windows at any offset: near up to 12 sources (3 .98, 7 and 11 .97 to .98), of 15 neither always (.98 to 1.03).
+enum Spread : uint32_t {
+    kInOrder = 0,
+    kFar = 1,                // unit_of_wave
+    kNear = 2,               // near_step_of_wave
+    kPairs = 3,              // pair_step_of_wave
+};
+constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024, kNearMeanSpan = 64 * 1024;
+constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed)
 {
-    return mean_span >= (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan);
+    return odd && nsrc > 1 && (packed ? nsrc <= 8 || mean_span >= kSpreadMeanSpan : nsrc <= 3);
+}
+constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
+{
+    if (mean_span < (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan)) return kInOrder;
+    if (in_pairs(nsrc, mean_span, odd, packed)) return kPairs;
+    if (!odd || packed) return kFar;
+    return nsrc == 1 || (nsrc <= 12 && (windows || (!tensors && mean_span >= kNearMeanSpan))) ? kNear : kFar;
 }
 
 // LDS for one-wave workgroups to ask for, which they do not use, so that no more of them share a compute unit than its
@@ -149,6 +193,14 @@ constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
     if (nsrc == 3) return 24;
     const uint32_t some = nsrc < 12 ? 20 - nsrc : 8, many = 17 - 5 * nsrc / 8;
     return some > many ? some : many > 8 ? many : 8;
+}
+
+// The same for workgroups of two waves.  Two and three sources with the packed stream, 28, 24 and 20 waves: in spans of 14 KB
+// 350 / 345 / 365 and 426 / 427 / 425 us, of 200 KB 358 / 343 / 333 and 447 / 429 / 418; all others as above.
+constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
+{
+    if (packed && nsrc <= 3) return mean_span < kSpreadMeanSpan ? 24 : 20;
+    return crowd_waves(nsrc, mean_span, packed);
 }
 constexpr uint32_t crowd_lds(uint32_t waves) { return waves == 32 ? 0 : 160 * 1024 / waves / 512 * 512; }
 

@@ -61,7 +61,7 @@ struct StreamArgs {
     uint32_t grid;           // see head_of
     uint32_t last;           // LastRow
     uint32_t ragged;         // the destination has a row
-    uint32_t spread;         // steps in the order of unit_of_wave
+    uint32_t spread;         // Spread
     uint32_t run;            // kRuns: consecutive steps that one wave takes together
     uint32_t once, pack;     // k_stream_small: the destination is a source; with the packed stream
 };
@@ -356,7 +356,10 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
     for (uint64_t w = ((uint64_t)blockIdx.x * a.waves + wave) * (F == kRuns ? a.run : 1); w < a.nsteps;
          w += F != kRuns ? a.stride : (left -= done) ? done : done + (a.stride - 1) * (left = a.run)) {
         // streaming launches only: the few instructions more delay a short one by 0.2 us
-        const uint64_t step = SPREAD && a.spread ? unit_of_wave<U>(w, a.nsteps) : w;
+        uint64_t step = w;
+        if (SPREAD && a.spread)
+            step = a.spread == kFar ? unit_of_wave<U>(w, a.nsteps)
+                                    : a.spread == kNear ? near_step_of_wave(w, a.nsteps) : pair_step_of_wave(w, a.nsteps);
         uint64_t u = (a.first_step + step) * U;
         if (U > 1 && u < a.range.first) u = a.range.first;
         uint64_t end = (a.first_step + step + 1) * U;
@@ -556,7 +559,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.first_step = a.range.first / cfg.unroll;
     a.nsteps = a.range.last / cfg.unroll - a.first_step + 1;
     const uint64_t mean = pt.L / pt.T;
-    const uint32_t waves = cached || cfg.capped ? 4 : 1;
+    const uint32_t waves = cached || cfg.capped ? 4 : in_pairs(nsrc, mean, pt.odd, form == kPacked) ? 2 : 1;
     a.off = pt.off;
     a.unit_off = pt.unit_off;
     a.unit_span = pt.unit_span;
@@ -569,7 +572,8 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.dest_row = dtab ? dtab : pt.unit_off;
     if (pt.unit == kSmallUnit) return launch_small(a, nsrc, form, cfg, stream);
     a.run = 1;
-    a.spread = waves == 1 && cfg.nontemporal && a.first_step % 32 == 0 && spread_of(nsrc, mean, form == kPacked);
+    a.spread = waves == 4 || !cfg.nontemporal || a.first_step % 32
+                   ? kInOrder : spread_of(nsrc, mean, pt.odd, form == kPacked, a.ragged, pt.windows);
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
         a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, mean);
         if (a.run > 1) form = kRuns;
@@ -611,7 +615,9 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     const uint32_t g = stream_grid((a.nsteps + a.run - 1) / a.run, waves, cfg.capped ? cfg.max_wgs : 0);
     a.waves = waves;
     a.stride = (uint64_t)g * waves;
-    const uint32_t lds = waves == 1 ? crowd_lds(crowd_waves((uint32_t)nsrc, mean, form == kPacked)) : 0;
+    const uint32_t crowd = waves == 1 ? crowd_waves(nsrc, mean, form == kPacked)
+                                      : waves == 2 ? pair_waves(nsrc, mean, form == kPacked) : 32;
+    const uint32_t lds = waves * crowd_lds(crowd);
     hipLaunchKernelGGL(fn, dim3(g), dim3(64 * waves), lds, stream, a);
     return hipGetLastError();
 }

@@ -12,6 +12,14 @@ extern "C" uint64_t turned(uint32_t units, uint64_t u, uint64_t u0, uint64_t u1,
 {
     return units == 1 ? reft::turned<1>(u, u0, u1, turn) : reft::turned<2>(u, u0, u1, turn);
 }
+extern "C" uint64_t near_step(uint64_t w, uint64_t n) { return reft::near_step_of_wave(w, n); }
+extern "C" uint64_t pair_step(uint64_t w, uint64_t n) { return reft::pair_step_of_wave(w, n); }
+extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, bool odd, bool packed) { return reft::in_pairs(nsrc, mean, odd, packed); }
+extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bool tensors, bool windows)
+{
+    return reft::spread_of(nsrc, mean, odd, packed, tensors, windows);
+}
+extern "C" uint32_t pair_lds(uint32_t nsrc, uint64_t mean, bool packed) { return 2 * reft::crowd_lds(reft::pair_waves(nsrc, mean, packed)); }
 extern "C" uint32_t turn_of(uint64_t number, uint64_t kib) { return reft::turn_of(number, kib); }
 """
 
@@ -30,6 +38,13 @@ def rules(tmp_path_factory):
     lib.turned.restype = ctypes.c_uint64
     lib.turn_of.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
     lib.turn_of.restype = ctypes.c_uint32
+    for f in (lib.near_step, lib.pair_step):
+        f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
+        f.restype = ctypes.c_uint64
+    lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
+    lib.in_pairs.restype = ctypes.c_bool
+    lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
+    lib.pair_lds.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool]
     return lib
 
 
@@ -50,3 +65,46 @@ def test_turned_units_have_the_numbers_of_their_kib(rules, first, kib):
     n, turn = 100, rules.turn_of(first, kib)
     for u in range(first, first + n - turn):
         assert (u - (kib + rules.turned(1, u, first, first + n, turn) - first)) % 32 == 0
+
+
+@pytest.mark.parametrize("name", ["near_step", "pair_step"])
+def test_orders_are_permutations(rules, name):
+    """Inside 32 steps, each XCD on bits 1, 2 and 4; what is left stays in order."""
+    order, waves = getattr(rules, name), 2 if name == "pair_step" else 1
+    for n in (1, 31, 32, 33, 63, 64, 65, 1000, 4097):
+        steps = [order(w, n) for w in range(n)]
+        assert sorted(steps) == list(range(n))
+        assert all(u // 32 == w // 32 for w, u in enumerate(steps)) and steps[n // 32 * 32:] == list(range(n // 32 * 32, n))
+        for x in range(8):
+            assert len({steps[w] & 0b10110 for w in range(n // 32 * 32) if w // waves % 8 == x}) <= 1
+    for n in (1 << 33, (1 << 40) + 5):                # beyond 32 bits
+        at = n // 32 * 32 - 64
+        assert sorted(order(w, n) for w in range(at, n)) == list(range(at, n))
+    if waves == 2:
+        assert all(order(w, 64) + 1 == order(w + 1, 64) for w in range(0, 64, 2))
+
+
+def test_which_order_a_launch_takes(rules):
+    in_order, far, near, pairs = range(4)
+    k20, k32, k64 = 20 << 10, 32 << 10, 64 << 10
+    for nsrc in range(1, 17):
+        for odd in (False, True):
+            for packed in (False, True):
+                for windows in (False, True):
+                    for tensors in (False, True):
+                        got = [rules.spread_of(nsrc, mean, odd, packed, tensors, windows)
+                               for mean in (k20 - 1, k20, k32 - 1, k32, k64 - 1, k64)]
+                        alone = nsrc == 1 and not packed
+                        assert got[0] == in_order and got[1] == got[2] and (got[2] == in_order) == alone
+                        if not odd:
+                            assert set(got[3:]) == {far}
+                        elif packed or nsrc in (2, 3):
+                            assert set(got[3:]) == {far if nsrc == 1 else pairs}
+                        elif alone or (windows and nsrc <= 12):
+                            assert set(got[3:]) == {near}
+                        else:
+                            assert got[3] == far and got[4] == far and got[5] == (far if tensors or windows or nsrc > 12 else near)
+                        for mean, order in zip((k20 - 1, k20, k64), (got[0], got[1], got[5])):
+                            assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, odd, packed)
+                            assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
+            assert rules.in_pairs(nsrc, 5000, odd, True) == (odd and 2 <= nsrc <= 8)
