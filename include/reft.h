@@ -111,7 +111,8 @@ int reft_plan_split(const reft_plan *plan, double t_bubble, double t_ss, uint64_
  * "dma_min_bytes" / "gather_min_pieces": *gather_launches kernel launches on pack_stream (runs of
  * small pieces) and *copies hipMemcpyAsync calls on copy_stream.  With *gather_launches == 0 the
  * transport is pure DMA, pack_stream carries no work, and the caller may pass one stream for both
- * (one hardware queue less: see the note on streams under reft_snapshot_pack). */
+ * (one hardware queue less: see the note on streams under reft_snapshot_pack).  (Up to 4 MiB on one
+ * stream: one kernel where gather launches are reported, and no copies.) */
 int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *copies);
 
 /* ---- S1 + S2 + S3: bucketed snapshot of one shard into pinned host memory -----------------------
@@ -127,7 +128,10 @@ int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *
  *       is not cut at a bucket's end either: bytes of one span that are copied next to each other
  *       leave in one copy.  The ring's slots
  *       form two groups used alternately; the two streams synchronise through events once per
- *       group.  pack_stream may equal copy_stream (fully in order).  The tensors are read in
+ *       group.  pack_stream may equal copy_stream (fully in order); then up to 4 MiB that would be
+ *       gathered at least in part go across the link by a kernel of few workgroups, as in the direct
+ *       transport, if host_dst is device-accessible: that takes less time than setting up a copy,
+ *       also from kernels beside it.  The tensors are read in
  *       pack_stream's order: work queued on pack_stream before the call (say, the kernel that
  *       produced a parity buffer) completes before any byte is read, also by the copies.
  *   direct (staging == NULL)  the gather kernel itself stores into the pinned host buffer across
@@ -384,7 +388,7 @@ int reft_recovery_plan(uint32_t k, const uint32_t *copy_offsets, uint32_t n_copi
  * large pieces by hipMemcpyAsync on copy_stream straight into their tensors, runs of small pieces
  * by hipMemcpyAsync into a staging slot and a scatter kernel on unpack_stream) or direct (staging ==
  * NULL: the scatter kernel reads the pinned host snapshot across the link, per bucket, on
- * unpack_stream).  host_bytes must equal L (REFT_ESIZE).  Other arguments as for reft_snapshot_pack.
+ * unpack_stream; with one stream for both, a staged restore of up to 4 MiB as well).  host_bytes must equal L (REFT_ESIZE).  Other arguments as for reft_snapshot_pack.
  */
 int reft_restore(reft_plan *plan, const void *host_src, uint64_t host_bytes,
                  void *staging, uint64_t staging_bytes,

@@ -352,6 +352,13 @@ static uint64_t device_view_of_host(const void *host)
     return (uint64_t)(uintptr_t)d;
 }
 
+// The same for the `bytes` bytes from there on, or 0 if they are not one piece of such memory.
+static uint64_t device_view_of_host(const void *host, uint64_t bytes)
+{
+    const uint64_t a = device_view_of_host(host);
+    return a && device_view_of_host((const uint8_t *)host + bytes - 1) == a + bytes - 1 ? a : 0;
+}
+
 static int make_event(Event &e, unsigned flags = hipEventDisableTiming)
 {
     HIPCHK(hipEventCreateWithFlags(&e.ev, flags));
@@ -1146,6 +1153,17 @@ static int record_rest_done(reft_plan *p, hipStream_t s)
     return record(p->rest_done, s);
 }
 
+// Whether a staged call on one stream moves its bytes, [lo, hi) of the stream, by a kernel across the link, as a direct one
+// does.  Of up to 4 MiB that a kernel would gather or scatter in any case, it does so in less time than a copy takes to be
+// set up, to wait for that kernel and to move them, and disturbs kernels beside it no more.  us, copies / across the link
+// (and what a loop of GEMMs loses to either): saved, 0.5 MB 31 / 15 (6 / 5), 2 MB 57 / 41 (11 / 8), 4 MB 92 / 78 (18 / 17), 8 MB
+// 164 / 157 (28 / 51); loaded, 28 / 19 (7 / 5), 54 / 47 (12 / 10), 91 / 79 (20 / 17), 162 / 150 (29 / 40).
+constexpr uint64_t kLinkBytes = 4 << 20;
+static bool across_link(const std::vector<Run> &runs, uint64_t lo, uint64_t hi)
+{
+    return !runs.empty() && hi - lo <= kLinkBytes;
+}
+
 extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_ptrs, void *staging,
                                         uint64_t staging_bytes, void *host_dst, uint64_t host_cap,
                                         uint64_t bucket_begin, uint64_t bucket_end,
@@ -1195,6 +1213,14 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
     const PieceLists &pl = pieces_of(p, bucket_begin, bucket_end);
     const std::vector<Run> &runs = pl.runs;
     const std::vector<Dma> &dmas = pl.dmas;
+    const uint64_t lo = p->bstart[bucket_begin], hi = p->bstart[bucket_end];
+    if (uint64_t hview; ps == cs && across_link(runs, lo, hi) &&
+                        (hview = device_view_of_host((uint8_t *)host_dst + lo, hi - lo))) {
+        if ((rc = upload_ptrs(p, span_ptrs, 1, ps, &tab, &entry))) return rc;
+        HIPCHK(launch_gather(pt, tab, 1, false, false, nullptr, hview - lo, p->range(lo, hi), link_cfg(p, 3), ps));
+        if ((rc = release_ptrs(p, entry, ps))) return rc;
+        return record_pack_done(p, ps);
+    }
     const uint64_t stride = slot_stride(p);
     // The tensors are read on both streams.  The caller orders pack_stream behind whatever
     // produced them; copy_stream joins pack_stream here so the same ordering covers its copies.
@@ -2112,6 +2138,12 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
     const PieceLists &pl = pieces_of(p, 0, p->NB);
     const std::vector<Run> &runs = pl.runs;
     const std::vector<Dma> &dmas = pl.dmas;
+    if (uint64_t hview; us == cs && across_link(runs, 0, p->L) && (hview = device_view_of_host(host_src, p->L))) {
+        if ((rc = upload_ptrs(p, span_ptrs, 1, us, &tab, &entry))) return rc;
+        HIPCHK(launch_scatter(pt, tab, hview, p->all(), link_cfg(p, 4), us));
+        if ((rc = release_ptrs(p, entry, us))) return rc;
+        return record_rest_done(p, us);
+    }
     const uint64_t stride = slot_stride(p);
     const bool alone = us == cs;                          // one stream, in order by itself
     // The tensors are written on both streams.  The caller orders unpack_stream behind their last
