@@ -410,7 +410,7 @@ int reft_restore_wait(reft_plan *plan);
  *                  that write host memory use half as many again, those that read it twice as many;
  *                  none more than "max_wgs").
  *   "dma_min_bytes"     staged transport: spans of at least this size travel by DMA alone
- *                  (default 1 MiB; 0 = every span; a huge value = none, everything is gathered).
+ *                  (default 4 MiB; 0 = every span; a huge value = none, everything is gathered).
  *   "gather_min_pieces" staged transport: shortest run of pieces of smaller spans that is gathered
  *                  by a kernel instead of being copied piece by piece (default 8, at least 1).
  *   "dma_streams"  staged transport: 1 (default) = all piece copies on copy_stream; 2 = they

@@ -57,7 +57,7 @@ static std::atomic<uint64_t> g_tile_shift{18};   // read at plan creation
 static std::atomic<uint64_t> g_host_only{0};     // read at plan creation: no device tables
 static std::atomic<uint64_t> g_link_wgs{32};     // grid cap of kernels bound by the host link
 static std::atomic<uint64_t> g_small_pieces{1}; // spans starting in a tile that make it count as dense
-static std::atomic<uint64_t> g_dma_min{1 << 20}; // spans of at least this many bytes are copied by DMA
+static std::atomic<uint64_t> g_dma_min{4 << 20}; // spans of at least this many bytes are copied by DMA
 static std::atomic<uint64_t> g_gather_min{8};    // shortest run of smaller pieces worth a gather kernel
 static std::atomic<uint64_t> g_dma_streams{1};   // 2 = piece copies alternate with a helper stream
 static std::atomic<uint64_t> g_graph_copies{0};  // piece copies as a hipGraph: 0 off, 1 independent nodes, 2 chain
@@ -931,8 +931,12 @@ extern "C" int reft_plan_burst_stats(reft_plan *p, uint64_t stats[4])
 // 270 MB: 7.6 ms, a copy per bucket and span 45 ms).
 //
 // Where the line lies: a copy costs 9.3 us on the link beside its bytes, as much as 530 KB (spans of
-// 64 KiB, 256 KiB, 1 MiB, 4 MiB one by one: 6.3, 18.6, 37.5, 50.1 GB/s; gathered: 54.8 at all sizes);
-// gathering a span of 1 MiB costs the device 0.4 us, which kernels beside it lose.
+// 64 KiB, 256 KiB, 1 MiB, 4 MiB one by one: 6.3, 18.6, 37.5, 50.1 GB/s; gathered: 54.8 at all sizes), and a span that is
+// copied between smaller ones ends their run, whose next part has a kernel and a copy of its own.  Gathering a span of 1 MiB
+// costs the device 0.4 us and kernels beside it up to 2.  us, spans copied from 1 / 2 / 4 / 8 MiB on, alone, and beside a
+// loop of GEMMs (and what that loses): 128 MB in 256 spans (log-uniform 64 : 65536) 3941 / 2710 / 2319 / 2319, 13368 /
+// 6290 / 3208 / 3209 (639 / 91 / 79 / 86); 460 MB in 2424 10327 / 8343 / 8344 / 8345, 49885 / 12633 / 13369 / 13304 (1772 / 244 /
+// 328 / 362); but 400 MB in 200 of 1 to 4 MiB 8859 / 8442 / 7244 / 7242, 8876 / 8765 / 11019 / 11283 (220 / 214 / 398 / 268).
 static void classify_pieces(const reft_plan *p, uint64_t bucket_begin, uint64_t bucket_end,
                             uint64_t dma_min, uint64_t gather_min, std::vector<Run> &runs,
                             std::vector<Dma> &dmas)
