@@ -65,3 +65,64 @@ def test_in_place(dev, k, odd):  # noqa: F811
         assert torch.equal(par, torch.cat(shards[1]))
     finally:
         reft.reft_plan_destroy(plan)
+
+
+# more than 512 MiB of traffic, spans of 128 KiB and more on average at multiples of 64 bytes in the stream, in memory at such
+# and anywhere
+@pytest.mark.parametrize("align", [1, 64])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 8, 11, 16])
+def test_results_written_through(dev, k, align):  # noqa: F811
+    rng = np.random.default_rng(k)
+    sizes, total = [], (520 << 20) // (k + 1)
+    while sum(sizes) < total:
+        sizes.append(int(rng.integers(1, 8 << 10)) * 64)
+        if len(sizes) % 9 == 0:
+            sizes += [64, 0, 192]
+    sizes += [int(rng.integers(1, 64)) for _ in range(4)]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(k)
+    T, L = len(sizes), sum(sizes)
+    assert L // T >= 128 << 10
+
+    def spans():
+        return arena(sizes, rng.integers(0, 64, T) // align * align, dev, gen)
+
+    shards = [spans()[1] for _ in range(k)]
+    streams = [torch.cat(sh) for sh in shards]
+    want = streams[0].clone()
+    for st in streams[1:]:
+        want ^= st
+    plan = reft.reft_plan_create(sizes)
+    try:
+        flat = [t for sh in shards for t in sh]
+
+        def guarded():
+            raw = torch.full((L + 512,), 0x96, dtype=torch.uint8, device=dev)
+            at = 256 + int(rng.integers(0, 64)) // align * align
+            return raw, raw[at:at + L]
+
+        def check(raw, view, expected):
+            at = view.storage_offset()
+            assert torch.equal(view, expected)
+            assert bool((raw[:at] == 0x96).all()) and bool((raw[at + L:] == 0x96).all())
+
+        raw, par = guarded()
+        reft.reft_parity_encode(plan, flat, k, par)
+        check(raw, par, want)
+        raw2, packed = guarded()
+        raw, par = guarded()
+        reft.reft_parity_encode_pack(plan, flat, k, k - 1, par, packed)
+        check(raw, par, want)
+        check(raw2, packed, streams[k - 1])
+        raw2, outs = spans()
+        raw2.fill_(0x96)
+        before = raw2.clone()
+        rows = [None if s == 1 else t for s, sh in enumerate(shards) for t in sh]
+        reft.reft_reconstruct_spans(plan, rows, k, 1, par, outs)
+        assert torch.equal(torch.cat(outs), streams[1])
+        for t in outs:
+            t.fill_(0x96)
+        assert torch.equal(raw2, before)
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)
