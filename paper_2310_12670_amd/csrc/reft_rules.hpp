@@ -203,25 +203,28 @@ constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
     return crowd_waves(nsrc, mean_span, packed);
 }
 
-// Whether a launch of two sources and more writes its results through the L2 (st16_through): where units write whole cache
+// Whether a launch writes its results through the L2 (st16_through): where units write whole cache
 // lines, in spans long enough for an XCD to keep to its address bits, and far more than the cache holds.  Time over that of
 // results that wait in the L2 to be evicted, each with its best number of waves: spans of MBs, parity of 2, 3, 4, 5, 8, 12, 16 .92,
-// .93, .94, .98, .99, .99, .99, with the packed stream of 2, 3, 4, 5, 8, 12 .96, .97, .95, .96, .97, .99, decode of 4 .94, of 5 .98.
+// .93, .94, .98, .99, .99, .99, with the packed stream of 2, 3, 4, 5, 8, 12 .96, .97, .95, .96, .97, .99, decode of 4 .94, of 5 .98; copies .98 to .99, in spans of 0.1 to 0.5 MB 1.
 // But in odd streams 1.00 to 1.08 (partial lines from both sides go to memory one by one), aligned spans of 60 KB, of 2 sources,
 // 1.06, of 4 1.02, and 0.13 to 0.3 GB of traffic 1.00 to 1.06 (some of it would have stayed in the 256 MB cache).
 //
-// How many waves then share a compute unit (see crowd_waves), swept from 6 to 32 on 1.7 to 28 GB: parity of 3 sources 1032 /
+// How many waves then share a compute unit (see crowd_waves), swept from 6 to 32 on 1.7 to 28 GB: copies (25.8 GB) 3893 us
+// with 24 as they were, 3862 / 3815 / 3823 written through with 24 / 20 / 18, 835 / 831 / 824 / 824 (5.6 GB), parity of 3 sources 1032 /
 // 962 us with 24 / 18, of 4 1283 / 1203 with 16 / 15; with the packed stream of 2 350 / 340 with 28 / 20, of 3 442 / 434 with 24
 // / 16, of 4 534 / 519 with 16 / 14, of 5 634 / 626 with 15 / 13, of 8 2600 / 2554 with 12 / 10.
 constexpr uint64_t kThroughMeanSpan = 128 * 1024, kThroughTraffic = 512ull << 20;
-constexpr bool writes_through(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd)
+constexpr uint64_t kThroughMeanCopy = 1024 * 1024;
+constexpr bool writes_through(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed)
 {
-    return nsrc > 1 && !odd && mean_span >= kThroughMeanSpan && traffic >= kThroughTraffic;
+    if (odd || traffic < kThroughTraffic) return false;
+    return nsrc == 1 ? !packed && mean_span >= kThroughMeanCopy : mean_span >= kThroughMeanSpan;
 }
 constexpr uint32_t through_waves(uint32_t nsrc, bool packed)
 {
     if (packed) return nsrc == 2 ? 20 : nsrc == 3 ? 16 : nsrc < 11 ? 18 - nsrc : crowd_waves(nsrc, kThroughMeanSpan, true);
-    return nsrc == 3 ? 18 : nsrc == 4 ? 15 : crowd_waves(nsrc, kThroughMeanSpan, false);
+    return nsrc == 1 || nsrc == 3 ? 18 : nsrc == 4 ? 15 : crowd_waves(nsrc, kThroughMeanSpan, false);
 }
 constexpr uint32_t crowd_lds(uint32_t waves) { return waves == 32 ? 0 : 160 * 1024 / waves / 512 * 512; }
 

@@ -163,7 +163,7 @@ __device__ __forceinline__ void st16_at(uint64_t p, uint32_t at, u32x4 v)
 
 // The same where results are written through the L2 (writes_through).  As buffer accesses: they take the two bits of a store
 // together, and the loads' bases stay in scalar registers as they are (8 x 3.1 GB 4139 us with global accesses, 4130 with these
-// stores, 4103 with these loads, 4080 with both).
+// stores, 4103 with these loads, 4080 with both; copies with such loads 2 to 4 % more, so theirs are ordinary).
 typedef unsigned int u32x4_raw __attribute__((ext_vector_type(4)));
 constexpr int kNontemporal = 2, kDeviceScope = 16;            // bits nt and sc1
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(uint64_t p)
@@ -188,7 +188,7 @@ __device__ __forceinline__ void move_16(const Span<K> &o, int64_t from, uint32_t
     at = lane_offset(at);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        if constexpr (THROUGH) t[j] = ld16_through(o.s[j] + from, at);
+        if constexpr (THROUGH && K > 1) t[j] = ld16_through(o.s[j] + from, at);
         else t[j] = ld16_at<NT>(o.s[j] + from, at);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -248,7 +248,7 @@ __device__ __forceinline__ void move_unit(const StreamArgs &a, const Span<K> &o,
 
 // The first M KiB at most of the `len` bytes (at least 16) at byte `from` of the span, all loads of up to 32 chunks
 // before the first use.
-template <int K, int M, bool NT>
+template <int K, int M, bool NT, bool THROUGH>
 __device__ __forceinline__ void move_chunks(const Span<K> &o, int64_t from, int32_t len, bool twice, uint32_t lane)
 {
     constexpr int R = K * M <= 32 ? K : 32 / M;
@@ -273,14 +273,17 @@ __device__ __forceinline__ void move_chunks(const Span<K> &o, int64_t from, int3
     }
 #pragma unroll
     for (int c = 0; c < M; ++c)
-        if ((int32_t)(c * kUnit + lane * 16) + (twice ? 0 : 15) < len) st16_at<NT>(o.d + from, at[c], v[c]);
+        if ((int32_t)(c * kUnit + lane * 16) + (twice ? 0 : 15) < len) {
+            if constexpr (THROUGH) st16_through(o.d + from, at[c], v[c]);
+            else st16_at<NT>(o.d + from, at[c], v[c]);
+        }
 }
 
 // `n` units (at most U) of span o from u on together; as move_unit, where it says which bytes come twice.  us, one by one /
 // so: decode of 2 sources in spans of 70 KB by 16 workgroups 387 / 301, packed 311 / 261; parity of 8 in spans of 10 KB by 64
 // 0.64 / 0.55 of units of the stream; direct restore of 0.5 GB in spans of 10 KB 9913 / 9580; copies of 60,000 spans of
 // 1500 bytes 42 / 33 (of 700 bytes, whose steps have two spans, 31 / 33).
-template <int K, int U, bool NT>
+template <int K, int U, bool NT, bool THROUGH>
 __device__ __forceinline__ void move_units(const StreamArgs &a, const Span<K> &o, uint64_t u, uint32_t n, uint32_t lane)
 {
     const bool once = a.last == kLastDest;
@@ -293,19 +296,19 @@ __device__ __forceinline__ void move_units(const StreamArgs &a, const Span<K> &o
     if (twice && len < 16) len = 16;
     const int64_t from = p.t - len;
     if (len >= 16) {
-        if (U > 3 && len > 3 * (int32_t)kUnit) move_chunks<K, U, NT>(o, from, len, twice, lane);
-        else if (U > 2 && len > 2 * (int32_t)kUnit) move_chunks<K, 3, NT>(o, from, len, twice, lane);
-        else if (len > (int32_t)kUnit) move_chunks<K, 2, NT>(o, from, len, twice, lane);
-        else move_chunks<K, 1, NT>(o, from, len, twice, lane);
+        if (U > 3 && len > 3 * (int32_t)kUnit) move_chunks<K, U, NT, THROUGH>(o, from, len, twice, lane);
+        else if (U > 2 && len > 2 * (int32_t)kUnit) move_chunks<K, 3, NT, THROUGH>(o, from, len, twice, lane);
+        else if (len > (int32_t)kUnit) move_chunks<K, 2, NT, THROUGH>(o, from, len, twice, lane);
+        else move_chunks<K, 1, NT, THROUGH>(o, from, len, twice, lane);
         if (len > U * (int32_t)kUnit && (int32_t)lane * 16 < len - U * (int32_t)kUnit)
-            move_16<K, NT, false>(o, from, (uint32_t)lane_place((int32_t)(U * kUnit + lane * 16), len), true);
+            move_16<K, NT, false, THROUGH>(o, from, (uint32_t)lane_place((int32_t)(U * kUnit + lane * 16), len), true);
     }
     if (!twice && (int32_t)lane < (len & 15)) move_byte<K, false>(o, p.s + (len & ~15) + lane);
 }
 
 // The U units from u on, and kRuns the steps behind them, up to `most` in all, as far as all their bytes are
 // of span o and in the range; returns how many steps.
-template <int K, int U, bool NT, Form F>
+template <int K, int U, bool NT, Form F, bool THROUGH>
 __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K> &o, uint64_t u, uint32_t lane,
                                                uint32_t most)
 {
@@ -347,7 +350,10 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
             }
         }
 #pragma unroll
-        for (int c = 0; c < U; ++c) st16_at<NT>(o.d + x + c * kUnit, at, v[c]);
+        for (int c = 0; c < U; ++c) {
+            if constexpr (THROUGH) st16_through(o.d + x + c * kUnit, at, v[c]);
+            else st16_at<NT>(o.d + x + c * kUnit, at, v[c]);
+        }
         if constexpr (F != kRuns) return 1;
         x += S;
         if (done == most || x + S > o.hi) return done;
@@ -399,16 +405,16 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
         if constexpr (U == 1 && F != kRuns) {
             move_unit<K, NT, F, THROUGH>(a, o, u, lane);
         } else {
-            done = one ? move_steps<K, U, NT, F>(a, o, u, lane, left) : 0;
+            done = one ? move_steps<K, U, NT, F, THROUGH>(a, o, u, lane, left) : 0;
             if (done) continue;
             done = 1;
             for (;;) {
                 const uint64_t part = end < o.u1 ? end : o.u1;
                 if constexpr (K > kMaxSrc) {                // (as many loads as registers allow in one unit already)
-                    for (; u < part; ++u) move_unit<K, NT, F>(a, o, u, lane);
+                    for (; u < part; ++u) move_unit<K, NT, F, THROUGH>(a, o, u, lane);
                 } else {
-                    if (part - u == 1) move_unit<K, NT, F>(a, o, u, lane);
-                    else move_units<K, U, NT>(a, o, u, (uint32_t)(part - u), lane);
+                    if (part - u == 1) move_unit<K, NT, F, THROUGH>(a, o, u, lane);
+                    else move_units<K, U, NT, THROUGH>(a, o, u, (uint32_t)(part - u), lane);
                     u = part;
                 }
                 if (u == end) break;
@@ -518,7 +524,9 @@ static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 #define REFT_PICK_SPREAD(K)                                                                       \
     (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, true> : k_stream<K, K == 1 ? 2 : 1, true, kPlain, true>)
 
-#define REFT_PICK_THROUGH(K) k_stream<K, 1, true, kPlain, true, true>
+#define REFT_PICK_THROUGH(K)                                                                      \
+    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, true, true>                                   \
+                     : k_stream<K, K == 1 ? 2 : 1, true, kPlain, true, true>)
 
 #define REFT_PICK_PACK(K)                                                                         \
     (through ? k_stream<K, 1, true, kPacked, true, K != 1>                                        \
@@ -604,7 +612,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.run = 1;
     a.spread = waves == 4 || !cfg.nontemporal || a.first_step % 32
                    ? kInOrder : spread_of(nsrc, mean, pt.odd, form == kPacked, a.ragged, pt.windows);
-    const bool through = a.spread && writes_through(nsrc, mean, traffic, pt.odd) && form != kInPlace;
+    const bool through = a.spread && form != kInPlace && writes_through(nsrc, mean, traffic, pt.odd, form == kPacked);
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
         a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, mean);
         if (a.run > 1) form = kRuns;
@@ -613,10 +621,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     case kPlain:
         if (through) {
             switch (nsrc) {
-            case 2: fn = REFT_PICK_THROUGH(2); break;
-            case 3: fn = REFT_PICK_THROUGH(3); break;
-            case 4: fn = REFT_PICK_THROUGH(4); break;
-                REFT_CASES_5_8(REFT_PICK_THROUGH) REFT_CASES_9_16(REFT_PICK_THROUGH)
+                REFT_CASES_4(REFT_PICK_THROUGH) REFT_CASES_5_8(REFT_PICK_THROUGH) REFT_CASES_9_16(REFT_PICK_THROUGH)
             default: return hipErrorInvalidValue;
             }
             break;

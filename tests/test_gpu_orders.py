@@ -126,3 +126,39 @@ def test_results_written_through(dev, k, align):  # noqa: F811
     finally:
         torch.cuda.synchronize()
         reft.reft_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("align", [1, 64])
+def test_copies_written_through(dev, align):  # noqa: F811
+    """Packed and unpacked, in spans of 1 MiB and more on average: whole steps of two units, and what is left of a span."""
+    rng = np.random.default_rng(align)
+    sizes = []
+    while sum(sizes) < 260 << 20:
+        sizes.append(int(rng.integers(1, 64 << 10)) * 64)
+        if len(sizes) % 20 == 0:
+            sizes += [0, 64]
+    sizes.append(5)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(align)
+    T, L = len(sizes), sum(sizes)
+    assert L // T >= 1 << 20 and 2 * L >= 512 << 20
+    shard = arena(sizes, rng.integers(0, 64, T) // align * align, dev, gen)[1]
+    want = torch.cat(shard)
+    plan = reft.reft_plan_create(sizes)
+    try:
+        raw = torch.full((L + 512,), 0x96, dtype=torch.uint8, device=dev)
+        at = 256 + int(rng.integers(0, 64)) // align * align
+        packed = raw[at:at + L]
+        reft.reft_pack_device(plan, shard, packed)
+        assert torch.equal(packed, want)
+        assert bool((raw[:at] == 0x96).all()) and bool((raw[at + L:] == 0x96).all())
+        raw2, outs = arena(sizes, rng.integers(0, 64, T) // align * align, dev, gen)
+        raw2.fill_(0x96)
+        reft.reft_unpack_device(plan, packed, outs)
+        assert torch.equal(torch.cat(outs), want)
+        for t in outs:
+            t.fill_(0x96)
+        assert bool((raw2 == 0x96).all())
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)

@@ -20,7 +20,10 @@ extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, bool odd, bool packe
     return reft::spread_of(nsrc, mean, odd, packed, tensors, windows);
 }
 extern "C" uint32_t pair_lds(uint32_t nsrc, uint64_t mean, bool packed) { return 2 * reft::crowd_lds(reft::pair_waves(nsrc, mean, packed)); }
-extern "C" bool writes_through(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd) { return reft::writes_through(nsrc, mean, traffic, odd); }
+extern "C" bool writes_through(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd, bool packed)
+{
+    return reft::writes_through(nsrc, mean, traffic, odd, packed);
+}
 extern "C" uint32_t through_waves(uint32_t nsrc, bool packed) { return reft::through_waves(nsrc, packed); }
 extern "C" uint32_t crowd_waves(uint32_t nsrc, uint64_t mean, bool packed) { return reft::crowd_waves(nsrc, mean, packed); }
 extern "C" uint32_t crowd_lds(uint32_t waves) { return reft::crowd_lds(waves); }
@@ -48,7 +51,7 @@ def rules(tmp_path_factory):
     lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
     lib.in_pairs.restype = ctypes.c_bool
     lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
-    lib.writes_through.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_bool]
+    lib.writes_through.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
     lib.writes_through.restype = ctypes.c_bool
     lib.through_waves.argtypes = [ctypes.c_uint32, ctypes.c_bool]
     lib.crowd_waves.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool]
@@ -119,13 +122,14 @@ def test_which_order_a_launch_takes(rules):
 
 
 def test_which_launches_write_through(rules):
-    """Long spans, aligned, of several sources and more than twice the cache; and LDS for no more waves than those are to have."""
+    """Long spans, aligned, and more than twice the cache; and LDS for no more waves than those are to have."""
     for nsrc in range(1, 17):
-        for mean in ((128 << 10) - 1, 128 << 10):
-            for traffic in ((512 << 20) - 1, 512 << 20):
-                for odd in (False, True):
-                    assert rules.writes_through(nsrc, mean, traffic, odd) == (
-                        nsrc > 1 and mean == 128 << 10 and traffic == 512 << 20 and not odd)
         for packed in (False, True):
+            least = 1 << 20 if nsrc == 1 else 128 << 10
+            for mean in (least - 1, least):
+                for traffic in ((512 << 20) - 1, 512 << 20):
+                    for odd in (False, True):
+                        assert rules.writes_through(nsrc, mean, traffic, odd, packed) == (
+                            mean == least and traffic == 512 << 20 and not odd and not (nsrc == 1 and packed))
             waves = rules.through_waves(nsrc, packed)
             assert 8 <= waves <= rules.crowd_waves(nsrc, 128 << 10, packed) and rules.crowd_lds(waves) <= 64 << 10
