@@ -205,6 +205,7 @@ struct PieceLists {
 struct PtrEntry {
     bool live = false;
     uint64_t pos = 0, len = 0, hash = 0, tick = 0;
+    uint64_t upload = 0;    // number of the upload that brought it, of all of the plan's
     int in_place = -1;      // whether a source lies where the result for in_place_vb goes (see in_place());
     uint64_t in_place_vb = 0;   // -1: not looked at
     hipStream_t up_stream = nullptr;
@@ -224,10 +225,19 @@ constexpr uint32_t kContig = 0xffffffffu, kZeros = 0xfffffffeu;
 constexpr uint32_t kOut = 0xffffffffu;   // the tensors that receive a decoded shard
 }  // namespace
 
+// Pointers that a caller passed, and where in the derived plan's cache the rows made of them went.
+struct SeenPointers {
+    std::vector<const void *> ptrs;
+    int entry = 0;
+    uint64_t upload = 0;              // 0: none
+};
+
 struct DerivedPlan {
     reft_plan *plan = nullptr;
     uint32_t nwin = 0;
     std::vector<RowRecipe> recipe;
+    SeenPointers seen[2];             // of the two most recent sets, seen[last] the newer one's
+    int last = 0;
 };
 
 struct reft_plan {
@@ -251,7 +261,7 @@ struct reft_plan {
     uint32_t *d_unit_span = nullptr, *d_tile_span = nullptr;
     // cache of pointer tables: a pool of ring_cap pointers (pinned host mirror and device copy)
     // handed out front to back, and the tables that currently live in it
-    uint64_t ring_cap = 0, ring_head = 0, ring_tick = 0;
+    uint64_t ring_cap = 0, ring_head = 0, ring_tick = 0, uploads = 0;
     // Room below null_end is left to the null stream: kernels on it may have read tables there without an event
     // behind them, so that only what comes behind them on that stream may overwrite that room.  The null stream's tables
     // lie in the first null_cap pointers' room as far as null_most allows; the rest is other streams' in any case, and
@@ -469,6 +479,16 @@ static int retire_entry(PtrEntry &e)
     return REFT_OK;
 }
 
+// A live entry's table for work on stream s.
+static int use_entry(reft_plan *p, int entry, hipStream_t s, const uint64_t **dev_tab)
+{
+    PtrEntry &e = p->ring[entry];
+    if (e.up_stream != s && e.uploaded.recorded) HIPCHK(hipStreamWaitEvent(s, e.uploaded.ev, 0));
+    e.tick = ++p->ring_tick;
+    *dev_tab = p->d_ptr + e.pos;
+    return REFT_OK;
+}
+
 // Make `rows` x T pointers available on the device: reuse the cached table that already holds
 // exactly these pointers (a trainer passes the same tensors every iteration; a stream other than
 // the one that uploaded it waits for the upload only), else take the next room in the pool,
@@ -490,12 +510,8 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
         PtrEntry &e = p->ring[i];
         if (e.live && e.len == n && e.hash == h &&
             !memcmp(p->h_ptr + e.pos, ptrs, n * sizeof(uint64_t))) {
-            if (e.up_stream != s && e.uploaded.recorded)
-                HIPCHK(hipStreamWaitEvent(s, e.uploaded.ev, 0));
-            e.tick = ++p->ring_tick;
-            *dev_tab = p->d_ptr + e.pos;
             *entry = i;
-            return REFT_OK;
+            return use_entry(p, i, s, dev_tab);
         }
     }
     const uint64_t pos = p->ring_head + n > most || p->ring_head < least ? least : p->ring_head;
@@ -524,6 +540,7 @@ static int upload_ptrs(reft_plan *p, const void *const *ptrs, uint32_t rows, hip
     e.hash = h;
     e.in_place = -1;
     e.tick = ++p->ring_tick;
+    e.upload = ++p->uploads;
     p->ring_head = pos + n;
     *dev_tab = p->d_ptr + pos;
     *entry = slot;
@@ -1621,12 +1638,25 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     return REFT_OK;
 }
 
-// XOR of `nrows` host rows of span pointers into a contiguous destination or, if dst_row is
-// given, into the destination's own spans.  The rows are uploaded as one table through the
-// plan's cache (rows and dst_row may lie in the plan's row_buf).  apart: a contiguous destination overlaps
-// no source, by the entry point's rules.
+// XOR of `nrows` rows of a table in the plan's cache into a contiguous destination or, with `tensors`, into the spans of
+// the table's last row.  apart: a contiguous destination overlaps no source, by the entry point's rules.
+static int xor_table(reft_plan *p, int entry, const uint64_t *tab, uint32_t nrows, bool tensors, void *dst_contig, bool apart,
+                     hipStream_t s)
+{
+    int rc;
+    const uint64_t at = (uint64_t)nrows * p->T;
+    const void *const *dst_row = tensors ? (const void *const *)(p->h_ptr + p->ring[entry].pos + at) : nullptr;
+    const bool over_source = (tensors || !apart) && in_place(p, entry, (uint64_t)(uintptr_t)dst_contig);
+    if ((rc = xor_passes(p, tab, nrows, tensors ? tab + at : nullptr, dst_row, dst_contig, over_source, p->burst_ctr,
+                         kCtrBlocks, &p->burst_next, s)))
+        return rc;
+    return release_ptrs(p, entry, s);
+}
+
+// The same of host rows, which are uploaded as one table through the plan's cache; dst_row: the tensors, or null (rows and
+// dst_row may lie in the plan's row_buf).
 static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const void *const *dst_row,
-                    void *dst_contig, bool apart, hipStream_t s)
+                    void *dst_contig, bool apart, hipStream_t s, int *used = nullptr)
 {
     int rc;
     const uint64_t T = p->T;
@@ -1641,12 +1671,8 @@ static int xor_rows(reft_plan *p, const void *const *rows, uint32_t nrows, const
     } else {
         if ((rc = upload_ptrs(p, rows, nrows, s, &tab, &entry))) return rc;
     }
-    const uint64_t *dtab = dst_row ? tab + (uint64_t)nrows * T : nullptr;
-    const bool over_source = (dst_row || !apart) && in_place(p, entry, (uint64_t)(uintptr_t)dst_contig);
-    if ((rc = xor_passes(p, tab, nrows, dtab, dst_row, dst_contig, over_source, p->burst_ctr, kCtrBlocks,
-                         &p->burst_next, s)))
-        return rc;
-    return release_ptrs(p, entry, s);
+    if (used) *used = entry;
+    return xor_table(p, entry, tab, nrows, dst_row != nullptr, dst_contig, apart, s);
 }
 
 extern "C" int reft_parity_encode(reft_plan *p, const void *const *shard_span_ptrs, uint32_t k,
@@ -1800,7 +1826,7 @@ static int ensure_zeros(reft_plan *p)
 // their windows (every span boundary of every window becomes a boundary), with the recipe that turns
 // the caller's pointers into its rows.  Built on first use and kept in the base plan.
 static int derived_plan(reft_plan *p, uint64_t key, const std::vector<Segment> &segs,
-                        const DerivedPlan **out)
+                        DerivedPlan **out)
 {
     int rc = ensure_zeros(p);
     if (rc) return rc;
@@ -1873,6 +1899,63 @@ static int derived_rows(const reft_plan *p, const DerivedPlan &dp, const void *c
     return REFT_OK;
 }
 
+// What a call's rows are made of: the shards' span pointers but those of member `skip`, and of a decode the parity units and
+// the tensors.
+struct CallerPointers {
+    const void *const *shards;
+    const void *const *parity, *const *out;                // null in an encode
+    uint64_t T;
+    uint32_t k, skip;
+
+    // each(pointers, count) for every piece of it, until one answers false
+    template <class Each>
+    bool all(Each each) const
+    {
+        return each(shards, skip * T) && each(shards + (skip + 1) * T, (k - 1 - skip) * T) &&
+               (!parity || (each(parity, skip) && each(parity + skip + 1, k - 1 - skip))) && (!out || each(out, T));
+    }
+};
+
+// The XOR that a derived plan stands for.  Its rows are many times the caller's pointers, to make, to compare and to keep: so
+// these are compared, with those of the last two sets, and where they are the same and their rows still in the derived
+// plan's cache, that table is used.  (One unit and one decode, 8 members of 34 MB in 9236 spans: 117 us of host work, 26 so.)
+static int xor_derived(reft_plan *p, DerivedPlan &dp, const CallerPointers &from, void *dst_contig, hipStream_t s)
+{
+    int rc;
+    reft_plan *d = dp.plan;
+    const bool tensors = from.out != nullptr;
+    const uint32_t nrows = dp.nwin - (tensors ? 1 : 0);
+    for (int i = 0; i < 2; ++i) {
+        const int at = dp.last ^ i;
+        const SeenPointers &seen = dp.seen[at];
+        if (!seen.upload || !d->ring[seen.entry].live || d->ring[seen.entry].upload != seen.upload) continue;
+        const void *const *had = seen.ptrs.data();
+        if (!from.all([&](const void *const *ptrs, uint64_t n) {
+                const bool same = n == 0 || !memcmp(had, ptrs, n * sizeof *ptrs);
+                had += n;
+                return same;
+            }))
+            continue;
+        const uint64_t *tab = nullptr;
+        dp.last = at;
+        if ((rc = use_entry(d, seen.entry, s, &tab))) return rc;
+        return xor_table(d, seen.entry, tab, nrows, tensors, dst_contig, false, s);
+    }
+    if ((rc = derived_rows(p, dp, from.shards, from.parity, from.out))) return rc;
+    SeenPointers &seen = dp.seen[dp.last ^= 1];
+    seen.upload = 0;
+    seen.ptrs.clear();
+    from.all([&](const void *const *ptrs, uint64_t n) {
+        seen.ptrs.insert(seen.ptrs.end(), ptrs, ptrs + n);
+        return true;
+    });
+    const void **rows = d->row_buf.data();
+    if ((rc = xor_rows(d, rows, nrows, tensors ? rows + (size_t)nrows * d->T : nullptr, dst_contig, false, s, &seen.entry)))
+        return rc;
+    seen.upload = d->ring[seen.entry].upload;
+    return REFT_OK;
+}
+
 extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard_span_ptrs,
                                           uint32_t k, uint32_t member, void *parity_dev,
                                           reft_stream stream)
@@ -1889,7 +1972,7 @@ extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard
     if (Lseg == 0) return REFT_OK;
     if (!parity_dev) return fail(REFT_EINVAL, "reft_parity_encode_rotated: null parity buffer");
     const uint64_t key = (1ull << 56) | ((uint64_t)k << 32) | member;
-    const DerivedPlan *dp = nullptr;
+    DerivedPlan *dp = nullptr;
     auto it = p->derived.find(key);
     if (it != p->derived.end()) {
         dp = &it->second;
@@ -1899,9 +1982,8 @@ extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard
             if (j != member) seg.wins.push_back(WinSpec{false, j, (uint64_t)rot_index(member, j) * Lseg});
         if ((rc = derived_plan(p, key, {seg}, &dp))) return rc;
     }
-    reft_plan *d = dp->plan;
-    if ((rc = derived_rows(p, *dp, shard_span_ptrs, nullptr, nullptr))) return rc;
-    return xor_rows(d, d->row_buf.data(), dp->nwin, nullptr, parity_dev, false, (hipStream_t)stream);
+    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, nullptr, nullptr, p->T, k, member}, parity_dev,
+                       (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode_rotated")
 }
 
@@ -1928,7 +2010,7 @@ extern "C" int reft_reconstruct_rotated(reft_plan *p, const void *const *shard_s
     // the lost shard's and one launch decodes it (one unit and one decode, 16 members of 842 MB: 5.1 ms
     // with 16 launches of two passes each, 2.46 with one launch for either).
     const uint64_t key = (2ull << 56) | ((uint64_t)k << 32) | lost;
-    const DerivedPlan *dp = nullptr;
+    DerivedPlan *dp = nullptr;
     auto it = p->derived.find(key);
     if (it != p->derived.end()) {
         dp = &it->second;
@@ -1948,12 +2030,8 @@ extern "C" int reft_reconstruct_rotated(reft_plan *p, const void *const *shard_s
         }
         if ((rc = derived_plan(p, key, segs, &dp))) return rc;
     }
-    reft_plan *d = dp->plan;
-    if ((rc = derived_rows(p, *dp, shard_span_ptrs, parity_ptrs, (const void *const *)out_span_ptrs)))
-        return rc;
-    const void **rows = d->row_buf.data();
-    return xor_rows(d, rows, dp->nwin - 1, rows + (size_t)(dp->nwin - 1) * d->T, nullptr, false,
-                    (hipStream_t)stream);
+    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, parity_ptrs, (const void *const *)out_span_ptrs, p->T, k, lost},
+                       nullptr, (hipStream_t)stream);
     REFT_GUARD_END("reft_reconstruct_rotated")
 }
 
