@@ -164,9 +164,12 @@ enum Spread : uint32_t {
     kPairs = 3,              // pair_step_of_wave
 };
 constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024, kNearMeanSpan = 64 * 1024;
+constexpr uint64_t kShortMeanSpan = 5 * 1024, kMiddleMeanSpan = 12 * 1024;
 constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed)
 {
-    return odd && nsrc > 1 && (packed ? nsrc <= 8 || mean_span >= kSpreadMeanSpan : nsrc <= 3);
+    if (!odd || nsrc < 2) return false;
+    if (packed) return nsrc <= 8 || mean_span >= kSpreadMeanSpan;
+    return nsrc <= 3 || mean_span < (nsrc < 12 ? kSpreadMeanSpan : kMiddleMeanSpan);
 }
 constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
 {
@@ -195,12 +198,24 @@ constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
     return some > many ? some : many > 8 ? many : 8;
 }
 
-// The same for workgroups of two waves.  Two and three sources with the packed stream, 28, 24 and 20 waves: in spans of 14 KB
-// 350 / 345 / 365 and 426 / 427 / 425 us, of 200 KB 358 / 343 / 333 and 447 / 429 / 418; all others as above.
+// The same for workgroups of two waves.  In spans below 20 KiB a wave waits longer for its look-ups than for its data, the
+// shorter they are the more, so that more waves keep as many bytes in flight; swept from 8 to 32 on 0.5 to 2 GB.  Time over that
+// of single waves, as many as crowd_waves says (2 and 3 sources, and with the packed stream: of pairs, as many), in spans of 2.5,
+// 3.5, 7 and 14 KB: parity of 2 .98, .98, .99, 1, of 3 .96, .95, .98, 1, of 4 .91, .94, .96, .99, of 5 .90, .93, .95, .97, of 6 .94,
+// .96, .97, .99, of 8 .94, .96, .99, .99, of 12 1, .96, .99, (1.01), of 16 1, .94, .98, (1.01); decode of 2 .93, .95, .96, 1, of 4
+// .92, .93, .96, .98, of 8 1.04, .95, .99, .99, of 12 1.02, 1.04, .98, (1); a rotated unit and decode of 5 members .88, .89, .93, .97,
+// of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97, .99, 1, of 4 .97, .98, 1, 1.  In longer spans, 28, 24 and 20 waves
+// with the packed stream of 2 358 / 343 / 333 us, of 3 447 / 429 / 418 (200 KB).
 constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 {
-    if (packed && nsrc <= 3) return mean_span < kSpreadMeanSpan ? 24 : 20;
-    return crowd_waves(nsrc, mean_span, packed);
+    constexpr uint32_t least[3][12] = {{32, 32, 32, 28, 24, 20, 20, 16, 14, 16, 16, 16},
+                                       {32, 32, 32, 28, 20, 16, 16, 14, 12, 14, 14, 14},
+                                       {32, 32, 28, 24, 20, 16, 16, 14, 12, 12, 12, 12}};
+    const uint32_t usual = crowd_waves(nsrc, mean_span, packed);
+    if (mean_span >= kSpreadMeanSpan) return packed && nsrc <= 3 ? 20 : usual;
+    if (!packed) return nsrc >= 12 ? 12 : least[mean_span < kShortMeanSpan ? 0 : mean_span < kMiddleMeanSpan ? 1 : 2][nsrc];
+    if (nsrc <= 3) return nsrc == 2 && mean_span < kMiddleMeanSpan ? 28 : 24;
+    return nsrc <= 6 && mean_span < kShortMeanSpan ? usual + 2 : usual;
 }
 
 // Whether a launch writes its results through the L2 (st16_through): where units write whole cache

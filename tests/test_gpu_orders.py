@@ -162,3 +162,14 @@ def test_copies_written_through(dev, align):  # noqa: F811
     finally:
         torch.cuda.synchronize()
         reft.reft_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("k", [4, 7, 11, 12, 16])
+@pytest.mark.parametrize("mean", [3000, 8000, 15_000])
+def test_pairs_of_waves_in_short_spans(dev, k, mean):  # noqa: F811
+    """More traffic than the cache holds in odd spans of less than 20 KiB on average: two waves a workgroup, in order."""
+    rng = np.random.default_rng(k * mean)
+    sizes = []
+    while sum(sizes) < TRAFFIC // (k + 1):
+        sizes.append(int(rng.integers(0, 2 * mean)) | 1)
+    check_all(dev, sizes, k, None, seed=k, align=1)
