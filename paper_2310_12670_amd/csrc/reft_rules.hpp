@@ -167,7 +167,8 @@ constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024, kNe
 constexpr uint64_t kShortMeanSpan = 5 * 1024, kMiddleMeanSpan = 12 * 1024;
 constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed)
 {
-    if (!odd || nsrc < 2) return false;
+    if (!odd) return false;
+    if (nsrc == 1) return !packed && mean_span >= kShortMeanSpan && mean_span < kSpreadMeanSpan;
     if (packed) return nsrc <= 8 || mean_span >= kSpreadMeanSpan;
     return nsrc <= 3 || mean_span < (nsrc < 12 ? kSpreadMeanSpan : kMiddleMeanSpan);
 }
@@ -204,7 +205,7 @@ constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 // 3.5, 7 and 14 KB: parity of 2 .98, .98, .99, 1, of 3 .96, .95, .98, 1, of 4 .91, .94, .96, .99, of 5 .90, .93, .95, .97, of 6 .94,
 // .96, .97, .99, of 8 .94, .96, .99, .99, of 12 1, .96, .99, (1.01), of 16 1, .94, .98, (1.01); decode of 2 .93, .95, .96, 1, of 4
 // .92, .93, .96, .98, of 8 1.04, .95, .99, .99, of 12 1.02, 1.04, .98, (1); a rotated unit and decode of 5 members .88, .89, .93, .97,
-// of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97, .99, 1, of 4 .97, .98, 1, 1.  In longer spans, 28, 24 and 20 waves
+// of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97, .99, 1, of 4 .97, .98, 1, 1; copies 1, 1, .995, .99.  In longer spans, 28, 24 and 20 waves
 // with the packed stream of 2 358 / 343 / 333 us, of 3 447 / 429 / 418 (200 KB).
 constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 {

@@ -119,7 +119,7 @@ def test_which_order_a_launch_takes(rules):
                             assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, odd, packed)
                             assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
             for mean, most in ((600, 16), ((12 << 10) - 1, 16), (12 << 10, 11), (k20 - 1, 11), (k20, 3)):
-                assert rules.in_pairs(nsrc, mean, odd, False) == (odd and 2 <= nsrc <= most)
+                assert rules.in_pairs(nsrc, mean, odd, False) == (odd and nsrc <= most and (nsrc > 1 or 5 << 10 <= mean < k20))
                 assert rules.in_pairs(nsrc, mean, odd, True) == (odd and 2 <= nsrc <= (8 if mean < k20 else 16))
                 for packed in (False, True):
                     assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
