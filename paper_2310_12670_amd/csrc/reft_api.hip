@@ -952,8 +952,9 @@ extern "C" int reft_plan_burst_stats(reft_plan *p, uint64_t stats[4])
 // copied between smaller ones ends their run, whose next part has a kernel and a copy of its own.  Gathering a span of 1 MiB
 // costs the device 0.4 us and kernels beside it up to 2.  us, spans copied from 1 / 2 / 4 / 8 MiB on, alone, and beside a
 // loop of GEMMs (and what that loses): 128 MB in 256 spans (log-uniform 64 : 65536) 3941 / 2710 / 2319 / 2319, 13368 /
-// 6290 / 3208 / 3209 (639 / 91 / 79 / 86); 460 MB in 2424 10327 / 8343 / 8344 / 8345, 49885 / 12633 / 13369 / 13304 (1772 / 244 /
-// 328 / 362); but 400 MB in 200 of 1 to 4 MiB 8859 / 8442 / 7244 / 7242, 8876 / 8765 / 11019 / 11283 (220 / 214 / 398 / 268).
+// 6290 / 3208 / 3209 (639 / 91 / 79 / 86); 460 MB in 2424 10327 / 8343 / 8344 / 8345, 49885 / 12633 / 13369 / 13304 (1772
+// / 244 / 328 / 362); but 400 MB in 200 of 1 to 4 MiB 8859 / 8442 / 7244 / 7242, 8876 / 8765 / 11019 / 11283 (220 / 214 /
+// 398 / 268).
 static void classify_pieces(const reft_plan *p, uint64_t bucket_begin, uint64_t bucket_end,
                             uint64_t dma_min, uint64_t gather_min, std::vector<Run> &runs,
                             std::vector<Dma> &dmas)
@@ -1156,8 +1157,8 @@ static int staging_slots(const reft_plan *p, const void *staging, uint64_t stagi
 // Before a staged call puts anything into the ring of slots, on stream s: a call that had one stream for everything left no
 // events behind its slots, but is through where its completion event `done` is.
 //
-// (Such calls need no events between their kernels and copies.  Each made the device write its caches back and what was behind
-// it wait: 14.7 MB in 256 tensors saved and loaded 578 us with them, 562 without, 2 MB 127 and 111.)
+// (Such calls need no events between their kernels and copies.  Each made the device write its caches back and what was
+// behind it wait: 14.7 MB in 256 tensors saved and loaded 578 us with them, 562 without, 2 MB 127 and 111.)
 static int ring_taken(hipStream_t s, bool alone, hipStream_t last, const Event &done)
 {
     return alone && last != s ? wait_on(s, done) : REFT_OK;
@@ -1177,8 +1178,8 @@ static int record_rest_done(reft_plan *p, hipStream_t s)
 // Whether a staged call on one stream moves its bytes, [lo, hi) of the stream, by a kernel across the link, as a direct one
 // does.  Of up to 4 MiB that a kernel would gather or scatter in any case, it does so in less time than a copy takes to be
 // set up, to wait for that kernel and to move them, and disturbs kernels beside it no more.  us, copies / across the link
-// (and what a loop of GEMMs loses to either): saved, 0.5 MB 31 / 15 (6 / 5), 2 MB 57 / 41 (11 / 8), 4 MB 92 / 78 (18 / 17), 8 MB
-// 164 / 157 (28 / 51); loaded, 28 / 19 (7 / 5), 54 / 47 (12 / 10), 91 / 79 (20 / 17), 162 / 150 (29 / 40).
+// (and what a loop of GEMMs loses to either): saved, 0.5 MB 31 / 15 (6 / 5), 2 MB 57 / 41 (11 / 8), 4 MB 92 / 78 (18 /
+// 17), 8 MB 164 / 157 (28 / 51); loaded, 28 / 19 (7 / 5), 54 / 47 (12 / 10), 91 / 79 (20 / 17), 162 / 150 (29 / 40).
 constexpr uint64_t kLinkBytes = 4 << 20;
 static bool across_link(const std::vector<Run> &runs, uint64_t lo, uint64_t hi)
 {

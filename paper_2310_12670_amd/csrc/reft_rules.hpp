@@ -37,15 +37,16 @@ constexpr uint64_t unit_bytes(uint64_t L, uint64_t T)
 // In streams of long spans (64 KiB on average) the units lie on the stream's own grid of KiB, and are numbered so that
 // their numbers are the KiB's modulo `align` + 1 (some numbers between spans have no bytes): where a shard's tensors lie
 // in memory in order, an XCD then keeps to the same address bits from span to span (see unit_of_wave; where they do not,
-// turn_of sees to it inside each span).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a capped grid's few
-// waves look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256 KiB modulo 8, that
-// is for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain order / spread /
-// on the grid modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x 2030 / 1889 /
-// 1825 / 1815; of 300 KB, 8 x 961 / 952 / 969 / 929, 12 x 1420 / 1384 / 1397 / 1356, 16 with the packed stream 2087 / 2015
-// / 2037 / 1983; a rotated unit and decode, 16 x 842 MB in pieces of 1.3 MB, 2481 spread, 2406 on the grid.  In other
-// streams one more piece per span would cost more, and the spans' places have little to do with the units' numbers (8 x
-// 132 MB in spans of 10 KB 204.6 us in plain order, 206.2 spread); and below 5 MiB no launch of 16 sources and two
-// results at most leaves the cache, so that none would spread them (2 MB in spans of 300 KB 2.9 us, 3.1 on the grid).
+// turn_of sees to it inside each span).  Modulo 32 that holds for all the bits, but costs 16 numbers a span, which a
+// capped grid's few waves look up in vain (spans of 70 KB, 64 workgroups, packed: 5 % more than modulo 8); so below 256
+// KiB modulo 8, that is for the bits in which XCDs differ, but for one.  us, units that begin with their spans, in plain
+// order / spread / on the grid modulo 8 / modulo 32 and spread: 8 x 0.6 GB in spans of 70 KB 1061 / 1007 / 971 / 964, 16 x
+// 2030 / 1889 / 1825 / 1815; of 300 KB, 8 x 961 / 952 / 969 / 929, 12 x 1420 / 1384 / 1397 / 1356, 16 with the packed
+// stream 2087 / 2015 / 2037 / 1983; a rotated unit and decode, 16 x 842 MB in pieces of 1.3 MB, 2481 spread, 2406 on the
+// grid.  In other streams one more piece per span would cost more, and the spans' places have little to do with the units'
+// numbers (8 x 132 MB in spans of 10 KB 204.6 us in plain order, 206.2 spread); and below 5 MiB no launch of 16 sources
+// and two results at most leaves the cache, so that none would spread them (2 MB in spans of 300 KB 2.9 us, 3.1 on the
+// grid).
 constexpr uint64_t kGridMeanSpan = 64 * 1024, kWideMeanSpan = 256 * 1024, kGridMinBytes = 5 << 20;
 constexpr uint32_t align_of(uint64_t L, uint64_t T)
 {
@@ -150,13 +151,14 @@ constexpr bool odd_stream(uint64_t bytes, uint64_t L) { return bytes > L / 2; }
 // 28 KB -2 to -4 %), and copies, two units a wave, gain from 32 KiB on only (14 KB +1 %, 43 KB -2 %).
 //
 // Odd streams: two results, or two or three sources, in pairs, a wave's neighbour in its own workgroup, so that both
-// parts of a line that they share are in the same L2 at once.  Time of kFar / kNear / pairs, in spans of 14, 43 and 200 KB and
-// 2 MB: with the packed stream, 2 sources 1 / .93 / .90, 1 / .92 / .92, 1 / .92 / .93 and 1 / .99 / .95, 5 sources 1 / .97 / .95,
-// 1 / .97 / .95, 1 / .95 / .93 and 1 / .98 / .97, 8 sources 1 / .97 / .96, .97 / .97, .98 / .98, .98 / .99, 12 sources 1 / 1 /
-// 1.06, .99 / .99, .99 / .96, .99 / .95; parity of 2 1 / 1 / .96, .95 / .97, .94 / .96, .97 / .96.  One result and more
-// sources, all alike but for the result: near, from 64 KiB and up to 12 sources (4 sources .99, .97, .98 of kFar in 43 and 200
-// KB and 2 MB, 8 .99, .98, .98, 16 1.04, 1.05, .99); alike but for one source (decodes): far (near 0 to 2 % more).  Rows that
-// are windows at any offset: near up to 12 sources (3 .98, 7 and 11 .97 to .98), of 15 neither always (.98 to 1.03).
+// parts of a line that they share are in the same L2 at once.  Time of kFar / kNear / pairs, in spans of 14, 43 and 200 KB
+// and 2 MB: with the packed stream, 2 sources 1 / .93 / .90, 1 / .92 / .92, 1 / .92 / .93 and 1 / .99 / .95, 5 sources 1 /
+// .97 / .95, 1 / .97 / .95, 1 / .95 / .93 and 1 / .98 / .97, 8 sources 1 / .97 / .96, .97 / .97, .98 / .98, .98 / .99, 12
+// sources 1 / 1 / 1.06, .99 / .99, .99 / .96, .99 / .95; parity of 2 1 / 1 / .96, .95 / .97, .94 / .96, .97 / .96.  One
+// result and more sources, all alike but for the result: near, from 64 KiB and up to 12 sources (4 sources .99, .97, .98
+// of kFar in 43 and 200 KB and 2 MB, 8 .99, .98, .98, 16 1.04, 1.05, .99); alike but for one source (decodes): far (near 0
+// to 2 % more).  Rows that are windows at any offset: near up to 12 sources (3 .98, 7 and 11 .97 to .98), of 15 neither
+// always (.98 to 1.03).
 enum Spread : uint32_t {
     kInOrder = 0,
     kFar = 1,                // unit_of_wave
@@ -185,11 +187,11 @@ constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, bool odd, bool pac
 // Swept from 8 to 30 requested waves on 0.1 to 14 GB, in spans of 10 KB to 10 MB (encode, decode, with packed stream,
 // rotated, copies): with 4 sources and more the best is 16, 15, 14, 13, 12 (8 sources), 12, 11, 11, 10 (12), 9, 9, 8, 8,
 // and one more or less costs 0.2 to 1 %.  (These are requests; in the blocks of 1280 bytes in which LDS is handed out
-// 28, 24, 15, 13, 12, 11 and 10 come to 25, 21, 14, 12, 11, 10 and 9 waves.)  us, with 80 KiB in flight as the rule (22 waves with 4 sources, 12 with 8, 8
-// from 12 on) / with this one: 4 sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10: 1482 / 1428, 12: 1779 / 1713.  All
-// that fit / so many: 3 sources 582 / 575 in long spans, 370 / 342 (0.5 GB each) in short ones; 2 sources 273 / 263 in
-// spans below a MiB, but 425 / 436 in longer ones; copies 3996 / 3911 and 567 / 559, in spans below 64 KiB 354 / 369; two
-// copies of one source (with the packed stream) 319 / 328 (0.6 GB in spans of 70 KB).
+// 28, 24, 15, 13, 12, 11 and 10 come to 25, 21, 14, 12, 11, 10 and 9 waves.)  us, with 80 KiB in flight as the rule (22
+// waves with 4 sources, 12 with 8, 8 from 12 on) / with this one: 4 sources 738 / 720, 5: 871 / 852, 9: 1392 / 1310, 10:
+// 1482 / 1428, 12: 1779 / 1713.  All that fit / so many: 3 sources 582 / 575 in long spans, 370 / 342 (0.5 GB each) in
+// short ones; 2 sources 273 / 263 in spans below a MiB, but 425 / 436 in longer ones; copies 3996 / 3911 and 567 / 559, in
+// spans below 64 KiB 354 / 369; two copies of one source (with the packed stream) 319 / 328 (0.6 GB in spans of 70 KB).
 constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 {
     if (nsrc == 1) return mean_span >= 64 * 1024 && !packed ? 24 : 32;
@@ -200,13 +202,14 @@ constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 }
 
 // The same for workgroups of two waves.  In spans below 20 KiB a wave waits longer for its look-ups than for its data, the
-// shorter they are the more, so that more waves keep as many bytes in flight; swept from 8 to 32 on 0.5 to 2 GB.  Time over that
-// of single waves, as many as crowd_waves says (2 and 3 sources, and with the packed stream: of pairs, as many), in spans of 2.5,
-// 3.5, 7 and 14 KB: parity of 2 .98, .98, .99, 1, of 3 .96, .95, .98, 1, of 4 .91, .94, .96, .99, of 5 .90, .93, .95, .97, of 6 .94,
-// .96, .97, .99, of 8 .94, .96, .99, .99, of 12 1, .96, .99, (1.01), of 16 1, .94, .98, (1.01); decode of 2 .93, .95, .96, 1, of 4
-// .92, .93, .96, .98, of 8 1.04, .95, .99, .99, of 12 1.02, 1.04, .98, (1); a rotated unit and decode of 5 members .88, .89, .93, .97,
-// of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97, .99, 1, of 4 .97, .98, 1, 1; copies 1, 1, .995, .99.  In longer spans, 28, 24 and 20 waves
-// with the packed stream of 2 358 / 343 / 333 us, of 3 447 / 429 / 418 (200 KB).
+// shorter they are the more, so that more waves keep as many bytes in flight; swept from 8 to 32 on 0.5 to 2 GB.  Time
+// over that of single waves, as many as crowd_waves says (2 and 3 sources, and with the packed stream: of pairs, as many),
+// in spans of 2.5, 3.5, 7 and 14 KB: parity of 2 .98, .98, .99, 1, of 3 .96, .95, .98, 1, of 4 .91, .94, .96, .99, of 5
+// .90, .93, .95, .97, of 6 .94, .96, .97, .99, of 8 .94, .96, .99, .99, of 12 1, .96, .99, (1.01), of 16 1, .94, .98,
+// (1.01); decode of 2 .93, .95, .96, 1, of 4 .92, .93, .96, .98, of 8 1.04, .95, .99, .99, of 12 1.02, 1.04, .98, (1); a
+// rotated unit and decode of 5 members .88, .89, .93, .97, of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97,
+// .99, 1, of 4 .97, .98, 1, 1; copies 1, 1, .995, .99.  In longer spans, 28, 24 and 20 waves with the packed stream of 2
+// 358 / 343 / 333 us, of 3 447 / 429 / 418 (200 KB).
 constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 {
     constexpr uint32_t least[3][12] = {{32, 32, 32, 28, 24, 20, 20, 16, 14, 16, 16, 16},
@@ -221,15 +224,16 @@ constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 
 // Whether a launch writes its results through the L2 (st16_through): where units write whole cache
 // lines, in spans long enough for an XCD to keep to its address bits, and far more than the cache holds.  Time over that of
-// results that wait in the L2 to be evicted, each with its best number of waves: spans of MBs, parity of 2, 3, 4, 5, 8, 12, 16 .92,
-// .93, .94, .98, .99, .99, .99, with the packed stream of 2, 3, 4, 5, 8, 12 .96, .97, .95, .96, .97, .99, decode of 4 .94, of 5 .98; copies .98 to .99, in spans of 0.1 to 0.5 MB 1.
-// But in odd streams 1.00 to 1.08 (partial lines from both sides go to memory one by one), aligned spans of 60 KB, of 2 sources,
-// 1.06, of 4 1.02, and 0.13 to 0.3 GB of traffic 1.00 to 1.06 (some of it would have stayed in the 256 MB cache).
+// results that wait in the L2 to be evicted, each with its best number of waves: spans of MBs, parity of 2, 3, 4, 5, 8,
+// 12, 16 .92, .93, .94, .98, .99, .99, .99, with the packed stream of 2, 3, 4, 5, 8, 12 .96, .97, .95, .96, .97, .99,
+// decode of 4 .94, of 5 .98; copies .98 to .99, in spans of 0.1 to 0.5 MB 1. But in odd streams 1.00 to 1.08 (partial
+// lines from both sides go to memory one by one), aligned spans of 60 KB, of 2 sources, 1.06, of 4 1.02, and 0.13 to 0.3
+// GB of traffic 1.00 to 1.06 (some of it would have stayed in the 256 MB cache).
 //
 // How many waves then share a compute unit (see crowd_waves), swept from 6 to 32 on 1.7 to 28 GB: copies (25.8 GB) 3893 us
-// with 24 as they were, 3862 / 3815 / 3823 written through with 24 / 20 / 18, 835 / 831 / 824 / 824 (5.6 GB), parity of 3 sources 1032 /
-// 962 us with 24 / 18, of 4 1283 / 1203 with 16 / 15; with the packed stream of 2 350 / 340 with 28 / 20, of 3 442 / 434 with 24
-// / 16, of 4 534 / 519 with 16 / 14, of 5 634 / 626 with 15 / 13, of 8 2600 / 2554 with 12 / 10.
+// with 24 as they were, 3862 / 3815 / 3823 written through with 24 / 20 / 18, 835 / 831 / 824 / 824 (5.6 GB), parity of 3
+// sources 1032 / 962 us with 24 / 18, of 4 1283 / 1203 with 16 / 15; with the packed stream of 2 350 / 340 with 28 / 20,
+// of 3 442 / 434 with 24 / 16, of 4 534 / 519 with 16 / 14, of 5 634 / 626 with 15 / 13, of 8 2600 / 2554 with 12 / 10.
 constexpr uint64_t kThroughMeanSpan = 128 * 1024, kThroughTraffic = 512ull << 20;
 constexpr uint64_t kThroughMeanCopy = 1024 * 1024;
 constexpr bool writes_through(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed)

@@ -162,8 +162,8 @@ __device__ __forceinline__ void st16_at(uint64_t p, uint32_t at, u32x4 v)
 }
 
 // The same where results are written through the L2 (writes_through).  As buffer accesses: they take the two bits of a store
-// together, and the loads' bases stay in scalar registers as they are (8 x 3.1 GB 4139 us with global accesses, 4130 with these
-// stores, 4103 with these loads, 4080 with both; copies with such loads 2 to 4 % more, so theirs are ordinary).
+// together, and the loads' bases stay in scalar registers as they are (8 x 3.1 GB 4139 us with global accesses, 4130 with
+// these stores, 4103 with these loads, 4080 with both; copies with such loads 2 to 4 % more, so theirs are ordinary).
 typedef unsigned int u32x4_raw __attribute__((ext_vector_type(4)));
 constexpr int kNontemporal = 2, kDeviceScope = 16;            // bits nt and sc1
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(uint64_t p)
@@ -360,8 +360,8 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
     }
 }
 
-// The workgroup (1 or 4 waves) has no meaning beyond the dispatch.  Unless the caller caps the grid
-// there is one wave per step, dispatched in order, so that the chip moves through its streams in
+// The workgroup (1, 2 or 4 waves) has no meaning beyond the dispatch, but that two waves share an L2 (in_pairs).
+// Unless the caller caps the grid there is one wave per step, dispatched in order, so that the chip moves through its streams in
 // narrow windows; that is what HBM likes best here (copy of 2 GiB by 1 KiB units: 6.6 TB/s with
 // workgroups of 64 threads, 6.5 with 256, 6.2 with 1024; 4.8 - 5.9 with a persistent grid).
 //
@@ -427,8 +427,8 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 // Streams of tiny spans (kSmallMeanSpan): units of kSmallUnit bytes, each one's by 16 lanes, so that a wave moves four of
 // them, U times over; what a wave knows of its span in k_stream, each lane loads here for its own.  Bound by the rate at
 // which waves start (about 4 per ns) and by that chain of loads.  us, units of the stream (see above) / a wave per span
-// / so: 100,000 spans of 40 bytes packed 8.8 / 24.4 / 7.5, parity of 8 32.3 / 40.7 / 19.9; of 300 bytes 19.9 / 26.0 / 16.7 and
-// 91.8 / 102 / 58; 4 MB in 300 by 16 workgroups, two units per lane in flight, 108 / 128 / 47 and 246 / 269 / 91.
+// / so: 100,000 spans of 40 bytes packed 8.8 / 24.4 / 7.5, parity of 8 32.3 / 40.7 / 19.9; of 300 bytes 19.9 / 26.0 / 16.7
+// and 91.8 / 102 / 58; 4 MB in 300 by 16 workgroups, two units per lane in flight, 108 / 128 / 47 and 246 / 269 / 91.
 template <int K, int U>
 __global__ void __launch_bounds__(256) k_stream_small(const StreamArgs a)
 {
