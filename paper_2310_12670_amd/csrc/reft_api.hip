@@ -1572,9 +1572,13 @@ static bool few_dense_tiles(const reft_plan *p)
 }
 
 // Whether `rows` rows go through the burst kernel: very long rows, few span boundaries.  A launch into tensors
-// needs rows four times as long.
-static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
+// needs rows four times as long, and what the stream kernel writes through the L2 is only taken where the caller has
+// set from where on.
+static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors, bool over_source, const LaunchCfg &cfg)
 {
+    if (g_burst_min_bytes.load() == kBurstMinBytes && !over_source && !cfg.capped && cfg.nontemporal && p->T &&
+        writes_through(rows, p->L / p->T, (rows + 1ull) * p->L, p->odd, false))
+        return false;
     return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
            rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
@@ -1612,7 +1616,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     // Very long rows: reads and writes are separated in time with the burst kernel.  Destination spans that are not
     // all aligned alike relative to their stream offsets, which its staging image cannot represent, keep the stream
     // kernel, and more rows go through it in one pass, up to kMaxStreamSrc.
-    bool burst = burst_applies(p, nrows, dst_row != nullptr);
+    bool burst = burst_applies(p, nrows, dst_row != nullptr, over_source, cfg);
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     if (burst && dst_row) {
         bool have = false;
