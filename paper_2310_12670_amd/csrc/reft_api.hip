@@ -1576,11 +1576,13 @@ static bool few_dense_tiles(const reft_plan *p)
 // set from where on.
 static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors, bool over_source, const LaunchCfg &cfg)
 {
-    if (g_burst_min_bytes.load() == kBurstMinBytes && !over_source && !cfg.capped && cfg.nontemporal && p->T &&
+    const uint64_t least = g_burst_min_bytes.load();
+    if (!g_burst.load() || p->L / (tensors ? 4 : 1) < least || rows > (uint32_t)kMaxSrc || rows < g_burst_min_rows.load())
+        return false;
+    if (least == kBurstMinBytes && !over_source && !cfg.capped && cfg.nontemporal &&
         writes_through(rows, p->L / p->T, (rows + 1ull) * p->L, p->odd, false))
         return false;
-    return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
-           rows >= g_burst_min_rows.load() && few_dense_tiles(p);
+    return few_dense_tiles(p);
 }
 
 // Whether some span's result goes to where a source row of the cached table has that very span.  The
