@@ -431,12 +431,9 @@ int reft_restore_wait(reft_plan *plan);
  *                  (default 1; 4294967295 = never, 0 = always): see "burst".
  *   "burst"        1 (default) = the XOR calls use the write-burst variant of the kernel where it
  *                  applies: at least "burst_min_rows" rows (default 7; at most 8 count), at least
- *                  "burst_min_bytes" stream bytes (default 13 GiB, and at exactly that only where the
- *                  stream kernel does not write the result through the L2: most spans at places that are no
- *                  multiples of 64 bytes, or under 128 KiB on average, a result on one of the sources,
- *                  "max_wgs" set or "nontemporal" 0; four times that where the result goes into
- *                  tensors), at most one tile in eight dense in small spans (see "small_pieces"),
- *                  and, for a decode into tensors, every tensor's address aligned
+ *                  "burst_min_bytes" stream bytes (default 13 GiB; four times that where the result
+ *                  goes into tensors), at most one tile in eight dense in small spans (see
+ *                  "small_pieces"), and, for a decode into tensors, every tensor's address aligned
  *                  alike (mod 16) relative to its stream offset.  reft_reconstruct goes by the same
  *                  two values where they are set, and at their defaults (7 and 13 GiB exactly) uses
  *                  the variant from 5 sources and 8 MiB on.  The variant keeps reads and writes apart in time: reader

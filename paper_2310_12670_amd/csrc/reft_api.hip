@@ -1572,17 +1572,11 @@ static bool few_dense_tiles(const reft_plan *p)
 }
 
 // Whether `rows` rows go through the burst kernel: very long rows, few span boundaries.  A launch into tensors
-// needs rows four times as long, and what the stream kernel writes through the L2 is only taken where the caller has
-// set from where on.
-static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors, bool over_source, const LaunchCfg &cfg)
+// needs rows four times as long.
+static bool burst_applies(const reft_plan *p, uint32_t rows, bool tensors)
 {
-    const uint64_t least = g_burst_min_bytes.load();
-    if (!g_burst.load() || p->L / (tensors ? 4 : 1) < least || rows > (uint32_t)kMaxSrc || rows < g_burst_min_rows.load())
-        return false;
-    if (least == kBurstMinBytes && !over_source && !cfg.capped && cfg.nontemporal &&
-        writes_through(rows, p->L / p->T, (rows + 1ull) * p->L, p->odd, false))
-        return false;
-    return few_dense_tiles(p);
+    return g_burst.load() && p->L / (tensors ? 4 : 1) >= g_burst_min_bytes.load() && rows <= (uint32_t)kMaxSrc &&
+           rows >= g_burst_min_rows.load() && few_dense_tiles(p);
 }
 
 // Whether some span's result goes to where a source row of the cached table has that very span.  The
@@ -1618,7 +1612,7 @@ static int xor_passes(reft_plan *p, const uint64_t *tab, uint32_t nrows, const u
     // Very long rows: reads and writes are separated in time with the burst kernel.  Destination spans that are not
     // all aligned alike relative to their stream offsets, which its staging image cannot represent, keep the stream
     // kernel, and more rows go through it in one pass, up to kMaxStreamSrc.
-    bool burst = burst_applies(p, nrows, dst_row != nullptr, over_source, cfg);
+    bool burst = burst_applies(p, nrows, dst_row != nullptr);
     uint64_t vb = (uint64_t)(uintptr_t)dst_contig;
     if (burst && dst_row) {
         bool have = false;

@@ -275,9 +275,7 @@ inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
 // 1.03, 1.01, 7 of 3.1 GB 1.02; 8 of 11.8 GB 1.025, 1.011, 1.000, 1.003, of 11.4 GB 0.999, 1.006, 0.996, 0.998, of 15.0 GB
 // 1.001, 0.993, 0.998, 0.991, of 15.4 GB 1.003, 0.996, 0.994, 0.997; 7 of 11.8 GB 1.028 to 1.005, of 15.0 GB 1.004, 1.000,
 // 0.998, 0.996, of 15.4 GB 1.010, 0.999, 0.993, 0.997.  Into tensors, 7 and 8 rows of 11.4 to 15.4 GB, 1.002 to 1.024 (so
-// only from four times the bytes on, more than the memory holds).  Streams that are written through (writes_through; all of
-// the above are): 8 rows of 15.0 and 15.4 GB 1.007 to 1.013, 7 1.017 to 1.033, into tensors 1.020 to 1.032, so
-// these are left to the stream kernel.
+// only from four times the bytes on, more than the memory holds).
 constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 13ull << 30;
 
 // The same two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes
