@@ -275,7 +275,9 @@ inline uint32_t link_cap(uint64_t link_wgs, uint32_t halves, uint32_t max_wgs)
 // 1.03, 1.01, 7 of 3.1 GB 1.02; 8 of 11.8 GB 1.025, 1.011, 1.000, 1.003, of 11.4 GB 0.999, 1.006, 0.996, 0.998, of 15.0 GB
 // 1.001, 0.993, 0.998, 0.991, of 15.4 GB 1.003, 0.996, 0.994, 0.997; 7 of 11.8 GB 1.028 to 1.005, of 15.0 GB 1.004, 1.000,
 // 0.998, 0.996, of 15.4 GB 1.010, 0.999, 0.993, 0.997.  Into tensors, 7 and 8 rows of 11.4 to 15.4 GB, 1.002 to 1.024 (so
-// only from four times the bytes on, more than the memory holds).
+// only from four times the bytes on, more than the memory holds).  Since results are written through (writes_through), 8
+// rows of 15.0 GB 0.9985, 0.9983, 0.9979, 0.9933, 0.9970 on five sets of a Llama-shaped job's tensors, 1.010 and 1.012 on two
+// made one after the other: a tie by where the tensors lie, so the rows stay.
 constexpr uint64_t kBurstMinRows = 7, kBurstMinBytes = 13ull << 30;
 
 // The same two for reft_reconstruct.  Its ordinary kernel (tiles, a persistent grid) mixes reads and writes
