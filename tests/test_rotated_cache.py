@@ -7,29 +7,10 @@ import random
 import numpy as np
 import pytest
 
-import test_table_cache
 from test_table_cache import lib  # noqa: F401  (a fixture)
 
 SIZES = [4096, 17, 0, 70_000, 333, 1 << 16, 900, 5]
 T, L = len(SIZES), sum(SIZES)
-
-test_table_cache.SOURCE = test_table_cache.SOURCE.replace(
-    "static hipError_t kernel(",
-    "static const uint64_t *last_tab;\nstatic uint64_t last_words;\nstatic hipError_t kernel(", 1).replace(
-    "    Clock &c = on(s);\n    for (auto part :",
-    "    last_tab = tab;\n    last_words = n + (row ? m : 0);\n    Clock &c = on(s);\n    for (auto part :", 1).replace(
-    "uint64_t sim_races() { return races; }",
-    """uint64_t sim_races() { return races; }
-uint64_t sim_uploads() { return uploads.size(); }
-uint64_t sim_table(uint64_t *out)                             // what the last kernel's table was uploaded from
-{
-    for (size_t i = uploads.size(); i-- > 0;)
-        if (uploads[i].lo <= (uintptr_t)last_tab && (uintptr_t)last_tab < uploads[i].hi) {
-            memcpy(out, (const void *)(sources[i].lo + ((uintptr_t)last_tab - uploads[i].lo)), last_words * 8);
-            return last_words;
-        }
-    return 0;
-}""", 1)
 
 
 class Rotated:

@@ -30,6 +30,8 @@ static Clock host;                                           // what the host ha
 static std::vector<Op> reads, uploads, sources;
 static uintptr_t current;                                    // the stream of the call under way
 static uint64_t races, foreign, events, unpinned;
+static const uint64_t *last_tab;                             // the last kernel's rows of pointers, and how many pointers
+static uint64_t last_words;
 static std::map<uintptr_t, size_t> pinned;
 
 static void join(Clock &a, const Clock &b)
@@ -66,6 +68,8 @@ static void look_up_all(const reft::PlanTables &pt)
 }
 static hipError_t kernel(const uint64_t *tab, uint64_t n, const uint64_t *row, uint64_t m, hipStream_t s)
 {
+    last_tab = tab;
+    last_words = n + (row ? m : 0);
     Clock &c = on(s);
     for (auto part : {std::pair<const uint64_t *, uint64_t>{tab, n}, {row, row ? m : 0}}) {
         if (!part.second) continue;
@@ -79,6 +83,16 @@ static hipError_t kernel(const uint64_t *tab, uint64_t n, const uint64_t *row, u
 extern "C" {
 void sim_call(uintptr_t s) { current = s; }
 uint64_t sim_races() { return races; }
+uint64_t sim_uploads() { return uploads.size(); }
+uint64_t sim_table(uint64_t *out)                            // what the last kernel's table was uploaded from
+{
+    for (size_t i = uploads.size(); i-- > 0;)
+        if (uploads[i].lo <= (uintptr_t)last_tab && (uintptr_t)last_tab < uploads[i].hi) {
+            memcpy(out, (const void *)(sources[i].lo + ((uintptr_t)last_tab - uploads[i].lo)), last_words * 8);
+            return last_words;
+        }
+    return 0;
+}
 uint64_t sim_foreign() { return foreign; }
 uint64_t sim_events() { return events; }
 
