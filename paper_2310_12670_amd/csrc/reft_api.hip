@@ -316,7 +316,9 @@ struct reft_plan {
         return PlanTables{d_off, d_unit_off, d_unit_span, d_tile_span, T, L, unit_shift, burst_shift, grid, unit, odd, windows};
     }
 
-    // lo < hi <= L
+    // lo < hi <= L.  All numbers of a span whose bytes are all in the range are dealt, also those behind its units that have
+    // no bytes (see align_of): a span that is turned has units under every one of them.  (Without them a launch that ended
+    // with such a span in front of the stream's end left up to 31 KiB of it unmoved.)
     StreamRange range(uint64_t lo, uint64_t hi) const
     {
         StreamRange r{lo, hi, 0, unit_off[T] - 1};
@@ -326,7 +328,8 @@ struct reft_plan {
         }
         if (hi < L) {
             const uint64_t i = (uint64_t)(std::upper_bound(off.begin(), off.end() - 1, hi - 1) - off.begin()) - 1;
-            r.last = unit_off[i] + last_unit_at(hi - 1 - off[i], head_of(off[i], grid, unit), unit);
+            r.last = hi == off[i + 1] ? unit_off[i + 1] - 1
+                                      : unit_off[i] + last_unit_at(hi - 1 - off[i], head_of(off[i], grid, unit), unit);
         }
         return r;
     }

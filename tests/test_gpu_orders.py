@@ -173,3 +173,49 @@ def test_pairs_of_waves_in_short_spans(dev, k, mean):  # noqa: F811
     while sum(sizes) < TRAFFIC // (k + 1):
         sizes.append(int(rng.integers(0, 2 * mean)) | 1)
     check_all(dev, sizes, k, None, seed=k, align=1)
+
+
+# a gathered run long enough for its launch to be spread, which ends with a span in front of the stream's end: because a span
+# that is copied follows, or because a bucket ends there
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("buckets", [False, True])
+@pytest.mark.parametrize("size", [70_001, 300_001, 1_500_000])
+def test_runs_that_end_with_a_span(dev, size, buckets, two):  # noqa: F811
+    n = (56 << 20) // size
+    sizes = [size] * n + ([size] * n + [5, 9 << 20] if buckets else [9 << 20, 5] + [size] * 9)
+    rng = np.random.default_rng(size)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(size)
+    T, L = len(sizes), sum(sizes)
+    lists = [size * n, size * n, 5 + (9 << 20)] if buckets else [L]
+    plan = reft.reft_plan_create(sizes, lists)
+    try:
+        a = torch.cuda.Stream()
+        b = torch.cuda.Stream() if two else a
+        ring = torch.empty(2 * reft.reft_plan_staging_slot_bytes(plan) + 256, dtype=torch.uint8, device=dev)[256:]
+        _, tensors = arena(sizes, rng.integers(0, 512, T), dev, gen)
+        want = torch.cat(tensors).cpu()
+        host = torch.zeros(L, dtype=torch.uint8, pin_memory=True)
+        for lo in range(len(lists)):
+            host.fill_(0x33)
+            ring.fill_(0x96)
+            torch.cuda.synchronize()
+            reft.reft_snapshot_pack_range(plan, tensors, ring, host, lo, len(lists), a, b)
+            reft.reft_snapshot_wait(plan)
+            begin = sum(lists[:lo])
+            assert torch.equal(host[begin:], want[begin:]) and bool((host[:begin] == 0x33).all()), lo
+        host.copy_(want)
+        for align in (1, 512):
+            raw, outs = arena(sizes, rng.integers(0, 512, T) // align * align, dev, gen)
+            raw.fill_(0x96)
+            ring.fill_(0x33)
+            torch.cuda.synchronize()
+            reft.reft_restore(plan, host, ring, outs, a, b)
+            reft.reft_restore_wait(plan)
+            assert torch.equal(torch.cat(outs).cpu(), want), align
+            for t in outs:
+                t.fill_(0x96)
+            assert bool((raw == 0x96).all())
+    finally:
+        torch.cuda.synchronize()
+        reft.reft_plan_destroy(plan)

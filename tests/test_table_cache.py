@@ -16,6 +16,7 @@ CSRC = os.path.join(ROOT, "paper_2310_12670_amd", "csrc")
 SOURCE = r"""
 #include <hip/hip_runtime_api.h>
 #include "reft_internal.hpp"
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -32,6 +33,8 @@ static uintptr_t current;                                    // the stream of th
 static uint64_t races, foreign, events, unpinned;
 static const uint64_t *last_tab;                             // the last kernel's rows of pointers, and how many pointers
 static uint64_t last_words;
+struct Launch { reft::PlanTables pt; reft::StreamRange range; };
+static std::vector<Launch> launches;                         // of the stream kernel
 static std::map<uintptr_t, size_t> pinned;
 
 static void join(Clock &a, const Clock &b)
@@ -135,7 +138,7 @@ uint64_t sim_end()                                           // operations that 
     uint64_t n = 0;
     for (auto *ops : {&reads, &uploads})
         for (const Op &o : *ops) n += !known(host, o);
-    streams.clear(), host.clear(), reads.clear(), uploads.clear(), sources.clear();
+    streams.clear(), host.clear(), reads.clear(), uploads.clear(), sources.clear(), launches.clear();
     races = foreign = events = unpinned = 0;
     return n;
 }
@@ -173,13 +176,21 @@ char __hip_fatbin[1];
 
 namespace reft {
 hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool, bool, const uint64_t *dtab, uint64_t,
-                         const StreamRange &, const LaunchCfg &, hipStream_t s) { look_up_all(pt); return kernel(tab, nrows * pt.T, dtab, pt.T, s); }
+                         const StreamRange &r, const LaunchCfg &, hipStream_t s)
+{
+    launches.push_back(Launch{pt, r});
+    look_up_all(pt);
+    return kernel(tab, nrows * pt.T, dtab, pt.T, s);
+}
 hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t, uint64_t, const StreamRange &,
                               const LaunchCfg &, hipStream_t s) { return kernel(tab, nrows * pt.T, nullptr, 0, s); }
 hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows, const uint64_t *dtab, uint64_t, uint64_t,
                                uint64_t, const LaunchCfg &, const BurstCfg &, hipStream_t s) { return kernel(tab, nrows * pt.T, dtab, pt.T, s); }
-hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t, const StreamRange &, const LaunchCfg &,
-                          hipStream_t s) { return kernel(tab, pt.T, nullptr, 0, s); }
+hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t, const StreamRange &r, const LaunchCfg &, hipStream_t s)
+{
+    launches.push_back(Launch{pt, r});
+    return kernel(tab, pt.T, nullptr, 0, s);
+}
 hipError_t launch_xor_contig(const SrcBases &, int, uint64_t, uint64_t, uint32_t, const LaunchCfg &, hipStream_t) { return hipSuccess; }
 hipError_t launch_xor_contig_burst(const SrcBases &, int, uint64_t, uint64_t, const LaunchCfg &, const BurstCfg &, hipStream_t) { return hipSuccess; }
 }
@@ -190,10 +201,8 @@ T, L = len(SIZES), sum(SIZES)
 BUF = 1 << 40
 
 
-@pytest.fixture(scope="module")
-def lib(tmp_path_factory):
-    d = tmp_path_factory.mktemp("table_cache")
-    (d / "runtime.cpp").write_text(SOURCE)
+def compile_with(runtime_source, d):
+    (d / "runtime.cpp").write_text(runtime_source)
     api, runtime, so = str(d / "api.o"), str(d / "runtime.o"), str(d / "lib.so")
     subprocess.run(["hipcc", "--offload-host-only", "--offload-arch=gfx950", "-fuse-cuid=none", "-O1", "-std=c++17", "-fPIC",
                     "-c", "-o", api, os.path.join(CSRC, "reft_api.hip")], check=True)
@@ -212,6 +221,11 @@ def lib(tmp_path_factory):
     for f in (lib.sim_races, lib.sim_foreign, lib.sim_events, lib.sim_end, lib.sim_unpinned):
         f.restype = u64
     return lib
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return compile_with(SOURCE, tmp_path_factory.mktemp("table_cache"))
 
 
 class Calls:
