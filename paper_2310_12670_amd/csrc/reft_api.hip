@@ -365,11 +365,19 @@ static uint64_t device_view_of_host(const void *host)
     return (uint64_t)(uintptr_t)d;
 }
 
-// The same for the `bytes` bytes from there on, or 0 if they are not one piece of such memory.
+// The same for the `bytes` bytes from there on, or 0 unless one allocation holds all of them (between two that both ends
+// lie in there may be memory that the GPU does not see).
 static uint64_t device_view_of_host(const void *host, uint64_t bytes)
 {
     const uint64_t a = device_view_of_host(host);
-    return a && device_view_of_host((const uint8_t *)host + bytes - 1) == a + bytes - 1 ? a : 0;
+    hipDeviceptr_t base = nullptr;
+    size_t n = 0;
+    if (!a) return 0;
+    if (hipMemGetAddressRange(&base, &n, (hipDeviceptr_t)(uintptr_t)a) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return a - (uint64_t)(uintptr_t)base + bytes <= n ? a : 0;
 }
 
 static int make_event(Event &e, unsigned flags = hipEventDisableTiming)

@@ -35,18 +35,25 @@ static const uint64_t *last_tab;                             // the last kernel'
 static uint64_t last_words;
 struct Launch { reft::PlanTables pt; reft::StreamRange range; };
 static std::vector<Launch> launches;                         // of the stream kernel
+static uintptr_t thread;                                     // the calling thread, which hipStreamPerThread's stream is of
+static std::map<uintptr_t, size_t> mapped;                   // host memory that kernels see, at its own addresses
+struct Access { Op op; bool write; };
+static std::vector<Access> accesses;                         // of kernels to contiguous memory, and of copies
+static uint64_t clashes, copies;
+static int64_t copies_left = -1;                             // copies up to one that fails
 static std::map<uintptr_t, size_t> pinned;
 
 static void join(Clock &a, const Clock &b)
 {
     for (auto &x : b) a[x.first] = a[x.first] < x.second ? x.second : a[x.first];
 }
+static uintptr_t id(hipStream_t s) { return s == hipStreamPerThread ? 1000 + thread : (uintptr_t)s; }
 static Clock &on(hipStream_t s)
 {
     if ((uintptr_t)s != current) ++foreign;
-    Clock &c = streams[(uintptr_t)s];
+    Clock &c = streams[id(s)];
     join(c, host);
-    ++c[(uintptr_t)s];
+    ++c[id(s)];
     return c;
 }
 static bool known(Clock &c, const Op &o) { return c[o.stream] >= o.index; }
@@ -57,7 +64,14 @@ static void check(const std::vector<Op> &ops, uintptr_t lo, uintptr_t hi, Clock 
 }
 static Op op(const void *p, size_t n, hipStream_t s, Clock &c)
 {
-    return Op{(uintptr_t)p, (uintptr_t)p + n, (uintptr_t)s, c[(uintptr_t)s]};
+    return Op{(uintptr_t)p, (uintptr_t)p + n, id(s), c[id(s)]};
+}
+static void access(uint64_t p, uint64_t n, bool write, hipStream_t s, Clock &c)
+{
+    const Op o = op((const void *)p, n, s, c);
+    for (const Access &a : accesses)
+        if (a.op.lo < o.hi && o.lo < a.op.hi && (a.write || write) && !known(c, a.op)) ++clashes;
+    accesses.push_back(Access{o, write});
 }
 // Every unit's span by the look-up table, as a wave finds it, against the unit numbers.
 static void look_up_all(const reft::PlanTables &pt)
@@ -85,8 +99,13 @@ static hipError_t kernel(const uint64_t *tab, uint64_t n, const uint64_t *row, u
 
 extern "C" {
 void sim_call(uintptr_t s) { current = s; }
+void sim_thread(uintptr_t t) { thread = t; }
+void sim_map(uintptr_t p, size_t n) { mapped[p] = n; }
+void sim_fail(int64_t copies) { copies_left = copies; }
+uint64_t sim_clashes() { return clashes; }                   // accesses to the same memory that nothing keeps in order
 uint64_t sim_races() { return races; }
 uint64_t sim_uploads() { return uploads.size(); }
+uint64_t sim_copies() { return copies; }
 uint64_t sim_table(uint64_t *out)                            // what the last kernel's table was uploaded from
 {
     for (size_t i = uploads.size(); i-- > 0;)
@@ -101,7 +120,11 @@ uint64_t sim_events() { return events; }
 
 hipError_t hipMemcpyAsync(void *d, const void *h, size_t n, hipMemcpyKind, hipStream_t s)
 {
+    ++copies;
+    if (copies_left >= 0 && copies_left-- == 0) return hipErrorNotSupported;
     Clock &c = on(s);
+    access((uint64_t)h, n, false, s, c);
+    access((uint64_t)d, n, true, s, c);
     const Op to = op(d, n, s, c), from = op(h, n, s, c);
     check(reads, to.lo, to.hi, c);
     check(uploads, to.lo, to.hi, c);
@@ -121,7 +144,7 @@ hipError_t hipEventQuery(hipEvent_t e)
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { join(on(s), ((Event *)e)->clock); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t s) { join(host, streams[(uintptr_t)s]); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { join(host, streams[id(s)]); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { for (auto &x : streams) join(host, x.second); return hipSuccess; }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *, unsigned) { return hipErrorNotSupported; }
@@ -138,8 +161,9 @@ uint64_t sim_end()                                           // operations that 
     uint64_t n = 0;
     for (auto *ops : {&reads, &uploads})
         for (const Op &o : *ops) n += !known(host, o);
-    streams.clear(), host.clear(), reads.clear(), uploads.clear(), sources.clear(), launches.clear();
-    races = foreign = events = unpinned = 0;
+    streams.clear(), host.clear(), reads.clear(), uploads.clear(), sources.clear(), launches.clear(), accesses.clear(), mapped.clear();
+    races = foreign = events = unpinned = clashes = thread = 0;
+    copies_left = -1;
     return n;
 }
 hipError_t hipMemcpy(void *d, const void *h, size_t n, hipMemcpyKind)
@@ -156,7 +180,20 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { memset(p,
 const char *hipGetErrorString(hipError_t) { return "no GPU"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { static char x[1 << 20]; *p = x; return hipSuccess; }
-hipError_t hipHostGetDevicePointer(void **, void *, unsigned) { return hipErrorNotSupported; }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *n, hipDeviceptr_t p)
+{
+    auto it = mapped.upper_bound((uintptr_t)p);
+    if (it == mapped.begin() || (uintptr_t)p >= (--it)->first + it->second) return hipErrorInvalidValue;
+    *base = (hipDeviceptr_t)it->first;
+    *n = it->second;
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned)
+{
+    size_t n;
+    *d = h;
+    return hipMemGetAddressRange(&h, &n, h);
+}
 hipError_t hipGraphAddMemcpyNode1D(hipGraphNode_t *, hipGraph_t, const hipGraphNode_t *, size_t, void *, const void *, size_t,
                                    hipMemcpyKind) { return hipErrorNotSupported; }
 hipError_t hipGraphCreate(hipGraph_t *, unsigned) { return hipErrorNotSupported; }
@@ -175,21 +212,25 @@ char __hip_fatbin[1];
 }
 
 namespace reft {
-hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool, bool, const uint64_t *dtab, uint64_t,
+hipError_t launch_gather(const PlanTables &pt, const uint64_t *tab, int nrows, bool, bool, const uint64_t *dtab, uint64_t vb,
                          const StreamRange &r, const LaunchCfg &, hipStream_t s)
 {
     launches.push_back(Launch{pt, r});
     look_up_all(pt);
-    return kernel(tab, nrows * pt.T, dtab, pt.T, s);
+    kernel(tab, nrows * pt.T, dtab, pt.T, s);
+    if (!dtab) access(vb + r.lo, r.hi - r.lo, true, s, on(s));
+    return hipSuccess;
 }
 hipError_t launch_gather_pack(const PlanTables &pt, const uint64_t *tab, int nrows, uint64_t, uint64_t, const StreamRange &,
                               const LaunchCfg &, hipStream_t s) { return kernel(tab, nrows * pt.T, nullptr, 0, s); }
 hipError_t launch_gather_burst(const PlanTables &pt, const uint64_t *tab, int nrows, const uint64_t *dtab, uint64_t, uint64_t,
                                uint64_t, const LaunchCfg &, const BurstCfg &, hipStream_t s) { return kernel(tab, nrows * pt.T, dtab, pt.T, s); }
-hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t, const StreamRange &r, const LaunchCfg &, hipStream_t s)
+hipError_t launch_scatter(const PlanTables &pt, const uint64_t *tab, uint64_t vb, const StreamRange &r, const LaunchCfg &, hipStream_t s)
 {
     launches.push_back(Launch{pt, r});
-    return kernel(tab, pt.T, nullptr, 0, s);
+    kernel(tab, pt.T, nullptr, 0, s);
+    access(vb + r.lo, r.hi - r.lo, false, s, on(s));
+    return hipSuccess;
 }
 hipError_t launch_xor_contig(const SrcBases &, int, uint64_t, uint64_t, uint32_t, const LaunchCfg &, hipStream_t) { return hipSuccess; }
 hipError_t launch_xor_contig_burst(const SrcBases &, int, uint64_t, uint64_t, const LaunchCfg &, const BurstCfg &, hipStream_t) { return hipSuccess; }
