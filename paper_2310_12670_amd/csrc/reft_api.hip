@@ -279,9 +279,9 @@ struct reft_plan {
     // stream on which the most recent snapshot's completion event was recorded
     hipStream_t last_pack_stream = nullptr;
     // the last snapshot (restore) that used the ring of slots had one stream for everything and left no events behind the
-    // slots: its completion event says when they are free, or that stream's order
+    // slots: its completion event says when they are free
     bool pack_alone = false, rest_alone = false;
-    hipStream_t pack_stream = nullptr, rest_stream = nullptr;
+    hipStream_t rest_stream = nullptr;                        // on which rest_done was recorded
     // device address of the library's static scratch on this plan's GPU (see reft_parity_encode_noalloc)
     unsigned char *scratch = nullptr;
     // bucket pipelines
@@ -400,6 +400,10 @@ static int wait_on(hipStream_t s, const Event &e)
     return REFT_OK;
 }
 
+// Whether work given to `a` and to `b`, maybe by two threads in turn, runs in order by itself: hipStreamPerThread is one
+// handle for a stream of every thread's own.
+static bool same_stream(hipStream_t a, hipStream_t b) { return a == b && a != hipStreamPerThread; }
+
 // ------------------------------------------------------------------------------------------------
 // static device memory of the library
 // ------------------------------------------------------------------------------------------------
@@ -494,7 +498,7 @@ static int retire_entry(PtrEntry &e)
 static int use_entry(reft_plan *p, int entry, hipStream_t s, const uint64_t **dev_tab)
 {
     PtrEntry &e = p->ring[entry];
-    if (e.up_stream != s && e.uploaded.recorded) HIPCHK(hipStreamWaitEvent(s, e.uploaded.ev, 0));
+    if (!same_stream(e.up_stream, s) && e.uploaded.recorded) HIPCHK(hipStreamWaitEvent(s, e.uploaded.ev, 0));
     e.tick = ++p->ring_tick;
     *dev_tab = p->d_ptr + e.pos;
     return REFT_OK;
@@ -569,7 +573,7 @@ static int release_ptrs(reft_plan *p, int entry, hipStream_t s)
     }
     int i = -1;
     for (int u = 0; u < kUsers && i < 0; ++u)
-        if (e.used[u].recorded && e.user[u] == s) i = u;
+        if (e.used[u].recorded && same_stream(e.user[u], s)) i = u;
     for (int u = 0; u < kUsers && i < 0; ++u)
         if (!e.used[u].recorded) i = u;
     for (int u = 0; u < kUsers && i < 0; ++u)
@@ -1142,7 +1146,7 @@ static int issue_piece_copies(reft_plan *p, const std::vector<Dma> &dmas, hipStr
 static int record_pack_done(reft_plan *p, hipStream_t s)
 {
     int rc;
-    if (p->pack_done.recorded && p->last_pack_stream != s && (rc = wait_on(s, p->pack_done))) return rc;
+    if (p->pack_done.recorded && !same_stream(p->last_pack_stream, s) && (rc = wait_on(s, p->pack_done))) return rc;
     p->last_pack_stream = s;
     return record(p->pack_done, s);
 }
@@ -1169,20 +1173,16 @@ static int staging_slots(const reft_plan *p, const void *staging, uint64_t stagi
 // events behind its slots, but is through where its completion event `done` is.
 //
 // (Such calls need no events between their kernels and copies.  Each made the device write its caches back and what was
-// behind it wait: 14.7 MB in 256 tensors saved and loaded 578 us with them, 562 without, 2 MB 127 and 111.)
-static int ring_taken(hipStream_t s, bool alone, hipStream_t last, const Event &done)
-{
-    return alone && last != s ? wait_on(s, done) : REFT_OK;
-}
+// behind it wait: 14.7 MB in 256 tensors saved and loaded 578 us with them, 562 without, 2 MB 127 and 111.  A wait for an
+// event of the same stream costs nothing there, so none is left out: a handle does not tell whether it is the same.)
+static int ring_taken(hipStream_t s, bool alone, const Event &done) { return alone ? wait_on(s, done) : REFT_OK; }
 
 // Record the restore completion event, which also stands for the ring of slots' last use (see ring_taken).
 static int record_rest_done(reft_plan *p, hipStream_t s)
 {
     int rc;
-    if (p->rest_alone && p->rest_stream != s) {
-        if ((rc = wait_on(s, p->rest_done))) return rc;
-        p->rest_stream = s;
-    }
+    if (p->rest_alone && !same_stream(p->rest_stream, s) && (rc = wait_on(s, p->rest_done))) return rc;
+    p->rest_stream = s;
     return record(p->rest_done, s);
 }
 
@@ -1267,9 +1267,8 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
         const bool alone = ps == cs;                      // one stream, in order by itself
-        if ((rc = ring_taken(ps, p->pack_alone, p->pack_stream, p->pack_done))) return rc;
+        if ((rc = ring_taken(ps, p->pack_alone, p->pack_done))) return rc;
         p->pack_alone = alone;
-        p->pack_stream = ps;
         uint64_t batch = 0;
         for (uint64_t r0 = 0; r0 < runs.size(); r0 += per_group, ++batch) {
             const int g = (int)(batch % (uint64_t)ngroups);
@@ -2262,9 +2261,8 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
         const LaunchCfg cfg = launch_cfg(p);
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
-        if ((rc = ring_taken(cs, p->rest_alone, p->rest_stream, p->rest_done))) return rc;
+        if ((rc = ring_taken(cs, p->rest_alone, p->rest_done))) return rc;
         p->rest_alone = alone;
-        p->rest_stream = cs;
         uint64_t batch = 0;
         for (uint64_t r0 = 0; r0 < runs.size(); r0 += per_group, ++batch) {
             const int g = (int)(batch % (uint64_t)ngroups);

@@ -20,9 +20,10 @@ def lib(tmp_path_factory):
     lib.sim_map.argtypes = [u64, u64]
     lib.sim_fail.argtypes = [ctypes.c_int64]
     lib.sim_thread.argtypes = [u64]
+    lib.reft_snapshot_wait.argtypes = lib.reft_restore_wait.argtypes = [p]
     lib.reft_plan_staging_slot_bytes.argtypes = [p]
     lib.reft_plan_staging_slot_bytes.restype = u64
-    lib.sim_clashes.restype = lib.sim_uploads.restype = lib.sim_copies.restype = u64
+    lib.sim_clashes.restype = lib.sim_unfinished.restype = lib.sim_uploads.restype = lib.sim_copies.restype = u64
     return lib
 
 
@@ -60,4 +61,39 @@ def test_kernels_see_host_memory_of_one_piece(lib, pieces, copied, load):
     before = lib.sim_copies()
     assert c.call(load, 1, 1, host=HOST) == 0
     assert (lib.sim_copies() > before + 1) == copied      # (the pointers' upload is a copy in any case)
+    c.end()
+
+
+PER_THREAD = 2               # hipStreamPerThread: one handle, a stream of its own in every thread
+
+
+@pytest.mark.parametrize("load", [False, True])
+@pytest.mark.parametrize("second", [(PER_THREAD, PER_THREAD), (PER_THREAD, 5), (5, PER_THREAD), (5, 5)])
+@pytest.mark.parametrize("first", [(PER_THREAD, PER_THREAD), (PER_THREAD, 4), (4, PER_THREAD), (4, 4)])
+def test_threads_whose_streams_share_a_handle(lib, first, second, load):
+    """One thread's calls after another's, on the same ring: one after the other, whatever their streams."""
+    c = Calls(lib, 100_000)
+    for i in range(4):
+        lib.sim_thread(i)
+        assert c.call(load, *(first if i % 2 == 0 else second)) == 0
+        assert lib.sim_clashes() == 0
+        assert lib.sim_races() == 0
+    lib.sim_call(PER_THREAD)
+    assert (lib.reft_restore_wait if load else lib.reft_snapshot_wait)(c.plan) == 0
+    # tables, slots and the host's memory are free once the host knows that the last call has ended
+    assert lib.sim_unfinished() == 0
+    c.end()
+
+
+def test_pointer_tables_of_threads_whose_streams_share_a_handle(lib):
+    """A table that one thread's call has uploaded, used by another's, and overwritten once neither reads it any more."""
+    p = ctypes.c_void_p
+    lib.reft_pack_device.argtypes = [p, p, p, ctypes.c_uint64, p]
+    c = Calls(lib)
+    for i in range(400):
+        lib.sim_thread(i % 3)
+        lib.sim_call(PER_THREAD)
+        ptrs = (ctypes.c_void_p * T)(*range((1 << 44) + (i // 5 << 30), (1 << 44) + (i // 5 << 30) + T))
+        assert lib.reft_pack_device(c.plan, ptrs, HOST + (i << 30), L, PER_THREAD) == 0
+        assert lib.sim_races() == 0
     c.end()

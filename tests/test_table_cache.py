@@ -128,7 +128,8 @@ hipError_t hipMemcpyAsync(void *d, const void *h, size_t n, hipMemcpyKind, hipSt
     const Op to = op(d, n, s, c), from = op(h, n, s, c);
     check(reads, to.lo, to.hi, c);
     check(uploads, to.lo, to.hi, c);
-    check(sources, from.lo, from.hi, host);                  // the host has just written there
+    auto it = pinned.upper_bound(from.lo);                   // the host has just written there
+    if (it != pinned.begin() && from.lo < (--it)->first + it->second) check(sources, from.lo, from.hi, host);
     uploads.push_back(to);
     sources.push_back(from);
     return hipSuccess;
@@ -156,6 +157,12 @@ static hipError_t release(void *p) { free(p); return hipSuccess; }
 hipError_t hipFree(void *p) { return release(p); }
 hipError_t hipHostFree(void *p) { pinned.erase((uintptr_t)p); return release(p); }
 uint64_t sim_unpinned() { return unpinned; }
+uint64_t sim_unfinished()                                    // accesses that the host does not know to have ended
+{
+    uint64_t n = 0;
+    for (const Access &a : accesses) n += !known(host, a.op);
+    return n;
+}
 uint64_t sim_end()                                           // operations that the host does not know to have ended
 {
     uint64_t n = 0;
