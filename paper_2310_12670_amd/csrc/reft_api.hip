@@ -1177,6 +1177,32 @@ static int staging_slots(const reft_plan *p, const void *staging, uint64_t stagi
 // event of the same stream costs nothing there, so none is left out: a handle does not tell whether it is the same.)
 static int ring_taken(hipStream_t s, bool alone, const Event &done) { return alone ? wait_on(s, done) : REFT_OK; }
 
+// Where a staged call ends before its completion event is recorded: what it has queued, first work on `first`, then work on
+// `second` that waits for it, still uses slots and its pointer table.
+struct FailedCall {
+    reft_plan *p;
+    hipStream_t first, second, reader;        // reader: of the two, the one whose kernels read the table
+    Event *filled, *free;
+    int entry = 0;
+    bool armed = false;
+
+    int done(int rc)
+    {
+        if (rc == REFT_OK) armed = false;
+        return rc;
+    }
+    ~FailedCall()
+    {
+        if (!armed) return;
+        char text[sizeof g_err];
+        memcpy(text, g_err, sizeof text);
+        if (first == second || (record(filled[0], first) == REFT_OK && wait_on(second, filled[0]) == REFT_OK))
+            for (int g = 0; g < kGroups; ++g) (void)record(free[g], second);
+        (void)release_ptrs(p, entry, reader);
+        memcpy(g_err, text, sizeof text);
+    }
+};
+
 // Record the restore completion event, which also stands for the ring of slots' last use (see ring_taken).
 static int record_rest_done(reft_plan *p, hipStream_t s)
 {
@@ -1261,8 +1287,10 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         if ((rc = record(p->pack_begin, ps))) return rc;
         if ((rc = wait_on(cs, p->pack_begin))) return rc;
     }
+    FailedCall failed{p, ps, cs, ps, p->pack_filled, p->pack_free};
     if (!runs.empty()) {
-        if ((rc = upload_ptrs(p, span_ptrs, 1, ps, &tab, &entry))) return rc;
+        if ((rc = upload_ptrs(p, span_ptrs, 1, ps, &tab, &failed.entry))) return rc;
+        failed.armed = true;
         const LaunchCfg cfg = launch_cfg(p);
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
@@ -1293,7 +1321,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
             }
             if (!alone && (rc = record(p->pack_free[g], cs))) return rc;
         }
-        if ((rc = release_ptrs(p, entry, ps))) return rc;
+        if ((rc = release_ptrs(p, failed.entry, ps))) return rc;
     }
     const uint64_t gmode = g_graph_copies.load();
     if (gmode && g_dma_streams.load() == 1 && dmas.size() >= 8) {
@@ -1305,7 +1333,7 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
                })))
         return rc;
     // completion: every copy above is on copy_stream, the gathered ones behind their kernels
-    return record_pack_done(p, cs);
+    return failed.done(record_pack_done(p, cs));
     REFT_GUARD_END("reft_snapshot_pack")
 }
 
@@ -2256,8 +2284,10 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
                                          st);
                })))
         return rc;
+    FailedCall failed{p, cs, us, us, p->rest_filled, p->rest_free};
     if (!runs.empty()) {
-        if ((rc = upload_ptrs(p, span_ptrs, 1, us, &tab, &entry))) return rc;
+        if ((rc = upload_ptrs(p, span_ptrs, 1, us, &tab, &failed.entry))) return rc;
+        failed.armed = true;
         const LaunchCfg cfg = launch_cfg(p);
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
@@ -2286,11 +2316,11 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
             }
             if (!alone && (rc = record(p->rest_free[g], us))) return rc;
         }
-        if ((rc = release_ptrs(p, entry, us))) return rc;
+        if ((rc = release_ptrs(p, failed.entry, us))) return rc;
     }
     // completion on unpack_stream: behind the scatter kernels and behind every direct copy
     if (!alone && ((rc = record(p->rest_copied, cs)) || (rc = wait_on(us, p->rest_copied)))) return rc;
-    return record_rest_done(p, us);
+    return failed.done(record_rest_done(p, us));
     REFT_GUARD_END("reft_restore")
 }
 

@@ -97,3 +97,19 @@ def test_pointer_tables_of_threads_whose_streams_share_a_handle(lib):
         assert lib.reft_pack_device(c.plan, ptrs, HOST + (i << 30), L, PER_THREAD) == 0
         assert lib.sim_races() == 0
     c.end()
+
+
+@pytest.mark.parametrize("load", [False, True])
+@pytest.mark.parametrize("then", [(1, 1), (4, 5), (3, 4), (2, 2)])
+@pytest.mark.parametrize("streams", [(1, 1), (1, 3)])
+@pytest.mark.parametrize("copies", [1, 2, 3, 5, 6])
+def test_calls_that_fail_midway(lib, copies, streams, then, load):
+    """What a failed call has queued still reads and writes the slots: a later call keeps behind it."""
+    c = Calls(lib, 100_000)
+    assert c.call(load, *streams) == 0
+    lib.sim_fail(copies + 1)                               # the pointers' upload, and then so many
+    assert c.call(load, *streams) != 0
+    lib.sim_fail(-1)
+    assert c.call(load, *then) == 0
+    assert lib.sim_clashes() == 0
+    c.end()
