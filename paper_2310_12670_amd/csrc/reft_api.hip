@@ -225,6 +225,16 @@ constexpr uint32_t kContig = 0xffffffffu, kZeros = 0xfffffffeu;
 constexpr uint32_t kOut = 0xffffffffu;   // the tensors that receive a decoded shard
 }  // namespace
 
+// What a plan knows of the rings of slots that staged calls were given.
+struct SlotRing {
+    bool alone = false;               // the last call had one stream for everything and left no events behind its slots: its
+                                      // completion event says when they are free
+    int known = 0;
+    struct Layout {                   // where groups lay: group g at `at` + g * `bytes`
+        uint64_t at, bytes;
+    } layout[4];                      // no two in the same memory
+};
+
 // Pointers that a caller passed, and where in the derived plan's cache the rows made of them went.
 struct SeenPointers {
     std::vector<const void *> ptrs;
@@ -278,9 +288,7 @@ struct reft_plan {
     uint64_t pieces_tick = 0;
     // stream on which the most recent snapshot's completion event was recorded
     hipStream_t last_pack_stream = nullptr;
-    // the last snapshot (restore) that used the ring of slots had one stream for everything and left no events behind the
-    // slots: its completion event says when they are free
-    bool pack_alone = false, rest_alone = false;
+    SlotRing pack_ring, rest_ring;                            // of snapshots, and of restores
     hipStream_t rest_stream = nullptr;                        // on which rest_done was recorded
     // device address of the library's static scratch on this plan's GPU (see reft_parity_encode_noalloc)
     unsigned char *scratch = nullptr;
@@ -1169,13 +1177,37 @@ static int staging_slots(const reft_plan *p, const void *staging, uint64_t stagi
     return REFT_OK;
 }
 
-// Before a staged call puts anything into the ring of slots, on stream s: a call that had one stream for everything left no
-// events behind its slots, but is through where its completion event `done` is.
+// Before a staged call puts anything into the ring of slots, on stream s.  Its groups then wait for the events behind the same
+// group of calls before, free[g], the first one first.  Before that it waits for what these do not stand for:
 //
+// A call that had one stream for everything left none behind its slots, but is through where its completion event `done` is.
 // (Such calls need no events between their kernels and copies.  Each made the device write its caches back and what was
 // behind it wait: 14.7 MB in 256 tensors saved and loaded 578 us with them, 562 without, 2 MB 127 and 111.  A wait for an
 // event of the same stream costs nothing there, so none is left out: a handle does not tell whether it is the same.)
-static int ring_taken(hipStream_t s, bool alone, const Event &done) { return alone ? wait_on(s, done) : REFT_OK; }
+//
+// Where a ring takes part of the memory of one with groups of another size or at another place, a group's memory may have
+// been the other group's.
+static int ring_taken(SlotRing &r, hipStream_t s, uint64_t at, uint64_t group_bytes, bool alone, const Event *free, const Event &done)
+{
+    int rc;
+    if (r.alone && (rc = wait_on(s, done))) return rc;
+    bool is_known = false, apart = true;
+    for (int i = 0; i < r.known; ++i) {
+        const SlotRing::Layout &l = r.layout[i];
+        if (l.at == at && l.bytes == group_bytes) is_known = true;
+        else if (l.at < at + kGroups * group_bytes && at < l.at + kGroups * l.bytes) apart = false;
+    }
+    if (!is_known) {
+        if (!apart || r.known == (int)(sizeof r.layout / sizeof *r.layout)) {
+            for (int g = 0; g < kGroups; ++g)
+                if ((rc = wait_on(s, free[g]))) return rc;
+            r.known = 0;
+        }
+        r.layout[r.known++] = SlotRing::Layout{at, group_bytes};
+    }
+    r.alone = alone;
+    return REFT_OK;
+}
 
 // Where a staged call ends before its completion event is recorded: what it has queued, first work on `first`, then work on
 // `second` that waits for it, still uses slots and its pointer table.
@@ -1207,7 +1239,7 @@ struct FailedCall {
 static int record_rest_done(reft_plan *p, hipStream_t s)
 {
     int rc;
-    if (p->rest_alone && !same_stream(p->rest_stream, s) && (rc = wait_on(s, p->rest_done))) return rc;
+    if (p->rest_ring.alone && !same_stream(p->rest_stream, s) && (rc = wait_on(s, p->rest_done))) return rc;
     p->rest_stream = s;
     return record(p->rest_done, s);
 }
@@ -1295,8 +1327,8 @@ extern "C" int reft_snapshot_pack_range(reft_plan *p, const void *const *span_pt
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
         const bool alone = ps == cs;                      // one stream, in order by itself
-        if ((rc = ring_taken(ps, p->pack_alone, p->pack_done))) return rc;
-        p->pack_alone = alone;
+        if ((rc = ring_taken(p->pack_ring, ps, (uint64_t)(uintptr_t)staging, per_group * stride, alone, p->pack_free, p->pack_done)))
+            return rc;
         uint64_t batch = 0;
         for (uint64_t r0 = 0; r0 < runs.size(); r0 += per_group, ++batch) {
             const int g = (int)(batch % (uint64_t)ngroups);
@@ -2291,8 +2323,8 @@ extern "C" int reft_restore(reft_plan *p, const void *host_src, uint64_t host_by
         const LaunchCfg cfg = launch_cfg(p);
         const int ngroups = nslots >= kGroups ? kGroups : 1;
         const uint64_t per_group = (uint64_t)(nslots / ngroups);
-        if ((rc = ring_taken(cs, p->rest_alone, p->rest_done))) return rc;
-        p->rest_alone = alone;
+        if ((rc = ring_taken(p->rest_ring, cs, (uint64_t)(uintptr_t)staging, per_group * stride, alone, p->rest_free, p->rest_done)))
+            return rc;
         uint64_t batch = 0;
         for (uint64_t r0 = 0; r0 < runs.size(); r0 += per_group, ++batch) {
             const int g = (int)(batch % (uint64_t)ngroups);

@@ -113,3 +113,18 @@ def test_calls_that_fail_midway(lib, copies, streams, then, load):
     assert c.call(load, *then) == 0
     assert lib.sim_clashes() == 0
     c.end()
+
+
+@pytest.mark.parametrize("load", [False, True])
+@pytest.mark.parametrize("calls", [[(2, 0), (6, 0)], [(6, 0), (2, 0)], [(6, 0), (2, 0), (6, 0)], [(4, 0), (4, 2), (4, 0)], [(6, 1), (3, 0), (6, 1), (2, 4)],
+                                   [(2, 0), (2, 8), (2, 0), (2, 8)], [(1, 0), (4, 0), (1, 2), (8, 0), (3, 3)],
+                                   [(2, 2 * i) for i in range(9)] + [(9, 0), (2, 4), (64, 0)]])
+@pytest.mark.parametrize("alone", [(), (0, 2), (1,), (0, 1, 2, 3)])
+def test_rings_of_other_sizes_and_places(lib, calls, alone, load):
+    """Calls whose rings lie in the same memory with other numbers of slots, or in part of it; `alone`: those on one stream."""
+    c = Calls(lib, 40_000)
+    for i, (slots, first) in enumerate(calls):
+        a = 10 + 2 * i
+        assert c.call(load, a, a if i in alone else a + 1, RING + first * c.slot, slots) == 0
+        assert lib.sim_clashes() == 0, i
+    c.end()
