@@ -1229,7 +1229,8 @@ struct FailedCall {
         char text[sizeof g_err];
         memcpy(text, g_err, sizeof text);
         if (first == second || (record(filled[0], first) == REFT_OK && wait_on(second, filled[0]) == REFT_OK))
-            for (int g = 0; g < kGroups; ++g) (void)record(free[g], second);
+            for (int g = 0; g < kGroups; ++g)        // (a group that it has not come to may still be an earlier call's)
+                if (wait_on(second, free[g]) == REFT_OK) (void)record(free[g], second);
         (void)release_ptrs(p, entry, reader);
         memcpy(g_err, text, sizeof text);
     }

@@ -1,6 +1,7 @@
 """Staged snapshots and restores without a GPU (the runtime of test_table_cache.py, which sees two accesses to the same memory
 that neither a stream's order nor an event keeps apart): whose memory kernels touch, and the ring of slots from call to call."""
 import ctypes
+import random
 
 import pytest
 
@@ -128,3 +129,21 @@ def test_rings_of_other_sizes_and_places(lib, calls, alone, load):
         assert c.call(load, a, a if i in alone else a + 1, RING + first * c.slot, slots) == 0
         assert lib.sim_clashes() == 0, i
     c.end()
+
+
+@pytest.mark.parametrize("load", [False, True])
+@pytest.mark.parametrize("seed", range(20))
+def test_calls_in_any_order(lib, seed, load):
+    """Rings anywhere in one piece of memory, one stream and two, threads that share a handle, a call in ten that fails."""
+    rng = random.Random(seed)
+    for bucket in (0, 20_000, 40_000, 150_000):
+        c = Calls(lib, bucket)
+        for i in range(25):
+            first = rng.choice((None, 1, 3, 4, 5, PER_THREAD))
+            second = first if rng.random() < 0.5 else rng.choice((None, 1, 3, 4, 5, PER_THREAD))
+            lib.sim_thread(rng.randrange(3))
+            lib.sim_fail(rng.randrange(8) if rng.random() < 0.1 else -1)
+            c.call(load, first, second, RING + rng.randrange(12) * c.slot, rng.choice((1, 2, 3, 5, 8, 64)))
+            lib.sim_fail(-1)
+            assert lib.sim_clashes() == 0, i
+        c.end()
