@@ -152,7 +152,7 @@ def test_calls_in_any_order(lib, seed, load):
 @pytest.mark.parametrize("load", [False, True])
 def test_a_failed_call_keeps_what_other_groups_wait_for(lib, load):
     """Two groups of slots under way; a call elsewhere that fails in its first group; one across the second group's slots."""
-    c = Calls(lib, 20_000)
+    c = Calls(lib, 40_000)
     assert c.call(load, 4, 1, RING + c.slot, 8) == 0
     lib.sim_fail(3)
     assert c.call(load, 5, 5, RING + 11 * c.slot, 1) != 0
