@@ -155,7 +155,7 @@ def test_a_failed_call_keeps_what_other_groups_wait_for(lib, load):
     c = Calls(lib, 40_000)
     assert c.call(load, 4, 1, RING + c.slot, 8) == 0
     lib.sim_fail(3)
-    assert c.call(load, 5, 5, RING + 11 * c.slot, 1) != 0
+    assert c.call(load, 5, 6, RING + 11 * c.slot, 1) != 0
     lib.sim_fail(-1)
     assert c.call(load, 3, 3, RING + 6 * c.slot, 5) == 0
     assert lib.sim_clashes() == 0
