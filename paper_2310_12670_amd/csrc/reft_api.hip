@@ -242,10 +242,18 @@ struct SeenPointers {
     uint64_t upload = 0;              // 0: none
 };
 
+// The spans whose pointers a recipe may ask for: of member `of`'s shard or, with kOut, of the tensors.
+struct PointerRange {
+    uint32_t of;
+    uint64_t first, end;
+};
+
 struct DerivedPlan {
     reft_plan *plan = nullptr;
     uint32_t nwin = 0;
     std::vector<RowRecipe> recipe;
+    std::vector<PointerRange> uses;   // one for each member
+    std::vector<uint32_t> units;      // members whose parity units it asks for
     SeenPointers seen[2];             // of the two most recent sets, seen[last] the newer one's
     int last = 0;
 };
@@ -1894,6 +1902,17 @@ static int ensure_zeros(reft_plan *p)
     return REFT_OK;
 }
 
+static void add_use(std::vector<PointerRange> &uses, uint32_t of, uint64_t first, uint64_t end)
+{
+    for (PointerRange &r : uses)
+        if (r.of == of) {
+            r.first = std::min(r.first, first);
+            r.end = std::max(r.end, end);
+            return;
+        }
+    uses.push_back(PointerRange{of, first, end});
+}
+
 // The plan whose stream is the segments one after the other and whose spans are the merged pieces of
 // their windows (every span boundary of every window becomes a boundary), with the recipe that turns
 // the caller's pointers into its rows.  Built on first use and kept in the base plan.
@@ -1902,12 +1921,18 @@ static int derived_plan(reft_plan *p, uint64_t key, const std::vector<Segment> &
 {
     int rc = ensure_zeros(p);
     if (rc) return rc;
+    DerivedPlan dp;
     std::vector<uint64_t> sizes;
     std::vector<std::pair<uint32_t, uint64_t>> piece;      // (segment, offset in it) of every piece
     for (uint32_t g = 0; g < segs.size(); ++g) {
         std::vector<uint64_t> cuts{0, segs[g].len};
         for (const WinSpec &win : segs[g].wins) {
-            if (win.contig) continue;
+            if (win.contig) {
+                dp.units.push_back(win.of);
+                continue;
+            }
+            add_use(dp.uses, win.of, (uint64_t)(std::upper_bound(p->off.begin(), p->off.end(), win.w) - p->off.begin()) - 1,
+                    (uint64_t)(std::lower_bound(p->off.begin(), p->off.end() - 1, win.w + segs[g].len) - p->off.begin()));
             // span starts strictly inside (w, w + len); off[T] = L makes the end of the stream a
             // boundary too, so the zero extension of the last segment starts on a piece boundary
             auto lo = std::upper_bound(p->off.begin(), p->off.end(), win.w);
@@ -1920,7 +1945,6 @@ static int derived_plan(reft_plan *p, uint64_t key, const std::vector<Segment> &
             piece.emplace_back(g, cuts[i]);
         }
     }
-    DerivedPlan dp;
     if ((rc = reft_plan_create(sizes.data(), sizes.size(), nullptr, 0, 0, &dp.plan))) return rc;
     struct Guard {
         reft_plan *d;
@@ -1971,26 +1995,29 @@ static int derived_rows(const reft_plan *p, const DerivedPlan &dp, const void *c
     return REFT_OK;
 }
 
-// What a call's rows are made of: the shards' span pointers but those of member `skip`, and of a decode the parity units and
-// the tensors.
+// The pointers that a call was given: the shards' and, of a decode, the parity units and the tensors.
 struct CallerPointers {
     const void *const *shards;
     const void *const *parity, *const *out;                // null in an encode
     uint64_t T;
-    uint32_t k, skip;
 
-    // each(pointers, count) for every piece of it, until one answers false
+    // each(pointers, count) for every piece that the plan's rows are made of, until one answers false
     template <class Each>
-    bool all(Each each) const
+    bool all(const DerivedPlan &dp, Each each) const
     {
-        return each(shards, skip * T) && each(shards + (skip + 1) * T, (k - 1 - skip) * T) &&
-               (!parity || (each(parity, skip) && each(parity + skip + 1, k - 1 - skip))) && (!out || each(out, T));
+        for (const PointerRange &r : dp.uses)
+            if (!each((r.of == kOut ? out : shards + r.of * T) + r.first, r.end - r.first)) return false;
+        for (uint32_t i : dp.units)
+            if (!each(parity + i, 1)) return false;
+        return true;
     }
 };
 
 // The XOR that a derived plan stands for.  Its rows are many times the caller's pointers, to make, to compare and to keep: so
 // these are compared, with those of the last two sets, and where they are the same and their rows still in the derived
 // plan's cache, that table is used.  (One unit and one decode, 8 members of 34 MB in 9236 spans: 117 us of host work, 26 so.)
+// Of a unit that is a window of each member's pointers.  (All of them compared, a unit of 16 members' 76 MB in 11,490 spans
+// took 25 us a call, so 17, and 17 to 33 with its rows made each time.)
 static int xor_derived(reft_plan *p, DerivedPlan &dp, const CallerPointers &from, void *dst_contig, hipStream_t s)
 {
     int rc;
@@ -2002,7 +2029,7 @@ static int xor_derived(reft_plan *p, DerivedPlan &dp, const CallerPointers &from
         const SeenPointers &seen = dp.seen[at];
         if (!seen.upload || !d->ring[seen.entry].live || d->ring[seen.entry].upload != seen.upload) continue;
         const void *const *had = seen.ptrs.data();
-        if (!from.all([&](const void *const *ptrs, uint64_t n) {
+        if (!from.all(dp, [&](const void *const *ptrs, uint64_t n) {
                 const bool same = n == 0 || !memcmp(had, ptrs, n * sizeof *ptrs);
                 had += n;
                 return same;
@@ -2017,7 +2044,7 @@ static int xor_derived(reft_plan *p, DerivedPlan &dp, const CallerPointers &from
     SeenPointers &seen = dp.seen[dp.last ^= 1];
     seen.upload = 0;
     seen.ptrs.clear();
-    from.all([&](const void *const *ptrs, uint64_t n) {
+    from.all(dp, [&](const void *const *ptrs, uint64_t n) {
         seen.ptrs.insert(seen.ptrs.end(), ptrs, ptrs + n);
         return true;
     });
@@ -2054,7 +2081,7 @@ extern "C" int reft_parity_encode_rotated(reft_plan *p, const void *const *shard
             if (j != member) seg.wins.push_back(WinSpec{false, j, (uint64_t)rot_index(member, j) * Lseg});
         if ((rc = derived_plan(p, key, {seg}, &dp))) return rc;
     }
-    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, nullptr, nullptr, p->T, k, member}, parity_dev,
+    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, nullptr, nullptr, p->T}, parity_dev,
                        (hipStream_t)stream);
     REFT_GUARD_END("reft_parity_encode_rotated")
 }
@@ -2102,7 +2129,7 @@ extern "C" int reft_reconstruct_rotated(reft_plan *p, const void *const *shard_s
         }
         if ((rc = derived_plan(p, key, segs, &dp))) return rc;
     }
-    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, parity_ptrs, (const void *const *)out_span_ptrs, p->T, k, lost},
+    return xor_derived(p, *dp, CallerPointers{shard_span_ptrs, parity_ptrs, (const void *const *)out_span_ptrs, p->T},
                        nullptr, (hipStream_t)stream);
     REFT_GUARD_END("reft_reconstruct_rotated")
 }
