@@ -167,17 +167,28 @@ enum Spread : uint32_t {
 };
 constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024, kNearMeanSpan = 64 * 1024;
 constexpr uint64_t kShortMeanSpan = 5 * 1024, kMiddleMeanSpan = 12 * 1024;
-constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed)
+// Whether a launch has workgroups of two waves.  In spans below 20 KiB for what pair_waves says of it, as long as that pays; time
+// over that of single waves, on 132 / 400 MB a row (windows: 400 to 1200 MB a shard, cut by that), in spans of 3.5, 5, 7, 11,
+// 14 and 18 KB.  Rows: 3, 4, 6 and 8 sources .95 to .995 / .91 to .95, .98 to 1.015 / .93 to .98, .97 to 1.00 / .94 to .985, .97
+// to 1.00 / .97 to 1.04, .96 to 1.00 / .97 to 1.03, .97 to 1.00 / .985 to 1.02; 9 to 16 sources .95 to 1.00 / .95 to 1.00, but .97
+// to 1.025 / .97 to 1.04, .99 to 1.03 / .99 to 1.04, .995 to 1.04 / 1.02 to 1.06, .98 to 1.03, .99 to 1.05.  Windows into
+// tensors .91 to .98 up to 10 KB, .96 to .99 of 12 to 18 KB (up to 11 sources); into a unit, of 5 sources and more, .95 to 1.01
+// up to 10 KB, 1.02 to 1.08 of 12 to 17 KB, of 3 and 4 sources .94 to .97, once 1.06.
+constexpr uint64_t kPairsOfMany = 4 * 1024, kPairsOfUnit = 11 * 1024;
+constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
 {
     if (!odd) return false;
     if (nsrc == 1) return !packed && mean_span >= kShortMeanSpan && mean_span < kSpreadMeanSpan;
     if (packed) return nsrc <= 8 || mean_span >= kSpreadMeanSpan;
-    return nsrc <= 3 || mean_span < (nsrc < 12 ? kSpreadMeanSpan : kMiddleMeanSpan);
+    if (nsrc <= 3) return true;
+    if (!windows) return mean_span < (nsrc <= 8 ? kSpreadMeanSpan : kPairsOfMany);
+    if (!tensors) return mean_span < (nsrc == 4 ? kSpreadMeanSpan : kPairsOfUnit);
+    return mean_span < (nsrc < 12 ? kSpreadMeanSpan : kMiddleMeanSpan);
 }
 constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
 {
     if (mean_span < (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan)) return kInOrder;
-    if (in_pairs(nsrc, mean_span, odd, packed)) return kPairs;
+    if (in_pairs(nsrc, mean_span, odd, packed, tensors, windows)) return kPairs;
     if (!odd || packed) return kFar;
     return nsrc == 1 || (nsrc <= 12 && (windows || (!tensors && mean_span >= kNearMeanSpan))) ? kNear : kFar;
 }
@@ -202,14 +213,10 @@ constexpr uint32_t crowd_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 }
 
 // The same for workgroups of two waves.  In spans below 20 KiB a wave waits longer for its look-ups than for its data, the
-// shorter they are the more, so that more waves keep as many bytes in flight; swept from 8 to 32 on 0.5 to 2 GB.  Time
-// over that of single waves, as many as crowd_waves says (2 and 3 sources, and with the packed stream: of pairs, as many),
-// in spans of 2.5, 3.5, 7 and 14 KB: parity of 2 .98, .98, .99, 1, of 3 .96, .95, .98, 1, of 4 .91, .94, .96, .99, of 5
-// .90, .93, .95, .97, of 6 .94, .96, .97, .99, of 8 .94, .96, .99, .99, of 12 1, .96, .99, (1.01), of 16 1, .94, .98,
-// (1.01); decode of 2 .93, .95, .96, 1, of 4 .92, .93, .96, .98, of 8 1.04, .95, .99, .99, of 12 1.02, 1.04, .98, (1); a
-// rotated unit and decode of 5 members .88, .89, .93, .97, of 12 .98, .90, .96, .97; with the packed stream of 2 .96, .97,
-// .99, 1, of 4 .97, .98, 1, 1; copies 1, 1, .995, .99.  In longer spans, 28, 24 and 20 waves with the packed stream of 2
-// 358 / 343 / 333 us, of 3 447 / 429 / 418 (200 KB).
+// shorter they are the more, so that more waves keep as many bytes in flight; swept from 8 to 32 on 0.5 to 2 GB (what it gives
+// is said at in_pairs; over pairs of waves, as many as crowd_waves says, with the packed stream of 2 .96, .97, .99, 1 in spans
+// of 2.5, 3.5, 7 and 14 KB, of 4 .97, .98, 1, 1).  In longer spans, 28, 24 and 20 waves with the packed stream of 2 358 / 343
+// / 333 us, of 3 447 / 429 / 418 (200 KB).
 constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 {
     constexpr uint32_t least[3][12] = {{32, 32, 32, 28, 24, 20, 20, 16, 14, 16, 16, 16},

@@ -14,7 +14,10 @@ extern "C" uint64_t turned(uint32_t units, uint64_t u, uint64_t u0, uint64_t u1,
 }
 extern "C" uint64_t near_step(uint64_t w, uint64_t n) { return reft::near_step_of_wave(w, n); }
 extern "C" uint64_t pair_step(uint64_t w, uint64_t n) { return reft::pair_step_of_wave(w, n); }
-extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, bool odd, bool packed) { return reft::in_pairs(nsrc, mean, odd, packed); }
+extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bool tensors, bool windows)
+{
+    return reft::in_pairs(nsrc, mean, odd, packed, tensors, windows);
+}
 extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bool tensors, bool windows)
 {
     return reft::spread_of(nsrc, mean, odd, packed, tensors, windows);
@@ -48,7 +51,7 @@ def rules(tmp_path_factory):
     for f in (lib.near_step, lib.pair_step):
         f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
         f.restype = ctypes.c_uint64
-    lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
+    lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.in_pairs.restype = ctypes.c_bool
     lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.writes_through.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
@@ -116,13 +119,24 @@ def test_which_order_a_launch_takes(rules):
                         else:
                             assert got[3] == far and got[4] == far and got[5] == (far if tensors or windows or nsrc > 12 else near)
                         for mean, order in zip((k20 - 1, k20, k64), (got[0], got[1], got[5])):
-                            assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, odd, packed)
+                            assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, odd, packed, tensors, windows)
                             assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
-            for mean, most in ((600, 16), ((12 << 10) - 1, 16), (12 << 10, 11), (k20 - 1, 11), (k20, 3)):
-                assert rules.in_pairs(nsrc, mean, odd, False) == (odd and nsrc <= most and (nsrc > 1 or 5 << 10 <= mean < k20))
-                assert rules.in_pairs(nsrc, mean, odd, True) == (odd and 2 <= nsrc <= (8 if mean < k20 else 16))
-                for packed in (False, True):
-                    assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
+            for tensors in (False, True):
+                for windows in (False, True):
+                    for mean in (600, (4 << 10) - 1, 4 << 10, (5 << 10) - 1, 5 << 10, (11 << 10) - 1, 11 << 10, (12 << 10) - 1,
+                                 12 << 10, k20 - 1, k20):
+                        if not windows:
+                            most = 16 if mean < 4 << 10 else 8 if mean < k20 else 3
+                        elif tensors:
+                            most = 16 if mean < 12 << 10 else 11 if mean < k20 else 3
+                        else:
+                            most = 16 if mean < 11 << 10 else 4 if mean < k20 else 3
+                        assert rules.in_pairs(nsrc, mean, odd, False, tensors, windows) == (
+                            odd and nsrc <= most and (nsrc > 1 or 5 << 10 <= mean < k20))
+                        assert rules.in_pairs(nsrc, mean, odd, True, tensors, windows) == (
+                            odd and 2 <= nsrc <= (8 if mean < k20 else 16))
+                        for packed in (False, True):
+                            assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
 
 
 def test_which_launches_write_through(rules):
