@@ -229,24 +229,41 @@ constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
     return nsrc <= 6 && mean_span < kShortMeanSpan ? usual + 2 : usual;
 }
 
-// Whether a launch writes its results through the L2 (st16_through): where units write whole cache
-// lines, in spans long enough for an XCD to keep to its address bits, and far more than the cache holds.  Time over that of
-// results that wait in the L2 to be evicted, each with its best number of waves: spans of MBs, parity of 2, 3, 4, 5, 8,
-// 12, 16 .92, .93, .94, .98, .99, .99, .99, with the packed stream of 2, 3, 4, 5, 8, 12 .96, .97, .95, .96, .97, .99,
-// decode of 4 .94, of 5 .98; copies .98 to .99, in spans of 0.1 to 0.5 MB 1. But in odd streams 1.00 to 1.08 (partial
-// lines from both sides go to memory one by one), aligned spans of 60 KB, of 2 sources, 1.06, of 4 1.02, and 0.13 to 0.3
-// GB of traffic 1.00 to 1.06 (some of it would have stayed in the 256 MB cache).
+// Whether a launch writes its results through the L2 (st16_through): in spans long enough for an XCD to keep to its address
+// bits, and far more than the cache holds.  In odd streams partial lines from both sides go to memory one by one: 1.00 to 1.08 of
+// the time.
+//
+// Time over that of results that wait in the L2 to be evicted, with loads as they were there, on the same memory in one process:
+// tensors of a job one behind the other, each allocated by itself, in a heap full of holes, and as a benchmark's job has them,
+// 0.16 to 11.8 GB a row.  Spans of 1 MB and more, parity of 2 .93 to 1.01, of 3 .92 to .98, of 4 .93 to 1.00, of 5 .93 to .99, of 6
+// to 8 .96 to 1.00, of 10 to 16 .98 to 1.00; decodes of 2 and 3 .92 to .99, of 4 .94 to 1.00, of 5 .94 to .99, of 6 to 12 .98 to
+// 1.00; with the packed stream of 2 .91 to .98 (1.0 MB: .96 to 1.02), of 3 .94 to .98, of 5 and 8 .93 to .98, of 12 .98 to 1.00.
+// (With five sources and more stores alone, of the two changes, .97 to 1.00, loads alone .98 to 1.01, both together the least
+// nearly everywhere.  In six processes, on two sets of memory each, parity and decode of 8 x 3.1 GB .982 to .988, of 8 x 2.5 GB
+// .981 to .992, where one set differs from another by up to 4 %.)  Spans of 150, 200, 300 and 600 KB: parity of 2, 3 and 4 .99 to
+// 1.07, .96 to 1.08 and .98 to 1.07, decodes .97 to 1.06, .95 to 1.05 and .98 to 1.04, with the packed stream of 2 .96 to 1.07; but
+// parity of 5 .95 to 1.01, of 8 .95 to .99, of 10 to 16 .98 to 1.01, decodes of 5 to 12 .95 to 1.00, with the packed stream of 3, 5
+// and 8 .92 to 1.01.  Below 0.5 GB of traffic 1.00 to 1.06 (some of it would have stayed in the 256 MB cache).
+//
+// Copies, 0.5 / 1.2 / 2.4 / 5 to 13 GB of traffic: spans of 1.2 MB 1.04 / 1.01 to 1.03 / 1.00 to 1.01 / .99 to 1.01, of 2.5 MB 1.03 /
+// 1.00 to 1.02 / .99 to 1.01 / .99 to 1.01, of 8 MB 1.03 / 1.00 to 1.02 / .99 to 1.01 / .98 to 1.00, of 40 MB - / .99 to 1.01 / .99 /
+// .98 to .99; of 0.15 to 0.6 MB .97 to 1.06.
+//
+// Where the results lie makes no difference to that: 2 to 12 sources, spans of 1 to 10 MB, results 1, 4, 16 or 32 bytes off a cache
+// line .91 to 1.00, as on one; a tenth to nearly half of the stream at odd places .93 to .99; copies of 8 and 40 MB spans, 2.4 GB
+// of traffic and more, .99 to 1.02 at such places (1.002 on average).
 //
 // How many waves then share a compute unit (see crowd_waves), swept from 6 to 32 on 1.7 to 28 GB: copies (25.8 GB) 3893 us
 // with 24 as they were, 3862 / 3815 / 3823 written through with 24 / 20 / 18, 835 / 831 / 824 / 824 (5.6 GB), parity of 3
 // sources 1032 / 962 us with 24 / 18, of 4 1283 / 1203 with 16 / 15; with the packed stream of 2 350 / 340 with 28 / 20,
 // of 3 442 / 434 with 24 / 16, of 4 534 / 519 with 16 / 14, of 5 634 / 626 with 15 / 13, of 8 2600 / 2554 with 12 / 10.
-constexpr uint64_t kThroughMeanSpan = 128 * 1024, kThroughTraffic = 512ull << 20;
-constexpr uint64_t kThroughMeanCopy = 1024 * 1024;
+constexpr uint64_t kThroughMeanSpan = 128 * 1024, kThroughMeanFew = 1024 * 1024, kThroughTraffic = 512ull << 20;
+constexpr uint64_t kThroughMeanCopy = 4096 * 1024, kThroughTrafficCopy = 2ull << 30;
 constexpr bool writes_through(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed)
 {
-    if (odd || traffic < kThroughTraffic) return false;
-    return nsrc == 1 ? !packed && mean_span >= kThroughMeanCopy : mean_span >= kThroughMeanSpan;
+    if (odd) return false;
+    if (nsrc == 1) return !packed && mean_span >= kThroughMeanCopy && traffic >= kThroughTrafficCopy;
+    return mean_span >= (nsrc <= (packed ? 2u : 4u) ? kThroughMeanFew : kThroughMeanSpan) && traffic >= kThroughTraffic;
 }
 constexpr uint32_t through_waves(uint32_t nsrc, bool packed)
 {

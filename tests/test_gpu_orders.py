@@ -67,22 +67,23 @@ def test_in_place(dev, k, odd):  # noqa: F811
         reft.reft_plan_destroy(plan)
 
 
-# more than 512 MiB of traffic, spans of 128 KiB and more on average at multiples of 64 bytes in the stream, in memory at such
-# and anywhere
+# more than 512 MiB of traffic, spans of 128 KiB (1 MiB with up to four sources) and more on average at multiples of 64 bytes in
+# the stream, in memory at such and anywhere; of 24 shards eight (in the parity and in the decode) are added in a second pass
 @pytest.mark.parametrize("align", [1, 64])
-@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 8, 11, 16])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 8, 11, 16, 24])
 def test_results_written_through(dev, k, align):  # noqa: F811
     rng = np.random.default_rng(k)
-    sizes, total = [], (520 << 20) // (k + 1)
+    sizes, total = [], (520 << 20) // (k + 1 if k <= 16 else k - 16 + 2)
+    least = 1 << 20 if k <= 4 else 128 << 10
     while sum(sizes) < total:
-        sizes.append(int(rng.integers(1, 8 << 10)) * 64)
+        sizes.append(int(rng.integers(1, least // 16)) * 64)
         if len(sizes) % 9 == 0:
             sizes += [64, 0, 192]
     sizes += [int(rng.integers(1, 64)) for _ in range(4)]
     gen = torch.Generator(device=dev)
     gen.manual_seed(k)
     T, L = len(sizes), sum(sizes)
-    assert L // T >= 128 << 10
+    assert L // T >= least
 
     def spans():
         return arena(sizes, rng.integers(0, 64, T) // align * align, dev, gen)
@@ -130,18 +131,18 @@ def test_results_written_through(dev, k, align):  # noqa: F811
 
 @pytest.mark.parametrize("align", [1, 64])
 def test_copies_written_through(dev, align):  # noqa: F811
-    """Packed and unpacked, in spans of 1 MiB and more on average: whole steps of two units, and what is left of a span."""
+    """Packed and unpacked, 1 GiB in spans of 4 MiB and more on average: whole steps of two units, and what is left of a span."""
     rng = np.random.default_rng(align)
     sizes = []
-    while sum(sizes) < 260 << 20:
-        sizes.append(int(rng.integers(1, 64 << 10)) * 64)
+    while sum(sizes) < 1 << 30:
+        sizes.append(int(rng.integers(1, 320 << 10)) * 64)
         if len(sizes) % 20 == 0:
             sizes += [0, 64]
     sizes.append(5)
     gen = torch.Generator(device=dev)
     gen.manual_seed(align)
     T, L = len(sizes), sum(sizes)
-    assert L // T >= 1 << 20 and 2 * L >= 512 << 20
+    assert L // T >= 4 << 20 and 2 * L >= 2 << 30
     shard = arena(sizes, rng.integers(0, 64, T) // align * align, dev, gen)[1]
     want = torch.cat(shard)
     plan = reft.reft_plan_create(sizes)

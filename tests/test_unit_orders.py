@@ -140,14 +140,17 @@ def test_which_order_a_launch_takes(rules):
 
 
 def test_which_launches_write_through(rules):
-    """Long spans, aligned, and more than twice the cache; and LDS for no more waves than those are to have."""
+    """Long spans, aligned, and more than twice the cache, longer ones of few sources, and of copies with far more;
+    and LDS for no more waves than those are to have."""
     for nsrc in range(1, 17):
         for packed in (False, True):
-            least = 1 << 20 if nsrc == 1 else 128 << 10
+            copy = nsrc == 1
+            least = 4 << 20 if copy else 1 << 20 if nsrc <= (2 if packed else 4) else 128 << 10
+            most = 2 << 30 if copy else 512 << 20
             for mean in (least - 1, least):
-                for traffic in ((512 << 20) - 1, 512 << 20):
+                for traffic in (most - 1, most):
                     for odd in (False, True):
                         assert rules.writes_through(nsrc, mean, traffic, odd, packed) == (
-                            mean == least and traffic == 512 << 20 and not odd and not (nsrc == 1 and packed))
+                            mean == least and traffic == most and not odd and not (copy and packed))
             waves = rules.through_waves(nsrc, packed)
             assert 8 <= waves <= rules.crowd_waves(nsrc, 128 << 10, packed) and rules.crowd_lds(waves) <= 64 << 10
