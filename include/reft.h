@@ -111,8 +111,10 @@ int reft_plan_split(const reft_plan *plan, double t_bubble, double t_ss, uint64_
  * "dma_min_bytes" / "gather_min_pieces": *gather_launches kernel launches on pack_stream (runs of
  * small pieces) and *copies hipMemcpyAsync calls on copy_stream.  With *gather_launches == 0 the
  * transport is pure DMA, pack_stream carries no work, and the caller may pass one stream for both
- * (one hardware queue less: see the note on streams under reft_snapshot_pack).  (Up to 4 MiB on one
- * stream: one kernel where gather launches are reported, and no copies.) */
+ * (one hardware queue less: see the note on streams under reft_snapshot_pack).  The counts
+ * are those of calls with two streams.  A call with one stream for both that moves up to 4 MiB, where
+ * *gather_launches is not 0 and the host buffer is device-accessible, makes one kernel launch and no
+ * copy instead (see reft_snapshot_pack). */
 int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *copies);
 
 /* ---- S1 + S2 + S3: bucketed snapshot of one shard into pinned host memory -----------------------

@@ -985,7 +985,11 @@ extern "C" int reft_plan_burst_stats(reft_plan *p, uint64_t stats[4])
 // loop of GEMMs (and what that loses): 128 MB in 256 spans (log-uniform 64 : 65536) 3941 / 2710 / 2319 / 2319, 13368 /
 // 6290 / 3208 / 3209 (639 / 91 / 79 / 86); 460 MB in 2424 10327 / 8343 / 8344 / 8345, 49885 / 12633 / 13369 / 13304 (1772
 // / 244 / 328 / 362); but 400 MB in 200 of 1 to 4 MiB 8859 / 8442 / 7244 / 7242, 8876 / 8765 / 11019 / 11283 (220 / 214 /
-// 398 / 268).
+// 398 / 268).  That is one stream for kernels and copies, beside long GEMMs.  Such states saved and loaded again, copied from 1 / 4
+// MiB on, alone, beside GEMMs of 0.13 ms, and of 0.8 ms: 423 MB in 160 on one stream 17767 / 15354, 17912 / 16457, 17934 / 22964;
+// on two, as calls beside compute should have, 17896 / 15245, 17980 / 15559, 17946 / 18386 (the GEMMs lose 0.2 to 0.6 ms / 0.3 to
+// 0.4 ms).  And seven of them and two smaller ones in turn, 681 MB in 436, on two 31401 / 24735, 37910 / 25408, 76010 / 28372.
+// So the line does not depend on a span's neighbours: of copies one stream beside long GEMMs alone would gain.
 static void classify_pieces(const reft_plan *p, uint64_t bucket_begin, uint64_t bucket_end,
                             uint64_t dma_min, uint64_t gather_min, std::vector<Run> &runs,
                             std::vector<Dma> &dmas)
