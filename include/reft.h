@@ -113,8 +113,8 @@ int reft_plan_split(const reft_plan *plan, double t_bubble, double t_ss, uint64_
  * transport is pure DMA, pack_stream carries no work, and the caller may pass one stream for both
  * (one hardware queue less: see the note on streams under reft_snapshot_pack).  The counts
  * are those of calls with two streams.  A call with one stream for both that moves up to 4 MiB, where
- * *gather_launches is not 0 and the host buffer is device-accessible, makes one kernel launch and no
- * copy instead (see reft_snapshot_pack). */
+ * *gather_launches is not 0 and one device-accessible allocation holds the host buffer, makes one
+ * kernel launch and no copy instead (see reft_snapshot_pack). */
 int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *copies);
 
 /* ---- S1 + S2 + S3: bucketed snapshot of one shard into pinned host memory -----------------------
@@ -132,8 +132,8 @@ int reft_plan_staged_work(reft_plan *plan, uint64_t *gather_launches, uint64_t *
  *       form two groups used alternately; the two streams synchronise through events once per
  *       group.  pack_stream may equal copy_stream (fully in order); then up to 4 MiB that would be
  *       gathered at least in part go across the link by a kernel of few workgroups, as in the direct
- *       transport, if host_dst is device-accessible: that takes less time than setting up a copy,
- *       also from kernels beside it.  The tensors are read in
+ *       transport, if one device-accessible allocation holds all of these bytes of host_dst: that takes
+ *       less time than setting up a copy, also from kernels beside it.  The tensors are read in
  *       pack_stream's order: work queued on pack_stream before the call (say, the kernel that
  *       produced a parity buffer) completes before any byte is read, also by the copies.
  *   direct (staging == NULL)  the gather kernel itself stores into the pinned host buffer across
