@@ -159,12 +159,23 @@ constexpr bool odd_stream(uint64_t bytes, uint64_t L) { return bytes > L / 2; }
 // of kFar in 43 and 200 KB and 2 MB, 8 .99, .98, .98, 16 1.04, 1.05, .99); alike but for one source (decodes): far (near 0
 // to 2 % more).  Rows that are windows at any offset: near up to 12 sources (3 .98, 7 and 11 .97 to .98), of 15 neither
 // always (.98 to 1.03).
+//
+// Below 512 MiB of traffic units are not turned, and lie on the cache lines only, but where they go in pairs: a launch has few
+// waves there, for which the first unit's longer way and what the kernel works out for turns come to more than the order of
+// address bits saves (some of the data is in the 256 MB cache besides).  Time over that of units in plain numbers there, of
+// launches one after the other on the same memory / on 4 to 8 sets in turn, turned / not turned and in a kernel that knows of no
+// other order: 100 MiB 1.05 / 1.02 and 1.00 / 1.00, 130 MiB 1.04 / 1.01 and 1.00 / 1.00, 200 MiB 1.02 / 1.01 and 1.00 / 1.00, 480
+// MiB 1.00 / 1.00 and 1.00 / 1.00 (the same for odd streams but for pairs; parity of 5 and more, of spans of 64 KiB and more,
+// 1.04 / 1.02 and 1.00 / 1.00; copies 1.01 / 1.00 and 1.00 / 1.00, but odd ones in spans of 32 to 64 KiB .98 / .97 and .99 / .98).
+// From there on, turned and not: 0.6 and 0.9 GiB .99, .99, 1.3 GiB .98, .98, 2 GiB .97, .98, 4 GiB .97, .98.
 enum Spread : uint32_t {
     kInOrder = 0,
     kFar = 1,                // unit_of_wave
     kNear = 2,               // near_step_of_wave
     kPairs = 3,              // pair_step_of_wave
+    kFarUnturned = 4,        // unit_of_wave
 };
+constexpr uint64_t kTurnTraffic = 512ull << 20;
 constexpr uint64_t kSpreadMeanSpan = 20 * 1024, kSpreadMeanCopy = 32 * 1024, kNearMeanSpan = 64 * 1024;
 constexpr uint64_t kShortMeanSpan = 5 * 1024, kMiddleMeanSpan = 12 * 1024;
 // Whether a launch has workgroups of two waves.  In spans below 20 KiB for what pair_waves says of it, as long as that pays; time
@@ -185,10 +196,12 @@ constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed
     if (!tensors) return mean_span < (nsrc == 4 ? kSpreadMeanSpan : kPairsOfUnit);
     return mean_span < (nsrc < 12 ? kSpreadMeanSpan : kMiddleMeanSpan);
 }
-constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
+constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
     if (mean_span < (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan)) return kInOrder;
     if (in_pairs(nsrc, mean_span, odd, packed, tensors, windows)) return kPairs;
+    const bool near_copy = odd && nsrc == 1 && !packed && mean_span < kNearMeanSpan;
+    if (traffic < kTurnTraffic && !near_copy) return kFarUnturned;
     if (!odd || packed) return kFar;
     return nsrc == 1 || (nsrc <= 12 && (windows || (!tensors && mean_span >= kNearMeanSpan))) ? kNear : kFar;
 }
@@ -259,6 +272,7 @@ constexpr uint32_t pair_waves(uint32_t nsrc, uint64_t mean_span, bool packed)
 // of 3 442 / 434 with 24 / 16, of 4 534 / 519 with 16 / 14, of 5 634 / 626 with 15 / 13, of 8 2600 / 2554 with 12 / 10.
 constexpr uint64_t kThroughMeanSpan = 128 * 1024, kThroughMeanFew = 1024 * 1024, kThroughTraffic = 512ull << 20;
 constexpr uint64_t kThroughMeanCopy = 4096 * 1024, kThroughTrafficCopy = 2ull << 30;
+static_assert(kTurnTraffic <= kThroughTraffic);       // (no kernel that writes through knows kFarUnturned)
 constexpr bool writes_through(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed)
 {
     if (odd) return false;

@@ -103,13 +103,20 @@ struct Span {
     uint32_t turn;           // see turn_of (0 where some of the span is not in the range)
 };
 
+// What a kernel knows of the orders in which a launch may deal its steps (Spread).
+enum Deal {
+    kAsNumbered = 0,         // kInOrder alone
+    kFarAlone = 1,           // kFarUnturned alone
+    kAnyOrder = 2,           // all but kFarUnturned
+};
+
 // Span i, everything in one go (what the last source and the destination have no table for comes from another one
 // and is not used: a branch there costs the wave another wait).
 //
 // The lead: a span's units lie so that the first source, and with it those that are aligned like it, is read in
 // whole cache lines, or, where it stands (nearly) alone, the destination is written in such.  (Shards of tensors at
 // odd stream offsets are aligned alike: 8 x 56 MB encoded in 87 instead of 108 us.)
-template <int K, bool SPREAD>
+template <int K, Deal D>
 __device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
 {
     Span<K> o;
@@ -132,7 +139,7 @@ __device__ __forceinline__ Span<K> load_span(const StreamArgs &a, uint64_t i)
 #pragma unroll
     for (int j = 1; j < K; ++j) alike += (((uint32_t)o.s[j] ^ (uint32_t)o.s[0]) & 15u) == 0;
     const uint64_t ref = (2 * alike >= K ? o.s[0] : o.d) + o.head;
-    const bool wide = SPREAD && a.spread && o.u1 - o.u0 > kTurned;
+    const bool wide = D == kAnyOrder && a.spread && o.u1 - o.u0 > kTurned;
     o.lead = (uint32_t)(0 - ref) & ((wide ? kMaxLead : kLineLead) - 1);
     o.turn = wide && b >= a.range.lo && e <= a.range.hi ? turn_of(o.u0, (ref + o.lead - kUnit) / kUnit) : 0;
     return o;
@@ -371,9 +378,9 @@ __device__ __forceinline__ uint32_t move_steps(const StreamArgs &a, const Span<K
 // and 1186 / 315 / 102 (tiles walked by workgroups: 1620 / 432 / 145), parity of 4: 3563 / 906 / 247 and
 // 2593 / 677 / 196 (3168 / 817 / 253).
 //
-// SPREAD: for launches that may deal their steps in an order other than a.first_step, a.first_step + 1, ...  (Where short
-// spans are copied, what the kernel would have to ask and to work out for that costs 1 to 6 %.)
-template <int K, int U, bool NT, Form F = kPlain, bool SPREAD = false, bool THROUGH = false>
+// D: see Deal.  (Where short spans are copied, what the kernel would have to ask and to work out for the orders costs 1 to 6 %,
+// and launches of 20 to 80 us, whose waves are few, 1 to 2.)
+template <int K, int U, bool NT, Form F = kPlain, Deal D = kAsNumbered, bool THROUGH = false>
 __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
 {
     const uint32_t lane = threadIdx.x & 63;
@@ -389,16 +396,17 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
          w += F != kRuns ? a.stride : (left -= done) ? done : done + (a.stride - 1) * (left = a.run)) {
         // streaming launches only: the few instructions more delay a short one by 0.2 us
         uint64_t step = w;
-        if (SPREAD && a.spread)
+        if (D == kFarAlone) step = unit_of_wave<U>(w, a.nsteps);
+        if (D == kAnyOrder && a.spread)
             step = a.spread == kFar ? unit_of_wave<U>(w, a.nsteps)
                                     : a.spread == kNear ? near_step_of_wave(w, a.nsteps) : pair_step_of_wave(w, a.nsteps);
         uint64_t u = (a.first_step + step) * U;
         if (U > 1 && u < a.range.first) u = a.range.first;
         uint64_t end = (a.first_step + step + 1) * U;
         if (U > 1 && end > a.range.last + 1) end = a.range.last + 1;
-        Span<K> o = load_span<K, SPREAD>(a, span_of(a, u, lane));
+        Span<K> o = load_span<K, D>(a, span_of(a, u, lane));
         const bool one = end - u == U && end <= o.u1;
-        if (SPREAD && one) {
+        if (D == kAnyOrder && one) {
             u = turned<U>(u, o.u0, o.u1, o.turn);
             end = u + U;
         }
@@ -418,7 +426,7 @@ __global__ void __launch_bounds__(256) k_stream(const StreamArgs a)
                     u = part;
                 }
                 if (u == end) break;
-                o = load_span<K, SPREAD>(a, span_of(a, u, lane));
+                o = load_span<K, D>(a, span_of(a, u, lane));
             }
         }
     }
@@ -522,20 +530,25 @@ static uint32_t long_stream_unroll(int nsrc) { return nsrc == 1 ? 2 : 1; }
 
 // (only one source has two units a step in a launch that spreads them)
 #define REFT_PICK_SPREAD(K)                                                                       \
-    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, true> : k_stream<K, K == 1 ? 2 : 1, true, kPlain, true>)
+    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, kAnyOrder> : k_stream<K, K == 1 ? 2 : 1, true, kPlain, kAnyOrder>)
+
+#define REFT_PICK_FAR(K)                                                                          \
+    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, kFarAlone> : k_stream<K, K == 1 ? 2 : 1, true, kPlain, kFarAlone>)
 
 #define REFT_PICK_THROUGH(K)                                                                      \
-    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, true, true>                                   \
-                     : k_stream<K, K == 1 ? 2 : 1, true, kPlain, true, true>)
+    (cfg.unroll == 1 ? k_stream<K, 1, true, kPlain, kAnyOrder, true>                              \
+                     : k_stream<K, K == 1 ? 2 : 1, true, kPlain, kAnyOrder, true>)
 
 #define REFT_PICK_PACK(K)                                                                         \
-    (through ? k_stream<K, 1, true, kPacked, true, K != 1>                                        \
-     : a.spread ? k_stream<K, 1, true, kPacked, true>                                             \
+    (through ? k_stream<K, 1, true, kPacked, kAnyOrder, K != 1>                                   \
+     : a.spread == kFarUnturned ? k_stream<K, 1, true, kPacked, kFarAlone>                        \
+     : a.spread ? k_stream<K, 1, true, kPacked, kAnyOrder>                                        \
                 : cfg.nontemporal ? k_stream<K, 1, true, kPacked> : k_stream<K, 1, false, kPacked>)
 
 #define REFT_PICK_RUNS(K) (cfg.nontemporal ? k_stream<K, 4, true, kRuns> : k_stream<K, 4, false, kRuns>)
 
-#define REFT_PICK_IN_PLACE(K) k_stream<K, 1, true, kInPlace, true>
+#define REFT_PICK_IN_PLACE(K)                                                                     \
+    (a.spread == kFarUnturned ? k_stream<K, 1, true, kInPlace, kFarAlone> : k_stream<K, 1, true, kInPlace, kAnyOrder>)
 
 #define REFT_PICK_SMALL(K) (two ? k_stream_small<K, 2> : k_stream_small<K, 1>)
 
@@ -612,7 +625,7 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     if (pt.unit == kSmallUnit) return launch_small(a, nsrc, form, cfg, stream);
     a.run = 1;
     a.spread = waves == 4 || !cfg.nontemporal || a.first_step % 32
-                   ? kInOrder : spread_of(nsrc, mean, pt.odd, form == kPacked, a.ragged, pt.windows);
+                   ? kInOrder : spread_of(nsrc, mean, traffic, pt.odd, form == kPacked, a.ragged, pt.windows);
     const bool through = a.spread && form != kInPlace && writes_through(nsrc, mean, traffic, pt.odd, form == kPacked);
     if (form == kPlain && cfg.runs && cfg.unroll == 4) {
         a.run = run_of_units(a.nsteps, waves * (uint64_t)cfg.max_wgs, nsrc, mean);
@@ -623,6 +636,13 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
         if (through) {
             switch (nsrc) {
                 REFT_CASES_4(REFT_PICK_THROUGH) REFT_CASES_5_8(REFT_PICK_THROUGH) REFT_CASES_9_16(REFT_PICK_THROUGH)
+            default: return hipErrorInvalidValue;
+            }
+            break;
+        }
+        if (a.spread == kFarUnturned) {
+            switch (nsrc) {
+                REFT_CASES_4(REFT_PICK_FAR) REFT_CASES_5_8(REFT_PICK_FAR) REFT_CASES_9_16(REFT_PICK_FAR)
             default: return hipErrorInvalidValue;
             }
             break;

@@ -24,7 +24,7 @@ static uint64_t not_moved(const Launch &l, int order, uint64_t place, bool own_p
     const uint64_t first_step = r.first / U, n = r.last / U - first_step + 1;
     if (first_step % 32) order = 0;
     for (uint64_t w = 0; w < n; ++w) {
-        const uint64_t step = order == kFar ? unit_of_wave<U>(w, n) : order == kNear ? near_step_of_wave(w, n)
+        const uint64_t step = order == kFar || order == kFarUnturned ? unit_of_wave<U>(w, n) : order == kNear ? near_step_of_wave(w, n)
                               : order == kPairs ? pair_step_of_wave(w, n) : w;
         uint64_t u = (first_step + step) * U, end = u + U;
         if (u < r.first) u = r.first;
@@ -33,7 +33,7 @@ static uint64_t not_moved(const Launch &l, int order, uint64_t place, bool own_p
             const uint64_t i = std::upper_bound(pt.unit_off, pt.unit_off + pt.T + 1, u) - pt.unit_off - 1;
             const uint64_t b = pt.off[i], e = pt.off[i + 1], u0 = pt.unit_off[i], u1 = pt.unit_off[i + 1];
             const uint64_t head = head_of(b, pt.grid), ref = (own_places ? place * (2 * i + 1) : place + b) + head;
-            const bool wide = order && u1 - u0 > kTurned;
+            const bool wide = order && order != kFarUnturned && u1 - u0 > kTurned;
             const uint32_t lead = (uint32_t)(0 - ref) & ((wide ? kMaxLead : kLineLead) - 1);
             const uint32_t turn = wide && b >= r.lo && e <= r.hi ? turn_of(u0, (ref + lead - kUnit) / kUnit) : 0;
             if (turns && end <= u1) {
@@ -91,7 +91,7 @@ def check(lib, sizes, buckets, rng):
         assert lib.reft_restore(plan, HOST, L, RING, 1 << 34, ptrs, 1, 1 + two) == 0
     for i in range(lib.sim_launches()):
         runs += 1
-        for order in range(4):
+        for order in range(5):
             for units in (1, 2):
                 place = rng.randrange(1 << 30) if rng.random() < 0.5 else rng.randrange(1 << 30) // 512 * 512
                 assert lib.sim_not_moved(i, order, units, place, rng.random() < 0.5) == 0, (sizes[:3], i, order, units, place)

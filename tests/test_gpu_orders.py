@@ -11,6 +11,8 @@ from test_gpu_stream import arena, check_all, dev, stream_kernel_only  # noqa: F
 
 pytestmark = pytest.mark.gpu
 TRAFFIC = 110 << 20
+# where units are not turned (but for pairs of waves and odd copies of short spans), and where they are
+BOTH = pytest.mark.parametrize("traffic", [TRAFFIC, 520 << 20])
 
 
 def sizes_of(kib, total, odd, seed):
@@ -31,26 +33,29 @@ def sizes_of(kib, total, odd, seed):
 @pytest.mark.parametrize("odd", [True, False])
 @pytest.mark.parametrize("kib", [0, 21, 70])
 @pytest.mark.parametrize("k", [1, 2, 3, 5, 8, 9, 13, 16])
-def test_every_call(dev, k, kib, odd):  # noqa: F811
-    check_all(dev, sizes_of(kib, TRAFFIC // (k + 1), odd, k), k, None, seed=k + kib, align=1 if odd else 16)
+@BOTH
+def test_every_call(dev, traffic, k, kib, odd):  # noqa: F811
+    check_all(dev, sizes_of(kib, traffic // (k + 1), odd, k), k, None, seed=k + kib, align=1 if odd else 16)
 
 
 @pytest.mark.parametrize("odd", [True, False])
 @pytest.mark.parametrize("k", [3, 8, 14, 16])
-def test_windows(dev, k, odd):  # noqa: F811
+@BOTH
+def test_windows(dev, traffic, k, odd):  # noqa: F811
     gen = torch.Generator(device=dev)
     gen.manual_seed(k)
     # the decode's k - 1 rows and result are what leaves the cache, the unit's k - 1 windows are a part of that
-    sizes = sizes_of(300, TRAFFIC // k, odd, k)
+    sizes = sizes_of(300, traffic // k, odd, k)
     shards = [arena(sizes, [0] * len(sizes), dev, gen)[1] for _ in range(k)]
     check_rotated(dev, shards, sizes, losts=[0, k - 1])
 
 
 @pytest.mark.parametrize("odd", [True, False])
 @pytest.mark.parametrize("k", [2, 3, 4, 9])
-def test_in_place(dev, k, odd):  # noqa: F811
+@BOTH
+def test_in_place(dev, traffic, k, odd):  # noqa: F811
     """The lost shard decoded over the parity: every byte read and written once."""
-    sizes = sizes_of(70, TRAFFIC // (k + 1), odd, k)
+    sizes = sizes_of(70, traffic // (k + 1), odd, k)
     off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
     gen = torch.Generator(device=dev)
     gen.manual_seed(k)

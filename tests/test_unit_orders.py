@@ -18,9 +18,9 @@ extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bo
 {
     return reft::in_pairs(nsrc, mean, odd, packed, tensors, windows);
 }
-extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bool tensors, bool windows)
+extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
-    return reft::spread_of(nsrc, mean, odd, packed, tensors, windows);
+    return reft::spread_of(nsrc, mean, traffic, odd, packed, tensors, windows);
 }
 extern "C" uint32_t pair_lds(uint32_t nsrc, uint64_t mean, bool packed) { return 2 * reft::crowd_lds(reft::pair_waves(nsrc, mean, packed)); }
 extern "C" bool writes_through(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd, bool packed)
@@ -53,7 +53,7 @@ def rules(tmp_path_factory):
         f.restype = ctypes.c_uint64
     lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.in_pairs.restype = ctypes.c_bool
-    lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
+    lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.writes_through.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
     lib.writes_through.restype = ctypes.c_bool
     lib.through_waves.argtypes = [ctypes.c_uint32, ctypes.c_bool]
@@ -99,17 +99,21 @@ def test_orders_are_permutations(rules, name):
 
 
 def test_which_order_a_launch_takes(rules):
-    in_order, far, near, pairs = range(4)
+    in_order, far, near, pairs, unturned = range(5)
     k20, k32, k64 = 20 << 10, 32 << 10, 64 << 10
     for nsrc in range(1, 17):
         for odd in (False, True):
             for packed in (False, True):
                 for windows in (False, True):
                     for tensors in (False, True):
-                        got = [rules.spread_of(nsrc, mean, odd, packed, tensors, windows)
-                               for mean in (k20 - 1, k20, k32 - 1, k32, k64 - 1, k64)]
+                        got, short = [[rules.spread_of(nsrc, mean, traffic, odd, packed, tensors, windows)
+                                       for mean in (k20 - 1, k20, k32 - 1, k32, k64 - 1, k64)]
+                                      for traffic in (512 << 20, (512 << 20) - 1)]
                         alone = nsrc == 1 and not packed
                         assert got[0] == in_order and got[1] == got[2] and (got[2] == in_order) == alone
+                        # below 512 MiB of traffic: those that keep to address bits, but odd copies of short spans
+                        assert short == [order if order in (in_order, pairs) or (alone and odd and i < 5) else unturned
+                                         for i, order in enumerate(got)]
                         if not odd:
                             assert set(got[3:]) == {far}
                         elif packed or nsrc in (2, 3):
