@@ -185,10 +185,24 @@ constexpr uint64_t kShortMeanSpan = 5 * 1024, kMiddleMeanSpan = 12 * 1024;
 // to 1.025 / .97 to 1.04, .99 to 1.03 / .99 to 1.04, .995 to 1.04 / 1.02 to 1.06, .98 to 1.03, .99 to 1.05.  Windows into
 // tensors .91 to .98 up to 10 KB, .96 to .99 of 12 to 18 KB (up to 11 sources); into a unit, of 5 sources and more, .95 to 1.01
 // up to 10 KB, 1.02 to 1.08 of 12 to 17 KB, of 3 and 4 sources .94 to .97, once 1.06.
+//
+// In longer spans from some traffic on.  Time over that of single waves, of launches one after the other on the same memory / on 4
+// to 8 sets in turn, of 100, 130, 165, 205, 290 and 410 MiB: with the packed stream of 2 .97 / .95, .98 / .955, .95 / .94, .94 / .92,
+// .92 / .92, .92 / .91, of 3 1.01 / .985, .99 / .97, .97 / .95, .98 / .95, .94 / .95, .94 / .93, of 4 to 8 1.02 to 1.05 / 1.00, 1.015 to
+// 1.03 / .99 to 1.00, .99 to 1.01 / .98 to .99, .99 to 1.00 / .97 to .98, .965 to .99 / .96 to .98, .96 to .98 / .96 to .98, of 12 and 16
+// 1.06 to 1.10 / 1.02 to 1.07, 1.05 / 1.02 to 1.03, 1.01 to 1.05 / 1.01 to 1.03, 1.02 to 1.03 / 1.01 to 1.02, 1.01 to 1.02 / 1.00 to
+// 1.01, .99 / .99; rows, 2 sources 1.03 / 1.00, 1.02 / .99, 1.00 / .98, 1.00 / .98, .98 / .975, .985 / .975, 3 1.045 / 1.01, 1.04 / 1.00,
+// 1.025 / .99, 1.005 / .99, 1.00 / .98, .985 / .975; and of 0.5, 1 GiB and more .92 to 1.00, .92 to .99, .88 to .98.
 constexpr uint64_t kPairsOfMany = 4 * 1024, kPairsOfUnit = 11 * 1024;
-constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed, bool tensors, bool windows)
+constexpr uint64_t least_paired_traffic(uint32_t nsrc, bool packed)
+{
+    if (packed) return nsrc <= 3 ? 0 : nsrc <= 8 ? 160ull << 20 : 352ull << 20;
+    return nsrc == 2 ? 144ull << 20 : 192ull << 20;
+}
+constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
     if (!odd) return false;
+    if (mean_span >= kSpreadMeanSpan && !windows && traffic < least_paired_traffic(nsrc, packed)) return false;
     if (nsrc == 1) return !packed && mean_span >= kShortMeanSpan && mean_span < kSpreadMeanSpan;
     if (packed) return nsrc <= 8 || mean_span >= kSpreadMeanSpan;
     if (nsrc <= 3) return true;
@@ -199,7 +213,7 @@ constexpr bool in_pairs(uint32_t nsrc, uint64_t mean_span, bool odd, bool packed
 constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
     if (mean_span < (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan)) return kInOrder;
-    if (in_pairs(nsrc, mean_span, odd, packed, tensors, windows)) return kPairs;
+    if (in_pairs(nsrc, mean_span, traffic, odd, packed, tensors, windows)) return kPairs;
     const bool near_copy = odd && nsrc == 1 && !packed && mean_span < kNearMeanSpan;
     if (traffic < kTurnTraffic && !near_copy) return kFarUnturned;
     if (!odd || packed) return kFar;

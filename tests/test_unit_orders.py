@@ -14,9 +14,9 @@ extern "C" uint64_t turned(uint32_t units, uint64_t u, uint64_t u0, uint64_t u1,
 }
 extern "C" uint64_t near_step(uint64_t w, uint64_t n) { return reft::near_step_of_wave(w, n); }
 extern "C" uint64_t pair_step(uint64_t w, uint64_t n) { return reft::pair_step_of_wave(w, n); }
-extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, bool odd, bool packed, bool tensors, bool windows)
+extern "C" bool in_pairs(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
-    return reft::in_pairs(nsrc, mean, odd, packed, tensors, windows);
+    return reft::in_pairs(nsrc, mean, traffic, odd, packed, tensors, windows);
 }
 extern "C" uint32_t spread_of(uint32_t nsrc, uint64_t mean, uint64_t traffic, bool odd, bool packed, bool tensors, bool windows)
 {
@@ -51,7 +51,7 @@ def rules(tmp_path_factory):
     for f in (lib.near_step, lib.pair_step):
         f.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
         f.restype = ctypes.c_uint64
-    lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64] + [ctypes.c_bool] * 4
+    lib.in_pairs.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.in_pairs.restype = ctypes.c_bool
     lib.spread_of.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64] + [ctypes.c_bool] * 4
     lib.writes_through.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_bool, ctypes.c_bool]
@@ -123,7 +123,7 @@ def test_which_order_a_launch_takes(rules):
                         else:
                             assert got[3] == far and got[4] == far and got[5] == (far if tensors or windows or nsrc > 12 else near)
                         for mean, order in zip((k20 - 1, k20, k64), (got[0], got[1], got[5])):
-                            assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, odd, packed, tensors, windows)
+                            assert order == in_order or (order == pairs) == rules.in_pairs(nsrc, mean, 512 << 20, odd, packed, tensors, windows)
                             assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
             for tensors in (False, True):
                 for windows in (False, True):
@@ -135,12 +135,27 @@ def test_which_order_a_launch_takes(rules):
                             most = 16 if mean < 12 << 10 else 11 if mean < k20 else 3
                         else:
                             most = 16 if mean < 11 << 10 else 4 if mean < k20 else 3
-                        assert rules.in_pairs(nsrc, mean, odd, False, tensors, windows) == (
+                        assert rules.in_pairs(nsrc, mean, 512 << 20, odd, False, tensors, windows) == (
                             odd and nsrc <= most and (nsrc > 1 or 5 << 10 <= mean < k20))
-                        assert rules.in_pairs(nsrc, mean, odd, True, tensors, windows) == (
+                        assert rules.in_pairs(nsrc, mean, 512 << 20, odd, True, tensors, windows) == (
                             odd and 2 <= nsrc <= (8 if mean < k20 else 16))
                         for packed in (False, True):
                             assert rules.pair_lds(nsrc, mean, packed) <= 64 << 10
+
+
+def test_pairs_in_longer_spans_from_some_traffic_on(rules):
+    """Spans of 20 KiB and more, but for windows; in shorter ones the traffic makes no difference."""
+    k20, MiB = 20 << 10, 1 << 20
+    for nsrc in range(2, 17):
+        for packed in (False, True):
+            least = (1 if nsrc <= 3 else 160 if nsrc <= 8 else 352) if packed else 144 if nsrc == 2 else 192
+            for traffic in (97 * MiB, least * MiB - 1, least * MiB, 1 << 40):
+                for tensors in (False, True):
+                    usual = rules.in_pairs(nsrc, k20, 1 << 40, True, packed, tensors, False)
+                    assert rules.in_pairs(nsrc, k20, traffic, True, packed, tensors, False) == (usual and (least == 1 or traffic >= least * MiB))
+                    for mean, windows in ((k20, True), (k20 - 1, False), (3 << 10, False), (k20 - 1, True)):
+                        assert rules.in_pairs(nsrc, mean, traffic, True, packed, tensors, windows) == rules.in_pairs(
+                            nsrc, mean, 1 << 40, True, packed, tensors, windows)
 
 
 def test_which_launches_write_through(rules):
