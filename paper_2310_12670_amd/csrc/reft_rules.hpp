@@ -158,7 +158,9 @@ constexpr bool odd_stream(uint64_t bytes, uint64_t L) { return bytes > L / 2; }
 // result and more sources, all alike but for the result: near, from 64 KiB and up to 12 sources (4 sources .99, .97, .98
 // of kFar in 43 and 200 KB and 2 MB, 8 .99, .98, .98, 16 1.04, 1.05, .99); alike but for one source (decodes): far (near 0
 // to 2 % more).  Rows that are windows at any offset: near up to 12 sources (3 .98, 7 and 11 .97 to .98), of 15 neither
-// always (.98 to 1.03).
+// always (.98 to 1.03).  Copies: near up to 64 KiB (.98, far .99); in longer spans, of 4 to 12 GB of traffic, far .99 / .98, 1.00 /
+// 1.00 and 1.00 / .985 of plain numbers (spans of 64 to 256 KB, up to 1 MB, longer; packed / unpacked), near .98 / 1.00, 1.04 / 1.03 and
+// 1.02 / 1.00.
 //
 // Below 512 MiB of traffic units are not turned, and lie on the cache lines only, but where they go in pairs: a launch has few
 // waves there, for which the first unit's longer way and what the kernel works out for turns come to more than the order of
@@ -214,10 +216,10 @@ constexpr Spread spread_of(uint32_t nsrc, uint64_t mean_span, uint64_t traffic, 
 {
     if (mean_span < (nsrc == 1 && !packed ? kSpreadMeanCopy : kSpreadMeanSpan)) return kInOrder;
     if (in_pairs(nsrc, mean_span, traffic, odd, packed, tensors, windows)) return kPairs;
-    const bool near_copy = odd && nsrc == 1 && !packed && mean_span < kNearMeanSpan;
-    if (traffic < kTurnTraffic && !near_copy) return kFarUnturned;
-    if (!odd || packed) return kFar;
-    return nsrc == 1 || (nsrc <= 12 && (windows || (!tensors && mean_span >= kNearMeanSpan))) ? kNear : kFar;
+    if (odd && nsrc == 1 && !packed && mean_span < kNearMeanSpan) return kNear;
+    if (traffic < kTurnTraffic) return kFarUnturned;
+    if (!odd || packed || nsrc == 1) return kFar;
+    return nsrc <= 12 && (windows || (!tensors && mean_span >= kNearMeanSpan)) ? kNear : kFar;
 }
 
 // LDS for one-wave workgroups to ask for, which they do not use, so that no more of them share a compute unit than its

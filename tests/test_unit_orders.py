@@ -118,7 +118,9 @@ def test_which_order_a_launch_takes(rules):
                             assert set(got[3:]) == {far}
                         elif packed or nsrc in (2, 3):
                             assert set(got[3:]) == {far if nsrc == 1 else pairs}
-                        elif alone or (windows and nsrc <= 12):
+                        elif alone:
+                            assert got[3:] == [near, near, far]
+                        elif windows and nsrc <= 12:
                             assert set(got[3:]) == {near}
                         else:
                             assert got[3] == far and got[4] == far and got[5] == (far if tensors or windows or nsrc > 12 else near)
