@@ -61,7 +61,7 @@ constexpr uint64_t first_number(uint64_t least, uint64_t off, uint64_t align)
 
 // Unit j of a span moves its bytes [s, t), none if s >= t, as far as they lie in [lo, hi), which may reach below 0 or
 // lie behind the span.  All units but the first start `lead` (below kMaxLead) bytes later than they otherwise would,
-// the first moves those bytes as well.  Launches that spread their units move them to the KiB of the addresses, others,
+// the first moves those bytes as well.  Launches that turn their units move them to the KiB of the addresses, others,
 // where the first unit's wave should not take twice as long as the rest, to the cache lines.
 constexpr uint32_t kMaxLead = 1024, kLineLead = 128;
 struct Piece {
@@ -150,7 +150,7 @@ constexpr bool odd_stream(uint64_t bytes, uint64_t L) { return bytes > L / 2; }
 // In spans below 20 KiB on average the numbers of units mean too little (4 KB: 0 to +2 %, 7 KB 0 %, 14 KB -1 to +1 %,
 // 28 KB -2 to -4 %), and copies, two units a wave, gain from 32 KiB on only (14 KB +1 %, 43 KB -2 %).
 //
-// Odd streams: two results, or two or three sources, in pairs, a wave's neighbour in its own workgroup, so that both
+// Odd streams: two results, or two or three sources, in pairs (see in_pairs), a wave's neighbour in its own workgroup, so that both
 // parts of a line that they share are in the same L2 at once.  Time of kFar / kNear / pairs, in spans of 14, 43 and 200 KB
 // and 2 MB: with the packed stream, 2 sources 1 / .93 / .90, 1 / .92 / .92, 1 / .92 / .93 and 1 / .99 / .95, 5 sources 1 /
 // .97 / .95, 1 / .97 / .95, 1 / .95 / .93 and 1 / .98 / .97, 8 sources 1 / .97 / .96, .97 / .97, .98 / .98, .98 / .99, 12

@@ -610,8 +610,8 @@ static hipError_t launch_stream(const PlanTables &pt, StreamArgs a, const uint64
     a.first_step = a.range.first / cfg.unroll;
     a.nsteps = a.range.last / cfg.unroll - a.first_step + 1;
     const uint64_t mean = pt.L / pt.T;
-    const bool pairs = in_pairs(nsrc, mean, traffic, pt.odd, form == kPacked, dtab != nullptr, pt.windows);
-    const uint32_t waves = cached || cfg.capped ? 4 : pairs ? 2 : 1;
+    const uint32_t waves = cached || cfg.capped ? 4
+                           : in_pairs(nsrc, mean, traffic, pt.odd, form == kPacked, dtab != nullptr, pt.windows) ? 2 : 1;
     a.off = pt.off;
     a.unit_off = pt.unit_off;
     a.unit_span = pt.unit_span;
